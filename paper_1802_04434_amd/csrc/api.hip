@@ -71,9 +71,9 @@ inline bool written_spans_overlap(Span *s, int n) {
 // runtime call is neither reported as ours nor cleared.
 template <typename Args>
 int launch(void (*kernel)(Args), size_t grid, unsigned lds_bytes, hipStream_t stream, const Args &a,
-           int block = ss::kBlock) {
+           int block = ss::kBlock, int grid_y = 1) {
     void *params[1] = {const_cast<Args *>(&a)};
-    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)grid),
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)grid, (unsigned)grid_y),
                                          dim3((unsigned)block), params, lds_bytes, stream);
     if (e != hipSuccess) {
         g_last_hip_error = (int)e;
@@ -89,9 +89,9 @@ struct Tiling {
     size_t words_total;
 };
 
-inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = ss::kBlock) {
+inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = ss::kBlock, int per_lane = ss::kQuad) {
     Tiling t;
-    const size_t tile = (size_t)rows * block * ss::kQuad;
+    const size_t tile = (size_t)rows * block * per_lane;
     t.words_total = ss_packed_bytes(d) / 4;
     t.n_tiles = d / tile;
     const size_t done = t.n_tiles * tile;
@@ -109,9 +109,16 @@ inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = s
 constexpr size_t kStreamingMinD = (size_t)1 << 20;
 constexpr int kLdsPerUnitKB = 160;   // what the reservations below assume; checked against the device
 
-// when ss_signum_vote_step is given packed_out buffers it may run as M + 2 launches (see there)
-constexpr size_t kSplitMinD = (size_t)1 << 24;
-constexpr int kSplitMinWorkers = 2;
+// Given packed_out buffers, the step runs as two launches - pack_kernel over all workers, then vote
+// and update - from 2^20 coordinates and this many gradient elements on.  The one-pass kernel that
+// also writes the bits keeps 2M + 1 buffers open and stays at 6.1 TB/s; the two launches reach 6.4-6.8
+// but cost a second launch and tail (~2.5 us), which small and latency-bound steps do not earn back.
+// One pass -> two launches, us: fp32, M = 7: 0.7 M 12.2 -> 14.4, 1.1 M 22.9 -> 19.4, 4.4 M 70 -> 66,
+// 25.6 M 386 -> 358; M = 16: 1.1 M 48 -> 40, 25.6 M 871 -> 780; M = 2: 1.1 M 8.7 -> 8.9, 4.4 M 27.0 -> 25.8,
+// 25.6 M 138 -> 129; bf16, M = 8: 1.1 M 21.8 -> 19.8, 25.6 M 388 -> 341; M = 2: 4.4 M 22.8 -> 23.2, 25.6 M 120 -> 115.
+inline bool split_pays(int M, size_t d) {
+    return M >= 2 && d >= ((size_t)1 << 20) && d * (size_t)M >= ((size_t)1 << (M >= 4 ? 23 : 24));
+}
 
 // LDS of one compute unit of the current device, in KB; 0 if the runtime will not say.  A pure
 // query: nothing is remembered between calls.
@@ -160,14 +167,14 @@ void fill_step_args(ss::StepArgs<NPTR> &a, int M, const void *const *g, float *c
     a.d = d;
 }
 
-template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB, bool LOADS_FIRST, bool HAS_M, bool VOTE, typename G>
+template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB, bool LOADS_FIRST, bool HAS_M, typename G>
 int launch_step_shape(ss::StepArgs<NPTR> &a, size_t d, hipStream_t stream) {
     const Tiling t = make_tiling(d, R, true, BLOCK);
     a.n_tiles = t.n_tiles;
     a.words_total = t.words_total;
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    return launch(ss::step_kernel<MT, NPTR, BLOCK, BW, R, HOLD_KB, LOADS_FIRST, HAS_M, VOTE, G>, grid, 0, stream, a, BLOCK);
+    return launch(ss::step_kernel<MT, NPTR, BLOCK, BW, R, HOLD_KB, LOADS_FIRST, HAS_M, G>, grid, 0, stream, a, BLOCK);
 }
 
 // what distinguishes the variants of the step (see ss_step_flags)
@@ -177,7 +184,7 @@ struct StepVariant {
 };
 
 // MT > 0: M fixed at compile time; MT == 0: any M up to SS_MAX_WORKERS
-template <int MT, bool HAS_M, bool VOTE, typename G>
+template <int MT, bool HAS_M, typename G>
 int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const *packed, float beta, float delta,
                   float *x, uint32_t *voted, StepVariant var, size_t d, hipStream_t stream) {
     constexpr int NPTR = MT > 0 ? MT : SS_MAX_WORKERS;
@@ -188,18 +195,10 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
     a.sums = var.sums;
     constexpr bool kBf16 = std::is_same<G, ss::Bf16Grad>::value;
     if constexpr (MT == 1) {
-        // a single worker is two or three streams whatever the shape: no cap needed
-        if constexpr (!VOTE && HAS_M) {
-            // pack over a large vector: one row per block, six blocks per unit
-            if (d >= kLargeD && caps_apply()) return launch_step_shape<1, NPTR, 256, 1, 1, 24, true, true, false, G>(a, d, stream);
-        }
-        if constexpr (VOTE) {
-            // the whole step for one worker (Algorithm 1, or Signum on one worker): the same shape from
-            // 2^27 coordinates on (+5-12 % without momentum, +1-8 % with)
-            if (d >= ((size_t)1 << 27) && caps_apply()) return launch_step_shape<1, NPTR, 256, 1, 1, 24, true, HAS_M, true, G>(a, d, stream);
-        }
-        constexpr int R = VOTE ? 2 : 4;
-        return launch_step_shape<1, NPTR, 256, 1, R, 0, false, HAS_M, VOTE, G>(a, d, stream);
+        // a single worker is two or three streams whatever the shape: two rows and no cap, and from 2^27
+        // coordinates on one row and six blocks per unit (+5-12 % without momentum, +1-8 % with)
+        if (d >= ((size_t)1 << 27) && caps_apply()) return launch_step_shape<1, NPTR, 256, 1, 1, 24, true, HAS_M, G>(a, d, stream);
+        return launch_step_shape<1, NPTR, 256, 1, 2, 0, false, HAS_M, G>(a, d, stream);
     } else {
         // Streaming shapes.  Each keeps roughly 16-24 KB of loads in flight per compute unit (see
         // step_kernels.hpp) and was picked by measurement among block sizes 64-1024, 1-8 workers per
@@ -208,21 +207,21 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
         if (d >= kStreamingMinD && lds_per_unit_kb() == kLdsPerUnitKB) {
             if constexpr (!HAS_M) {
                 // gradients only: four (bf16: eight) loads per lane make up for the missing momentum stream
-                return launch_step_shape<MT, NPTR, 256, 2, kBf16 ? 4 : 2, 64, true, false, VOTE, G>(a, d, stream);
+                return launch_step_shape<MT, NPTR, 256, 2, kBf16 ? 4 : 2, 64, true, false, G>(a, d, stream);
             } else if constexpr (!kBf16) {
                 // fp32: one 512-thread block per unit, one worker and one row at a time
-                return launch_step_shape<MT, NPTR, 512, 1, 1, 96, true, true, VOTE, G>(a, d, stream);
+                return launch_step_shape<MT, NPTR, 512, 1, 1, 96, true, true, G>(a, d, stream);
             } else {
                 // bf16 gradients (a wave's gradient load is half as long): from four workers on, four
                 // 128-thread blocks per unit that take two workers at a time; below that, two
                 // 256-thread blocks with two rows, the loads left to the compiler's own interleaving
-                if (M >= 4) return launch_step_shape<MT, NPTR, 128, 2, 1, 40, true, true, VOTE, G>(a, d, stream);
-                return launch_step_shape<MT, NPTR, 256, 1, 2, 64, false, true, VOTE, G>(a, d, stream);
+                if (M >= 4) return launch_step_shape<MT, NPTR, 128, 2, 1, 40, true, true, G>(a, d, stream);
+                return launch_step_shape<MT, NPTR, 256, 1, 2, 64, false, true, G>(a, d, stream);
             }
         }
         constexpr int R = MT > 0 ? latency_rows(MT, HAS_M) : 1;
         constexpr int BW = MT > 0 ? latency_batch(MT) : 8;
-        return launch_step_shape<MT, NPTR, 256, BW, R, 0, false, HAS_M, VOTE, G>(a, d, stream);
+        return launch_step_shape<MT, NPTR, 256, BW, R, 0, false, HAS_M, G>(a, d, stream);
     }
 }
 
@@ -230,11 +229,78 @@ template <bool HAS_M, typename G>
 int launch_step(int M, const void *const *g, float *const *m, uint32_t *const *packed, float beta,
                 float delta, float *x, uint32_t *voted, StepVariant var, size_t d, hipStream_t stream) {
 #define SS_CASE(n) \
-    case n: return launch_step_m<n, HAS_M, true, G>(M, g, m, packed, beta, delta, x, voted, var, d, stream)
+    case n: return launch_step_m<n, HAS_M, G>(M, g, m, packed, beta, delta, x, voted, var, d, stream)
     switch (M) {
         SS_CASE(1); SS_CASE(2); SS_CASE(3); SS_CASE(4); SS_CASE(5); SS_CASE(6); SS_CASE(7); SS_CASE(8);
         SS_CASE(16);
-        default: return launch_step_m<0, HAS_M, true, G>(M, g, m, packed, beta, delta, x, voted, var, d, stream);
+        default: return launch_step_m<0, HAS_M, G>(M, g, m, packed, beta, delta, x, voted, var, d, stream);
+    }
+#undef SS_CASE
+}
+
+// The workers' half of a step: n workers, one launch (see pack_kernel).
+template <int NPTR>
+int launch_pack_shape(void (*kernel)(ss::PackArgs<NPTR>), ss::PackArgs<NPTR> &a, int n, int block, int rows, int per_lane,
+                      hipStream_t stream) {
+    const Tiling t = make_tiling(a.d, rows, true, block, per_lane);
+    a.n_tiles = t.n_tiles;
+    a.words_total = t.words_total;
+    const size_t grid = t.n_tiles + t.tail_blocks;
+    if (grid > kMaxGrid) return SS_ERR_ARG;
+    return launch(kernel, grid, 0, stream, a, block, n);
+}
+
+template <int NPTR>
+int launch_pack(int n, const void *const *g, ss_dtype gdt, float *const *m, uint32_t *const *packed, float beta,
+                unsigned flags, size_t d, hipStream_t stream) {
+    ss::PackArgs<NPTR> a;
+    for (int w = 0; w < n; ++w) a.w[w] = ss::PackWorker{g[w], m ? m[w] : nullptr, packed[w]};
+    a.beta = beta;
+    a.omb = 1.0f - beta;
+    a.warmup = (flags & SS_STEP_WARMUP) ? 1 : 0;
+    a.d = d;
+    if (m) {
+        if (gdt == SS_F32) return launch_pack_shape(ss::pack_kernel<NPTR, 64, 1, true, ss::F32Grad>, a, n, 64, 1, 4, stream);
+        return launch_pack_shape(ss::pack_kernel<NPTR, 64, 1, true, ss::Bf16Grad>, a, n, 64, 1, 4, stream);
+    }
+    if (gdt == SS_BF16) return launch_pack_shape(ss::pack_bf16_kernel<NPTR, 64, 2>, a, n, 64, 2, 8, stream);
+    // fp32 gradients only: one worker at d = 25.6 M 16.2 us with four rows of 256 threads against 17.6
+    // with two of 128; several workers the other way round (d = 25.6 M, M = 8 130 against 127 us,
+    // d = 138 M, M = 16 1.55 against 1.39 ms)
+    if constexpr (NPTR == 1) return launch_pack_shape(ss::pack_kernel<1, 256, 4, false, ss::F32Grad>, a, n, 256, 4, 4, stream);
+    else return launch_pack_shape(ss::pack_kernel<NPTR, 128, 2, false, ss::F32Grad>, a, n, 128, 2, 4, stream);
+}
+
+// Vote and update from packed bits.  Four rows per block and four blocks per unit; from 2^28
+// coordinates on one row and no cap (d = 400 M, M = 8: 563 us against 590; d = 138 M, M = 16: 213 against 203).
+template <int MT>
+int launch_vote_apply(const uint32_t *const *packed, int M, uint32_t *voted, float *x, float delta, size_t d,
+                      hipStream_t stream) {
+    constexpr int NPTR = MT > 0 ? MT : SS_MAX_WORKERS;
+    ss::VoteApplyArgs<NPTR> a;
+    for (int w = 0; w < M; ++w) a.packed[w] = packed[w];
+    a.voted = voted;
+    a.x = x;
+    a.delta = delta;
+    a.M = M;
+    a.d = d;
+    a.words_total = ss_packed_bytes(d) / 4;
+    const bool large = d >= kLargeD;
+    const size_t words = large ? 32 : 128;
+    const size_t grid = (a.words_total + words - 1) / words;
+    if (grid > kMaxGrid) return SS_ERR_ARG;
+    if (large) return launch(ss::vote_apply_kernel<MT, NPTR, 1, 0>, grid, 0, stream, a);
+    return launch(ss::vote_apply_kernel<MT, NPTR, 4, 40>, grid, 0, stream, a);
+}
+
+int dispatch_vote_apply(const uint32_t *const *packed, int M, uint32_t *voted, float *x, float delta, size_t d,
+                        hipStream_t stream) {
+#define SS_CASE(n) \
+    case n: return launch_vote_apply<n>(packed, M, voted, x, delta, d, stream)
+    switch (M) {
+        SS_CASE(2); SS_CASE(3); SS_CASE(4); SS_CASE(5); SS_CASE(6); SS_CASE(7); SS_CASE(8);
+        SS_CASE(9); SS_CASE(10); SS_CASE(11); SS_CASE(12); SS_CASE(13); SS_CASE(14); SS_CASE(15); SS_CASE(16);
+        default: return launch_vote_apply<0>(packed, M, voted, x, delta, d, stream);
     }
 #undef SS_CASE
 }
@@ -331,19 +397,7 @@ static int signum_pack_impl(const void *g, ss_dtype gdt, float *m, float beta, u
     Span spans[3] = {span(g, d * grad_bytes(gdt), false), span(m, d * sizeof(float), true),
                      span(packed, ss_packed_bytes(d), true)};
     if (written_spans_overlap(spans, 3)) return SS_ERR_ARG;
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const void *gs[1] = {g};
-    float *ms[1] = {m};
-    uint32_t *ps[1] = {packed};
-    const StepVariant var{flags, nullptr};
-    if (m) {
-        if (gdt == SS_F32)
-            return launch_step_m<1, true, false, ss::F32Grad>(1, gs, ms, ps, beta, 0.0f, nullptr, nullptr, var, d, stream);
-        return launch_step_m<1, true, false, ss::Bf16Grad>(1, gs, ms, ps, beta, 0.0f, nullptr, nullptr, var, d, stream);
-    }
-    if (gdt == SS_F32)
-        return launch_step_m<1, false, false, ss::F32Grad>(1, gs, ms, ps, beta, 0.0f, nullptr, nullptr, var, d, stream);
-    return launch_step_m<1, false, false, ss::Bf16Grad>(1, gs, ms, ps, beta, 0.0f, nullptr, nullptr, var, d, stream);
+    return launch_pack<1>(1, &g, gdt, m ? &m : nullptr, &packed, beta, flags, d, static_cast<hipStream_t>(hip_stream));
 }
 
 int ss_signum_pack(const void *g, ss_dtype gdt, float *m, float beta, uint32_t *packed, size_t d,
@@ -449,22 +503,14 @@ int ss_signum_vote_step_ex(const void *const *g, ss_dtype gdt, float *const *m, 
         spans[n++] = span(sums_out, d, true);
         if (written_spans_overlap(spans, n)) return SS_ERR_ARG;
     }
-    // A large vector, and the caller wants every worker's bits anyway: then those buffers can carry
-    // the signs from launch to launch, and M pack launches + vote + apply (each touching two or
-    // three buffers chip-wide at a time) are never slower than the one-pass kernel that also writes
-    // the bits, and up to 10 % faster (measured for M = 2 .. 16 at 2^25, 1.4 * 2^27 and 2^29
-    // coordinates: fp32 0-8 %, bf16 2-10 %).  Same results, bit for bit.
-    if (packed_out && !sums_out && !(flags & SS_STEP_SUM_UPDATE) && d >= kSplitMinD && M >= kSplitMinWorkers) {
-        for (int w = 0; w < M; ++w) {
-            const int rc = signum_pack_impl(g[w], gdt, m ? m[w] : nullptr, beta, packed_out[w], d,
-                                            flags & SS_STEP_WARMUP, hip_stream);
-            if (rc != SS_OK) return rc;
-        }
-        const int rc = ss_majority_vote(packed_out, M, voted, d, hip_stream);
-        if (rc != SS_OK) return rc;
-        return ss_sign_apply(x, voted, delta, d, hip_stream);
-    }
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    if (packed_out && !sums_out && !(flags & SS_STEP_SUM_UPDATE) && split_pays(M, d)) {
+        // the caller's bit buffers carry the signs from one launch to the next; same results, bit for bit
+        const int rc = M <= 16 ? launch_pack<16>(M, g, gdt, m, packed_out, beta, flags, d, stream)
+                               : launch_pack<SS_MAX_WORKERS>(M, g, gdt, m, packed_out, beta, flags, d, stream);
+        if (rc != SS_OK) return rc;
+        return dispatch_vote_apply(packed_out, M, voted, x, delta, d, stream);
+    }
     const StepVariant var{flags, sums_out};
     if (m) {
         if (gdt == SS_F32)

@@ -6,8 +6,8 @@
 //             one 128-bit access per fp32 buffer, one 64-bit access for bf16
 //   8 lanes   own 32 consecutive coordinates = one packed word
 //   wave      64 lanes = 256 coordinates = 8 packed words
-//   block     B threads = 4 B coordinates per row, R rows per block (B = 256 = kBlock
-//             everywhere but in the step kernel's streaming shapes, which use 128-512)
+//   block     B threads = 4 B coordinates per row, R rows per block (B = 256 = kBlock where a
+//             kernel does not say otherwise; the step and pack kernels use 64-512)
 // The coordinates that do not fill a whole tile go through a scalar path in
 // extra blocks at the end of the same grid (one coordinate per lane; there a
 // wave ballot is already in packed-word order).
@@ -95,6 +95,14 @@ __device__ __forceinline__ uint32_t combine8(uint32_t nibble, int lane) {
     v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, false);
     v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E /* quad_perm [2,3,0,1] */, 0xF, 0xF, false);
     v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141 /* row_half_mirror */, 0xF, 0xF, false);
+    return v;
+}
+
+// the same for a byte of signs (8 coordinates) in each of 4 neighbouring lanes
+__device__ __forceinline__ uint32_t combine4(uint32_t byte, int lane) {
+    uint32_t v = byte << ((lane & 3) * 8);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, false);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E /* quad_perm [2,3,0,1] */, 0xF, 0xF, false);
     return v;
 }
 

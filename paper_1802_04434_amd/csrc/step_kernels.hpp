@@ -1,14 +1,15 @@
-// The streaming kernel behind ss_signum_vote_step and ss_signum_pack.
+// The streaming kernels behind ss_signum_vote_step and ss_signum_pack.
 //
-// One template covers both: per worker the momentum update and sign of
-// Algorithm 2 (or the plain sign of Algorithm 1), the optional per-worker
-// packed bits, and - when VOTE is set - the majority vote and parameter
-// update of Algorithm 3, all while each gradient, momentum and parameter
-// element is read once and written once (arxiv 1802.04434).
+// step_kernel does the whole step in one pass: per worker the momentum update
+// and sign of Algorithm 2 (or the plain sign of Algorithm 1), the optional
+// per-worker packed bits, the majority vote and the parameter update of
+// Algorithm 3, each gradient, momentum and parameter element read once and
+// written once (arxiv 1802.04434).  pack_kernel does the workers' half alone,
+// for one worker or for all of them in one launch.
 //
 // The path is bound by HBM traffic (12 bytes per worker and coordinate plus
 // 8 for x, against a handful of ALU operations).  What decides how close to
-// the DRAM's rate it runs, all measured on MI355X:
+// the DRAM's rate step_kernel runs, all measured on MI355X:
 //
 //  * The loads of a stage (BW workers x R rows, gradient and momentum) are
 //    issued into registers before the first dependent operation or store: a
@@ -35,14 +36,14 @@ namespace ss {
 template <int NPTR>
 struct StepArgs {
     PtrTable<NPTR> p;
-    float *x;            // VOTE only
-    uint32_t *voted;     // VOTE only
+    float *x;
+    uint32_t *voted;
     float beta, omb, delta;
     int M;               // number of workers in use (<= NPTR)
     int write_packed;    // per-worker bits wanted
     int warmup;          // Theorem 3 warm-up: signs come from g while m is still updated
     int sum_update;      // Section 4 "(good)": x <- x - delta * (sum of signs) instead of its sign
-    int8_t *sums;        // VOTE only, may be NULL: per-coordinate sum of signs
+    int8_t *sums;        // may be NULL: per-coordinate sum of signs
     size_t d;            // coordinates
     size_t n_tiles;      // blocks on the vector path (R rows of kRowCoords coordinates each)
     size_t words_total;  // words of a packed buffer including zero padding
@@ -130,7 +131,7 @@ __device__ __forceinline__ void step_stage(const StepArgs<NPTR> &a, int w0, cons
 // R      : rows per block
 // HOLD_KB: kilobytes of LDS the block reserves and never uses, which caps how
 //          many blocks share a compute unit (0: no cap)
-template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB, bool LOADS_FIRST, bool HAS_M, bool VOTE, typename G>
+template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB, bool LOADS_FIRST, bool HAS_M, typename G>
 __global__ __launch_bounds__(BLOCK) void step_kernel(const StepArgs<NPTR> a) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -147,34 +148,32 @@ __global__ __launch_bounds__(BLOCK) void step_kernel(const StepArgs<NPTR> a) {
         for (int r = 0; r < R; ++r) {
             q[r] = (tile * R + r) * BLOCK + tid;
             counts[r] = 0;
-            if (VOTE) xv[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + q[r]);
+            xv[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + q[r]);
         }
         int w0 = 0;
         if constexpr (BW > 1) {
             for (; w0 + BW <= M; w0 += BW) step_stage<BW, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, q, counts, lane);
         }
         for (; w0 < M; ++w0) step_stage<1, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, q, counts, lane);
-        if (VOTE) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const uint32_t nib = vote_nibble(counts[r], T);
-                f32x4 v = xv[r];
-                if (a.sum_update) {
-                    v.x = step_sum(v.x, a.delta, sum_at(counts[r], 0, M));
-                    v.y = step_sum(v.y, a.delta, sum_at(counts[r], 1, M));
-                    v.z = step_sum(v.z, a.delta, sum_at(counts[r], 2, M));
-                    v.w = step_sum(v.w, a.delta, sum_at(counts[r], 3, M));
-                } else {
-                    v.x = step(v.x, a.delta, nib & 1u);
-                    v.y = step(v.y, a.delta, nib & 2u);
-                    v.z = step(v.z, a.delta, nib & 4u);
-                    v.w = step(v.w, a.delta, nib & 8u);
-                }
-                st_stream(reinterpret_cast<f32x4 *>(a.x) + q[r], v);
-                if (a.sums) reinterpret_cast<uint32_t *>(a.sums)[q[r]] = sums_word(counts[r], M);
-                const uint32_t word = combine8(nib, lane);
-                if ((lane & 7) == 0) a.voted[q[r] >> 3] = word;
+        for (int r = 0; r < R; ++r) {
+            const uint32_t nib = vote_nibble(counts[r], T);
+            f32x4 v = xv[r];
+            if (a.sum_update) {
+                v.x = step_sum(v.x, a.delta, sum_at(counts[r], 0, M));
+                v.y = step_sum(v.y, a.delta, sum_at(counts[r], 1, M));
+                v.z = step_sum(v.z, a.delta, sum_at(counts[r], 2, M));
+                v.w = step_sum(v.w, a.delta, sum_at(counts[r], 3, M));
+            } else {
+                v.x = step(v.x, a.delta, nib & 1u);
+                v.y = step(v.y, a.delta, nib & 2u);
+                v.z = step(v.z, a.delta, nib & 4u);
+                v.w = step(v.w, a.delta, nib & 8u);
             }
+            st_stream(reinterpret_cast<f32x4 *>(a.x) + q[r], v);
+            if (a.sums) reinterpret_cast<uint32_t *>(a.sums)[q[r]] = sums_word(counts[r], M);
+            const uint32_t word = combine8(nib, lane);
+            if ((lane & 7) == 0) a.voted[q[r] >> 3] = word;
         }
         return;
     }
@@ -205,15 +204,134 @@ __global__ __launch_bounds__(BLOCK) void step_kernel(const StepArgs<NPTR> a) {
             if (writes_word) a.p.packed[w][word] = (uint32_t)(lane == 0 ? mask : mask >> 32);
         }
     }
-    if (VOTE) {
-        const bool vneg = in && count >= T;
-        if (in) {
-            a.x[i] = a.sum_update ? step_sum(a.x[i], a.delta, M - 2 * count) : step(a.x[i], a.delta, vneg);
-            if (a.sums) a.sums[i] = (int8_t)(M - 2 * count);
-        }
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(vneg);
-        if (writes_word) a.voted[word] = (uint32_t)(lane == 0 ? mask : mask >> 32);
+    const bool vneg = in && count >= T;
+    if (in) {
+        a.x[i] = a.sum_update ? step_sum(a.x[i], a.delta, M - 2 * count) : step(a.x[i], a.delta, vneg);
+        if (a.sums) a.sums[i] = (int8_t)(M - 2 * count);
     }
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(vneg);
+    if (writes_word) a.voted[word] = (uint32_t)(lane == 0 ? mask : mask >> 32);
+}
+
+// ---------------------------------------------------------------- pack ----
+
+struct PackWorker {
+    const void *g;
+    float *m;            // NULL without momentum
+    uint32_t *packed;
+};
+
+template <int NPTR>
+struct PackArgs {
+    PackWorker w[NPTR];  // blockIdx.y selects the worker
+    float beta, omb;
+    int warmup;          // Theorem 3 warm-up: signs come from g while m is still updated
+    size_t d;
+    size_t n_tiles;      // blocks on the vector path, R rows of BLOCK * 4 coordinates each
+    size_t words_total;  // words of a packed buffer including zero padding
+};
+
+// What does not fill a tile, and the zero padding: one coordinate per lane, the wave ballot is two
+// packed words in order.
+template <bool HAS_M, typename G, int NPTR>
+__device__ __forceinline__ void pack_tail(const PackArgs<NPTR> &a, const PackWorker &w, size_t i, int lane) {
+    const bool in = i < a.d;
+    float v = 0.0f;
+    if (in) {
+        const float gi = G::load1(w.g, i);
+        v = gi;
+        if (HAS_M) {
+            v = momentum(a.beta, a.omb, w.m[i], gi);
+            w.m[i] = v;
+            if (a.warmup) v = gi;
+        }
+    }
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(in && v < 0.0f);
+    const size_t word = i >> 5;
+    if ((lane & 31) == 0 && word < a.words_total) w.packed[word] = (uint32_t)(lane == 0 ? mask : mask >> 32);
+}
+
+// Momentum update, sign and packed bits of Algorithm 2 for NPTR >= gridDim.y workers (m == NULL:
+// Algorithm 1's sign of g).  Bound by HBM: 12.125 bytes per worker and coordinate with fp32
+// gradients.  The grid is worker-major - all of a worker's tiles, then the next worker's - so that
+// only three buffers are open chip-wide at a time, and a launch over all workers has one tail
+// where M launches have M.
+//
+// With momentum a block is ONE wave with one row: the dispatcher refills a finished wave's slot at
+// once, where a block of four holds its slots until its slowest wave is done.  Measured against
+// 256 threads of one / four rows, none with a cap on the resident blocks (the cap that step_kernel
+// needs for its 2M + 1 streams gains nothing here): d = 25.6 M, M = 7 fp32 320 us against 332 / 342
+// (6,780 GB/s), d = 138 M, M = 16 3.94 ms against 4.11 / 4.44 (6,816 GB/s), d = 400 M, M = 8 bf16
+// 4.89 ms against 5.00 / 5.52; 1.1 M, M = 7 15.4 us against 15.8 / 16.1.  Without momentum there is
+// one stream and a lane wants more rows in flight; the host's launch_pack has those shapes.
+template <int NPTR, int BLOCK, int R, bool HAS_M, typename G>
+__global__ __launch_bounds__(BLOCK) void pack_kernel(const PackArgs<NPTR> a) {
+    const PackWorker w = a.w[NPTR == 1 ? 0 : blockIdx.y];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const size_t tile = blockIdx.x;
+    if (tile < a.n_tiles) {
+        size_t q[R];
+        f32x4 gv[R], mv[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            q[r] = (tile * R + r) * BLOCK + tid;
+            gv[r] = G::load4(w.g, q[r]);
+            if (HAS_M) mv[r] = ld_stream(reinterpret_cast<const f32x4 *>(w.m) + q[r]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            f32x4 v = gv[r];
+            if (HAS_M) {
+                v.x = momentum(a.beta, a.omb, mv[r].x, v.x);
+                v.y = momentum(a.beta, a.omb, mv[r].y, v.y);
+                v.z = momentum(a.beta, a.omb, mv[r].z, v.z);
+                v.w = momentum(a.beta, a.omb, mv[r].w, v.w);
+                st_stream(reinterpret_cast<f32x4 *>(w.m) + q[r], v);
+            }
+            const uint32_t word = combine8(neg_nibble((HAS_M && a.warmup) ? gv[r] : v), lane);
+            if ((lane & 7) == 0) w.packed[q[r] >> 3] = word;
+        }
+        return;
+    }
+    pack_tail<HAS_M, G>(a, w, a.n_tiles * (size_t)(R * BLOCK * kQuad) + (tile - a.n_tiles) * BLOCK + tid, lane);
+}
+
+// pack_kernel for bf16 gradients without momentum: a lane loads 128 bits - eight coordinates, one
+// byte of signs - and four lanes share a word.  The quad geometry above halves the gradient's
+// loads to 64 bits and doubles their number: d = 25.6 M, M = 8 68 us (6,390 GB/s) against 78 with
+// four rows of 256 threads and quads, d = 138 M, M = 16 720 us against 833, one worker at 25.6 M
+// 9.8 against 10.8.
+template <int NPTR, int BLOCK, int R>
+__global__ __launch_bounds__(BLOCK) void pack_bf16_kernel(const PackArgs<NPTR> a) {
+    const PackWorker w = a.w[NPTR == 1 ? 0 : blockIdx.y];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const size_t tile = blockIdx.x;
+    if (tile < a.n_tiles) {
+        size_t o[R];    // octet of coordinates
+        u32x4 gv[R];    // eight bf16, the lower coordinate in the lower half of a word
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            o[r] = (tile * R + r) * BLOCK + tid;
+            gv[r] = ld_stream(reinterpret_cast<const u32x4 *>(w.g) + o[r]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            uint32_t byte = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                byte |= neg_bit(widen_bf16((uint16_t)gv[r][k])) << (2 * k);
+                byte |= neg_bit(widen_bf16((uint16_t)(gv[r][k] >> 16))) << (2 * k + 1);
+            }
+            const uint32_t word = combine4(byte, lane);
+            if ((lane & 3) == 0) w.packed[o[r] >> 2] = word;
+        }
+        return;
+    }
+    pack_tail<false, Bf16Grad>(a, w, a.n_tiles * (size_t)(R * BLOCK * 2 * kQuad) + (tile - a.n_tiles) * BLOCK + tid, lane);
 }
 
 }  // namespace ss

@@ -212,6 +212,102 @@ __global__ __launch_bounds__(kBlock) void apply_kernel(const ApplyArgs a) {
     }
 }
 
+// ------------------------------------------------------- vote + apply ----
+// The server's vote and the workers' update in one launch, for a step whose sign bits are in
+// memory already (pack_kernel over all workers): the voted word goes from the lane that computes
+// it through LDS to the lanes that own its coordinates of x, instead of through HBM and another
+// launch.
+
+template <int NPTR>
+struct VoteApplyArgs {
+    const uint32_t *packed[NPTR];
+    uint32_t *voted;
+    float *x;
+    float delta;
+    int M;
+    size_t d;
+    size_t words_total;   // words of a packed buffer including zero padding
+};
+
+// MT workers at compile time; MT == 0: a.M at run time, added into binary count planes.
+// A block owns R rows of 1024 coordinates: its first 32 R lanes vote on a word each.  Bound by HBM:
+// 8.125 + M / 8 bytes per coordinate; d = 25.6 M, M = 7: 34.5 us (6,650 GB/s) where the two
+// launches take 5.4 + 33.2 us and a gap.  HOLD_KB caps the blocks per compute unit.
+template <int MT, int NPTR, int R, int HOLD_KB>
+__global__ __launch_bounds__(kBlock) void vote_apply_kernel(const VoteApplyArgs<NPTR> a) {
+    reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.voted);
+    constexpr int kWords = 32 * R;   // voted words of a block
+    __shared__ uint32_t vote[kWords];
+    const int tid = threadIdx.x;
+    const size_t wi = (size_t)blockIdx.x * kWords + tid;
+    const size_t base = (size_t)blockIdx.x * (R * kRowCoords);
+    const bool full = base + (size_t)(R * kRowCoords) <= a.d;
+    const bool votes = tid < kWords && wi < a.words_total;
+    uint32_t in[MT > 0 ? MT : 1];
+    if (MT > 0 && votes) {
+#pragma unroll
+        for (int w = 0; w < MT; ++w) in[w] = a.packed[w][wi];
+    }
+    f32x4 xv[R];
+    f32x4 *const xq = reinterpret_cast<f32x4 *>(a.x + base) + tid;
+    if (full) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) xv[r] = ld_stream(xq + r * kBlock);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (votes) {
+        uint32_t ge;
+        if constexpr (MT > 0) {
+            ge = majority_word<MT>(in);
+        } else {
+            const int T = a.M / 2 + 1;
+            uint32_t plane[kPlanes];
+#pragma unroll
+            for (int k = 0; k < kPlanes; ++k) plane[k] = 0;
+            for (int w0 = 0; w0 < a.M; w0 += 8) {
+                uint32_t word[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) word[j] = a.packed[w0 + j < a.M ? w0 + j : w0][wi];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    uint32_t carry = w0 + j < a.M ? word[j] : 0u;
+#pragma unroll
+                    for (int k = 0; k < kPlanes; ++k) {
+                        const uint32_t t = plane[k] & carry;
+                        plane[k] ^= carry;
+                        carry = t;
+                    }
+                }
+            }
+            ge = 0xFFFFFFFFu;
+#pragma unroll
+            for (int k = 0; k < kPlanes; ++k) ge = ge_step(ge, plane[k], T, k);
+        }
+        ge &= live_mask(wi, a.d);
+        a.voted[wi] = ge;
+        vote[tid] = ge;
+    }
+    __syncthreads();
+    if (full) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t nib = vote[r * 32 + (tid >> 3)] >> ((tid & 7) * 4);
+            f32x4 v = xv[r];
+            v.x = step(v.x, a.delta, nib & 1u);
+            v.y = step(v.y, a.delta, nib & 2u);
+            v.z = step(v.z, a.delta, nib & 4u);
+            v.w = step(v.w, a.delta, nib & 8u);
+            st_stream(xq + r * kBlock, v);
+        }
+        return;
+    }
+    // the last block: one coordinate per lane
+    for (int i = tid; base + i < a.d; i += kBlock) {
+        const bool neg = (vote[i >> 5] >> (i & 31)) & 1u;
+        a.x[base + i] = step(a.x[base + i], a.delta, neg);
+    }
+}
+
 // ------------------------------------------------ "(good)": vote sums ----
 // Section 4's first scheme sends back the sum of the workers' signs instead of
 // its sign.  Bit-sliced like the vote: a lane loads 128 coordinates (four words)
