@@ -102,11 +102,17 @@ inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = s
 
 // ------------------------------------------------------------------------
 // Launch shapes of the step kernel (see step_kernels.hpp for the reasoning).
-//   streaming shape, d >= kStreamingMinD and several workers: one worker at a
-//     time, and a reservation of LDS that no kernel touches, sized so that the
+//   streaming shape, several workers and more data than the 256 MB memory-side cache holds: one or
+//     two workers at a time, and a reservation of LDS that no kernel touches, sized so that the
 //     wanted number of blocks fits in a compute unit's LDS
-//   latency shape, smaller d: all workers' loads at once, no cap
-constexpr size_t kStreamingMinD = (size_t)1 << 20;
+//   latency shape, everything smaller: one-wave blocks that issue the loads of up to eight workers
+//     at once, no cap
+// The line between them, by graph replay over three sets of buffers (us, latency against streaming
+// shape): fp32 M = 7 1.1 M coordinates (92 MB) 19.1 / 22.8, 2.2 M 37.4 / 39.6, 4.4 M 72.2 / 72.1,
+// 12 M 194 / 184; M = 2 4.4 M 25.0 / 27.8; M = 16 1.1 M 42.4 / 47.6, 2.2 M (422 MB) 85 / 84; bf16 M = 8
+// 2.2 M 35.4 / 36.8; gradients only: fp32 M = 7 4.4 M (123 MB) 27.6 / 29.9, 12 M (336 MB) 72.9 / 72.0,
+// bf16 M = 8 4.4 M 19.2 / 22.9, 12 M (192 MB) 48.6 / 52.2.
+inline bool streams(int M, size_t d, size_t worker_bytes) { return d * (size_t)M * worker_bytes >= ((size_t)1 << 28); }
 constexpr int kLdsPerUnitKB = 160;   // what the reservations below assume; checked against the device
 
 // Given packed_out buffers, the step runs as two launches - pack_kernel over all workers, then vote
@@ -139,12 +145,6 @@ constexpr size_t kLargeD = (size_t)1 << 28;
 
 // the reservations are sized for a unit with kLdsPerUnitKB of LDS: on anything else, no cap
 inline bool caps_apply() { return lds_per_unit_kb() == kLdsPerUnitKB; }
-
-constexpr int latency_rows(int m, bool has_m) {
-    const int streams = m * (has_m ? 2 : 1);
-    return streams >= 8 ? 1 : streams >= 4 ? 2 : 4;
-}
-constexpr int latency_batch(int m) { return m < 8 ? m : 8; }
 
 template <int NPTR>
 void fill_step_args(ss::StepArgs<NPTR> &a, int M, const void *const *g, float *const *m, uint32_t *const *packed,
@@ -195,16 +195,17 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
     a.sums = var.sums;
     constexpr bool kBf16 = std::is_same<G, ss::Bf16Grad>::value;
     if constexpr (MT == 1) {
-        // a single worker is two or three streams whatever the shape: two rows and no cap, and from 2^27
-        // coordinates on one row and six blocks per unit (+5-12 % without momentum, +1-8 % with)
-        if (d >= ((size_t)1 << 27) && caps_apply()) return launch_step_shape<1, NPTR, 256, 1, 1, 24, true, HAS_M, G>(a, d, stream);
+        // a single worker is two or three streams whatever the shape: no cap; from 2^25 coordinates on
+        // one-wave blocks (138 M: 460 us against 500, without momentum 257 / 284, bf16 217 / 236; 60 M:
+        // 200 / 208, 112 / 122, 97 / 100; at 25.6 M 87 / 86, 51 / 51, 43 / 43)
+        if (d >= ((size_t)1 << 25)) return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, HAS_M, G>(a, d, stream);
         return launch_step_shape<1, NPTR, 256, 1, 2, 0, false, HAS_M, G>(a, d, stream);
     } else {
         // Streaming shapes.  Each keeps roughly 16-24 KB of loads in flight per compute unit (see
         // step_kernels.hpp) and was picked by measurement among block sizes 64-1024, 1-8 workers per
         // stage, 1-8 rows and 1-5 blocks per unit, with the workloads' own buffer placement.  The
         // reservations only mean what they should on a part with the LDS size they were sized for.
-        if (d >= kStreamingMinD && lds_per_unit_kb() == kLdsPerUnitKB) {
+        if (streams(M, d, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0)) && lds_per_unit_kb() == kLdsPerUnitKB) {
             if constexpr (!HAS_M) {
                 // gradients only: four (bf16: eight) loads per lane make up for the missing momentum stream
                 return launch_step_shape<MT, NPTR, 256, 2, kBf16 ? 4 : 2, 64, true, false, G>(a, d, stream);
@@ -219,9 +220,14 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
                 return launch_step_shape<MT, NPTR, 256, 1, 2, 64, false, true, G>(a, d, stream);
             }
         }
-        constexpr int R = MT > 0 ? latency_rows(MT, HAS_M) : 1;
-        constexpr int BW = MT > 0 ? latency_batch(MT) : 8;
-        return launch_step_shape<MT, NPTR, 256, BW, R, 0, false, HAS_M, G>(a, d, stream);
+        // Latency shape.  Four waves a block, two or four rows where a worker or three leave room for them
+        // and the compiler's order of the loads (what this was before): d = 272,474 fp32 M = 7 6.2 us
+        // against 5.5, M = 3 3.7 / 2.8, M = 16 13.5 / 11.0, M = 15 13.6 / 10.6 (its last seven workers are
+        // one stage now); 10,007 M = 3 2.8 / 2.2.  Sixteen workers' gradients alone keep four waves
+        // (272,474: 5.6 against 5.8; 700,001: 9.2 against 9.6).
+        constexpr int BW = MT > 0 && MT < 8 ? MT : 8;
+        constexpr int B = !HAS_M && MT == 16 ? 256 : 64;
+        return launch_step_shape<MT, NPTR, B, BW, 1, 0, true, HAS_M, G>(a, d, stream);
     }
 }
 
@@ -347,6 +353,8 @@ int launch_ternary_shape(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     if (grid > kMaxGrid) return SS_ERR_ARG;
     return launch(ss::ternary_step_kernel<BLOCK, BW, R, HOLD_KB, LOADS_FIRST, HAS_M, VOTE, G>, grid, 0, stream, a, BLOCK);
 }
+
+constexpr size_t kStreamingMinD = (size_t)1 << 20;
 
 template <bool HAS_M, bool VOTE, typename G>
 int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {

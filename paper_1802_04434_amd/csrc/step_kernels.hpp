@@ -26,8 +26,8 @@
 //    The host picks the shape (launch_step_m in api.hip).
 //  * A tile costs (number of stages) x (one memory latency); the x load goes out
 //    with the first stage's loads and the x store overlaps the next tile.
-//    Small d is latency bound instead: there all M workers' loads go out
-//    together (BW = M) and nothing is held back.
+//    Small d is latency bound instead: there the loads of up to eight workers
+//    go out together from one-wave blocks, and nothing is held back.
 #pragma once
 #include "common.hpp"
 
@@ -123,11 +123,22 @@ __device__ __forceinline__ void step_stage(const StepArgs<NPTR> &a, int w0, cons
     if (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
 }
 
+// the n <= NMAX workers that the full stages leave over, as one stage of exactly that size
+template <int NMAX, int R, int BLOCK, bool LOADS_FIRST, bool HAS_M, typename G, int NPTR>
+__device__ __forceinline__ void step_rest(const StepArgs<NPTR> &a, int w0, int n, const size_t (&q)[R],
+                                          uint32_t (&counts)[R], int lane) {
+    if (n == NMAX) {
+        step_stage<NMAX, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, q, counts, lane);
+    } else if constexpr (NMAX > 1) {
+        step_rest<NMAX - 1, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, n, q, counts, lane);
+    }
+}
+
 // MT  > 0: number of workers known at compile time (M == MT)
 // MT == 0: a.M workers, looped at run time
 // BLOCK  : threads per block (a row is BLOCK * 4 coordinates)
 // BW     : workers per stage (whose loads are issued together); what M leaves
-//          over after the full stages goes one worker at a time
+//          over after the full stages is one smaller stage
 // R      : rows per block
 // HOLD_KB: kilobytes of LDS the block reserves and never uses, which caps how
 //          many blocks share a compute unit (0: no cap)
@@ -151,10 +162,12 @@ __global__ __launch_bounds__(BLOCK) void step_kernel(const StepArgs<NPTR> a) {
             xv[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + q[r]);
         }
         int w0 = 0;
-        if constexpr (BW > 1) {
-            for (; w0 + BW <= M; w0 += BW) step_stage<BW, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, q, counts, lane);
+        for (; w0 + BW <= M; w0 += BW) step_stage<BW, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, q, counts, lane);
+        if constexpr (MT > 0) {
+            if constexpr (MT % BW != 0) step_stage<MT % BW, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, q, counts, lane);
+        } else if constexpr (BW > 1) {
+            step_rest<BW - 1, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, M - w0, q, counts, lane);
         }
-        for (; w0 < M; ++w0) step_stage<1, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, q, counts, lane);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const uint32_t nib = vote_nibble(counts[r], T);
