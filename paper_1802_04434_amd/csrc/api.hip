@@ -354,26 +354,34 @@ int launch_ternary_shape(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     return launch(ss::ternary_step_kernel<BLOCK, BW, R, HOLD_KB, LOADS_FIRST, HAS_M, VOTE, G>, grid, 0, stream, a, BLOCK);
 }
 
-constexpr size_t kStreamingMinD = (size_t)1 << 20;
-
+// The ternary kernel takes any M at run time.  Below the line of streams() it runs one-wave blocks with
+// the loads of up to eight workers out first (d = 272,474: fp32 M = 7 6.0 us against 11.3 with two rows of
+// 256 threads and one worker at a time, M = 12 9.1 / 17.7, without momentum M = 7 3.7 / 9.3; 1.1 M, M = 7
+// 18.9 / 25.2; one worker at 60 M 185 / 200).  Above it, gradients only, the same with two rows and about
+// fifteen blocks per unit (138 M: fp32 M = 7 845 us against 902 for two workers a stage and 1,320 for one,
+// bf16 M = 8 550 / 649 / 1,010; 17.6 M: 109 / 118 / 172 and 73 / 87 / 132).
 template <bool HAS_M, bool VOTE, typename G>
 int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     constexpr bool kBf16 = std::is_same<G, ss::Bf16Grad>::value;
-    if (VOTE && a.M >= 2 && d >= kStreamingMinD && lds_per_unit_kb() == kLdsPerUnitKB) {
-        // bf16 gradients with momentum, from four workers on: the binary step's shape for that case
-        if (kBf16 && HAS_M && a.M >= 4) return launch_ternary_shape<128, 2, 1, 40, true, HAS_M, VOTE, G>(a, d, stream);
-        // otherwise two blocks per unit, one worker at a time (the one-block-per-unit shape of
-        // the binary step measured 7 % slower here)
-        return launch_ternary_shape<256, 1, 2, 64, false, HAS_M, VOTE, G>(a, d, stream);
-    }
-    if constexpr (!VOTE && HAS_M) {
-        // one worker's ternary pack: four blocks of two rows per unit, six of one row over a large vector
-        if (caps_apply()) {
-            if (d >= kLargeD) return launch_ternary_shape<256, 1, 1, 24, true, true, false, G>(a, d, stream);
-            if (d >= kStreamingMinD) return launch_ternary_shape<256, 1, 2, 40, true, true, false, G>(a, d, stream);
+    if constexpr (VOTE) {
+        if (a.M >= 2 && streams(a.M, d, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0)) && caps_apply()) {
+            if constexpr (!HAS_M) {
+                return launch_ternary_shape<64, 8, 2, 10, true, false, true, G>(a, d, stream);
+            } else {
+                // bf16 gradients with momentum, from four workers on: the binary step's shape for that case
+                if (kBf16 && a.M >= 4) return launch_ternary_shape<128, 2, 1, 40, true, true, true, G>(a, d, stream);
+                // otherwise two blocks per unit, one worker at a time (the one-block-per-unit shape of
+                // the binary step measured 7 % slower here)
+                return launch_ternary_shape<256, 1, 2, 64, false, true, true, G>(a, d, stream);
+            }
         }
+        return launch_ternary_shape<64, 8, 1, 0, true, HAS_M, true, G>(a, d, stream);
+    } else if constexpr (HAS_M) {
+        // one worker's ternary pack: pack_kernel's shape
+        return launch_ternary_shape<64, 1, 1, 0, true, true, false, G>(a, d, stream);
+    } else {
+        return launch_ternary_shape<256, 1, 2, 0, false, false, false, G>(a, d, stream);
     }
-    return launch_ternary_shape<256, 1, 2, 0, false, HAS_M, VOTE, G>(a, d, stream);
 }
 
 template <bool VOTE>

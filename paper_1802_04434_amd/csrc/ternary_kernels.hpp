@@ -11,8 +11,8 @@
 // "negative" and "zero" (never both set).
 //
 // The kernels mirror the binary ones: a streaming kernel for the worker's pack
-// and for the fused step (one worker at a time, same lane geometry, optional
-// cap on resident blocks through an LDS reservation), a small server kernel and an apply kernel.
+// and for the fused step (same lane geometry and stages, optional cap on resident
+// blocks through an LDS reservation), a small server kernel and an apply kernel.
 #pragma once
 #include "step_kernels.hpp"
 #include "vote_apply_kernels.hpp"
@@ -96,7 +96,18 @@ __device__ __forceinline__ void ternary_stage(const TernaryStepArgs &a, int w0, 
     if (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
 }
 
-// BLOCK threads per block, BW workers per stage (what M leaves over goes one at a time), R rows
+// the n <= NMAX workers that the full stages leave over, as one stage of exactly that size
+template <int NMAX, int R, bool LOADS_FIRST, bool HAS_M, bool VOTE, typename G>
+__device__ __forceinline__ void ternary_rest(const TernaryStepArgs &a, int w0, int n, const size_t (&q)[R],
+                                             uint32_t (&n_neg)[R], uint32_t (&n_zero)[R], int lane) {
+    if (n == NMAX) {
+        ternary_stage<NMAX, R, LOADS_FIRST, HAS_M, VOTE, G>(a, w0, q, n_neg, n_zero, lane);
+    } else if constexpr (NMAX > 1) {
+        ternary_rest<NMAX - 1, R, LOADS_FIRST, HAS_M, VOTE, G>(a, w0, n, q, n_neg, n_zero, lane);
+    }
+}
+
+// BLOCK threads per block, BW workers per stage (what M leaves over is one smaller stage), R rows
 // per block, HOLD_KB of LDS reserved to cap the blocks per compute unit, LOADS_FIRST as in the
 // binary step kernel
 template <int BLOCK, int BW, int R, int HOLD_KB, bool LOADS_FIRST, bool HAS_M, bool VOTE, typename G>
@@ -119,10 +130,8 @@ __global__ __launch_bounds__(BLOCK) void ternary_step_kernel(const TernaryStepAr
             if (VOTE) xv[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + q[r]);
         }
         int w0 = 0;
-        if constexpr (BW > 1) {
-            for (; w0 + BW <= M; w0 += BW) ternary_stage<BW, R, LOADS_FIRST, HAS_M, VOTE, G>(a, w0, q, n_neg, n_zero, lane);
-        }
-        for (; w0 < M; ++w0) ternary_stage<1, R, LOADS_FIRST, HAS_M, VOTE, G>(a, w0, q, n_neg, n_zero, lane);
+        for (; w0 + BW <= M; w0 += BW) ternary_stage<BW, R, LOADS_FIRST, HAS_M, VOTE, G>(a, w0, q, n_neg, n_zero, lane);
+        if constexpr (BW > 1) ternary_rest<BW - 1, R, LOADS_FIRST, HAS_M, VOTE, G>(a, w0, M - w0, q, n_neg, n_zero, lane);
         if (VOTE) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {

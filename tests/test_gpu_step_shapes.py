@@ -94,3 +94,24 @@ def test_step_on_both_sides_of_a_launch_shape(ss, oracle, d, M, dtype, momentum)
     for w in range(M if momentum else 0):
         assert_same_floats(m_dev[w], m[w], "m[%d]" % w)
     assert_same_floats(x_dev, x, "x")
+
+
+@pytest.mark.parametrize("d,M,dtype,momentum", [
+    (1, 9, "f32", True), (255, 8, "bf16", True), (257, 15, "f32", False), (70_001, 16, "bf16", True), (70_001, 23, "f32", False),
+    ((1 << 28) // 28 + 511, 7, "f32", False), ((1 << 28) // 32 + 1, 16, "bf16", False), ((1 << 28) // 24 - 300, 2, "f32", True),
+])
+def test_ternary_step(ss, oracle, d, M, dtype, momentum):
+    # stages of eight workers and what they leave over, and both sides of the 2^28-byte rule
+    rng = np.random.default_rng(d + M)
+    g = [make_grad(rng, d, dtype, scale=0.2) for _ in range(M)]
+    m = [make_momentum(rng, d) for _ in range(M)] if momentum else None
+    x = (rng.standard_normal(d) * 0.05).astype(np.float32)
+    m_dev = [torch.from_numpy(a).to(DEV) for a in m] if momentum else None
+    x_dev = torch.from_numpy(x).to(DEV)
+    neg, zero = dirty_bits(ss, d), dirty_bits(ss, d)
+    ss.signum_vote_step_ternary([t.to(DEV) for t in g], m_dev, 0.9, 0.1, 2, 1e-4, x_dev, neg, zero)
+    want_neg, want_zero = oracle.signum_vote_step_ternary([synth.as_numpy(t) for t in g], m, 0.9, 0.1, 2, 1e-4, x)
+    assert np.array_equal(bits_np(neg), want_neg) and np.array_equal(bits_np(zero), want_zero)
+    for w in range(M if momentum else 0):
+        assert_same_floats(m_dev[w], m[w], "m[%d]" % w)
+    assert_same_floats(x_dev, x, "x")
