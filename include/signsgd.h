@@ -196,6 +196,27 @@ int ss_signum_vote_step_ex(const void *const *g, ss_dtype gdt, float *const *m,
                            int8_t *sums_out, size_t d, unsigned flags,
                            void *hip_stream);
 
+/*
+ * ss_signum_vote_step_ex for a caller that can lend device memory for the length
+ * of the call: with it a large step runs as two launches that hand the workers'
+ * bits over through that memory (over slabs of the vector, should it be small),
+ * which is 3-10 % faster than one pass over all workers' buffers at once.  Results
+ * are the same, bit for bit.
+ *   scratch        work  scratch_bytes of device memory, 16-byte aligned, contents
+ *                        immaterial before and after; it must stay untouched by others
+ *                        until the enqueued work has run.  NULL or too small to help:
+ *                        one pass, as ss_signum_vote_step_ex.
+ * ss_step_scratch_bytes is the size that helps (128 MiB at most), 0 where one pass
+ * is as fast.  Everything else as for ss_signum_vote_step_ex; on SS_ERR_HIP the
+ * launches before the refused one stay enqueued.
+ */
+size_t ss_step_scratch_bytes(ss_dtype gdt, int has_momentum, int M, size_t d);
+int ss_signum_vote_step_scratch(const void *const *g, ss_dtype gdt,
+                                float *const *m, int M, float beta, float delta,
+                                float *x, uint32_t *voted, int8_t *sums_out,
+                                void *scratch, size_t scratch_bytes, size_t d,
+                                unsigned flags, void *hip_stream);
+
 /* ---- majority vote with abstention (Section 6, Discussion) ----
  *
  * The paper only sketches this extension: workers send their vote unless they

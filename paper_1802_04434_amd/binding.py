@@ -57,6 +57,10 @@ def load_library():
         L.ss_vote_sum.argtypes = [vp, i32, vp, sz, vp]
         L.ss_sum_apply.argtypes = [vp, vp, f32, sz, vp]
         L.ss_signum_vote_step_ex.argtypes = [vp, i32, vp, i32, f32, f32, vp, vp, vp, vp, sz, ctypes.c_uint, vp]
+        L.ss_step_scratch_bytes.restype = sz
+        L.ss_step_scratch_bytes.argtypes = [i32, i32, i32, sz]
+        L.ss_signum_vote_step_scratch.argtypes = [vp, i32, vp, i32, f32, f32, vp, vp, vp, vp, sz, sz, ctypes.c_uint, vp]
+        L.ss_signum_vote_step_scratch.restype = i32
         L.ss_welford_update.argtypes = [vp, i32, vp, vp, ctypes.c_uint64, sz, vp]
         L.ss_welford_sigma.argtypes = [vp, ctypes.c_uint64, vp, sz, vp]
         L.ss_density.argtypes = [vp, sz, vp, vp, vp]
@@ -233,14 +237,50 @@ def signum_vote_step_ex(g, m, beta, delta, x, voted, packed_out=None, sums_out=N
     g_arr = _ptr_array(gp)
     m_arr = _ptr_array(mp) if mp is not None else None
     p_arr = _ptr_array(pp) if pp is not None else None
+    sp = _dev(sums_out, torch.int8, d, "sums_out") if sums_out is not None else None
+    if p_arr is None and d >= _SCRATCH_MIN_D:
+        scratch = _lend(L.ss_step_scratch_bytes(gdt, int(mp is not None), M, d), x, stream)
+        if scratch is not None:
+            _check("ss_signum_vote_step_scratch", L.ss_signum_vote_step_scratch(
+                g_arr, gdt, m_arr, M, beta, delta, xp, vp, sp, scratch.data_ptr(), scratch.numel(), d,
+                int(flags or 0), _stream(stream)))
+            return voted
     if flags is None and sums_out is None:
         _check("ss_signum_vote_step", L.ss_signum_vote_step(
             g_arr, gdt, m_arr, M, beta, delta, xp, vp, p_arr, d, _stream(stream)))
     else:
-        sp = _dev(sums_out, torch.int8, d, "sums_out") if sums_out is not None else None
         _check("ss_signum_vote_step_ex", L.ss_signum_vote_step_ex(
             g_arr, gdt, m_arr, M, beta, delta, xp, vp, p_arr, sp, d, int(flags or 0), _stream(stream)))
     return voted
+
+
+_SCRATCH_MIN_D = 1 << 20      # below this the library never asks for scratch
+
+
+def _lend(nbytes, x, stream):
+    """Temporary device memory for one step from torch's caching allocator, on the step's own stream
+    (so that its reuse is ordered behind the step), or None: nothing wanted, no room, a stream or
+    device that torch's allocator would not order, or a stream under capture (a replay may not touch
+    memory that has been given back)."""
+    if nbytes == 0 or x.device.index != torch.cuda.current_device():
+        return None
+    if stream is None:
+        if torch.cuda.is_current_stream_capturing():
+            return None
+        return _empty_or_none(nbytes, x.device)
+    if not isinstance(stream, torch.cuda.Stream) or stream.device != x.device:
+        return None
+    with torch.cuda.stream(stream):
+        if torch.cuda.is_current_stream_capturing():
+            return None
+        return _empty_or_none(nbytes, x.device)
+
+
+def _empty_or_none(nbytes, device):
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except RuntimeError:      # out of memory, or no allocation allowed now (another thread captures)
+        return None
 
 
 def stream_copy(dst, src, nbytes, stream=None):

@@ -126,6 +126,31 @@ inline bool split_pays(int M, size_t d) {
     return M >= 2 && d >= ((size_t)1 << 20) && d * (size_t)M >= ((size_t)1 << (M >= 4 ? 23 : 24));
 }
 
+// With lent scratch memory the step takes the same two launches without packed_out, over slabs of the
+// vector whose bits fit into it.  kScratchBytes bounds what is asked for: at M = 16 a slab of 67 M
+// coordinates, 2 ms of work for each further pair of launches (~5 us).
+constexpr size_t kScratchBytes = (size_t)128 << 20;
+constexpr size_t kScratchMinSlab = (size_t)1 << 20;
+
+// coordinates of a slab: all d if the bits of M workers fit into `bytes`, otherwise equal parts of a
+// multiple of 8192 (every buffer's part stays 16-byte aligned); 0 if there is no room for 8192
+inline size_t scratch_slab(int M, size_t d, size_t bytes) {
+    if ((size_t)M * ss_packed_bytes(d) <= bytes) return d;
+    const size_t room = bytes / (size_t)M * 8 / 8192 * 8192;
+    if (room == 0) return 0;
+    const size_t parts = (d + room - 1) / room;
+    return std::min(room, ((d + parts - 1) / parts + 8191) / 8192 * 8192);
+}
+
+// One pass -> two launches with scratch, us: M = 5 fp32 2.2 M coordinates (132 MB of gradients and momentum)
+// 27.2 -> 27.2; M = 8 bf16 4.4 M (352 MB) 72 -> 65; M = 7 fp32 25.6 M 376 -> 357; M = 16 138 M 4,620 -> 4,170; M = 4 bf16
+// 8.0 M (320 MB) 64.7 -> 63.5; M = 3 fp32 8.0 M (288 MB) 60.4 -> 59.5; M = 2 fp32 12 M (288 MB) 65.8 -> 65.7,
+// 60 M 319 -> 294, bf16 17.6 M (352 MB) 77.6 -> 82.1, 60 M (1.2 GB) 263 -> 259.  Where a step takes less than ~40 us the
+// first allocation on a stream (~20 us, once) is not worth what is gained.
+inline bool scratch_pays(int M, size_t d, size_t worker_bytes) {
+    return d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 5 ? 28 : M >= 3 ? 29 : 30));
+}
+
 // LDS of one compute unit of the current device, in KB; 0 if the runtime will not say.  A pure
 // query: nothing is remembered between calls.
 inline int lds_per_unit_kb() {
@@ -279,36 +304,49 @@ int launch_pack(int n, const void *const *g, ss_dtype gdt, float *const *m, uint
 
 // Vote and update from packed bits.  Four rows per block and four blocks per unit; from 2^28
 // coordinates on one row and no cap (d = 400 M, M = 8: 563 us against 590; d = 138 M, M = 16: 213 against 203).
-template <int MT>
-int launch_vote_apply(const uint32_t *const *packed, int M, uint32_t *voted, float *x, float delta, size_t d,
-                      hipStream_t stream) {
+template <int MT, bool COUNTS>
+int launch_vote_apply(const uint32_t *const *packed, int M, uint32_t *voted, float *x, float delta, StepVariant var,
+                      size_t d, hipStream_t stream) {
     constexpr int NPTR = MT > 0 ? MT : SS_MAX_WORKERS;
     ss::VoteApplyArgs<NPTR> a;
     for (int w = 0; w < M; ++w) a.packed[w] = packed[w];
     a.voted = voted;
     a.x = x;
+    a.sums = var.sums;
     a.delta = delta;
     a.M = M;
+    a.sum_update = (var.flags & SS_STEP_SUM_UPDATE) ? 1 : 0;
     a.d = d;
     a.words_total = ss_packed_bytes(d) / 4;
     const bool large = d >= kLargeD;
     const size_t words = large ? 32 : 128;
     const size_t grid = (a.words_total + words - 1) / words;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    if (large) return launch(ss::vote_apply_kernel<MT, NPTR, 1, 0>, grid, 0, stream, a);
-    return launch(ss::vote_apply_kernel<MT, NPTR, 4, 40>, grid, 0, stream, a);
+    if (large) return launch(ss::vote_apply_kernel<MT, NPTR, 1, 0, COUNTS>, grid, 0, stream, a);
+    return launch(ss::vote_apply_kernel<MT, NPTR, 4, 40 - (COUNTS ? 4 : 0), COUNTS>, grid, 0, stream, a);
 }
 
-int dispatch_vote_apply(const uint32_t *const *packed, int M, uint32_t *voted, float *x, float delta, size_t d,
-                        hipStream_t stream) {
+int dispatch_vote_apply(const uint32_t *const *packed, int M, uint32_t *voted, float *x, float delta, StepVariant var,
+                        size_t d, hipStream_t stream) {
+    if (var.sums || (var.flags & SS_STEP_SUM_UPDATE))
+        return launch_vote_apply<0, true>(packed, M, voted, x, delta, var, d, stream);
 #define SS_CASE(n) \
-    case n: return launch_vote_apply<n>(packed, M, voted, x, delta, d, stream)
+    case n: return launch_vote_apply<n, false>(packed, M, voted, x, delta, var, d, stream)
     switch (M) {
         SS_CASE(2); SS_CASE(3); SS_CASE(4); SS_CASE(5); SS_CASE(6); SS_CASE(7); SS_CASE(8);
         SS_CASE(9); SS_CASE(10); SS_CASE(11); SS_CASE(12); SS_CASE(13); SS_CASE(14); SS_CASE(15); SS_CASE(16);
-        default: return launch_vote_apply<0>(packed, M, voted, x, delta, d, stream);
+        default: return launch_vote_apply<0, false>(packed, M, voted, x, delta, var, d, stream);
     }
 #undef SS_CASE
+}
+
+// the whole step as pack and vote-and-update launches
+int launch_two(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float delta, float *x,
+               uint32_t *voted, uint32_t *const *packed, StepVariant var, size_t d, hipStream_t stream) {
+    const int rc = M <= 16 ? launch_pack<16>(M, g, gdt, m, packed, beta, var.flags, d, stream)
+                           : launch_pack<SS_MAX_WORKERS>(M, g, gdt, m, packed, beta, var.flags, d, stream);
+    if (rc != SS_OK) return rc;
+    return dispatch_vote_apply(packed, M, voted, x, delta, var, d, stream);
 }
 
 // the votes read M buffers at once; with packed buffers beyond ~128 MB each (d >= 2^30) two blocks
@@ -487,9 +525,9 @@ int ss_sign_apply(float *x, const uint32_t *bits, float delta, size_t d, void *h
     return launch(ss::apply_kernel<4, 0, false>, grid, 0, stream, a);
 }
 
-int ss_signum_vote_step_ex(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float delta,
-                           float *x, uint32_t *voted, uint32_t *const *packed_out, int8_t *sums_out, size_t d,
-                           unsigned flags, void *hip_stream) {
+static int vote_step_impl(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float delta, float *x,
+                          uint32_t *voted, uint32_t *const *packed_out, int8_t *sums_out, size_t d, unsigned flags,
+                          void *scratch, size_t scratch_bytes, void *hip_stream) {
     if (M < 1 || M > SS_MAX_WORKERS) return SS_ERR_BAD_M;
     if (gdt != SS_F32 && gdt != SS_BF16) return SS_ERR_DTYPE;
     if (flags & ~(unsigned)(SS_STEP_WARMUP | SS_STEP_SUM_UPDATE)) return SS_ERR_ARG;
@@ -500,14 +538,14 @@ int ss_signum_vote_step_ex(const void *const *g, ss_dtype gdt, float *const *m, 
         if (m && !m[w]) return SS_ERR_NULL;
         if (packed_out && !packed_out[w]) return SS_ERR_NULL;
     }
-    if (!aligned16(x) || !aligned16(voted) || !aligned16(sums_out)) return SS_ERR_ALIGN;
+    if (!aligned16(x) || !aligned16(voted) || !aligned16(sums_out) || !aligned16(scratch)) return SS_ERR_ALIGN;
     for (int w = 0; w < M; ++w) {
         if (!aligned16(g[w])) return SS_ERR_ALIGN;
         if (m && !aligned16(m[w])) return SS_ERR_ALIGN;
         if (packed_out && !aligned16(packed_out[w])) return SS_ERR_ALIGN;
     }
     {
-        Span spans[3 * SS_MAX_WORKERS + 3];
+        Span spans[3 * SS_MAX_WORKERS + 4];
         int n = 0;
         for (int w = 0; w < M; ++w) {
             spans[n++] = span(g[w], d * grad_bytes(gdt), false);
@@ -517,17 +555,35 @@ int ss_signum_vote_step_ex(const void *const *g, ss_dtype gdt, float *const *m, 
         spans[n++] = span(x, d * sizeof(float), true);
         spans[n++] = span(voted, ss_packed_bytes(d), true);
         spans[n++] = span(sums_out, d, true);
+        spans[n++] = span(scratch, scratch_bytes, true);
         if (written_spans_overlap(spans, n)) return SS_ERR_ARG;
     }
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (packed_out && !sums_out && !(flags & SS_STEP_SUM_UPDATE) && split_pays(M, d)) {
-        // the caller's bit buffers carry the signs from one launch to the next; same results, bit for bit
-        const int rc = M <= 16 ? launch_pack<16>(M, g, gdt, m, packed_out, beta, flags, d, stream)
-                               : launch_pack<SS_MAX_WORKERS>(M, g, gdt, m, packed_out, beta, flags, d, stream);
-        if (rc != SS_OK) return rc;
-        return dispatch_vote_apply(packed_out, M, voted, x, delta, d, stream);
-    }
     const StepVariant var{flags, sums_out};
+    // the caller's bit buffers carry the signs from one launch to the next; same results, bit for bit
+    if (packed_out && split_pays(M, d)) return launch_two(g, gdt, m, M, beta, delta, x, voted, packed_out, var, d, stream);
+    if (scratch && !packed_out) {
+        // ... or the lent memory does, over as much of the vector at a time as it has room for
+        const size_t slab = scratch_slab(M, d, scratch_bytes);
+        if (slab >= kScratchMinSlab) {
+            const size_t stride = ss_packed_bytes(slab);
+            for (size_t lo = 0; lo < d; lo += slab) {
+                const size_t n = std::min(slab, d - lo);
+                const void *gs[SS_MAX_WORKERS];
+                float *ms[SS_MAX_WORKERS];
+                uint32_t *ps[SS_MAX_WORKERS];
+                for (int w = 0; w < M; ++w) {
+                    gs[w] = static_cast<const char *>(g[w]) + lo * grad_bytes(gdt);
+                    ms[w] = m ? m[w] + lo : nullptr;
+                    ps[w] = reinterpret_cast<uint32_t *>(static_cast<char *>(scratch) + w * stride);
+                }
+                const StepVariant part{flags, sums_out ? sums_out + lo : nullptr};
+                const int rc = launch_two(gs, gdt, m ? ms : nullptr, M, beta, delta, x + lo, voted + lo / 32, ps, part, n, stream);
+                if (rc != SS_OK) return rc;
+            }
+            return SS_OK;
+        }
+    }
     if (m) {
         if (gdt == SS_F32)
             return launch_step<true, ss::F32Grad>(M, g, m, packed_out, beta, delta, x, voted, var, d, stream);
@@ -536,6 +592,25 @@ int ss_signum_vote_step_ex(const void *const *g, ss_dtype gdt, float *const *m, 
     if (gdt == SS_F32)
         return launch_step<false, ss::F32Grad>(M, g, m, packed_out, beta, delta, x, voted, var, d, stream);
     return launch_step<false, ss::Bf16Grad>(M, g, m, packed_out, beta, delta, x, voted, var, d, stream);
+}
+
+int ss_signum_vote_step_ex(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float delta,
+                           float *x, uint32_t *voted, uint32_t *const *packed_out, int8_t *sums_out, size_t d,
+                           unsigned flags, void *hip_stream) {
+    return vote_step_impl(g, gdt, m, M, beta, delta, x, voted, packed_out, sums_out, d, flags, nullptr, 0, hip_stream);
+}
+
+size_t ss_step_scratch_bytes(ss_dtype gdt, int has_momentum, int M, size_t d) {
+    if (M < 2 || M > SS_MAX_WORKERS || (gdt != SS_F32 && gdt != SS_BF16) || !has_momentum) return 0;
+    if (d < kScratchMinSlab || !scratch_pays(M, d, grad_bytes(gdt) + sizeof(float) * 2)) return 0;
+    return (size_t)M * ss_packed_bytes(scratch_slab(M, d, kScratchBytes));
+}
+
+int ss_signum_vote_step_scratch(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float delta,
+                                float *x, uint32_t *voted, int8_t *sums_out, void *scratch, size_t scratch_bytes,
+                                size_t d, unsigned flags, void *hip_stream) {
+    return vote_step_impl(g, gdt, m, M, beta, delta, x, voted, nullptr, sums_out, d, flags, scratch,
+                          scratch ? scratch_bytes : 0, hip_stream);
 }
 
 int ss_signum_vote_step(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float delta,

@@ -223,21 +223,46 @@ struct VoteApplyArgs {
     const uint32_t *packed[NPTR];
     uint32_t *voted;
     float *x;
+    int8_t *sums;         // COUNTS only, may be NULL: per-coordinate sum of signs
     float delta;
     int M;
+    int sum_update;       // COUNTS only: x <- x - delta * (sum of signs) instead of its sign
     size_t d;
     size_t words_total;   // words of a packed buffer including zero padding
 };
 
+// one word of every worker, added into the binary planes of the count of "-" votes
+__device__ __forceinline__ void count_words(const uint32_t *const *packed, int M, size_t wi, uint32_t (&plane)[kPlanes]) {
+#pragma unroll
+    for (int k = 0; k < kPlanes; ++k) plane[k] = 0;
+    for (int w0 = 0; w0 < M; w0 += 8) {
+        uint32_t word[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) word[j] = packed[w0 + j < M ? w0 + j : w0][wi];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            uint32_t carry = w0 + j < M ? word[j] : 0u;
+#pragma unroll
+            for (int k = 0; k < kPlanes; ++k) {
+                const uint32_t t = plane[k] & carry;
+                plane[k] ^= carry;
+                carry = t;
+            }
+        }
+    }
+}
+
 // MT workers at compile time; MT == 0: a.M at run time, added into binary count planes.
+// COUNTS (with MT == 0): the planes themselves go through LDS, for the sums and the sum update.
 // A block owns R rows of 1024 coordinates: its first 32 R lanes vote on a word each.  Bound by HBM:
 // 8.125 + M / 8 bytes per coordinate; d = 25.6 M, M = 7: 34.5 us (6,650 GB/s) where the two
 // launches take 5.4 + 33.2 us and a gap.  HOLD_KB caps the blocks per compute unit.
-template <int MT, int NPTR, int R, int HOLD_KB>
+template <int MT, int NPTR, int R, int HOLD_KB, bool COUNTS>
 __global__ __launch_bounds__(kBlock) void vote_apply_kernel(const VoteApplyArgs<NPTR> a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.voted);
     constexpr int kWords = 32 * R;   // voted words of a block
-    __shared__ uint32_t vote[kWords];
+    constexpr int kShared = COUNTS ? kPlanes : 1;
+    __shared__ uint32_t vote[kShared][kWords];   // the voted words; COUNTS: the count planes
     const int tid = threadIdx.x;
     const size_t wi = (size_t)blockIdx.x * kWords + tid;
     const size_t base = (size_t)blockIdx.x * (R * kRowCoords);
@@ -262,49 +287,61 @@ __global__ __launch_bounds__(kBlock) void vote_apply_kernel(const VoteApplyArgs<
         } else {
             const int T = a.M / 2 + 1;
             uint32_t plane[kPlanes];
-#pragma unroll
-            for (int k = 0; k < kPlanes; ++k) plane[k] = 0;
-            for (int w0 = 0; w0 < a.M; w0 += 8) {
-                uint32_t word[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) word[j] = a.packed[w0 + j < a.M ? w0 + j : w0][wi];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    uint32_t carry = w0 + j < a.M ? word[j] : 0u;
-#pragma unroll
-                    for (int k = 0; k < kPlanes; ++k) {
-                        const uint32_t t = plane[k] & carry;
-                        plane[k] ^= carry;
-                        carry = t;
-                    }
-                }
-            }
+            count_words(a.packed, a.M, wi, plane);
             ge = 0xFFFFFFFFu;
 #pragma unroll
             for (int k = 0; k < kPlanes; ++k) ge = ge_step(ge, plane[k], T, k);
+            if constexpr (COUNTS) {
+#pragma unroll
+                for (int k = 0; k < kPlanes; ++k) vote[k][tid] = plane[k];
+            }
         }
         ge &= live_mask(wi, a.d);
         a.voted[wi] = ge;
-        vote[tid] = ge;
+        if constexpr (!COUNTS) vote[0][tid] = ge;
     }
     __syncthreads();
     if (full) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const uint32_t nib = vote[r * 32 + (tid >> 3)] >> ((tid & 7) * 4);
+            const int word = r * 32 + (tid >> 3), shift = (tid & 7) * 4;
             f32x4 v = xv[r];
-            v.x = step(v.x, a.delta, nib & 1u);
-            v.y = step(v.y, a.delta, nib & 2u);
-            v.z = step(v.z, a.delta, nib & 4u);
-            v.w = step(v.w, a.delta, nib & 8u);
+            if constexpr (COUNTS) {
+                uint32_t counts = 0;
+#pragma unroll
+                for (int k = 0; k < kPlanes; ++k) counts += spread_nibble((vote[k][word] >> shift) & 0xFu) << k;
+                if (a.sum_update) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] = step_sum(v[c], a.delta, sum_at(counts, c, a.M));
+                } else {
+                    const uint32_t nib = vote_nibble(counts, a.M / 2 + 1);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] = step(v[c], a.delta, (nib >> c) & 1u);
+                }
+                if (a.sums)
+                    st_stream(reinterpret_cast<uint32_t *>(a.sums + base) + tid + r * kBlock, sums_word(counts, a.M));
+            } else {
+                const uint32_t nib = vote[0][word] >> shift;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = step(v[c], a.delta, (nib >> c) & 1u);
+            }
             st_stream(xq + r * kBlock, v);
         }
         return;
     }
     // the last block: one coordinate per lane
     for (int i = tid; base + i < a.d; i += kBlock) {
-        const bool neg = (vote[i >> 5] >> (i & 31)) & 1u;
-        a.x[base + i] = step(a.x[base + i], a.delta, neg);
+        if constexpr (COUNTS) {
+            int count = 0;
+#pragma unroll
+            for (int k = 0; k < kPlanes; ++k) count += (int)((vote[k][i >> 5] >> (i & 31)) & 1u) << k;
+            const int S = a.M - 2 * count;
+            a.x[base + i] = a.sum_update ? step_sum(a.x[base + i], a.delta, S) : step(a.x[base + i], a.delta, S < 0);
+            if (a.sums) a.sums[base + i] = (int8_t)S;
+        } else {
+            const bool neg = (vote[0][i >> 5] >> (i & 31)) & 1u;
+            a.x[base + i] = step(a.x[base + i], a.delta, neg);
+        }
     }
 }
 

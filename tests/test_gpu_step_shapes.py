@@ -115,3 +115,88 @@ def test_ternary_step(ss, oracle, d, M, dtype, momentum):
     for w in range(M if momentum else 0):
         assert_same_floats(m_dev[w], m[w], "m[%d]" % w)
     assert_same_floats(x_dev, x, "x")
+
+
+@pytest.mark.parametrize("d,M,dtype,flags,sums,room", [
+    ((1 << 20), 8, "bf16", 0, False, 1 << 20),                  # one slab exactly
+    (3 * (1 << 20) + 8191, 5, "f32", 0, False, (1 << 20) + 16384),   # three slabs, ragged end
+    ((1 << 21) + 1, 9, "f32", 1, False, (1 << 20) + 8192),      # warm-up, last slab shorter
+    ((1 << 21) + 33, 7, "bf16", 2, True, (1 << 20) + 8192),     # sum update with the sums
+    ((1 << 20) + 1027, 17, "f32", 0, True, 1 << 22),            # sums, sign update, one slab
+    ((1 << 20) + 5, 6, "f32", 2, False, 1 << 22),
+    ((1 << 28) + 1057, 2, "bf16", 2, True, 1 << 29),            # vote-and-update blocks of one row
+    ((1 << 20) + 64, 4, "f32", 0, False, 1 << 19),              # too little room: one pass
+])
+def test_step_with_lent_scratch(ss, oracle, d, M, dtype, flags, sums, room):
+    import ctypes
+    L = ss.load_library()
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d + M)
+    T = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = [torch.randn(d, device=DEV, generator=gen).to(T) for _ in range(M)]
+    m = [torch.randn(d, device=DEV, generator=gen) * 0.3 for _ in range(M)]
+    x = torch.randn(d, device=DEV, generator=gen) * 0.05
+    m_np = [synth.as_numpy(t).copy() for t in m]
+    x_np = synth.as_numpy(x).copy()
+    nbytes = M * (room // 8)
+    guard = 4096
+    scratch = torch.full((nbytes + guard,), 0xA5, dtype=torch.uint8, device=DEV)
+    voted = dirty_bits(ss, d)
+    s_out = torch.full((d,), 99, dtype=torch.int8, device=DEV) if sums else None
+    ptrs = lambda ts: (ctypes.c_void_p * len(ts))(*[t.data_ptr() for t in ts])     # noqa: E731
+    rc = L.ss_signum_vote_step_scratch(ptrs(g), int(dtype == "bf16"), ptrs(m), M, 0.9, 1e-4, x.data_ptr(), voted.data_ptr(),
+                                       s_out.data_ptr() if sums else None, scratch.data_ptr(), nbytes, d, flags,
+                                       ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    g_np = [synth.as_numpy(t) for t in g]
+    want = oracle.signum_vote_step_ex(g_np, m_np, 0.9, 1e-4, x_np, flags)
+    assert np.array_equal(bits_np(voted), want[0])
+    if sums:
+        assert np.array_equal(s_out.cpu().numpy(), want[-1])
+    for w in range(M):
+        assert_same_floats(m[w], m_np[w], "m[%d]" % w)
+    assert_same_floats(x, x_np, "x")
+    assert bool((scratch[nbytes:] == 0xA5).all())       # nothing beyond what was lent
+
+
+def test_large_step_on_streams_and_under_capture(ss):
+    # the binding lends scratch on the step's own stream; a captured step takes one pass, and both agree
+    d, M = (1 << 28) // 60 + 12_345, 5
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(9)
+    g = [torch.randn(d, device=DEV, generator=gen) for _ in range(M)]
+    m0 = [torch.randn(d, device=DEV, generator=gen) * 0.3 for _ in range(M)]
+    x0 = torch.randn(d, device=DEV, generator=gen) * 0.05
+    assert ss.load_library().ss_step_scratch_bytes(0, 1, M, d) > 0
+
+    def fresh():
+        return [t.clone() for t in m0], x0.clone(), dirty_bits(ss, d)
+
+    results = []
+    m, x, v = fresh()
+    for _ in range(2):
+        ss.signum_vote_step(g, m, 0.9, 1e-4, x, v)
+    results.append((m, x, v))
+    side = torch.cuda.Stream()
+    m, x, v = fresh()
+    side.wait_stream(torch.cuda.current_stream())
+    for _ in range(2):
+        ss.signum_vote_step(g, m, 0.9, 1e-4, x, v, stream=side)
+    side.synchronize()
+    results.append((m, x, v))
+    m, x, v = fresh()
+    graph = torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        ss.signum_vote_step(g, m, 0.9, 1e-4, x, v)
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+        torch.empty(1 << 24, dtype=torch.uint8, device=DEV).fill_(255)     # the program's own memory between replays
+        torch.cuda.synchronize()
+    results.append((m, x, v))
+    torch.cuda.synchronize()
+    for m, x, v in results[1:]:
+        assert torch.equal(v, results[0][2])
+        assert torch.equal(x.view(torch.int32), results[0][1].view(torch.int32))
+        assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(m, results[0][0]))

@@ -234,3 +234,28 @@ def test_abstention_entry_points_validate_arguments(lib):
     assert step(one, 0, None, 1, f(0.9), f(0.1), 1, f(0.1), a, None, a, 8, None) == -1
     assert step(one, 0, None, 1, f(0.9), f(0.1), 1, f(0.1), a, a, odd, 8, None) == -3
     assert step(one, 9, None, 1, f(0.9), f(0.1), 1, f(0.1), a, a, a, 8, None) == -4
+
+
+def test_lent_scratch_is_bounded_and_validated(lib):
+    for gdt in (0, 1):
+        for M in (2, 3, 5, 7, 8, 16, 17, 64):
+            for d in (1 << 20, 3_000_001, 25_557_032, 138_357_544, 1_500_000_017, (1 << 33) + 5):
+                n = lib.ss_step_scratch_bytes(gdt, 1, M, d)
+                assert n <= 128 << 20 and n % (16 * M) == 0
+                assert n == 0 or n // M * 8 >= min(d, 1 << 20)
+    # nothing wanted: one worker, no momentum, small vectors, what a step would refuse
+    for args in ((0, 1, 1, 1 << 30), (0, 0, 8, 1 << 30), (0, 1, 8, 1 << 19), (2, 1, 8, 1 << 30), (0, 1, 65, 1 << 30), (0, 1, 0, 8)):
+        assert lib.ss_step_scratch_bytes(*args) == 0
+    two = (ctypes.c_void_p * 2)(0x100000, 0x200000)
+    m = (ctypes.c_void_p * 2)(0x300000, 0x400000)
+    x, voted, odd = ctypes.c_void_p(0x500000), ctypes.c_void_p(0x600000), ctypes.c_void_p(0x700008)
+
+    def step(scratch, nbytes, M=2, d=1024, flags=0):
+        return lib.ss_signum_vote_step_scratch(two, 0, m, M, 0.9, 0.1, x, voted, None, scratch, nbytes, d, flags, None)
+
+    assert step(odd, 64) == -3                                  # alignment
+    assert step(ctypes.c_void_p(0x500010), 64) == -5            # shares bytes with x
+    assert step(ctypes.c_void_p(0x100010), 64) == -5            # ... with a gradient
+    assert step(ctypes.c_void_p(0x700000), 64, M=65) == -2
+    assert step(ctypes.c_void_p(0x700000), 64, flags=4) == -5
+    assert step(ctypes.c_void_p(0x700000), 64, d=0) == 0
