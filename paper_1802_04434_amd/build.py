@@ -1,4 +1,5 @@
-"""Build libsignsgd.so (the C-ABI HIP library) for gfx950, in-tree.
+"""Build libsignsgd.so (the C-ABI HIP library) for gfx950 and the Python module
+that marshals torch tensors into it, in-tree.
 
     python -m paper_1802_04434_amd.build
 
@@ -33,6 +34,33 @@ def build(out=LIB, verbose=False):
     return out
 
 
+MARSHAL = os.path.join(HERE, "_marshal.so")
+
+
+def build_marshal(verbose=False):
+    """The CPython module between torch tensors and the library (csrc/marshal.cpp): plain host C++
+    against torch's headers; it finds libsignsgd.so next to itself."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    tmp = MARSHAL + ".tmp%d" % os.getpid()
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    for inc in cpp_extension.include_paths() + [os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", inc]
+    cmd += [os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L" + HERE, "-lsignsgd", "-L" + torch_lib, "-ltorch_python",
+            "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-L" + os.path.join(rocm, "lib"), "-lamdhip64",
+            "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
+
+
 ABI_CHECK = os.path.join(HERE, "abi_check")
 
 
@@ -54,4 +82,5 @@ def build_abi_check(verbose=False):
 
 if __name__ == "__main__":
     print(build(verbose=True))
+    print(build_marshal(verbose=True))
     print(build_abi_check(verbose=True))

@@ -1,0 +1,85 @@
+"""What the native marshalling refuses, and that it hands over what it is given: wrong
+memory, dtype, layout, length or number of tensors is an error before anything is launched."""
+import gc
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import paper_1802_04434_amd as ss
+
+DEV = "cuda"
+
+
+def test_refuses_what_is_not_a_device_tensor():
+    ss.load_library()
+    host = torch.zeros(64)
+    bits = torch.zeros(4, dtype=torch.int32)
+    with pytest.raises(TypeError, match=r"g\[0\] must live in device memory"):
+        ss.signum_vote_step([host], None, 0.9, 1e-4, host, bits)
+    with pytest.raises(TypeError, match=r"packed\[0\] must live"):
+        ss.majority_vote([bits], bits, 64)
+    with pytest.raises(TypeError, match="x must live"):
+        ss.sign_apply(host, bits, 1e-4)
+    with pytest.raises(TypeError, match="must be a tensor"):
+        ss.signum_pack(np.zeros(64, np.float32), None, 0.9, bits)
+    with pytest.raises(IndexError):
+        ss.signum_vote_step([], None, 0.9, 1e-4, host, bits)
+    with pytest.raises(TypeError):
+        ss.majority_vote(3, bits, 64)
+    with pytest.raises(TypeError):
+        ss.sum_apply(host, bits, 1e-4, d=6.5)
+    with pytest.raises(TypeError):
+        ss.density(host, host, None)
+
+
+@pytest.mark.gpu
+def test_refuses_dtype_layout_length_and_number():
+    d = 1000
+    f = [torch.zeros(d, device=DEV) for _ in range(3)]
+    bits = [ss.new_bits(d, DEV) for _ in range(3)]
+    x = torch.zeros(d, device=DEV)
+    with pytest.raises(TypeError, match="dtype"):
+        ss.signum_pack(f[0].half(), None, 0.9, bits[0])
+    with pytest.raises(TypeError, match=r"g\[1\] has dtype"):
+        ss.signum_vote_step([f[0], f[1].bfloat16()], None, 0.9, 1e-4, x, bits[0])
+    with pytest.raises(TypeError, match="contiguous with at least 1000"):
+        ss.signum_vote_step([torch.zeros(2 * d, device=DEV)[::2]], None, 0.9, 1e-4, x, bits[0])
+    with pytest.raises(TypeError, match=r"m\[0\] must be contiguous"):
+        ss.signum_vote_step([f[0]], [f[1][:d - 1]], 0.9, 1e-4, x, bits[0])
+    with pytest.raises(ValueError):
+        ss.signum_vote_step(f[:2], f[2:], 0.9, 1e-4, x, bits[0])
+    with pytest.raises(ValueError):
+        ss.quorum_vote(bits[:2], bits[2:], 1, bits[0], bits[1], d)
+    with pytest.raises(TypeError, match="voted has dtype"):
+        ss.majority_vote(bits[:2], x, d)
+    for M in (0, 65):
+        with pytest.raises(ss.SignSGDError) as e:
+            ss.majority_vote([bits[0]] * M, bits[1], d)
+        assert e.value.status == -2
+    with pytest.raises(ss.SignSGDError) as e:
+        ss.sign_apply(x[1:], bits[0], 1e-4)          # 4 bytes off a 16-byte boundary
+    assert e.value.status == -3
+    with pytest.raises(ss.SignSGDError) as e:
+        ss.signum_vote_step([x], None, 0.9, 1e-4, x, bits[0])
+    assert e.value.status == -5
+    torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+def test_tuples_parameters_streams_and_reference_counts():
+    d = 1000
+    g = tuple(torch.nn.Parameter(torch.randn(d, device=DEV)) for _ in range(3))
+    x = torch.zeros(d, device=DEV)
+    voted = ss.new_bits(d, DEV)
+    before = [sys.getrefcount(t) for t in (*g, x, voted)]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    for _ in range(50):
+        assert ss.signum_vote_step(g, None, 0.9, 1.0, x, voted, stream=side) is voted
+    side.synchronize()
+    gc.collect()
+    assert [sys.getrefcount(t) for t in (*g, x, voted)] == before
+    minus = sum((t.detach() < 0).int() for t in g) >= 2
+    assert torch.equal(x, torch.where(minus, 50.0, -50.0))
