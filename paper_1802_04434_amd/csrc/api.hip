@@ -160,12 +160,15 @@ inline int lds_per_unit_kb() {
     return bytes / 1024;
 }
 
-// The kernels that stream one or a few buffers (pack, apply, copy, Welford, the stand-alone votes)
-// are launched with as many blocks per unit as fit while the buffers are small; from about a
-// gigabyte per array on every one of them runs 3-12 % faster with roughly 24 KB of loads in flight
-// per compute unit (six 256-thread blocks of one row, or four of two rows), which an LDS
-// reservation enforces.  Measured on MI355X for 2^27 .. 1.5 * 2^30 coordinates; each entry point
-// states the shape it takes on either side of its threshold.
+// a launch may have at most 2^32 - 1 threads: with one row of quads a lane that is 2^34 coordinates
+constexpr size_t kOneRowMaxD = (size_t)1 << 33;
+
+// up to here sum_apply and copy keep four-wave blocks (see vote_apply_kernels.hpp)
+constexpr size_t kCachedD = (size_t)1 << 21;
+
+// apply and vote-and-update: from about a gigabyte per array on, one row per block (apply: with six
+// blocks per unit, roughly 24 KB of loads in flight, which an LDS reservation enforces) is 3-7 % faster
+// than four rows
 constexpr size_t kLargeD = (size_t)1 << 28;
 
 // the reservations are sized for a unit with kLdsPerUnitKB of LDS: on anything else, no cap
@@ -402,7 +405,7 @@ template <bool HAS_M, bool VOTE, typename G>
 int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     constexpr bool kBf16 = std::is_same<G, ss::Bf16Grad>::value;
     if constexpr (VOTE) {
-        if (a.M >= 2 && streams(a.M, d, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0)) && caps_apply()) {
+        if ((a.M >= 2 && streams(a.M, d, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0)) && caps_apply()) || d >= kOneRowMaxD) {
             if constexpr (!HAS_M) {
                 return launch_ternary_shape<64, 8, 2, 10, true, false, true, G>(a, d, stream);
             } else {
@@ -671,8 +674,8 @@ int ss_sum_apply(float *x, const int8_t *sums, float delta, size_t d, void *hip_
     if (!aligned16(x) || !aligned16(sums)) return SS_ERR_ALIGN;
     Span spans[2] = {span(x, d * sizeof(float), true), span(sums, d, false)};
     if (written_spans_overlap(spans, 2)) return SS_ERR_ARG;
-    const bool large = d >= kLargeD && caps_apply();   // then one row per block, six blocks per unit
-    const Tiling t = make_tiling(d, large ? 1 : 4, false);
+    const bool small = d < kCachedD;
+    const Tiling t = make_tiling(d, small ? 4 : 1, false, small ? ss::kBlock : ss::kWave);
     ss::SumApplyArgs a;
     a.x = x;
     a.sums = sums;
@@ -682,8 +685,8 @@ int ss_sum_apply(float *x, const int8_t *sums, float delta, size_t d, void *hip_
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (large) return launch(ss::sum_apply_kernel<1, 24, true>, grid, 0, stream, a);
-    return launch(ss::sum_apply_kernel<4, 0, false>, grid, 0, stream, a);
+    if (small) return launch(ss::sum_apply_kernel<ss::kBlock, 4>, grid, 0, stream, a);
+    return launch(ss::sum_apply_kernel<ss::kWave, 1>, grid, 0, stream, a, ss::kWave);
 }
 
 int ss_welford_update(const void *g, ss_dtype gdt, float *mean, float *m2, uint64_t n, size_t d, void *hip_stream) {
@@ -695,10 +698,7 @@ int ss_welford_update(const void *g, ss_dtype gdt, float *mean, float *m2, uint6
     Span spans[3] = {span(g, d * grad_bytes(gdt), false), span(mean, d * sizeof(float), true),
                      span(m2, d * sizeof(float), true)};
     if (written_spans_overlap(spans, 3)) return SS_ERR_ARG;
-    // five streams: from 2^27 coordinates on one row per block and six blocks per unit (+4 % at
-    // d = 138 M, +10 % at 1.5 G), below that two rows and no cap
-    const bool large = d >= ((size_t)1 << 27) && caps_apply();
-    const Tiling t = make_tiling(d, large ? 1 : 2, false);
+    const Tiling t = make_tiling(d, 1, false, ss::kWave);
     ss::WelfordArgs a;
     a.g = g;
     a.mean = mean;
@@ -709,12 +709,12 @@ int ss_welford_update(const void *g, ss_dtype gdt, float *mean, float *m2, uint6
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (large) {
-        if (gdt == SS_F32) return launch(ss::welford_update_kernel<1, 24, true, ss::F32Grad>, grid, 0, stream, a);
-        return launch(ss::welford_update_kernel<1, 24, true, ss::Bf16Grad>, grid, 0, stream, a);
+    if (d >= ((size_t)1 << 24) && caps_apply()) {
+        if (gdt == SS_F32) return launch(ss::welford_update_kernel<8, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
+        return launch(ss::welford_update_kernel<8, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
     }
-    if (gdt == SS_F32) return launch(ss::welford_update_kernel<2, 0, false, ss::F32Grad>, grid, 0, stream, a);
-    return launch(ss::welford_update_kernel<2, 0, false, ss::Bf16Grad>, grid, 0, stream, a);
+    if (gdt == SS_F32) return launch(ss::welford_update_kernel<0, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
+    return launch(ss::welford_update_kernel<0, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
 }
 
 int ss_welford_sigma(const float *m2, uint64_t n, float *sigma, size_t d, void *hip_stream) {
@@ -724,9 +724,8 @@ int ss_welford_sigma(const float *m2, uint64_t n, float *sigma, size_t d, void *
     if (!aligned16(m2) || !aligned16(sigma)) return SS_ERR_ALIGN;
     Span spans[2] = {span(m2, d * sizeof(float), false), span(sigma, d * sizeof(float), true)};
     if (written_spans_overlap(spans, 2)) return SS_ERR_ARG;
-    // two rows per block, six blocks per unit at every size (+2-9 % over four rows and no cap)
-    const bool capped = caps_apply();
-    const Tiling t = make_tiling(d, capped ? 2 : 4, false);
+    const bool two_rows = d >= kOneRowMaxD;
+    const Tiling t = make_tiling(d, two_rows ? 2 : 1, false, ss::kWave);
     ss::SigmaArgs a;
     a.m2 = m2;
     a.sigma = sigma;
@@ -736,8 +735,8 @@ int ss_welford_sigma(const float *m2, uint64_t n, float *sigma, size_t d, void *
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (capped) return launch(ss::welford_sigma_kernel<2, 24, true>, grid, 0, stream, a);
-    return launch(ss::welford_sigma_kernel<4, 0, false>, grid, 0, stream, a);
+    if (two_rows) return launch(ss::welford_sigma_kernel<2>, grid, 0, stream, a, ss::kWave);
+    return launch(ss::welford_sigma_kernel<1>, grid, 0, stream, a, ss::kWave);
 }
 
 size_t ss_density_workspace_bytes(void) { return sizeof(ss::DensityScratch); }
@@ -958,17 +957,14 @@ int ss_stream_copy(void *dst, const void *src, size_t nbytes, void *hip_stream) 
     Span spans[2] = {span(dst, nbytes, true), span(src, nbytes, false)};
     if (written_spans_overlap(spans, 2)) return SS_ERR_ARG;
     const size_t n_vec = nbytes / 16;
-    // four blocks of two rows per unit; six of one row from a gigabyte on; without the cap four rows
-    const bool capped = caps_apply();
-    const int rows = !capped ? 4 : (nbytes >= ((size_t)1 << 30) ? 1 : 2);
-    const size_t per_block = (size_t)ss::kBlock * rows;
+    const bool small = nbytes < 2 * sizeof(float) * kCachedD;
+    const size_t per_block = small ? ss::kBlock * 2 : ss::kWave;
     const size_t grid = (n_vec + per_block - 1) / per_block;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     const ss::CopyArgs a{static_cast<ss::f32x4 *>(dst), static_cast<const ss::f32x4 *>(src), n_vec};
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (rows == 1) return launch(ss::copy_kernel<1, 24>, grid, 0, stream, a);
-    if (rows == 2) return launch(ss::copy_kernel<2, 40>, grid, 0, stream, a);
-    return launch(ss::copy_kernel<4, 0>, grid, 0, stream, a);
+    if (small) return launch(ss::copy_kernel<ss::kBlock, 2>, grid, 0, stream, a);
+    return launch(ss::copy_kernel<ss::kWave, 1>, grid, 0, stream, a, ss::kWave);
 }
 
 }  // extern "C"

@@ -11,7 +11,7 @@
 // slots.  Every addition happens in an order that depends on d alone, so the
 // result is the same bits on every run.
 #pragma once
-#include "common.hpp"
+#include "vote_apply_kernels.hpp"
 
 namespace ss {
 
@@ -34,37 +34,32 @@ __device__ __forceinline__ void welford1(float g, float n, float &mean, float &m
     m2 = m2 + p;
 }
 
-template <int R, int HOLD_KB, bool LOADS_FIRST, typename G>
-__global__ __launch_bounds__(kBlock) void welford_update_kernel(const WelfordArgs a) {
+// One-wave blocks as apply_kernel (see there).  Five streams: with HOLD_KB = 8 twenty waves share a unit
+// instead of 32, us against no cap and against blocks of four waves as launched before: 25.6 M
+// coordinates 80.6 / 81.5 / 82.2, 138 M 422 / 433 / 452, 600 M 1,926 / 1,964 / 1,978; 4.4 M 16.7 / 16.2 / 16.5.
+template <int HOLD_KB, typename G>
+__global__ __launch_bounds__(kWave) void welford_update_kernel(const WelfordArgs a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, reinterpret_cast<uint32_t *>(a.mean));
     const int tid = threadIdx.x;
     const size_t tile = blockIdx.x;
     if (tile < a.n_tiles) {
-        size_t q[R];
-        f32x4 gv[R], mean[R], m2[R];
+        const size_t q = tile * kWave + tid;
+        const f32x4 gv = G::load4(a.g, q);
+        f32x4 mean = ld_stream(reinterpret_cast<const f32x4 *>(a.mean) + q);
+        f32x4 m2 = ld_stream(reinterpret_cast<const f32x4 *>(a.m2) + q);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            q[r] = (tile * R + r) * kBlock + tid;
-            gv[r] = G::load4(a.g, q[r]);
-            mean[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.mean) + q[r]);
-            m2[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.m2) + q[r]);
+        for (int c = 0; c < 4; ++c) {
+            float mean_c = mean[c], m2_c = m2[c];
+            welford1(gv[c], a.n, mean_c, m2_c);
+            mean[c] = mean_c;
+            m2[c] = m2_c;
         }
-        if (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                float mean_c = mean[r][c], m2_c = m2[r][c];
-                welford1(gv[r][c], a.n, mean_c, m2_c);
-                mean[r][c] = mean_c;
-                m2[r][c] = m2_c;
-            }
-            st_stream(reinterpret_cast<f32x4 *>(a.mean) + q[r], mean[r]);
-            st_stream(reinterpret_cast<f32x4 *>(a.m2) + q[r], m2[r]);
-        }
+        st_stream(reinterpret_cast<f32x4 *>(a.mean) + q, mean);
+        st_stream(reinterpret_cast<f32x4 *>(a.m2) + q, m2);
         return;
     }
-    const size_t i = a.n_tiles * (size_t)(R * kRowCoords) + (tile - a.n_tiles) * kBlock + tid;
+    const size_t i = a.n_tiles * (size_t)kWaveCoords + (tile - a.n_tiles) * kWave + tid;
     if (i < a.d) {
         float mean = a.mean[i], m2 = a.m2[i];
         welford1(G::load1(a.g, i), a.n, mean, m2);
@@ -86,17 +81,15 @@ __device__ __forceinline__ float sigma1(float m2, float n) {
     return __builtin_sqrtf(var);
 }
 
-template <int R, int HOLD_KB, bool LOADS_FIRST>
-__global__ __launch_bounds__(kBlock) void welford_sigma_kernel(const SigmaArgs a) {
-    reserve_lds<HOLD_KB>(a.d == ~(size_t)0, reinterpret_cast<uint32_t *>(a.sigma));
+// R rows: one, but for vectors whose one-row grid would have 2^32 threads
+template <int R>
+__global__ __launch_bounds__(kWave) void welford_sigma_kernel(const SigmaArgs a) {
     const int tid = threadIdx.x;
     const size_t tile = blockIdx.x;
     if (tile < a.n_tiles) {
         f32x4 v[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-            v[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.m2) + (tile * R + r) * kBlock + tid);
-        if (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
+        for (int r = 0; r < R; ++r) v[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.m2) + (tile * R + r) * kWave + tid);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             f32x4 s;
@@ -104,11 +97,11 @@ __global__ __launch_bounds__(kBlock) void welford_sigma_kernel(const SigmaArgs a
             s.y = sigma1(v[r].y, a.n);
             s.z = sigma1(v[r].z, a.n);
             s.w = sigma1(v[r].w, a.n);
-            st_stream(reinterpret_cast<f32x4 *>(a.sigma) + (tile * R + r) * kBlock + tid, s);
+            st_stream(reinterpret_cast<f32x4 *>(a.sigma) + (tile * R + r) * kWave + tid, s);
         }
         return;
     }
-    const size_t i = a.n_tiles * (size_t)(R * kRowCoords) + (tile - a.n_tiles) * kBlock + tid;
+    const size_t i = a.n_tiles * (size_t)(R * kWaveCoords) + (tile - a.n_tiles) * kWave + tid;
     if (i < a.d) a.sigma[i] = sigma1(a.m2[i], a.n);
 }
 

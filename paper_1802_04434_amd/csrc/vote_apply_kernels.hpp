@@ -424,6 +424,16 @@ __global__ __launch_bounds__(kBlock) void vote_sum_kernel(const VoteSumArgs a) {
     }
 }
 
+// sum_apply, copy, and Welford's update and sigma (stats_kernels.hpp) run as one-wave blocks of one row on
+// vectors that no cache holds: a finished wave's slot is refilled at once, and no cap on the resident
+// blocks is needed.  Against blocks of four waves with one to four rows, capped at some sizes, as launched
+// before (us): copy 25.6 M floats 32.1 / 33.9, 138 M 168 / 174, 600 M 719 / 738; sum apply 35.9 / 37.4,
+// 186 / 194, 801 / 842; sigma 32.2 / 33.7, 166 / 176, 714 / 777.  Cached vectors like fewer, larger blocks
+// (1.1 M: copy 2.3 / 2.8, sum apply 2.9 / 3.3).  The kernels that read shared words of bits (apply, ternary
+// apply) gain nothing from it: 25.6 M 33.4 against 33.1 and 34.0 against 33.4.
+constexpr int kWave = 64;
+constexpr int kWaveCoords = kWave * kQuad;
+
 struct SumApplyArgs {
     float *x;
     const int8_t *sums;
@@ -432,9 +442,8 @@ struct SumApplyArgs {
     size_t n_tiles;
 };
 
-template <int R, int HOLD_KB, bool LOADS_FIRST>
-__global__ __launch_bounds__(kBlock) void sum_apply_kernel(const SumApplyArgs a) {
-    reserve_lds<HOLD_KB>(a.d == ~(size_t)0, reinterpret_cast<uint32_t *>(a.x));
+template <int BLOCK, int R>
+__global__ __launch_bounds__(BLOCK) void sum_apply_kernel(const SumApplyArgs a) {
     const int tid = threadIdx.x;
     const size_t tile = blockIdx.x;
     if (tile < a.n_tiles) {
@@ -443,11 +452,10 @@ __global__ __launch_bounds__(kBlock) void sum_apply_kernel(const SumApplyArgs a)
         uint32_t sw[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            q[r] = (tile * R + r) * kBlock + tid;
+            q[r] = (tile * R + r) * BLOCK + tid;
             xv[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + q[r]);
             sw[r] = ld_stream(reinterpret_cast<const uint32_t *>(a.sums) + q[r]);
         }
-        if (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             f32x4 v = xv[r];
@@ -459,7 +467,7 @@ __global__ __launch_bounds__(kBlock) void sum_apply_kernel(const SumApplyArgs a)
         }
         return;
     }
-    const size_t i = a.n_tiles * (size_t)(R * kRowCoords) + (tile - a.n_tiles) * kBlock + tid;
+    const size_t i = a.n_tiles * (size_t)(R * BLOCK * kQuad) + (tile - a.n_tiles) * BLOCK + tid;
     if (i < a.d) a.x[i] = step_sum(a.x[i], a.delta, (int)a.sums[i]);
 }
 
@@ -471,18 +479,16 @@ struct CopyArgs {
     size_t n_vec;
 };
 
-template <int R, int HOLD_KB>
-__global__ __launch_bounds__(kBlock) void copy_kernel(const CopyArgs a) {
-    reserve_lds<HOLD_KB>(a.n_vec == ~(size_t)0, reinterpret_cast<uint32_t *>(a.dst));
-    const size_t base = (size_t)blockIdx.x * (kBlock * R) + threadIdx.x;
+template <int BLOCK, int R>
+__global__ __launch_bounds__(BLOCK) void copy_kernel(const CopyArgs a) {
+    const size_t base = (size_t)blockIdx.x * (BLOCK * R) + threadIdx.x;
     f32x4 v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r)
-        if (base + r * kBlock < a.n_vec) v[r] = ld_stream(a.src + base + r * kBlock);
-    __builtin_amdgcn_sched_barrier(0);
+        if (base + r * BLOCK < a.n_vec) v[r] = ld_stream(a.src + base + r * BLOCK);
 #pragma unroll
     for (int r = 0; r < R; ++r)
-        if (base + r * kBlock < a.n_vec) st_stream(a.dst + base + r * kBlock, v[r]);
+        if (base + r * BLOCK < a.n_vec) st_stream(a.dst + base + r * BLOCK, v[r]);
 }
 
 }  // namespace ss
