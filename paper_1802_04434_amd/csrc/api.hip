@@ -748,12 +748,12 @@ static int density_impl(const float *v, size_t d, double *out, ss::DensityScratc
     a.out = out;
     a.scratch = partials;
     a.d = d;
-    a.n_tiles = d / ((size_t)ss::kDensityRows * ss::kDensityThreads * ss::kQuad);
+    a.n_rows = d / ((size_t)ss::kDensityThreads * ss::kQuad);
+    a.n_tiles = a.n_rows / ss::kDensityRows;
     // every block gets the same number of tiles (the last one possibly fewer): the grid is a
     // function of d alone, which is what fixes the order of the additions
     const size_t per_block = (a.n_tiles + ss::kDensityMaxBlocks - 1) / ss::kDensityMaxBlocks;
-    size_t grid = per_block ? (a.n_tiles + per_block - 1) / per_block : 1;
-    if (grid == 0) grid = 1;
+    const size_t grid = per_block ? (a.n_tiles + per_block - 1) / per_block : 1;
     return launch(ss::density_kernel, grid, 0, stream, a, ss::kDensityThreads);
 }
 

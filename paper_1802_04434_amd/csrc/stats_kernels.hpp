@@ -106,19 +106,25 @@ __global__ __launch_bounds__(kWave) void welford_sigma_kernel(const SigmaArgs a)
 }
 
 // ------------------------------------------------------------- density ----
-// One launch, fixed summation order.  Block b owns tiles b, b + G, b + 2G, ...
-// (G = gridDim.x <= kDensityMaxBlocks, a function of d alone); each lane adds its elements in that
-// order in fp64, lanes combine through a shuffle tree, waves through LDS, and
-// the block's two sums go to slot b of a scratch array.  The block that takes
-// the last ticket adds the G slots in a fixed order (whichever block it is),
-// writes the result and puts the ticket back to zero for the next call.
+// One launch, fixed summation order.  Block b owns tiles b, b + G, b + 2G, ... of kDensityRows rows of
+// kDensityThreads quads (G = gridDim.x <= kDensityMaxBlocks, a function of d alone); the rows left over
+// go to the blocks one by one.  Each lane adds its elements in that order in fp64, lanes combine
+// through a shuffle tree, waves through LDS, and the block's two sums go to slot b of a scratch array.
+// The block that takes the last ticket adds the G slots in a fixed order (whichever block it is),
+// writes the result and puts the ticket back to zero for the next call.  A vector of less than two
+// tiles is one block's, which needs neither slots nor ticket.
+//
+// What does not fill a tile used to be added one coordinate a lane and turn, a chain of up to 32
+// dependent loads (us): d = 1,000 3.6 -> 2.2, 10,007 5.5 -> 2.7, 40,001 5.0 -> 4.4.  Dealing all rows out
+// evenly instead of whole tiles to 134 - 256 blocks costs 1 us at 4.4 M (more tickets) and gains
+// nothing at 25.6 M.
 
 // Few, large blocks: the tickets are atomics on one address and cost about 11 ns each, one after
 // the other, at the very end of the launch (measured: 780 blocks of 256 threads 25 us at
 // d = 25.6 M, 223 blocks of 512 threads 18 us; a plain read of the same bytes 16 us).
 constexpr int kDensityMaxBlocks = 256;
 constexpr int kDensityThreads = 512;
-constexpr int kDensityRows = 8;          // rows of kDensityThreads * 4 coordinates per tile
+constexpr int kDensityRows = 8;          // rows of a tile, whose loads are issued together
 
 // layout of the scratch area: ticket counter, then one pair of sums per block
 struct DensityScratch {
@@ -132,7 +138,8 @@ struct DensityArgs {
     double *out;       // out[0] = |v|_1, out[1] = |v|_2^2, out[2] = phi
     DensityScratch *scratch;
     size_t d;
-    size_t n_tiles;    // tiles of kDensityRows rows
+    size_t n_tiles;    // full tiles
+    size_t n_rows;     // full rows, those of the tiles included
 };
 
 __device__ __forceinline__ void accumulate(float v, double &l1, double &l2sq) {
@@ -166,6 +173,41 @@ __device__ __forceinline__ void block_sum(double &s1, double &s2, double (*part)
     __syncthreads();
 }
 
+__device__ __forceinline__ void density_result(const DensityArgs &a, double s1, double s2) {
+    a.out[0] = s1;
+    a.out[1] = s2;
+    a.out[2] = s2 > 0.0 ? s1 * s1 / ((double)a.d * s2) : 0.0;
+}
+
+// the quads of N rows first, then the rows into the running sums: the longest chain of additions is
+// 4 N + (batches per block), not their product
+template <int N>
+__device__ __forceinline__ void density_batch(const f32x4 *v, size_t row, size_t stride, double &l1, double &l2sq) {
+    f32x4 q[N];
+#pragma unroll
+    for (int r = 0; r < N; ++r) q[r] = ld_stream(v + (row + r * stride) * kDensityThreads);
+    double t1 = 0.0, t2 = 0.0;
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        accumulate(q[r].x, t1, t2);
+        accumulate(q[r].y, t1, t2);
+        accumulate(q[r].z, t1, t2);
+        accumulate(q[r].w, t1, t2);
+    }
+    l1 += t1;
+    l2sq += t2;
+}
+
+// the n <= NMAX rows that full batches leave over, as one batch of exactly that size
+template <int NMAX>
+__device__ __forceinline__ void density_rest(const f32x4 *v, size_t row, size_t stride, size_t n, double &l1, double &l2sq) {
+    if (n == NMAX) {
+        density_batch<NMAX>(v, row, stride, l1, l2sq);
+    } else if constexpr (NMAX > 1) {
+        density_rest<NMAX - 1>(v, row, stride, n, l1, l2sq);
+    }
+}
+
 __global__ __launch_bounds__(kDensityThreads) void density_kernel(const DensityArgs a) {
     constexpr int R = kDensityRows;
     constexpr int B = kDensityThreads;
@@ -174,29 +216,22 @@ __global__ __launch_bounds__(kDensityThreads) void density_kernel(const DensityA
     const int tid = threadIdx.x;
     const unsigned G = gridDim.x;
     double l1 = 0.0, l2sq = 0.0;
-    for (size_t tile = blockIdx.x; tile < a.n_tiles; tile += G) {
-        f32x4 v[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            v[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.v) + (tile * R + r) * B + tid);
-        // a tile's 32 elements first, then the tile into the running sums: the longest chain of
-        // additions is 32 + (tiles per block), not their product
-        double t1 = 0.0, t2 = 0.0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            accumulate(v[r].x, t1, t2);
-            accumulate(v[r].y, t1, t2);
-            accumulate(v[r].z, t1, t2);
-            accumulate(v[r].w, t1, t2);
-        }
-        l1 += t1;
-        l2sq += t2;
+    const f32x4 *const v = reinterpret_cast<const f32x4 *>(a.v) + tid;
+    for (size_t tile = blockIdx.x; tile < a.n_tiles; tile += G) density_batch<R>(v, tile * R, 1, l1, l2sq);
+    const size_t row = a.n_tiles * R + blockIdx.x;
+    if (row < a.n_rows) density_rest<R - 1>(v, row, G, (a.n_rows - row + G - 1) / G, l1, l2sq);
+    // what does not fill a row, by the last block: at most one quad a lane, then up to three coordinates
+    if (blockIdx.x == G - 1) {
+        const size_t quad = a.n_rows * B + tid;
+        if (quad < a.d / kQuad) density_batch<1>(v, a.n_rows, 0, l1, l2sq);
+        const size_t i = a.d / kQuad * kQuad + tid;
+        if (i < a.d) accumulate(a.v[i], l1, l2sq);
     }
-    // what does not fill a tile: spread over the whole grid, one element per thread and turn
-    const size_t done = a.n_tiles * (size_t)(R * B * kQuad);
-    for (size_t i = done + (size_t)blockIdx.x * B + tid; i < a.d; i += (size_t)G * B)
-        accumulate(a.v[i], l1, l2sq);
     block_sum(l1, l2sq, part);
+    if (G == 1) {
+        if (tid == 0) density_result(a, l1, l2sq);
+        return;
+    }
     if (tid == 0) {
         // Publish the slot, then take a ticket.  The slot is written with device-scope stores
         // (they go through to where every compute die sees them) and the wave waits until they
@@ -220,9 +255,7 @@ __global__ __launch_bounds__(kDensityThreads) void density_kernel(const DensityA
     }
     block_sum(s1, s2, part);
     if (tid == 0) {
-        a.out[0] = s1;
-        a.out[1] = s2;
-        a.out[2] = s2 > 0.0 ? s1 * s1 / ((double)a.d * s2) : 0.0;
+        density_result(a, s1, s2);
         __hip_atomic_store(&a.scratch->ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
