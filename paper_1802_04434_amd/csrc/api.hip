@@ -352,10 +352,12 @@ int launch_two(const void *const *g, ss_dtype gdt, float *const *m, int M, float
     return dispatch_vote_apply(packed, M, voted, x, delta, var, d, stream);
 }
 
-// the votes read M buffers at once; with packed buffers beyond ~128 MB each (d >= 2^30) two blocks
-// per unit are faster than eight (+12 % at d = 1.5 G, M = 8), below that nothing is gained
-constexpr size_t kVoteCapMinD = (size_t)1 << 30;
-constexpr int kVoteHoldKB = 64;
+// The votes read M buffers at once and are launched as four-wave blocks without a cap up to about
+// 2^27 coordinates.  Above that one-wave blocks, from four workers on, with a cap that leaves fewer waves
+// the more loads each has out (138 M: M = 16 50.0 us against 51.9, 24 70.5 / 75.9, but 8 27.0 / 26.7;
+// 390 M: M = 4 39.4 / 41.6, 8 71.0 / 75.8, 12 100 / 108, 16 132 / 142, 24 188 / 206, but 2 24.0 / 23.1).
+constexpr int kVoteWave = 64;
+constexpr int kVoteHoldKB = 64;   // ss_quorum_vote: two four-wave blocks per unit
 
 template <int M>
 int launch_vote_fixed(const uint32_t *const *packed, uint32_t *voted, size_t d, hipStream_t stream) {
@@ -365,10 +367,13 @@ int launch_vote_fixed(const uint32_t *const *packed, uint32_t *voted, size_t d, 
     a.M = M;
     a.d = d;
     a.n_vec = ss_packed_bytes(d) / 16;
-    const size_t grid = (a.n_vec + ss::kBlock - 1) / ss::kBlock;
+    constexpr int kHold = M >= 8 ? 20 : 8;
+    const bool waves = M >= 4 && caps_apply() && d >= (M >= 12 ? kLargeD / 2 : kLargeD);
+    const size_t block = waves ? kVoteWave : ss::kBlock;
+    const size_t grid = (a.n_vec + block - 1) / block;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    if (d >= kVoteCapMinD && caps_apply()) return launch(ss::vote_kernel<M, kVoteHoldKB>, grid, 0, stream, a);
-    return launch(ss::vote_kernel<M, 0>, grid, 0, stream, a);
+    if (waves) return launch(ss::vote_kernel<M, kVoteWave, kHold>, grid, 0, stream, a, kVoteWave);
+    return launch(ss::vote_kernel<M, ss::kBlock, 0>, grid, 0, stream, a);
 }
 
 int launch_vote_any(const uint32_t *const *packed, int M, uint32_t *voted, size_t d, hipStream_t stream) {
@@ -378,10 +383,11 @@ int launch_vote_any(const uint32_t *const *packed, int M, uint32_t *voted, size_
     a.M = M;
     a.d = d;
     a.n_vec = ss_packed_bytes(d) / 16;
-    const size_t grid = (a.n_vec + ss::kBlock - 1) / ss::kBlock;
+    const size_t grid = (a.n_vec + kVoteWave - 1) / kVoteWave;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    if (d >= kVoteCapMinD && caps_apply()) return launch(ss::vote_kernel_any<kVoteHoldKB>, grid, 0, stream, a);
-    return launch(ss::vote_kernel_any<0>, grid, 0, stream, a);
+    // 25.6 M: 14.5 us against 15.3 for four-wave blocks, 1.1 M 5.2 / 5.5
+    if (d >= kLargeD / 4) return launch(ss::vote_kernel_any<kVoteWave, 16>, grid, 0, stream, a, kVoteWave);
+    return launch(ss::vote_kernel_any<kVoteWave, 8>, grid, 0, stream, a, kVoteWave);
 }
 
 // launch helpers of the ternary (vote with abstention) kernels

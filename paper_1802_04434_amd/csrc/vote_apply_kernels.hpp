@@ -78,10 +78,10 @@ __device__ __forceinline__ uint32_t live_mask(size_t wi, size_t d) {
     return (1u << (unsigned)(d - lo)) - 1u;
 }
 
-template <int M, int HOLD_KB>
-__global__ __launch_bounds__(kBlock) void vote_kernel(const VoteArgs<M> a) {
+template <int M, int BLOCK, int HOLD_KB>
+__global__ __launch_bounds__(BLOCK) void vote_kernel(const VoteArgs<M> a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.voted);
-    const size_t u = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    const size_t u = (size_t)blockIdx.x * BLOCK + threadIdx.x;
     if (u >= a.n_vec) return;
     u32x4 in[M];
 #pragma unroll
@@ -145,10 +145,10 @@ __device__ __forceinline__ void ripple_all(const uint32_t *const *packed, int M,
     }
 }
 
-template <int HOLD_KB>
-__global__ __launch_bounds__(kBlock) void vote_kernel_any(const VoteArgs<64> a) {
+template <int BLOCK, int HOLD_KB>
+__global__ __launch_bounds__(BLOCK) void vote_kernel_any(const VoteArgs<64> a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.voted);
-    const size_t u = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    const size_t u = (size_t)blockIdx.x * BLOCK + threadIdx.x;
     if (u >= a.n_vec) return;
     const int T = a.M / 2 + 1;
     u32x4 plane[kPlanes];
