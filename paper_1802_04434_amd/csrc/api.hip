@@ -205,6 +205,16 @@ int launch_step_shape(ss::StepArgs<NPTR> &a, size_t d, hipStream_t stream) {
     return launch(ss::step_kernel<MT, NPTR, BLOCK, BW, R, HOLD_KB, LOADS_FIRST, HAS_M, G>, grid, 0, stream, a, BLOCK);
 }
 
+template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB>
+int launch_octets(ss::StepArgs<NPTR> &a, size_t d, hipStream_t stream) {
+    const Tiling t = make_tiling(d, R, true, BLOCK, 2 * ss::kQuad);
+    a.n_tiles = t.n_tiles;
+    a.words_total = t.words_total;
+    const size_t grid = t.n_tiles + t.tail_blocks;
+    if (grid > kMaxGrid) return SS_ERR_ARG;
+    return launch(ss::step_bf16_kernel<MT, NPTR, BLOCK, BW, R, HOLD_KB>, grid, 0, stream, a, BLOCK);
+}
+
 // what distinguishes the variants of the step (see ss_step_flags)
 struct StepVariant {
     unsigned flags;
@@ -235,8 +245,15 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
         // reservations only mean what they should on a part with the LDS size they were sized for.
         if (streams(M, d, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0)) && lds_per_unit_kb() == kLdsPerUnitKB) {
             if constexpr (!HAS_M) {
-                // gradients only: four (bf16: eight) loads per lane make up for the missing momentum stream
-                return launch_step_shape<MT, NPTR, 256, 2, kBf16 ? 4 : 2, 64, true, false, G>(a, d, stream);
+                // gradients only.  bf16 (step_bf16_kernel): the workers' loads out together, eight at most, from
+                // one-wave blocks, fewer of them per unit the more loads each has out.  Against two workers a
+                // stage in quads, us: 25.6 M M = 3 57.1 / 59.2, 7 88.3 / 94.2, 8 98.1 / 102.0, 12 129 / 136, 16 160 / 166;
+                // 138 M M = 2 (390 M) 713 / 776, 5 386 / 403, 8 529 / 531, 12 696 / 733, 16 872 / 925
+                if constexpr (kBf16 && MT > 0 && MT <= 3) return launch_octets<MT, NPTR, 64, 4, 1, 10>(a, d, stream);
+                else if constexpr (kBf16 && MT > 0 && MT <= 6) return launch_octets<MT, NPTR, 64, 8, 1, 16>(a, d, stream);
+                else if constexpr (kBf16) return launch_octets<MT, NPTR, 64, 8, 1, MT == 16 ? 24 : 20>(a, d, stream);
+                // fp32: four loads per lane make up for the missing momentum stream
+                else return launch_step_shape<MT, NPTR, 256, 2, 2, 64, true, false, G>(a, d, stream);
             } else if constexpr (!kBf16) {
                 // fp32: one 512-thread block per unit, one worker and one row at a time
                 return launch_step_shape<MT, NPTR, 512, 1, 1, 96, true, true, G>(a, d, stream);

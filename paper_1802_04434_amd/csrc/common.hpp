@@ -79,6 +79,17 @@ __device__ __forceinline__ uint32_t neg_nibble(f32x4 v) {
     return neg_bit(v.x) | (neg_bit(v.y) << 1) | (neg_bit(v.z) << 2) | (neg_bit(v.w) << 3);
 }
 
+// signs of eight bf16, the lower coordinate in the lower half of a word
+__device__ __forceinline__ uint32_t neg_byte_bf16(u32x4 v) {
+    uint32_t byte = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        byte |= neg_bit(widen_bf16((uint16_t)v[k])) << (2 * k);
+        byte |= neg_bit(widen_bf16((uint16_t)(v[k] >> 16))) << (2 * k + 1);
+    }
+    return byte;
+}
+
 // Algorithm 3's worker update for one coordinate: s = -1 where `neg`
 __device__ __forceinline__ float step(float x, float delta, bool neg) {
     return neg ? x + delta : x - delta;

@@ -134,6 +134,43 @@ __device__ __forceinline__ void step_rest(const StepArgs<NPTR> &a, int w0, int n
     }
 }
 
+// Scalar path for what does not fill a tile: one coordinate per lane, so
+// the 64-bit wave ballot is two packed words in order.  It also writes
+// the zero padding words.
+template <bool HAS_M, typename G, int NPTR>
+__device__ __forceinline__ void step_tail(const StepArgs<NPTR> &a, int M, size_t i, int lane) {
+    const bool in = i < a.d;
+    const size_t word = i >> 5;   // for lanes 0 and 32: the word this half-wave fills
+    const bool writes_word = (lane & 31) == 0 && word < a.words_total;
+    const int T = M / 2 + 1;
+    int count = 0;
+    for (int w = 0; w < M; ++w) {
+        float v = 0.0f;
+        if (in) {
+            const float gi = G::load1(a.p.g[w], i);
+            v = gi;
+            if (HAS_M) {
+                v = momentum(a.beta, a.omb, a.p.m[w][i], gi);
+                a.p.m[w][i] = v;
+                if (a.warmup) v = gi;
+            }
+        }
+        const bool neg = in && v < 0.0f;
+        count += neg ? 1 : 0;
+        if (a.write_packed) {
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(neg);
+            if (writes_word) a.p.packed[w][word] = (uint32_t)(lane == 0 ? mask : mask >> 32);
+        }
+    }
+    const bool vneg = in && count >= T;
+    if (in) {
+        a.x[i] = a.sum_update ? step_sum(a.x[i], a.delta, M - 2 * count) : step(a.x[i], a.delta, vneg);
+        if (a.sums) a.sums[i] = (int8_t)(M - 2 * count);
+    }
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(vneg);
+    if (writes_word) a.voted[word] = (uint32_t)(lane == 0 ? mask : mask >> 32);
+}
+
 // MT  > 0: number of workers known at compile time (M == MT)
 // MT == 0: a.M workers, looped at run time
 // BLOCK  : threads per block (a row is BLOCK * 4 coordinates)
@@ -191,39 +228,103 @@ __global__ __launch_bounds__(BLOCK) void step_kernel(const StepArgs<NPTR> a) {
         return;
     }
 
-    // Scalar path for what does not fill a tile: one coordinate per lane, so
-    // the 64-bit wave ballot is two packed words in order.  It also writes
-    // the zero padding words.
-    const size_t i = a.n_tiles * (size_t)(R * BLOCK * kQuad) + (tile - a.n_tiles) * BLOCK + tid;
-    const bool in = i < a.d;
-    const size_t word = i >> 5;   // for lanes 0 and 32: the word this half-wave fills
-    const bool writes_word = (lane & 31) == 0 && word < a.words_total;
-    int count = 0;
-    for (int w = 0; w < M; ++w) {
-        float v = 0.0f;
-        if (in) {
-            const float gi = G::load1(a.p.g[w], i);
-            v = gi;
-            if (HAS_M) {
-                v = momentum(a.beta, a.omb, a.p.m[w][i], gi);
-                a.p.m[w][i] = v;
-                if (a.warmup) v = gi;
+    step_tail<HAS_M, G>(a, M, a.n_tiles * (size_t)(R * BLOCK * kQuad) + (tile - a.n_tiles) * BLOCK + tid, lane);
+}
+
+// The whole step for bf16 gradients without momentum.  The quad geometry would load 64 bits of gradient a
+// lane; here a lane loads 128 bits, an octet of coordinates, and counts its votes in two words of byte
+// counters.  x stays in quads - two per lane, whole kilobytes per wave - and what a lane needs of
+// its quads' votes comes from the octets' lanes by two lane reads at the end.
+template <int NW, int R, int NPTR>
+__device__ __forceinline__ void octet_stage(const StepArgs<NPTR> &a, int w0, const size_t (&o)[R], uint32_t (&lo)[R],
+                                            uint32_t (&hi)[R], int lane) {
+    u32x4 gv[R][NW];    // eight bf16, the lower coordinate in the lower half of a word
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) gv[r][j] = ld_stream(reinterpret_cast<const u32x4 *>(a.p.g[w0 + j]) + o[r]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t byte = neg_byte_bf16(gv[r][j]);
+            lo[r] += spread_nibble(byte & 0xFu);
+            hi[r] += spread_nibble(byte >> 4);
+            if (a.write_packed) {
+                const uint32_t word = combine4(byte, lane);
+                if ((lane & 3) == 0) a.p.packed[w0 + j][o[r] >> 2] = word;
             }
         }
-        const bool neg = in && v < 0.0f;
-        count += neg ? 1 : 0;
-        if (a.write_packed) {
-            const uint64_t mask = __builtin_amdgcn_ballot_w64(neg);
-            if (writes_word) a.p.packed[w][word] = (uint32_t)(lane == 0 ? mask : mask >> 32);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int NMAX, int R, int NPTR>
+__device__ __forceinline__ void octet_rest(const StepArgs<NPTR> &a, int w0, int n, const size_t (&o)[R], uint32_t (&lo)[R],
+                                           uint32_t (&hi)[R], int lane) {
+    if (n == NMAX) {
+        octet_stage<NMAX, R>(a, w0, o, lo, hi, lane);
+    } else if constexpr (NMAX > 1) {
+        octet_rest<NMAX - 1, R>(a, w0, n, o, lo, hi, lane);
+    }
+}
+
+// BW, R, HOLD_KB as for step_kernel; a tile is R rows of BLOCK octets
+template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB>
+__global__ __launch_bounds__(BLOCK) void step_bf16_kernel(const StepArgs<NPTR> a) {
+    reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.p.packed[0]);
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int M = MT > 0 ? MT : a.M;
+    const int T = M / 2 + 1;
+    const size_t tile = blockIdx.x;
+    if (tile < a.n_tiles) {
+        size_t o[R];
+        uint32_t lo[R], hi[R];
+        f32x4 xv[R][2];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            o[r] = (tile * R + r) * BLOCK + tid;
+            lo[r] = hi[r] = 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) xv[r][h] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + 2 * (o[r] - lane) + 64 * h + lane);
         }
+        int w0 = 0;
+        for (; w0 + BW <= M; w0 += BW) octet_stage<BW, R>(a, w0, o, lo, hi, lane);
+        if constexpr (MT > 0) {
+            if constexpr (MT % BW != 0) octet_stage<MT % BW, R>(a, w0, o, lo, hi, lane);
+        } else {
+            octet_rest<BW - 1, R>(a, w0, M - w0, o, lo, hi, lane);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t byte = vote_nibble(lo[r], T) | (vote_nibble(hi[r], T) << 4);
+            const uint32_t word = combine4(byte, lane);
+            if ((lane & 3) == 0) a.voted[o[r] >> 2] = word;
+            if (a.sums) reinterpret_cast<uint64_t *>(a.sums)[o[r]] = sums_word(lo[r], M) | ((uint64_t)sums_word(hi[r], M) << 32);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                // quad `lane` of half h lies in the octet of lane 32 h + lane / 2
+                const int from = 32 * h + (lane >> 1);
+                f32x4 v = xv[r][h];
+                if (a.sum_update) {
+                    const uint32_t l = (uint32_t)__shfl((int)lo[r], from, 64), u = (uint32_t)__shfl((int)hi[r], from, 64);
+                    const uint32_t counts = (lane & 1) ? u : l;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] = step_sum(v[c], a.delta, sum_at(counts, c, M));
+                } else {
+                    const uint32_t nib = (uint32_t)__shfl((int)byte, from, 64) >> ((lane & 1) * 4);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] = step(v[c], a.delta, (nib >> c) & 1u);
+                }
+                st_stream(reinterpret_cast<f32x4 *>(a.x) + 2 * (o[r] - lane) + 64 * h + lane, v);
+            }
+        }
+        return;
     }
-    const bool vneg = in && count >= T;
-    if (in) {
-        a.x[i] = a.sum_update ? step_sum(a.x[i], a.delta, M - 2 * count) : step(a.x[i], a.delta, vneg);
-        if (a.sums) a.sums[i] = (int8_t)(M - 2 * count);
-    }
-    const uint64_t mask = __builtin_amdgcn_ballot_w64(vneg);
-    if (writes_word) a.voted[word] = (uint32_t)(lane == 0 ? mask : mask >> 32);
+    step_tail<false, Bf16Grad>(a, M, a.n_tiles * (size_t)(R * BLOCK * 2 * kQuad) + (tile - a.n_tiles) * BLOCK + tid, lane);
 }
 
 // ---------------------------------------------------------------- pack ----
@@ -333,13 +434,7 @@ __global__ __launch_bounds__(BLOCK) void pack_bf16_kernel(const PackArgs<NPTR> a
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            uint32_t byte = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                byte |= neg_bit(widen_bf16((uint16_t)gv[r][k])) << (2 * k);
-                byte |= neg_bit(widen_bf16((uint16_t)(gv[r][k] >> 16))) << (2 * k + 1);
-            }
-            const uint32_t word = combine4(byte, lane);
+            const uint32_t word = combine4(neg_byte_bf16(gv[r]), lane);
             if ((lane & 3) == 0) w.packed[o[r] >> 2] = word;
         }
         return;

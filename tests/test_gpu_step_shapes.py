@@ -200,3 +200,28 @@ def test_large_step_on_streams_and_under_capture(ss):
         assert torch.equal(v, results[0][2])
         assert torch.equal(x.view(torch.int32), results[0][1].view(torch.int32))
         assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(m, results[0][0]))
+
+
+@pytest.mark.parametrize("M,extra,flags", [(2, 1, 0), (3, 511, 2), (4, 513, 0), (6, 63, 2),
+                                                  (7, 0, 0), (8, 255, 2), (13, 129, 0), (16, 32, 2),
+                                                  (33, 17, 0)])
+def test_bf16_gradients_without_momentum_beyond_the_cache(ss, oracle, M, extra, flags):
+    # octets of coordinates per lane, from 2^28 bytes of gradients on (a tile is 512 coordinates)
+    d = ((1 << 28) // (2 * M) + 511) // 512 * 512 + extra
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(M)
+    g = [torch.randn(d, device=DEV, generator=gen).to(torch.bfloat16) for _ in range(M)]
+    special = torch.tensor([0x0000, -0x8000, 0x0001, -0x7FFF, 0x7F80, -0x0080, 0x7FC0, -0x0040], dtype=torch.int16, device=DEV)
+    for t in g:                                     # zeros, subnormals, infinities and NaN of both signs
+        t.view(torch.int16)[:8] = special
+        t.view(torch.int16)[d - 8:] = special
+    x = torch.randn(d, device=DEV, generator=gen) * 0.05
+    x_np = synth.as_numpy(x).copy()
+    voted = dirty_bits(ss, d)
+    sums = torch.full((d,), 99, dtype=torch.int8, device=DEV)
+    ss.signum_vote_step_ex(g, None, 0.9, 1e-4, x, voted, None, sums if flags else None, flags)
+    want = oracle.signum_vote_step_ex([synth.as_numpy(t) for t in g], None, 0.9, 1e-4, x_np, flags)
+    assert np.array_equal(bits_np(voted), want[0])
+    if flags:
+        assert np.array_equal(sums.cpu().numpy(), want[2])
+    assert_same_floats(x, x_np, "x")
