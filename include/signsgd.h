@@ -258,6 +258,17 @@ int ss_signum_vote_step_ternary(const void *const *g, ss_dtype gdt,
                                 uint32_t *voted_neg, uint32_t *voted_zero,
                                 size_t d, void *hip_stream);
 
+/* ss_signum_vote_step_ternary for a caller that can lend device memory, as
+ * ss_signum_vote_step_scratch does for the binary step (two planes per worker) */
+size_t ss_ternary_scratch_bytes(ss_dtype gdt, int has_momentum, int M, size_t d);
+int ss_signum_vote_step_ternary_scratch(const void *const *g, ss_dtype gdt,
+                                        float *const *m, int M, float beta,
+                                        float tau, int quorum, float delta,
+                                        float *x, uint32_t *voted_neg,
+                                        uint32_t *voted_zero, void *scratch,
+                                        size_t scratch_bytes, size_t d,
+                                        void *hip_stream);
+
 /* ---- gradient statistics (Section 3: equation (1) and Figure 1) ---- */
 
 /*

@@ -63,6 +63,10 @@ def load_library():
         L.ss_step_scratch_bytes.argtypes = [i32, i32, i32, sz]
         L.ss_signum_vote_step_scratch.argtypes = [vp, i32, vp, i32, f32, f32, vp, vp, vp, vp, sz, sz, ctypes.c_uint, vp]
         L.ss_signum_vote_step_scratch.restype = i32
+        L.ss_ternary_scratch_bytes.restype = sz
+        L.ss_ternary_scratch_bytes.argtypes = [i32, i32, i32, sz]
+        L.ss_signum_vote_step_ternary_scratch.argtypes = [vp, i32, vp, i32, f32, f32, i32, f32, vp, vp, vp, vp, sz, sz, vp]
+        L.ss_signum_vote_step_ternary_scratch.restype = i32
         L.ss_welford_update.argtypes = [vp, i32, vp, vp, ctypes.c_uint64, sz, vp]
         L.ss_welford_sigma.argtypes = [vp, ctypes.c_uint64, vp, sz, vp]
         L.ss_density.argtypes = [vp, sz, vp, vp, vp]

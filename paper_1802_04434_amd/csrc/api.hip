@@ -410,12 +410,13 @@ int launch_vote_any(const uint32_t *const *packed, int M, uint32_t *voted, size_
 // launch helpers of the ternary (vote with abstention) kernels
 template <int BLOCK, int BW, int R, int HOLD_KB, bool LOADS_FIRST, bool HAS_M, bool VOTE, typename G>
 int launch_ternary_shape(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
+    // the step is one grid over all workers' votes, the pack one row of the grid per worker
     const Tiling t = make_tiling(d, R, true, BLOCK);
     a.n_tiles = t.n_tiles;
     a.words_total = t.words_total;
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    return launch(ss::ternary_step_kernel<BLOCK, BW, R, HOLD_KB, LOADS_FIRST, HAS_M, VOTE, G>, grid, 0, stream, a, BLOCK);
+    return launch(ss::ternary_step_kernel<BLOCK, BW, R, HOLD_KB, LOADS_FIRST, HAS_M, VOTE, G>, grid, 0, stream, a, BLOCK, VOTE ? 1 : a.M);
 }
 
 // The ternary kernel takes any M at run time.  Below the line of streams() it runs one-wave blocks with
@@ -456,6 +457,33 @@ int dispatch_ternary(ss::TernaryStepArgs &a, ss_dtype gdt, bool has_m, size_t d,
     }
     if (gdt == SS_F32) return launch_ternary<false, VOTE, ss::F32Grad>(a, d, stream);
     return launch_ternary<false, VOTE, ss::Bf16Grad>(a, d, stream);
+}
+
+// answer and update from the planes a pack launch left in a.neg_out / a.zero_out; shapes as launch_vote_apply
+int launch_quorum_apply(const ss::TernaryStepArgs &t, uint32_t *voted_neg, uint32_t *voted_zero, float *x, size_t d,
+                        hipStream_t stream) {
+    ss::QuorumApplyArgs a;
+    a.neg = t.neg_out;
+    a.zero = t.zero_out;
+    a.plane_stride = t.plane_stride;
+    a.voted_neg = voted_neg;
+    a.voted_zero = voted_zero;
+    a.x = x;
+    a.delta = t.delta;
+    a.M = t.M;
+    a.quorum = std::min(t.quorum, t.M + 1);   // no quorum above M is ever met: same answers
+    a.d = d;
+    a.words_total = ss_packed_bytes(d) / 4;
+    const bool large = d >= kLargeD;
+    const size_t words = large ? 32 : 128;
+    const size_t grid = (a.words_total + words - 1) / words;
+    if (grid > kMaxGrid) return SS_ERR_ARG;
+    const int planes = count_planes(t.M);
+    if (planes <= 3)
+        return large ? launch(ss::quorum_apply_kernel<3, 1, 0>, grid, 0, stream, a) : launch(ss::quorum_apply_kernel<3, 4, 39>, grid, 0, stream, a);
+    if (planes <= 5)
+        return large ? launch(ss::quorum_apply_kernel<5, 1, 0>, grid, 0, stream, a) : launch(ss::quorum_apply_kernel<5, 4, 39>, grid, 0, stream, a);
+    return large ? launch(ss::quorum_apply_kernel<7, 1, 0>, grid, 0, stream, a) : launch(ss::quorum_apply_kernel<7, 4, 39>, grid, 0, stream, a);
 }
 
 }  // namespace
@@ -925,9 +953,9 @@ int ss_ternary_apply(float *x, const uint32_t *neg, const uint32_t *zero, float 
     return launch(ss::ternary_apply_kernel<4, 0, false>, grid, 0, stream, a);
 }
 
-int ss_signum_vote_step_ternary(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float tau,
-                                int quorum, float delta, float *x, uint32_t *voted_neg, uint32_t *voted_zero,
-                                size_t d, void *hip_stream) {
+static int ternary_step_impl(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float tau, int quorum,
+                             float delta, float *x, uint32_t *voted_neg, uint32_t *voted_zero, void *scratch,
+                             size_t scratch_bytes, size_t d, void *hip_stream) {
     if (M < 1 || M > SS_MAX_WORKERS) return SS_ERR_BAD_M;
     if (gdt != SS_F32 && gdt != SS_BF16) return SS_ERR_DTYPE;
     if (!(tau >= 0.0f) || quorum < 1) return SS_ERR_ARG;
@@ -937,13 +965,13 @@ int ss_signum_vote_step_ternary(const void *const *g, ss_dtype gdt, float *const
         if (!g[w]) return SS_ERR_NULL;
         if (m && !m[w]) return SS_ERR_NULL;
     }
-    if (!aligned16(x) || !aligned16(voted_neg) || !aligned16(voted_zero)) return SS_ERR_ALIGN;
+    if (!aligned16(x) || !aligned16(voted_neg) || !aligned16(voted_zero) || !aligned16(scratch)) return SS_ERR_ALIGN;
     for (int w = 0; w < M; ++w) {
         if (!aligned16(g[w])) return SS_ERR_ALIGN;
         if (m && !aligned16(m[w])) return SS_ERR_ALIGN;
     }
     {
-        Span spans[2 * SS_MAX_WORKERS + 3];
+        Span spans[2 * SS_MAX_WORKERS + 4];
         int n = 0;
         for (int w = 0; w < M; ++w) {
             spans[n++] = span(g[w], d * grad_bytes(gdt), false);
@@ -952,6 +980,7 @@ int ss_signum_vote_step_ternary(const void *const *g, ss_dtype gdt, float *const
         spans[n++] = span(x, d * sizeof(float), true);
         spans[n++] = span(voted_neg, ss_packed_bytes(d), true);
         spans[n++] = span(voted_zero, ss_packed_bytes(d), true);
+        spans[n++] = span(scratch, scratch_bytes, true);
         if (written_spans_overlap(spans, n)) return SS_ERR_ARG;
     }
     ss::TernaryStepArgs a{};
@@ -969,8 +998,47 @@ int ss_signum_vote_step_ternary(const void *const *g, ss_dtype gdt, float *const
     a.M = M;
     a.quorum = quorum;
     a.d = d;
-    return dispatch_ternary<true>(a, gdt, m != nullptr, d, static_cast<hipStream_t>(hip_stream));
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const size_t slab = scratch ? scratch_slab(2 * M, d, scratch_bytes) : 0;
+    if (slab < kScratchMinSlab) return dispatch_ternary<true>(a, gdt, m != nullptr, d, stream);
+    // pack over all workers, then answer and update, over as much of the vector as the lent memory holds
+    const size_t plane = ss_packed_bytes(slab) / 4;
+    a.neg_out = static_cast<uint32_t *>(scratch);
+    a.zero_out = a.neg_out + plane;
+    a.plane_stride = 2 * plane;
+    for (size_t lo = 0; lo < d; lo += slab) {
+        const size_t n = std::min(slab, d - lo);
+        for (int w = 0; w < M; ++w) {
+            a.g[w] = static_cast<const char *>(g[w]) + lo * grad_bytes(gdt);
+            a.m[w] = m ? m[w] + lo : nullptr;
+        }
+        a.d = n;
+        int rc = dispatch_ternary<false>(a, gdt, m != nullptr, n, stream);
+        if (rc == SS_OK) rc = launch_quorum_apply(a, voted_neg + lo / 32, voted_zero + lo / 32, x + lo, n, stream);
+        if (rc != SS_OK) return rc;
+    }
+    return SS_OK;
 }
+
+int ss_signum_vote_step_ternary(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float tau,
+                                int quorum, float delta, float *x, uint32_t *voted_neg, uint32_t *voted_zero,
+                                size_t d, void *hip_stream) {
+    return ternary_step_impl(g, gdt, m, M, beta, tau, quorum, delta, x, voted_neg, voted_zero, nullptr, 0, d, hip_stream);
+}
+
+size_t ss_ternary_scratch_bytes(ss_dtype gdt, int has_momentum, int M, size_t d) {
+    if (ss_step_scratch_bytes(gdt, has_momentum, M, d) == 0) return 0;
+    return (size_t)(2 * M) * ss_packed_bytes(scratch_slab(2 * M, d, kScratchBytes));
+}
+
+int ss_signum_vote_step_ternary_scratch(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta,
+                                        float tau, int quorum, float delta, float *x, uint32_t *voted_neg,
+                                        uint32_t *voted_zero, void *scratch, size_t scratch_bytes, size_t d,
+                                        void *hip_stream) {
+    return ternary_step_impl(g, gdt, m, M, beta, tau, quorum, delta, x, voted_neg, voted_zero, scratch,
+                             scratch ? scratch_bytes : 0, d, hip_stream);
+}
+
 
 int ss_stream_copy(void *dst, const void *src, size_t nbytes, void *hip_stream) {
     if (nbytes == 0) return SS_OK;

@@ -417,9 +417,11 @@ PyObject *signum_vote_step_ternary(PyObject *, PyObject *const *a, Py_ssize_t n)
         uint32_t *vneg = (uint32_t *)dev(a[7], kBits, words, "voted_neg");
         uint32_t *vzero = (uint32_t *)dev(a[8], kBits, words, "voted_zero");
         const hipStream_t s = stream_arg(a[10]);
+        const int device = tensor(a[6], "x").device().index();
         return unlocked([&] {
-            return ss_signum_vote_step_ternary(g.as<const void>(), gdt, has_m ? m.as<float>() : nullptr, g.n, beta, tau, quorum,
-                                               delta, x, vneg, vzero, d, s);
+            const Lent scratch(ss_ternary_scratch_bytes(gdt, has_m, g.n, d), device, s);
+            return ss_signum_vote_step_ternary_scratch(g.as<const void>(), gdt, has_m ? m.as<float>() : nullptr, g.n, beta, tau,
+                                                       quorum, delta, x, vneg, vzero, scratch.p, scratch.bytes, d, s);
         });
     });
 }

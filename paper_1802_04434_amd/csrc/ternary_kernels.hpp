@@ -22,8 +22,9 @@ namespace ss {
 struct TernaryStepArgs {
     const void *g[64];
     float *m[64];          // all NULL without momentum
-    uint32_t *neg_out;     // pack only: this worker's planes
-    uint32_t *zero_out;
+    uint32_t *neg_out;     // pack only: the planes of worker 0; the next worker's lie plane_stride words
+    uint32_t *zero_out;    // further (blockIdx.y selects the worker)
+    size_t plane_stride;
     float *x;              // fused only
     uint32_t *voted_neg;
     uint32_t *voted_zero;
@@ -50,6 +51,8 @@ __device__ __forceinline__ float step_ternary(float x, float delta, uint32_t ans
 template <int NW, int R, bool LOADS_FIRST, bool HAS_M, bool VOTE, typename G>
 __device__ __forceinline__ void ternary_stage(const TernaryStepArgs &a, int w0, const size_t (&q)[R],
                                               uint32_t (&n_neg)[R], uint32_t (&n_zero)[R], int lane) {
+    uint32_t *const neg_out = VOTE ? nullptr : a.neg_out + w0 * a.plane_stride;
+    uint32_t *const zero_out = VOTE ? nullptr : a.zero_out + w0 * a.plane_stride;
     f32x4 gv[R][NW], mv[R][NW];
 #pragma unroll
     for (int j = 0; j < NW; ++j) {
@@ -87,8 +90,8 @@ __device__ __forceinline__ void ternary_stage(const TernaryStepArgs &a, int w0, 
                 const uint32_t nw = combine8(neg_nib, lane);
                 const uint32_t zw = combine8(zero_nib, lane);
                 if ((lane & 7) == 0) {
-                    a.neg_out[q[r] >> 3] = nw;
-                    a.zero_out[q[r] >> 3] = zw;
+                    neg_out[q[r] >> 3] = nw;
+                    zero_out[q[r] >> 3] = zw;
                 }
             }
         }
@@ -129,9 +132,13 @@ __global__ __launch_bounds__(BLOCK) void ternary_step_kernel(const TernaryStepAr
             n_zero[r] = 0;
             if (VOTE) xv[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + q[r]);
         }
-        int w0 = 0;
-        for (; w0 + BW <= M; w0 += BW) ternary_stage<BW, R, LOADS_FIRST, HAS_M, VOTE, G>(a, w0, q, n_neg, n_zero, lane);
-        if constexpr (BW > 1) ternary_rest<BW - 1, R, LOADS_FIRST, HAS_M, VOTE, G>(a, w0, M - w0, q, n_neg, n_zero, lane);
+        if constexpr (VOTE) {
+            int w0 = 0;
+            for (; w0 + BW <= M; w0 += BW) ternary_stage<BW, R, LOADS_FIRST, HAS_M, true, G>(a, w0, q, n_neg, n_zero, lane);
+            if constexpr (BW > 1) ternary_rest<BW - 1, R, LOADS_FIRST, HAS_M, true, G>(a, w0, M - w0, q, n_neg, n_zero, lane);
+        } else {
+            ternary_stage<1, R, LOADS_FIRST, HAS_M, false, G>(a, blockIdx.y, q, n_neg, n_zero, lane);
+        }
         if (VOTE) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -163,7 +170,7 @@ __global__ __launch_bounds__(BLOCK) void ternary_step_kernel(const TernaryStepAr
     const size_t word = i >> 5;
     const bool writes_word = (lane & 31) == 0 && word < a.words_total;
     int n_neg = 0, n_zero = 0;
-    for (int w = 0; w < M; ++w) {
+    for (int w = VOTE ? 0 : (int)blockIdx.y; w < (VOTE ? M : (int)blockIdx.y + 1); ++w) {
         float v = 0.0f;
         if (in) {
             v = G::load1(a.g[w], i);
@@ -180,8 +187,8 @@ __global__ __launch_bounds__(BLOCK) void ternary_step_kernel(const TernaryStepAr
             const uint64_t nmask = __builtin_amdgcn_ballot_w64(neg);
             const uint64_t zmask = __builtin_amdgcn_ballot_w64(abstain);
             if (writes_word) {
-                a.neg_out[word] = (uint32_t)(lane == 0 ? nmask : nmask >> 32);
-                a.zero_out[word] = (uint32_t)(lane == 0 ? zmask : zmask >> 32);
+                a.neg_out[w * a.plane_stride + word] = (uint32_t)(lane == 0 ? nmask : nmask >> 32);
+                a.zero_out[w * a.plane_stride + word] = (uint32_t)(lane == 0 ? zmask : zmask >> 32);
             }
         }
     }
@@ -300,6 +307,105 @@ __global__ __launch_bounds__(kBlock) void quorum_vote_kernel(const QuorumVoteArg
     live.w = live_mask(4 * u + 3, a.d);
     st_stream(reinterpret_cast<u32x4 *>(a.voted_neg) + u, is_neg & live);
     st_stream(reinterpret_cast<u32x4 *>(a.voted_zero) + u, not_plus & ~is_neg & live);
+}
+
+// ----------------------------------------------------- server + apply ----
+// The answer and the update in one launch, from planes that one pack launch over all workers left in
+// memory (vote_apply_kernel's counterpart): a lane decides a word's 32 coordinates, LDS hands the
+// two words of the answer to the lanes that own x.
+
+struct QuorumApplyArgs {
+    const uint32_t *neg;      // worker 0's planes; the next worker's lie plane_stride words further
+    const uint32_t *zero;
+    size_t plane_stride;
+    uint32_t *voted_neg;
+    uint32_t *voted_zero;
+    float *x;
+    float delta;
+    int M;
+    int quorum;
+    size_t d;
+    size_t words_total;
+};
+
+// P planes of the counts, as quorum_vote_kernel.  A block owns R rows of 1024 coordinates.
+template <int P, int R, int HOLD_KB>
+__global__ __launch_bounds__(kBlock) void quorum_apply_kernel(const QuorumApplyArgs a) {
+    reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.voted_neg);
+    constexpr int kWords = 32 * R;
+    __shared__ uint32_t answer[2][kWords];
+    const int tid = threadIdx.x;
+    const size_t wi = (size_t)blockIdx.x * kWords + tid;
+    const size_t base = (size_t)blockIdx.x * (R * kRowCoords);
+    const bool full = base + (size_t)(R * kRowCoords) <= a.d;
+    f32x4 xv[R];
+    f32x4 *const xq = reinterpret_cast<f32x4 *>(a.x + base) + tid;
+    if (full) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) xv[r] = ld_stream(xq + r * kBlock);
+    }
+    if (tid < kWords && wi < a.words_total) {
+        uint32_t n[P], z[P];
+#pragma unroll
+        for (int k = 0; k < P; ++k) n[k] = z[k] = 0;
+        for (int w0 = 0; w0 < a.M; w0 += kQuorumBatch) {
+            uint32_t nw[kQuorumBatch], zw[kQuorumBatch];
+#pragma unroll
+            for (int j = 0; j < kQuorumBatch; ++j) {
+                const size_t at = (size_t)(w0 + j < a.M ? w0 + j : w0) * a.plane_stride + wi;
+                nw[j] = a.neg[at];
+                zw[j] = a.zero[at];
+            }
+#pragma unroll
+            for (int j = 0; j < kQuorumBatch; ++j) {
+                uint32_t cn = w0 + j < a.M ? nw[j] : 0u, cz = w0 + j < a.M ? zw[j] : 0u;   // never both: pack wrote them
+#pragma unroll
+                for (int k = 0; k < P; ++k) {
+                    const uint32_t tn = n[k] & cn, tz = z[k] & cz;
+                    n[k] ^= cn;
+                    z[k] ^= cz;
+                    cn = tn;
+                    cz = tz;
+                }
+            }
+        }
+        // t = 2 n + z against M + Q and M - Q + 1, from the lowest plane up
+        uint32_t is_neg = 0xFFFFFFFFu, not_plus = 0xFFFFFFFFu, carry = 0;
+        const int hi = a.M + a.quorum, lo = a.M - a.quorum + 1;
+#pragma unroll
+        for (int k = 0; k <= P; ++k) {
+            const uint32_t u = k > 0 ? n[k > 0 ? k - 1 : 0] : 0u, v = k < P ? z[k < P ? k : 0] : 0u;
+            const uint32_t uv = u ^ v, t = uv ^ carry;
+            carry = (u & v) | (uv & carry);
+            is_neg = ge_step(is_neg, t, hi, k);
+            not_plus = ge_step(not_plus, t, lo, k);
+        }
+        if (hi >= (2 << P)) is_neg = 0u;           // t < 2^(P + 1)
+        if (lo <= 0) not_plus = 0xFFFFFFFFu;
+        const uint32_t live = live_mask(wi, a.d);
+        const uint32_t neg = is_neg & live, zero = not_plus & ~is_neg & live;
+        a.voted_neg[wi] = neg;
+        a.voted_zero[wi] = zero;
+        answer[0][tid] = neg;
+        answer[1][tid] = zero;
+    }
+    __syncthreads();
+    if (full) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int word = r * 32 + (tid >> 3), shift = (tid & 7) * 4;
+            const uint32_t nn = answer[0][word] >> shift, zn = answer[1][word] >> shift;
+            f32x4 v = xv[r];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = step_ternary(v[c], a.delta, ((nn >> c) & 1u) | (((zn >> c) & 1u) << 1));
+            st_stream(xq + r * kBlock, v);
+        }
+        return;
+    }
+    for (int i = tid; base + i < a.d; i += kBlock) {
+        const uint32_t ans = ((answer[0][i >> 5] >> (i & 31)) & 1u) | (((answer[1][i >> 5] >> (i & 31)) & 1u) << 1);
+        a.x[base + i] = step_ternary(a.x[base + i], a.delta, ans);
+    }
 }
 
 // ------------------------------------------------------------ apply ----

@@ -225,3 +225,39 @@ def test_bf16_gradients_without_momentum_beyond_the_cache(ss, oracle, M, extra, 
     if flags:
         assert np.array_equal(sums.cpu().numpy(), want[2])
     assert_same_floats(x, x_np, "x")
+
+
+@pytest.mark.parametrize("d,M,dtype,momentum,quorum,room", [
+    ((1 << 20), 8, "bf16", True, 2, 1 << 20),                       # one slab exactly
+    (2 * (1 << 20) + 8191, 5, "f32", True, 1, (1 << 20) + 16384),   # two slabs, ragged end
+    ((1 << 21) + 33, 9, "bf16", False, 9, (1 << 20) + 8192),        # every worker has to agree
+    ((1 << 20) + 1027, 17, "f32", True, 100, 1 << 22),              # a quorum that is never met
+    ((1 << 20) + 129, 64, "bf16", True, 3, 1 << 21), ((1 << 20) + 31, 33, "f32", True, 64, 1 << 21),
+    ((1 << 28) + 1057, 2, "bf16", True, 2, 1 << 29),                # answer-and-update blocks of one row
+    ((1 << 20) + 64, 4, "f32", True, 2, 1 << 19),                   # too little room: one pass
+])
+def test_ternary_step_with_lent_scratch(ss, oracle, d, M, dtype, momentum, quorum, room):
+    import ctypes
+    L = ss.load_library()
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d + M)
+    T = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = [(torch.randn(d, device=DEV, generator=gen) * 0.3).to(T) for _ in range(M)]
+    m = [torch.randn(d, device=DEV, generator=gen) * 0.2 for _ in range(M)] if momentum else None
+    x = torch.randn(d, device=DEV, generator=gen) * 0.05
+    m_np = [synth.as_numpy(t).copy() for t in m] if momentum else None
+    x_np = synth.as_numpy(x).copy()
+    nbytes = 2 * M * (room // 8)
+    scratch = torch.full((nbytes + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    neg, zero = dirty_bits(ss, d), dirty_bits(ss, d)
+    ptrs = lambda ts: (ctypes.c_void_p * len(ts))(*[t.data_ptr() for t in ts])     # noqa: E731
+    rc = L.ss_signum_vote_step_ternary_scratch(
+        ptrs(g), int(dtype == "bf16"), ptrs(m) if momentum else None, M, 0.9, 0.1, quorum, 1e-4, x.data_ptr(), neg.data_ptr(),
+        zero.data_ptr(), scratch.data_ptr(), nbytes, d, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    want_neg, want_zero = oracle.signum_vote_step_ternary([synth.as_numpy(t) for t in g], m_np, 0.9, 0.1, quorum, 1e-4, x_np)
+    assert np.array_equal(bits_np(neg), want_neg) and np.array_equal(bits_np(zero), want_zero)
+    for w in range(M if momentum else 0):
+        assert_same_floats(m[w], m_np[w], "m[%d]" % w)
+    assert_same_floats(x, x_np, "x")
+    assert bool((scratch[nbytes:] == 0xA5).all())

@@ -243,6 +243,8 @@ def test_lent_scratch_is_bounded_and_validated(lib):
                 n = lib.ss_step_scratch_bytes(gdt, 1, M, d)
                 assert n <= 128 << 20 and n % (16 * M) == 0
                 assert n == 0 or n // M * 8 >= min(d, 1 << 20)
+                t = lib.ss_ternary_scratch_bytes(gdt, 1, M, d)
+                assert t <= 128 << 20 and t % (32 * M) == 0 and (t == 0) == (n == 0)
     # nothing wanted: one worker, no momentum, small vectors, what a step would refuse
     for args in ((0, 1, 1, 1 << 30), (0, 0, 8, 1 << 30), (0, 1, 8, 1 << 19), (2, 1, 8, 1 << 30), (0, 1, 65, 1 << 30), (0, 1, 0, 8)):
         assert lib.ss_step_scratch_bytes(*args) == 0
@@ -259,3 +261,13 @@ def test_lent_scratch_is_bounded_and_validated(lib):
     assert step(ctypes.c_void_p(0x700000), 64, M=65) == -2
     assert step(ctypes.c_void_p(0x700000), 64, flags=4) == -5
     assert step(ctypes.c_void_p(0x700000), 64, d=0) == 0
+
+    neg, zero = ctypes.c_void_p(0x600000), ctypes.c_void_p(0x680000)
+
+    def ternary(scratch, nbytes, quorum=1, d=1024):
+        return lib.ss_signum_vote_step_ternary_scratch(two, 0, m, 2, 0.9, 0.1, quorum, 0.1, x, neg, zero, scratch, nbytes, d, None)
+
+    assert ternary(odd, 64) == -3
+    assert ternary(ctypes.c_void_p(0x680010), 64) == -5         # shares bytes with a voted plane
+    assert ternary(ctypes.c_void_p(0x700000), 64, quorum=0) == -5
+    assert ternary(ctypes.c_void_p(0x700000), 64, d=0) == 0
