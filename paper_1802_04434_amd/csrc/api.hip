@@ -374,6 +374,11 @@ int launch_two(const void *const *g, ss_dtype gdt, float *const *m, int M, float
 // the more loads each has out (138 M: M = 16 50.0 us against 51.9, 24 70.5 / 75.9, but 8 27.0 / 26.7;
 // 390 M: M = 4 39.4 / 41.6, 8 71.0 / 75.8, 12 100 / 108, 16 132 / 142, 24 188 / 206, but 2 24.0 / 23.1).
 constexpr int kVoteWave = 64;
+// One word a lane instead of four (the *_word_kernels) up to here.  us, word against 128-bit lanes: sums
+// M = 16 10,007 coordinates 3.0 / 5.2, 4.4 M 4.4 / 6.2, 17.6 M 10.0 / 11.4, M = 7 1.1 M 3.0 / 3.8, 4.4 M 4.0 / 4.2, 8.8 M
+// 5.2 / 4.9; quorum M = 16 10,007 2.7 / 5.0, 4.4 M 5.2 / 7.5, 17.6 M 12.6 / 15.8, 40 M 34 / 30, M = 4 4.4 M 2.9 / 3.1, 8.8 M
+// 3.8 / 3.7; vote M = 24 10,007 3.1 / 4.5, 8.8 M 7.1 / 7.5, 17.6 M 12.0 / 11.7.
+inline bool word_lanes(int M, size_t d) { return d < ((size_t)1 << (M >= 9 ? 24 : 22)); }
 constexpr int kVoteHoldKB = 64;   // ss_quorum_vote: two four-wave blocks per unit
 
 template <int M>
@@ -400,6 +405,7 @@ int launch_vote_any(const uint32_t *const *packed, int M, uint32_t *voted, size_
     a.M = M;
     a.d = d;
     a.n_vec = ss_packed_bytes(d) / 16;
+    if (word_lanes(M, d)) return launch(ss::vote_word_kernel, (4 * a.n_vec + 63) / 64, 0, stream, a, 64);
     const size_t grid = (a.n_vec + kVoteWave - 1) / kVoteWave;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     // 25.6 M: 14.5 us against 15.3 for four-wave blocks, 1.1 M 5.2 / 5.5
@@ -697,6 +703,13 @@ int ss_vote_sum(const uint32_t *const *packed, int M, int8_t *sums, size_t d, vo
     const size_t grid = (a.n_vec + ss::kBlock - 1) / ss::kBlock;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    if (word_lanes(M, d)) {
+        const size_t blocks = (4 * a.n_vec + 63) / 64;
+        const int planes = count_planes(M);
+        if (planes <= 3) return launch(ss::vote_sum_word_kernel<3>, blocks, 0, stream, a, 64);
+        if (planes <= 5) return launch(ss::vote_sum_word_kernel<5>, blocks, 0, stream, a, 64);
+        return launch(ss::vote_sum_word_kernel<7>, blocks, 0, stream, a, 64);
+    }
     // beyond cache-resident sizes two blocks per unit instead of four (the tile in LDS already
     // limits them to four): +3 % at d = 138 M, +9 % at 1.5 G
     constexpr int kVoteSumHoldKB = 24;
@@ -909,6 +922,13 @@ int ss_quorum_vote(const uint32_t *const *neg, const uint32_t *const *zero, int 
     const size_t grid = (a.n_vec + ss::kBlock - 1) / ss::kBlock;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    if (word_lanes(M, d)) {
+        const size_t blocks = (4 * a.n_vec + 63) / 64;
+        const int planes = count_planes(M);
+        if (planes <= 3) return launch(ss::quorum_word_kernel<3>, blocks, 0, stream, a, 64);
+        if (planes <= 5) return launch(ss::quorum_word_kernel<5>, blocks, 0, stream, a, 64);
+        return launch(ss::quorum_word_kernel<7>, blocks, 0, stream, a, 64);
+    }
     // beyond cache-resident sizes two blocks per unit instead of eight: +2-4 % at d = 138 M, +9 % at 1.5 G
     const bool capped = d >= ((size_t)1 << 27) && caps_apply();
     switch (count_planes(M)) {

@@ -309,6 +309,63 @@ __global__ __launch_bounds__(kBlock) void quorum_vote_kernel(const QuorumVoteArg
     st_stream(reinterpret_cast<u32x4 *>(a.voted_zero) + u, not_plus & ~is_neg & live);
 }
 
+// The decision for one word of coordinates: neg_at(w) and zero_at(w) are where worker w's words lie, NB
+// workers' two words are out together.  As quorum_vote_kernel: counts n and z in P planes, t = 2 n + z
+// against M + Q and M - Q + 1 from the lowest plane up.
+template <int P, int NB, typename At1, typename At2>
+__device__ __forceinline__ void quorum_word(At1 neg_at, At2 zero_at, int M, int Q, uint32_t &is_neg, uint32_t &not_plus) {
+    uint32_t n[P], z[P];
+#pragma unroll
+    for (int k = 0; k < P; ++k) n[k] = z[k] = 0;
+    for (int w0 = 0; w0 < M; w0 += NB) {
+        uint32_t nw[NB], zw[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const int w = w0 + j < M ? w0 + j : w0;
+            nw[j] = *neg_at(w);
+            zw[j] = *zero_at(w);
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            uint32_t cz = w0 + j < M ? zw[j] : 0u;
+            uint32_t cn = w0 + j < M ? nw[j] & ~zw[j] : 0u;   // an abstention is not a vote
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                const uint32_t tn = n[k] & cn, tz = z[k] & cz;
+                n[k] ^= cn;
+                z[k] ^= cz;
+                cn = tn;
+                cz = tz;
+            }
+        }
+    }
+    is_neg = not_plus = 0xFFFFFFFFu;
+    uint32_t carry = 0;
+    const int hi = M + Q, lo = M - Q + 1;
+#pragma unroll
+    for (int k = 0; k <= P; ++k) {
+        const uint32_t u = k > 0 ? n[k > 0 ? k - 1 : 0] : 0u, v = k < P ? z[k < P ? k : 0] : 0u;
+        const uint32_t uv = u ^ v, t = uv ^ carry;
+        carry = (u & v) | (uv & carry);
+        is_neg = ge_step(is_neg, t, hi, k);
+        not_plus = ge_step(not_plus, t, lo, k);
+    }
+    if (hi >= (2 << P)) is_neg = 0u;           // t < 2^(P + 1)
+    if (lo <= 0) not_plus = 0xFFFFFFFFu;
+}
+
+// The server's answer for a vector of a few million coordinates: one word a lane (see vote_word_kernel)
+template <int P>
+__global__ __launch_bounds__(64) void quorum_word_kernel(const QuorumVoteArgs a) {
+    const size_t wi = (size_t)blockIdx.x * 64 + threadIdx.x;
+    if (wi >= 4 * a.n_vec) return;
+    uint32_t is_neg, not_plus;
+    quorum_word<P, 8>([&](int w) { return a.neg[w] + wi; }, [&](int w) { return a.zero[w] + wi; }, a.M, a.quorum, is_neg, not_plus);
+    const uint32_t live = live_mask(wi, a.d);
+    a.voted_neg[wi] = is_neg & live;
+    a.voted_zero[wi] = not_plus & ~is_neg & live;
+}
+
 // ----------------------------------------------------- server + apply ----
 // The answer and the update in one launch, from planes that one pack launch over all workers left in
 // memory (vote_apply_kernel's counterpart): a lane decides a word's 32 coordinates, LDS hands the
@@ -345,43 +402,9 @@ __global__ __launch_bounds__(kBlock) void quorum_apply_kernel(const QuorumApplyA
         for (int r = 0; r < R; ++r) xv[r] = ld_stream(xq + r * kBlock);
     }
     if (tid < kWords && wi < a.words_total) {
-        uint32_t n[P], z[P];
-#pragma unroll
-        for (int k = 0; k < P; ++k) n[k] = z[k] = 0;
-        for (int w0 = 0; w0 < a.M; w0 += kQuorumBatch) {
-            uint32_t nw[kQuorumBatch], zw[kQuorumBatch];
-#pragma unroll
-            for (int j = 0; j < kQuorumBatch; ++j) {
-                const size_t at = (size_t)(w0 + j < a.M ? w0 + j : w0) * a.plane_stride + wi;
-                nw[j] = a.neg[at];
-                zw[j] = a.zero[at];
-            }
-#pragma unroll
-            for (int j = 0; j < kQuorumBatch; ++j) {
-                uint32_t cn = w0 + j < a.M ? nw[j] : 0u, cz = w0 + j < a.M ? zw[j] : 0u;   // never both: pack wrote them
-#pragma unroll
-                for (int k = 0; k < P; ++k) {
-                    const uint32_t tn = n[k] & cn, tz = z[k] & cz;
-                    n[k] ^= cn;
-                    z[k] ^= cz;
-                    cn = tn;
-                    cz = tz;
-                }
-            }
-        }
-        // t = 2 n + z against M + Q and M - Q + 1, from the lowest plane up
-        uint32_t is_neg = 0xFFFFFFFFu, not_plus = 0xFFFFFFFFu, carry = 0;
-        const int hi = a.M + a.quorum, lo = a.M - a.quorum + 1;
-#pragma unroll
-        for (int k = 0; k <= P; ++k) {
-            const uint32_t u = k > 0 ? n[k > 0 ? k - 1 : 0] : 0u, v = k < P ? z[k < P ? k : 0] : 0u;
-            const uint32_t uv = u ^ v, t = uv ^ carry;
-            carry = (u & v) | (uv & carry);
-            is_neg = ge_step(is_neg, t, hi, k);
-            not_plus = ge_step(not_plus, t, lo, k);
-        }
-        if (hi >= (2 << P)) is_neg = 0u;           // t < 2^(P + 1)
-        if (lo <= 0) not_plus = 0xFFFFFFFFu;
+        uint32_t is_neg, not_plus;
+        quorum_word<P, kQuorumBatch>([&](int w) { return a.neg + w * a.plane_stride + wi; },
+                                     [&](int w) { return a.zero + w * a.plane_stride + wi; }, a.M, a.quorum, is_neg, not_plus);
         const uint32_t live = live_mask(wi, a.d);
         const uint32_t neg = is_neg & live, zero = not_plus & ~is_neg & live;
         a.voted_neg[wi] = neg;

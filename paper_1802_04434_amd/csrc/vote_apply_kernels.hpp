@@ -165,6 +165,43 @@ __global__ __launch_bounds__(BLOCK) void vote_kernel_any(const VoteArgs<64> a) {
     st_stream(reinterpret_cast<u32x4 *>(a.voted) + u, ge);
 }
 
+// One word of every worker, added into P binary planes of the count of "-" votes; NB workers' words are
+// out together.
+template <int P, int NB>
+__device__ __forceinline__ void count_words(const uint32_t *const *packed, int M, size_t wi, uint32_t (&plane)[P]) {
+#pragma unroll
+    for (int k = 0; k < P; ++k) plane[k] = 0;
+    for (int w0 = 0; w0 < M; w0 += NB) {
+        uint32_t word[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) word[j] = packed[w0 + j < M ? w0 + j : w0][wi];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            uint32_t carry = w0 + j < M ? word[j] : 0u;
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                const uint32_t t = plane[k] & carry;
+                plane[k] ^= carry;
+                carry = t;
+            }
+        }
+    }
+}
+
+// The vote for a vector of a few million coordinates: one word a lane, so that there are four times the
+// waves and sixteen workers' words are out at once.
+__global__ __launch_bounds__(64) void vote_word_kernel(const VoteArgs<64> a) {
+    const size_t wi = (size_t)blockIdx.x * 64 + threadIdx.x;
+    if (wi >= 4 * a.n_vec) return;
+    uint32_t plane[kPlanes];
+    count_words<kPlanes, 16>(a.packed, a.M, wi, plane);
+    const int T = a.M / 2 + 1;
+    uint32_t ge = 0xFFFFFFFFu;
+#pragma unroll
+    for (int k = 0; k < kPlanes; ++k) ge = ge_step(ge, plane[k], T, k);
+    a.voted[wi] = ge & live_mask(wi, a.d);
+}
+
 // --------------------------------------------------------------- apply ----
 
 struct ApplyArgs {
@@ -231,27 +268,6 @@ struct VoteApplyArgs {
     size_t words_total;   // words of a packed buffer including zero padding
 };
 
-// one word of every worker, added into the binary planes of the count of "-" votes
-__device__ __forceinline__ void count_words(const uint32_t *const *packed, int M, size_t wi, uint32_t (&plane)[kPlanes]) {
-#pragma unroll
-    for (int k = 0; k < kPlanes; ++k) plane[k] = 0;
-    for (int w0 = 0; w0 < M; w0 += 8) {
-        uint32_t word[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) word[j] = packed[w0 + j < M ? w0 + j : w0][wi];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            uint32_t carry = w0 + j < M ? word[j] : 0u;
-#pragma unroll
-            for (int k = 0; k < kPlanes; ++k) {
-                const uint32_t t = plane[k] & carry;
-                plane[k] ^= carry;
-                carry = t;
-            }
-        }
-    }
-}
-
 // MT workers at compile time; MT == 0: a.M at run time, added into binary count planes.
 // COUNTS (with MT == 0): the planes themselves go through LDS, for the sums and the sum update.
 // A block owns R rows of 1024 coordinates: its first 32 R lanes vote on a word each.  Bound by HBM:
@@ -287,7 +303,7 @@ __global__ __launch_bounds__(kBlock) void vote_apply_kernel(const VoteApplyArgs<
         } else {
             const int T = a.M / 2 + 1;
             uint32_t plane[kPlanes];
-            count_words(a.packed, a.M, wi, plane);
+            count_words<kPlanes, 8>(a.packed, a.M, wi, plane);
             ge = 0xFFFFFFFFu;
 #pragma unroll
             for (int k = 0; k < kPlanes; ++k) ge = ge_step(ge, plane[k], T, k);
@@ -422,6 +438,34 @@ __global__ __launch_bounds__(kBlock) void vote_sum_kernel(const VoteSumArgs a) {
                 a.sums[i] = (int8_t)(words[(i - first) >> 2] >> (8 * ((i - first) & 3)));
         }
     }
+}
+
+// The sums for a vector of a few million coordinates: one word, 32 sums, a lane.  A lane of the kernel
+// above turns 128 counts into bytes, some 800 instructions one after the other, which is all the time
+// a small launch takes.
+template <int P>
+__global__ __launch_bounds__(64) void vote_sum_word_kernel(const VoteSumArgs a) {
+    const size_t wi = (size_t)blockIdx.x * 64 + threadIdx.x;
+    if (wi * 32 >= a.d) return;
+    uint32_t plane[P];
+    count_words<P, 16>(a.packed, a.M, wi, plane);
+    uint32_t out[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        uint32_t counts = 0;
+#pragma unroll
+        for (int k = 0; k < P; ++k) counts += spread_nibble((plane[k] >> (4 * q)) & 0xFu) << k;
+        out[q] = sums_word(counts, a.M);
+    }
+    if (wi * 32 + 32 <= a.d) {
+        u32x4 *const to = reinterpret_cast<u32x4 *>(a.sums + wi * 32);
+        to[0] = u32x4{out[0], out[1], out[2], out[3]};
+        to[1] = u32x4{out[4], out[5], out[6], out[7]};
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 32; ++i)
+        if (wi * 32 + i < a.d) a.sums[wi * 32 + i] = (int8_t)(out[i >> 2] >> (8 * (i & 3)));
 }
 
 // sum_apply, copy, and Welford's update and sigma (stats_kernels.hpp) run as one-wave blocks of one row on

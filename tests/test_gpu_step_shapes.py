@@ -261,3 +261,27 @@ def test_ternary_step_with_lent_scratch(ss, oracle, d, M, dtype, momentum, quoru
         assert_same_floats(m[w], m_np[w], "m[%d]" % w)
     assert_same_floats(x, x_np, "x")
     assert bool((scratch[nbytes:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("d,M", [(d, M) for d in (1, 33, 2047, 2049, 70_001) for M in (3, 8, 9, 15, 16, 17, 33, 64)] +
+                         [((1 << 22) - 1, 8), ((1 << 22) + 31, 8), ((1 << 24) - 1, 9), ((1 << 24) + 1, 17)])
+def test_server_one_word_a_lane_and_four(ss, oracle, d, M):
+    # sums, quorum and vote on both sides of the line between the lanes of one word and of four
+    rng = np.random.default_rng(d + M)
+    n = ss.packed_bytes(d) // 4
+    neg = [rng.integers(0, 1 << 32, n, dtype=np.uint64).astype(np.uint32) for _ in range(M)]
+    zero = [rng.integers(0, 1 << 32, n, dtype=np.uint64).astype(np.uint32) for _ in range(M)]   # both may be set
+    neg_dev = [torch.from_numpy(a.view(np.int32)).to(DEV) for a in neg]
+    zero_dev = [torch.from_numpy(a.view(np.int32)).to(DEV) for a in zero]
+    sums = torch.full((d + 16,), 99, dtype=torch.int8, device=DEV)
+    ss.vote_sum(neg_dev, sums, d)
+    assert np.array_equal(sums[:d].cpu().numpy().astype(np.int32), oracle.vote_sum(neg, d))
+    assert bool((sums[d:] == 99).all())
+    for Q in (1, M, M + 5):
+        vn, vz = dirty_bits(ss, d), dirty_bits(ss, d)
+        ss.quorum_vote(neg_dev, zero_dev, Q, vn, vz, d)
+        want_n, want_z = oracle.quorum_vote(neg, zero, Q, d)
+        assert np.array_equal(bits_np(vn), want_n) and np.array_equal(bits_np(vz), want_z)
+    voted = dirty_bits(ss, d)
+    ss.majority_vote(neg_dev, voted, d)
+    assert np.array_equal(bits_np(voted), oracle.majority_vote(neg, d))
