@@ -5,7 +5,7 @@
 
 A step is one pass of the whole hot path over one batch of synthetic
 gradients that already sit in HBM: by default one ss_signum_vote_step call over
-all M workers (momentum, sign, vote, parameter update in one kernel).  The
+all M workers (momentum, sign, vote, parameter update).  The
 headline workload is C3: d = 25,557,032 fp32 parameters, M = 7, beta = 0.9.
 
 Prints ONE JSON line: params/s, the HBM roofline of the kernel (algorithmic
