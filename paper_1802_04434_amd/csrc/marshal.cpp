@@ -165,15 +165,24 @@ struct Lent {
             return;
         }
         if (status != hipStreamCaptureStatusNone) return;
+        // nothing here is captured, so a capture that another thread has open must not forbid (nor be
+        // broken by) the allocation
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
         try {
             p = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(wanted, stream);
             bytes = p ? wanted : 0;
         } catch (const std::exception &) {
-            p = nullptr;                // out of memory, or no allocation allowed now: one pass needs none
+            p = nullptr;                // out of memory: one pass needs none
         }
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
     ~Lent() {
-        if (p) c10::hip::HIPCachingAllocator::raw_delete(p);
+        if (!p) return;
+        try {
+            c10::hip::HIPCachingAllocator::raw_delete(p);
+        } catch (const std::exception &) {
+        }
     }
     Lent(const Lent &) = delete;
     Lent &operator=(const Lent &) = delete;

@@ -285,3 +285,42 @@ def test_server_one_word_a_lane_and_four(ss, oracle, d, M):
     voted = dirty_bits(ss, d)
     ss.majority_vote(neg_dev, voted, d)
     assert np.array_equal(bits_np(voted), oracle.majority_vote(neg, d))
+
+
+def test_large_step_while_another_thread_captures(ss):
+    # the scratch that the binding lends is allocated beside an open capture, which goes on unharmed
+    import threading
+    d, M = (1 << 28) // 60 + 77, 5
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(3)
+    g = [torch.randn(d, device=DEV, generator=gen) for _ in range(M)]
+    m = [torch.zeros(d, device=DEV) for _ in range(M)]
+    x = torch.zeros(d, device=DEV)
+    voted = dirty_bits(ss, d)
+    small_x, small_v = torch.zeros(1000, device=DEV), ss.new_bits(1000, DEV)
+    small_g = torch.ones(1000, device=DEV)
+    own, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    failed = []
+
+    def step():
+        try:
+            ss.signum_vote_step(g, m, 0.0, 1.0, x, voted, stream=other)
+        except Exception as e:      # noqa: BLE001
+            failed.append(e)
+
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=own):
+        ss.signum_vote_step([small_g], None, 0.0, 1.0, small_x, small_v)
+        t = threading.Thread(target=step)
+        t.start()
+        t.join()
+        ss.signum_vote_step([small_g], None, 0.0, 1.0, small_x, small_v)
+    assert not failed, failed
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+    assert bool((small_x == -4).all())
+    minus = sum((t < 0).int() for t in g) >= 3
+    assert torch.equal(x, torch.where(minus, 1.0, -1.0))
