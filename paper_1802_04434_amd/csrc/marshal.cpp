@@ -138,9 +138,13 @@ struct Workers {
     T *const *as() const { return reinterpret_cast<T *const *>(p); }
 };
 
-// dtype of the first of a sequence of gradients (they all have to have it)
+// dtype of the first of a sequence of gradients (they all have to have it); the sequence has a length and
+// is indexed as Python does it, so that a stacked tensor counts as one
 at::ScalarType first_dtype(PyObject *seq) {
-    PyObject *o = PySequence_GetItem(seq, 0);
+    if (PyObject_Size(seq) < 0) throw PyRaised();
+    PyObject *zero = PyLong_FromLong(0);
+    PyObject *o = zero ? PyObject_GetItem(seq, zero) : nullptr;
+    Py_XDECREF(zero);
     if (!o) throw PyRaised();
     const bool is_tensor = THPVariable_Check(o);
     const at::ScalarType t = is_tensor ? THPVariable_Unpack(o).scalar_type() : at::kFloat;

@@ -34,6 +34,33 @@ def test_refuses_what_is_not_a_device_tensor():
         ss.density(host, host, None)
 
 
+def test_a_stacked_tensor_is_one_tensor_per_worker():
+    # whatever len(), g[0] and iteration answer for is a sequence of workers; a tensor's rows are
+    host = torch.zeros(64)
+    bits = torch.zeros(4, dtype=torch.int32)
+    for g in (torch.zeros(3, 64), torch.nn.ParameterList([host, host])):
+        with pytest.raises(TypeError, match=r"g\[0\] must live in device memory"):
+            ss.signum_vote_step(g, None, 0.9, 1e-4, host, bits)
+        with pytest.raises(TypeError, match=r"g\[0\] must live in device memory"):
+            ss.signum_vote_step_ternary(g, None, 0.9, 0.1, 1, 1e-4, host, bits, bits)
+    with pytest.raises(TypeError):
+        ss.signum_vote_step((t for t in [host]), None, 0.9, 1e-4, host, bits)    # no length
+
+
+@pytest.mark.gpu
+def test_stacked_tensors_give_what_lists_give():
+    d, M = 1024, 3
+    g, m = torch.randn(M, d, device=DEV), torch.randn(M, d, device=DEV)
+    x = torch.randn(d, device=DEV)
+    packed = torch.zeros(M, d // 32, dtype=torch.int32, device=DEV)
+    a = [t.clone() for t in (m, x)] + [ss.new_bits(d, DEV)]
+    b = [t.clone() for t in (m, x)] + [ss.new_bits(d, DEV)]
+    ss.signum_vote_step(g, a[0], 0.9, 1e-4, a[1], a[2], packed)
+    ss.signum_vote_step(list(g), list(b[0]), 0.9, 1e-4, b[1], b[2])
+    assert all(torch.equal(s, t) for s, t in zip(a, b))
+    assert torch.equal(ss.majority_vote(packed, ss.new_bits(d, DEV), d), b[2])
+
+
 @pytest.mark.gpu
 def test_refuses_dtype_layout_length_and_number():
     d = 1000
