@@ -84,7 +84,20 @@ uint64_t wrapped(PyObject *o) {
     return v;
 }
 
-size_t size_arg(PyObject *o) { return (size_t)wrapped(o); }
+// a number of coordinates does not wrap: it is compared with the tensors' lengths
+size_t size_arg(PyObject *o) {
+    PyObject *i = PyNumber_Index(o);
+    if (!i) throw PyRaised();
+    const size_t v = PyLong_AsSize_t(i);
+    Py_DECREF(i);
+    if (v == (size_t)-1 && PyErr_Occurred()) {
+        PyErr_Clear();
+        PyErr_Format(PyExc_TypeError, "%R is no number of coordinates", o);
+        throw PyRaised();
+    }
+    return v;
+}
+
 int int_arg(PyObject *o) { return (int)(uint32_t)wrapped(o); }
 
 // number of coordinates: as given, or the tensor's own
@@ -319,7 +332,7 @@ PyObject *stream_copy(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return entry<4>(n, [&] {
         void *dst = tensor(a[0], "dst").data_ptr();
         const void *src = tensor(a[1], "src").data_ptr();
-        const size_t nbytes = size_arg(a[2]);
+        const size_t nbytes = wrapped(a[2]);
         const hipStream_t s = stream_arg(a[3]);
         return unlocked([&] { return ss_stream_copy(dst, src, nbytes, s); });
     });
@@ -333,7 +346,7 @@ PyObject *welford_update(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const ss_dtype gdt = grad_dtype(tensor(a[0], "g").scalar_type());
         float *mean = (float *)dev(a[1], kF32, d, "mean");
         float *m2 = (float *)dev(a[2], kF32, d, "m2");
-        const uint64_t k = size_arg(a[3]);
+        const uint64_t k = wrapped(a[3]);
         const hipStream_t s = stream_arg(a[5]);
         return unlocked([&] { return ss_welford_update(g, gdt, mean, m2, k, d, s); });
     });
@@ -344,7 +357,7 @@ PyObject *welford_sigma(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return entry<5>(n, [&] {
         const size_t d = coords(a[3], a[0], "m2");
         float *m2 = (float *)dev(a[0], kF32, d, "m2");
-        const uint64_t k = size_arg(a[1]);
+        const uint64_t k = wrapped(a[1]);
         float *sigma = (float *)dev(a[2], kF32, d, "sigma");
         const hipStream_t s = stream_arg(a[4]);
         return unlocked([&] { return ss_welford_sigma(m2, k, sigma, d, s); });

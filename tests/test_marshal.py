@@ -47,6 +47,18 @@ def test_a_stacked_tensor_is_one_tensor_per_worker():
         ss.signum_vote_step((t for t in [host]), None, 0.9, 1e-4, host, bits)    # no length
 
 
+@pytest.mark.parametrize("d", [(1 << 64) + 8, -1, -(1 << 64) + 8])
+def test_a_number_of_coordinates_is_not_cut_to_64_bits(d):
+    host = torch.zeros(64)
+    bits = torch.zeros(4, dtype=torch.int32)
+    with pytest.raises(TypeError, match="is no number of coordinates"):
+        ss.signum_pack(host, None, 0.9, bits, d=d)
+    with pytest.raises(TypeError, match="is no number of coordinates"):
+        ss.majority_vote([bits], bits, d)
+    with pytest.raises(TypeError, match="is no number of coordinates"):
+        ss.signum_vote_step([host], None, 0.9, 1e-4, host, bits, d=d)
+
+
 @pytest.mark.gpu
 def test_stacked_tensors_give_what_lists_give():
     d, M = 1024, 3
