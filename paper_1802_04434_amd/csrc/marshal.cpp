@@ -14,6 +14,7 @@
 #include <hip/hip_runtime_api.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <cstring>
 #include <exception>
 #include <stdexcept>
 
@@ -74,9 +75,23 @@ ss_dtype grad_dtype(at::ScalarType t) {
     throw PyRaised();
 }
 
+// a number may also come as the ctypes object that a ctypes call would take: what it holds, a new
+// reference; anything else unchanged
+PyObject *plain(PyObject *o, const char *ctype) {
+    if (!strcmp(Py_TYPE(o)->tp_name, ctype)) {
+        PyObject *v = PyObject_GetAttrString(o, "value");
+        if (!v) throw PyRaised();
+        return v;
+    }
+    Py_INCREF(o);
+    return o;
+}
+
 // integers wrap to the C type's width, as a ctypes call converts them
-uint64_t wrapped(PyObject *o) {
-    PyObject *i = PyNumber_Index(o);
+uint64_t wrapped(PyObject *o, const char *ctype = "c_ulong") {
+    PyObject *number = plain(o, ctype);
+    PyObject *i = PyNumber_Index(number);
+    Py_DECREF(number);
     if (!i) throw PyRaised();
     const uint64_t v = PyLong_AsUnsignedLongLongMask(i);
     Py_DECREF(i);
@@ -98,7 +113,7 @@ size_t size_arg(PyObject *o) {
     return v;
 }
 
-int int_arg(PyObject *o) { return (int)(uint32_t)wrapped(o); }
+int int_arg(PyObject *o) { return (int)(uint32_t)wrapped(o, "c_int"); }
 
 // number of coordinates: as given, or the tensor's own
 size_t coords(PyObject *d, PyObject *t, const char *name) {
@@ -106,7 +121,9 @@ size_t coords(PyObject *d, PyObject *t, const char *name) {
 }
 
 float float_arg(PyObject *o) {
-    const double v = PyFloat_AsDouble(o);
+    PyObject *number = plain(o, "c_float");
+    const double v = PyFloat_AsDouble(number);
+    Py_DECREF(number);
     if (v == -1.0 && PyErr_Occurred()) throw PyRaised();
     return (float)v;
 }
@@ -327,11 +344,22 @@ PyObject *signum_vote_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
     });
 }
 
+// a copy asks for no more than an address: of a tensor, or of whatever answers data_ptr() (a storage)
+void *address(PyObject *o) {
+    if (THPVariable_Check(o)) return THPVariable_Unpack(o).data_ptr();
+    PyObject *h = PyObject_CallMethod(o, "data_ptr", nullptr);
+    if (!h) throw PyRaised();
+    void *p = PyLong_AsVoidPtr(h);
+    Py_DECREF(h);
+    if (!p && PyErr_Occurred()) throw PyRaised();
+    return p;
+}
+
 // (dst, src, nbytes, stream)
 PyObject *stream_copy(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return entry<4>(n, [&] {
-        void *dst = tensor(a[0], "dst").data_ptr();
-        const void *src = tensor(a[1], "src").data_ptr();
+        void *dst = address(a[0]);
+        const void *src = address(a[1]);
         const size_t nbytes = wrapped(a[2]);
         const hipStream_t s = stream_arg(a[3]);
         return unlocked([&] { return ss_stream_copy(dst, src, nbytes, s); });

@@ -1,5 +1,6 @@
 """What the native marshalling refuses, and that it hands over what it is given: wrong
 memory, dtype, layout, length or number of tensors is an error before anything is launched."""
+import ctypes
 import gc
 import sys
 
@@ -57,6 +58,45 @@ def test_a_number_of_coordinates_is_not_cut_to_64_bits(d):
         ss.majority_vote([bits], bits, d)
     with pytest.raises(TypeError, match="is no number of coordinates"):
         ss.signum_vote_step([host], None, 0.9, 1e-4, host, bits, d=d)
+
+
+class _NullStream:
+    cuda_stream = 0
+
+
+def test_a_copy_takes_anything_with_an_address_and_sizes_as_ctypes_has_them():
+    # nothing is copied: no bytes, or a number of them that the library refuses
+    a, b = torch.zeros(64), torch.zeros(64)
+    for dst, src in ((a, b), (a.untyped_storage(), b.untyped_storage())):
+        ss.stream_copy(dst, src, 0, stream=_NullStream)
+        ss.stream_copy(dst, src, ctypes.c_size_t(0), stream=_NullStream)
+        for odd in (8, ctypes.c_uint64(8), (1 << 64) + 8):
+            with pytest.raises(ss.SignSGDError) as e:
+                ss.stream_copy(dst, src, odd, stream=_NullStream)
+            assert e.value.status == -5
+    with pytest.raises(TypeError):
+        ss.stream_copy(a, b, ctypes.c_float(8), stream=_NullStream)
+    with pytest.raises(TypeError):
+        ss.stream_copy(a, b, 8.0, stream=_NullStream)
+    with pytest.raises((AttributeError, TypeError)):
+        ss.stream_copy(np.zeros(64), b, 0, stream=_NullStream)
+
+
+@pytest.mark.gpu
+def test_numbers_as_ctypes_has_them():
+    d, f = 1000, ctypes.c_float
+    g, x = torch.randn(d, device=DEV), torch.randn(d, device=DEV)
+    m = [torch.zeros(d, device=DEV) for _ in range(2)]
+    x2, neg, zero, v = x.clone(), *(ss.new_bits(d, DEV) for _ in range(3))
+    ss.signum_vote_step([g], [m[0]], f(0.9), f(1e-4), x, v)
+    ss.signum_vote_step([g], [m[1]], 0.9, 1e-4, x2, v)
+    assert torch.equal(m[0], m[1]) and torch.equal(x, x2)
+    ss.signum_pack_ternary(g, None, f(0), f(0.1), neg, zero)
+    ss.quorum_vote([neg], [zero], ctypes.c_int(1), *(w := [ss.new_bits(d, DEV) for _ in range(2)]), d)
+    assert torch.equal(w[0], neg) and torch.equal(w[1], zero)
+    mean, m2 = torch.zeros(d, device=DEV), torch.zeros(d, device=DEV)
+    ss.welford_update(g, mean, m2, ctypes.c_uint64(1))
+    assert torch.equal(mean, g)
 
 
 @pytest.mark.gpu
