@@ -128,14 +128,27 @@ float float_arg(PyObject *o) {
     return (float)v;
 }
 
-hipStream_t stream_arg(PyObject *o) {
-    if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
-    PyObject *h = PyObject_GetAttrString(o, "cuda_stream");
+void *handle_arg(PyObject *o, const char *attribute) {
+    PyObject *h = PyObject_GetAttrString(o, attribute);
     if (!h) throw PyRaised();
     void *p = PyLong_AsVoidPtr(h);
     Py_DECREF(h);
     if (!p && PyErr_Occurred()) throw PyRaised();
-    return static_cast<hipStream_t>(p);
+    return p;
+}
+
+hipStream_t stream_arg(PyObject *o) {
+    if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
+    return static_cast<hipStream_t>(handle_arg(o, "cuda_stream"));
+}
+
+// whether the stream of a call is one of torch's own: the default stream or one of its pools.  A stream that
+// torch was handed (ExternalStream) has its handle for an id.
+bool own_stream(PyObject *o, hipStream_t handle) {
+    if (!handle) return true;
+    if (o == Py_None) return reinterpret_cast<void *>(c10::hip::getCurrentHIPStream().id()) != handle;
+    if (!PyObject_HasAttrString(o, "stream_id")) return false;
+    return handle_arg(o, "stream_id") != handle;
 }
 
 // the device addresses of a sequence of tensors, one per worker; of more than SS_MAX_WORKERS all are
@@ -184,15 +197,19 @@ at::ScalarType first_dtype(PyObject *seq) {
 
 // Temporary device memory for one step, from torch's caching allocator and tied to the step's own
 // stream (so that its reuse is ordered behind the step); given back when the step is enqueued.
-// None where nothing is wanted, there is no room, the tensors are not on the current device, or
-// the stream is under capture (a replay may not touch memory that has been given back).
+// None where nothing is wanted, there is no room, the tensors are not on the current device,
+// the stream is under capture (a replay may not touch memory that has been given back), or
+// it is not torch's own: the allocator knows a stream by its handle, and what is queued behind a handle
+// from elsewhere need not be one queue - hipStreamPerThread is another stream in every thread, and a
+// destroyed stream's handle may come back as a new one - so the next step under it could be lent
+// the block of one that still runs.
 struct Lent {
     void *p = nullptr;
     size_t bytes = 0;
 
-    Lent(size_t wanted, int device, hipStream_t stream) {
+    Lent(size_t wanted, int device, hipStream_t stream, bool own) {
         int current = -1;
-        if (wanted == 0 || hipGetDevice(&current) != hipSuccess || current != device) return;
+        if (wanted == 0 || !own || hipGetDevice(&current) != hipSuccess || current != device) return;
         hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
             (void)hipGetLastError();    // the default stream while another one captures
@@ -336,8 +353,9 @@ PyObject *signum_vote_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
                                               sums, d, flags, s);
             });
         const int device = x.device().index();
+        const bool own = own_stream(a[10], s);
         return unlocked([&] {
-            const Lent scratch(ss_step_scratch_bytes(gdt, has_m, g.n, d), device, s);
+            const Lent scratch(ss_step_scratch_bytes(gdt, has_m, g.n, d), device, s, own);
             return ss_signum_vote_step_scratch(g.as<const void>(), gdt, mp, g.n, beta, delta, xp, voted, sums, scratch.p,
                                                scratch.bytes, d, flags, s);
         });
@@ -472,8 +490,9 @@ PyObject *signum_vote_step_ternary(PyObject *, PyObject *const *a, Py_ssize_t n)
         uint32_t *vzero = (uint32_t *)dev(a[8], kBits, words, "voted_zero");
         const hipStream_t s = stream_arg(a[10]);
         const int device = tensor(a[6], "x").device().index();
+        const bool own = own_stream(a[10], s);
         return unlocked([&] {
-            const Lent scratch(ss_ternary_scratch_bytes(gdt, has_m, g.n, d), device, s);
+            const Lent scratch(ss_ternary_scratch_bytes(gdt, has_m, g.n, d), device, s, own);
             return ss_signum_vote_step_ternary_scratch(g.as<const void>(), gdt, has_m ? m.as<float>() : nullptr, g.n, beta, tau,
                                                        quorum, delta, x, vneg, vzero, scratch.p, scratch.bytes, d, s);
         });

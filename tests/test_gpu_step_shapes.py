@@ -324,3 +324,63 @@ def test_large_step_while_another_thread_captures(ss):
     assert bool((small_x == -4).all())
     minus = sum((t < 0).int() for t in g) >= 3
     assert torch.equal(x, torch.where(minus, 1.0, -1.0))
+
+
+class _Handle:
+    def __init__(self, stream):
+        self.cuda_stream = stream.cuda_stream
+
+
+def _large_step(ss, extra):
+    """a step for which scratch is lent; the call, binary or ternary, on fresh state and a stream, and its outputs"""
+    d, M = (1 << 28) // 60 + extra, 5
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(extra)
+    g = [torch.randn(d, device=DEV, generator=gen) for _ in range(M)]
+    m0 = [torch.randn(d, device=DEV, generator=gen) * 0.3 for _ in range(M)]
+    x0 = torch.randn(d, device=DEV, generator=gen) * 0.05
+    assert ss.load_library().ss_step_scratch_bytes(0, 1, M, d) > 0
+    assert ss.load_library().ss_ternary_scratch_bytes(0, 1, M, d) > 0
+
+    def state():
+        return [t.clone() for t in m0], x0.clone(), dirty_bits(ss, d), dirty_bits(ss, d)
+
+    def call(state, stream, ternary):
+        m, x, v, z = state
+        if ternary:
+            ss.signum_vote_step_ternary(g, m, 0.9, 0.1, 2, 1e-4, x, v, z, stream=stream)
+        else:
+            ss.signum_vote_step(g, m, 0.9, 1e-4, x, v, stream=stream)
+        return [t.view(torch.int32) for t in (*m, x, v, *([z] if ternary else []))]
+
+    return state, call
+
+
+def _allocator():
+    stats = torch.cuda.memory_stats()
+    return {k: stats[k] for k in ("allocation.all.allocated", "reserved_bytes.all.current", "num_alloc_retries", "num_ooms")}
+
+
+@pytest.mark.parametrize("ternary", [False, True])
+def test_scratch_is_lent_on_torch_s_own_streams_only(ss, ternary):
+    # a handle from elsewhere need not stand for one queue: there the step takes one pass and no memory
+    state, call = _large_step(ss, 1001)
+    pool = torch.cuda.Stream()
+    external = torch.cuda.ExternalStream(pool.cuda_stream)
+    states = [state() for _ in range(5)]
+    torch.cuda.synchronize()
+    before = _allocator()
+    want = call(states[0], None, ternary)
+    assert _allocator()["allocation.all.allocated"] == before["allocation.all.allocated"] + 1
+    call(states[1], pool, ternary)
+    pool.synchronize()
+    before = _allocator()
+    call(states[2], external, ternary)
+    call(states[3], _Handle(pool), ternary)
+    with torch.cuda.stream(external):
+        call(states[4], None, ternary)
+    assert _allocator() == before
+    torch.cuda.synchronize()
+    for m, x, v, z in states[1:]:
+        got = [t.view(torch.int32) for t in (*m, x, v, *([z] if ternary else []))]
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
