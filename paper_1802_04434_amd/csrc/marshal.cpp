@@ -14,6 +14,7 @@
 #include <hip/hip_runtime_api.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <algorithm>
 #include <cstring>
 #include <exception>
 #include <stdexcept>
@@ -195,8 +196,36 @@ at::ScalarType first_dtype(PyObject *seq) {
     return t;     // Workers says what is wrong with anything else
 }
 
+// What has to be free beyond the memory that a step borrows: the allocator rounds a request up (to 2 or 20 MiB
+// blocks, or as it is configured to), and what the program allocates next should not be what does not fit.
+constexpr size_t kLeaveFree = (size_t)1 << 30;
+
+// Whether torch's allocator can serve `wanted` bytes without more than a plain allocation.  One that it
+// cannot serve makes it wait for the device, give back everything it caches and try again, which a
+// step that is as well off with one pass must not cause.  Asked of the device (4-5 us) at every call: other
+// processes and other libraries take memory too.  Anything but torch's own caching allocator
+// may synchronise on each allocation.
+bool room_for(size_t wanted, int device) {
+    namespace allocator = c10::hip::HIPCachingAllocator;
+    if (allocator::name() != "native" || !allocator::isEnabled()) return false;
+    size_t free = 0, total = 0;
+    if (hipMemGetInfo(&free, &total) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const double fraction = allocator::getMemoryFraction((c10::DeviceIndex)device);
+    if (fraction < 1.0) {       // the program bounds what it takes of the device
+        const size_t bound = (size_t)(fraction * (double)total);
+        const size_t held = (size_t)allocator::getDeviceStats((c10::DeviceIndex)device).reserved_bytes[0].current;
+        free = std::min(free, bound > held ? bound - held : 0);
+    }
+    return free >= wanted + kLeaveFree;
+}
+
 // Temporary device memory for one step, from torch's caching allocator and tied to the step's own
-// stream (so that its reuse is ordered behind the step); given back when the step is enqueued.
+// stream (so that its reuse is ordered behind the step); given back when the step is enqueued.  The
+// allocator keeps a block for each stream that takes such steps, until it needs the memory or is told to
+// empty its cache.
 // None where nothing is wanted, there is no room, the tensors are not on the current device,
 // the stream is under capture (a replay may not touch memory that has been given back), or
 // it is not torch's own: the allocator knows a stream by its handle, and what is queued behind a handle
@@ -221,10 +250,10 @@ struct Lent {
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
         try {
-            p = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(wanted, stream);
+            if (room_for(wanted, device)) p = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(wanted, stream);
             bytes = p ? wanted : 0;
         } catch (const std::exception &) {
-            p = nullptr;                // out of memory: one pass needs none
+            p = nullptr;                // out of memory after all: one pass needs none
         }
         if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     }

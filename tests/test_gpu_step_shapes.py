@@ -384,3 +384,34 @@ def test_scratch_is_lent_on_torch_s_own_streams_only(ss, ternary):
     for m, x, v, z in states[1:]:
         got = [t.view(torch.int32) for t in (*m, x, v, *([z] if ternary else []))]
         assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("ternary", [False, True])
+def test_a_step_without_room_for_scratch_leaves_the_allocator_alone(ss, ternary):
+    # the program's memory is bounded to what it holds: nothing is asked for, so nothing that is cached is
+    # given back, no allocation is retried and none fails
+    state, call = _large_step(ss, 2002)
+    states = [state() for _ in range(4)]
+    torch.cuda.empty_cache()
+    want = call(states[0], None, ternary)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    cached = torch.empty(300 << 20, dtype=torch.uint8, device=DEV)
+    del cached
+    torch.cuda.synchronize()
+    total = torch.cuda.mem_get_info()[1]
+    for room in (1 << 20, 1 << 29):       # less than the scratch, and more than it but little
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + room) / total)
+        try:
+            before = _allocator()
+            got = call(states[1 if room == 1 << 20 else 2], side, ternary)
+            assert _allocator() == before
+        finally:
+            torch.cuda.set_per_process_memory_fraction(1.0)
+        side.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+    before = _allocator()
+    got = call(states[3], side, ternary)                # with room it is lent again
+    assert _allocator()["allocation.all.allocated"] == before["allocation.all.allocated"] + 1
+    side.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
