@@ -127,7 +127,8 @@ int ss_sign_apply(float *x, const uint32_t *bits, float delta, size_t d,
  * launches that hand the signs over through packed_out, which is faster there; the
  * results are the same.  Should the runtime refuse the second launch (SS_ERR_HIP),
  * the first stays enqueued: the momentum buffers have then been advanced by this
- * step and x has not.
+ * step and x has not.  A vector of more than 2^33 coordinates is stepped part by
+ * part, each as above; the parts before a refused launch stay enqueued.
  */
 int ss_signum_vote_step(const void *const *g, ss_dtype gdt, float *const *m,
                         int M, float beta, float delta, float *x,

@@ -126,17 +126,24 @@ inline bool split_pays(int M, size_t d) {
     return M >= 2 && d >= ((size_t)1 << 20) && d * (size_t)M >= ((size_t)1 << (M >= 4 ? 23 : 24));
 }
 
+// A launch may have at most 2^32 - 1 threads, which a shape with one row of quads a lane reaches at 2^34
+// coordinates.  Up to half of that every shape is safe, the blocks of a tail included; a step over a longer vector
+// runs over parts of this many coordinates, and kernels that are not cut take a shape of two rows.
+constexpr size_t kOneRowMaxD = (size_t)1 << 33;
+// no step is longer (nor fits: 4 bytes of x alone are 275 GB)
+constexpr size_t kStepMaxD = (size_t)1 << 36;
+
 // With lent scratch memory the step takes the same two launches without packed_out, over slabs of the
 // vector whose bits fit into it.  kScratchBytes bounds what is asked for: at M = 16 a slab of 67 M
 // coordinates, 2 ms of work for each further pair of launches (~5 us).
 constexpr size_t kScratchBytes = (size_t)128 << 20;
 constexpr size_t kScratchMinSlab = (size_t)1 << 20;
 
-// coordinates of a slab: all d if the bits of M workers fit into `bytes`, otherwise equal parts of a
+// coordinates of a slab: all d if the bits of M workers fit into `bytes` (and one launch), otherwise equal parts of a
 // multiple of 8192 (every buffer's part stays 16-byte aligned); 0 if there is no room for 8192
 inline size_t scratch_slab(int M, size_t d, size_t bytes) {
-    if ((size_t)M * ss_packed_bytes(d) <= bytes) return d;
-    const size_t room = bytes / (size_t)M * 8 / 8192 * 8192;
+    if (d <= kOneRowMaxD && (size_t)M * ss_packed_bytes(d) <= bytes) return d;
+    const size_t room = std::min(bytes / (size_t)M * 8 / 8192 * 8192, kOneRowMaxD);
     if (room == 0) return 0;
     const size_t parts = (d + room - 1) / room;
     return std::min(room, ((d + parts - 1) / parts + 8191) / 8192 * 8192);
@@ -159,9 +166,6 @@ inline int lds_per_unit_kb() {
     if (hipDeviceGetAttribute(&bytes, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess) return 0;
     return bytes / 1024;
 }
-
-// a launch may have at most 2^32 - 1 threads: with one row of quads a lane that is 2^34 coordinates
-constexpr size_t kOneRowMaxD = (size_t)1 << 33;
 
 // up to here sum_apply and copy keep four-wave blocks (see vote_apply_kernels.hpp)
 constexpr size_t kCachedD = (size_t)1 << 21;
@@ -585,6 +589,18 @@ int ss_sign_apply(float *x, const uint32_t *bits, float delta, size_t d, void *h
     return launch(ss::apply_kernel<4, 0, false>, grid, 0, stream, a);
 }
 
+// the step over a vector, or a part of one, that every launch shape covers
+static int step_part(bool two, const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float delta, float *x,
+                     uint32_t *voted, uint32_t *const *packed, StepVariant var, size_t d, hipStream_t stream) {
+    if (two) return launch_two(g, gdt, m, M, beta, delta, x, voted, packed, var, d, stream);
+    if (m) {
+        if (gdt == SS_F32) return launch_step<true, ss::F32Grad>(M, g, m, packed, beta, delta, x, voted, var, d, stream);
+        return launch_step<true, ss::Bf16Grad>(M, g, m, packed, beta, delta, x, voted, var, d, stream);
+    }
+    if (gdt == SS_F32) return launch_step<false, ss::F32Grad>(M, g, m, packed, beta, delta, x, voted, var, d, stream);
+    return launch_step<false, ss::Bf16Grad>(M, g, m, packed, beta, delta, x, voted, var, d, stream);
+}
+
 static int vote_step_impl(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float delta, float *x,
                           uint32_t *voted, uint32_t *const *packed_out, int8_t *sums_out, size_t d, unsigned flags,
                           void *scratch, size_t scratch_bytes, void *hip_stream) {
@@ -604,6 +620,7 @@ static int vote_step_impl(const void *const *g, ss_dtype gdt, float *const *m, i
         if (m && !aligned16(m[w])) return SS_ERR_ALIGN;
         if (packed_out && !aligned16(packed_out[w])) return SS_ERR_ALIGN;
     }
+    if (d > kStepMaxD) return SS_ERR_ARG;
     {
         Span spans[3 * SS_MAX_WORKERS + 4];
         int n = 0;
@@ -619,39 +636,31 @@ static int vote_step_impl(const void *const *g, ss_dtype gdt, float *const *m, i
         if (written_spans_overlap(spans, n)) return SS_ERR_ARG;
     }
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const StepVariant var{flags, sums_out};
-    // the caller's bit buffers carry the signs from one launch to the next; same results, bit for bit
-    if (packed_out && split_pays(M, d)) return launch_two(g, gdt, m, M, beta, delta, x, voted, packed_out, var, d, stream);
-    if (scratch && !packed_out) {
-        // ... or the lent memory does, over as much of the vector at a time as it has room for
-        const size_t slab = scratch_slab(M, d, scratch_bytes);
-        if (slab >= kScratchMinSlab) {
-            const size_t stride = ss_packed_bytes(slab);
-            for (size_t lo = 0; lo < d; lo += slab) {
-                const size_t n = std::min(slab, d - lo);
-                const void *gs[SS_MAX_WORKERS];
-                float *ms[SS_MAX_WORKERS];
-                uint32_t *ps[SS_MAX_WORKERS];
-                for (int w = 0; w < M; ++w) {
-                    gs[w] = static_cast<const char *>(g[w]) + lo * grad_bytes(gdt);
-                    ms[w] = m ? m[w] + lo : nullptr;
-                    ps[w] = reinterpret_cast<uint32_t *>(static_cast<char *>(scratch) + w * stride);
-                }
-                const StepVariant part{flags, sums_out ? sums_out + lo : nullptr};
-                const int rc = launch_two(gs, gdt, m ? ms : nullptr, M, beta, delta, x + lo, voted + lo / 32, ps, part, n, stream);
-                if (rc != SS_OK) return rc;
-            }
-            return SS_OK;
+    // Two launches that hand the signs over through the caller's bit buffers, or through the lent memory over as much
+    // of the vector at a time as it has room for; otherwise one pass.  Same results, bit for bit.
+    const size_t slab = scratch && !packed_out ? scratch_slab(M, d, scratch_bytes) : 0;
+    const bool lent = slab >= kScratchMinSlab;
+    const bool two = lent || (packed_out && split_pays(M, d));
+    const size_t part = lent ? slab : std::min(d, kOneRowMaxD);
+    if (!lent && part == d)
+        return step_part(two, g, gdt, m, M, beta, delta, x, voted, packed_out, StepVariant{flags, sums_out}, d, stream);
+    const size_t stride = ss_packed_bytes(part);
+    for (size_t lo = 0; lo < d; lo += part) {
+        const void *gs[SS_MAX_WORKERS];
+        float *ms[SS_MAX_WORKERS];
+        uint32_t *ps[SS_MAX_WORKERS];
+        for (int w = 0; w < M; ++w) {
+            gs[w] = static_cast<const char *>(g[w]) + lo * grad_bytes(gdt);
+            ms[w] = m ? m[w] + lo : nullptr;
+            if (lent) ps[w] = reinterpret_cast<uint32_t *>(static_cast<char *>(scratch) + w * stride);
+            else ps[w] = packed_out ? packed_out[w] + lo / 32 : nullptr;
         }
+        const int rc = step_part(two, gs, gdt, m ? ms : nullptr, M, beta, delta, x + lo, voted + lo / 32,
+                                 lent || packed_out ? ps : nullptr, StepVariant{flags, sums_out ? sums_out + lo : nullptr},
+                                 std::min(part, d - lo), stream);
+        if (rc != SS_OK) return rc;
     }
-    if (m) {
-        if (gdt == SS_F32)
-            return launch_step<true, ss::F32Grad>(M, g, m, packed_out, beta, delta, x, voted, var, d, stream);
-        return launch_step<true, ss::Bf16Grad>(M, g, m, packed_out, beta, delta, x, voted, var, d, stream);
-    }
-    if (gdt == SS_F32)
-        return launch_step<false, ss::F32Grad>(M, g, m, packed_out, beta, delta, x, voted, var, d, stream);
-    return launch_step<false, ss::Bf16Grad>(M, g, m, packed_out, beta, delta, x, voted, var, d, stream);
+    return SS_OK;
 }
 
 int ss_signum_vote_step_ex(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float delta,
