@@ -157,9 +157,11 @@ def test_vote_sum_and_quorum_vote_large(ss, oracle, M):
     assert np.array_equal(bits_np(vz), want_z)
 
 
-@pytest.mark.parametrize("M", [3, 17])
-def test_majority_vote_large(ss, oracle, M):
-    d = D30
+# one-wave blocks with a cap from 2^28 coordinates on, from twelve workers on from 2^27; never for three
+@pytest.mark.parametrize("M,d", [(3, D30), (17, D30), (4, (1 << 28) + 1), (8, (1 << 28) + 8191), (11, (1 << 28) + 127),
+                                 (8, (1 << 28) - 1), (12, (1 << 27) + 33), (16, (1 << 27) + 8193), (16, (1 << 27) - 129),
+                                 (24, (1 << 26) + 65)])
+def test_majority_vote_large(ss, oracle, M, d):
     n = ss.packed_bytes(d) // 4
     packed = [device_words(n, 90 + w) for w in range(M)]
     voted = dirty_bits(ss, d)

@@ -6,6 +6,8 @@ Sizes here are the ones the oracle finishes in seconds; they span several
 1024-coordinate tiles plus a ragged tail.  Full-size configurations are in
 test_gpu_configs.py.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -249,9 +251,9 @@ def test_fused_equals_three_call_path(ss):
 
 @pytest.mark.parametrize("M,dtype", [(7, "f32"), (16, "f32"), (8, "bf16")])
 def test_fused_equals_three_call_path_streaming_shape(ss, M, dtype):
-    # d >= 2^20, M >= 2: the fused call takes the streaming launch shape that the
-    # benchmark times; its outputs must be those of M packs + vote + apply, both with
-    # and without per-worker bits (ragged d, so the scalar tail takes part)
+    # with per-worker bits the call hands the signs over through packed_out, without them it takes one
+    # pass (M = 7 and 8: the latency shape) or, for M = 16, borrows scratch memory; the outputs must be
+    # those of M packs + vote + apply every time (ragged d, so the scalar tail takes part)
     d = 3 * (1 << 20) + 2048 + 77
     gen = torch.Generator(device=DEV)
     gen.manual_seed(100 + M)
@@ -438,8 +440,8 @@ def test_checkpoint_resume_is_bit_identical(ss):
 @pytest.mark.parametrize("M,dtype,momentum", [(2, "f32", True), (3, "bf16", True), (4, "f32", False),
                                               (9, "f32", True), (11, "bf16", False)])
 def test_fused_step_large_d_streaming_shape(ss, oracle, M, dtype, momentum):
-    # large enough for the one-worker-at-a-time launch shape with capped
-    # occupancy; ragged so that the scalar tail runs as well
+    # the first step in one pass (M = 3: the streaming shape, M = 2, 4, 11: the latency shape) or, M = 9, as two
+    # launches over borrowed scratch, the second through packed_out; ragged so that the scalar tail runs as well
     d = 9_000_000 + 1234 + 19
     cfg = synth.Config("large", 40 + M, d, M, dtype, 0.9 if momentum else None, 1e-4, 2, "normal", 0.1, 0.5)
     m = [np.zeros(d, np.float32) for _ in range(M)] if momentum else None
@@ -466,10 +468,9 @@ def test_fused_step_large_d_streaming_shape(ss, oracle, M, dtype, momentum):
 @pytest.mark.parametrize("M,dtype,momentum", [(13, "bf16", True), (6, "bf16", True), (33, "f32", True),
                                               (64, "f32", False), (17, "bf16", False)])
 def test_fused_step_streaming_shape_any_worker_count(ss, oracle, M, dtype, momentum):
-    # worker counts without a kernel of their own (the run-time-M kernel), in every streaming
-    # shape: stages of two workers plus a remainder (bf16 + momentum, odd M), one worker per stage
-    # (fp32 + momentum), several gradient loads per lane (no momentum); ragged d, two steps,
-    # per-worker bits on the second
+    # worker counts without a kernel of their own (the run-time-M kernel) and M = 6, with every kind of
+    # gradient: the first step in one pass (M = 64: the streaming shape, beyond 2^28 bytes of gradients) or, M = 33,
+    # over borrowed scratch, the second through packed_out where d M is 2^23 or more; ragged d
     d = (1 << 20) + 4096 + 333
     rng = np.random.default_rng(1000 + M)
     m = [make_momentum(rng, d) for _ in range(M)] if momentum else None
@@ -509,11 +510,14 @@ def test_fused_step_with_packed_out_at_many_workers(ss, oracle, M, dtype, flags)
     voted = dirty_bits(ss, d)
     packed = [dirty_bits(ss, d) for _ in range(M)]
     ss.signum_vote_step_ex(g_dev, m_dev, 0.9, 1e-4, x_dev, voted, packed, None, flags)
-    # the same call without packed_out (always the one-pass kernel)
+    # the same step without packed_out, and through the C ABI without scratch memory: the one-pass kernel
     m2 = [torch.from_numpy(a).to(DEV) for a in m]
     x2 = torch.from_numpy(x).to(DEV)
     voted2 = dirty_bits(ss, d)
-    ss.signum_vote_step_ex(g_dev, m2, 0.9, 1e-4, x2, voted2, None, None, flags)
+    table = lambda ts: (ctypes.c_void_p * M)(*[t.data_ptr() for t in ts])       # noqa: E731
+    assert ss.load_library().ss_signum_vote_step_ex(
+        table(g_dev), int(dtype == "bf16"), table(m2), M, 0.9, 1e-4, x2.data_ptr(), voted2.data_ptr(), None, None, d, flags,
+        ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
     assert torch.equal(voted, voted2) and torch.equal(x_dev.view(torch.int32), x2.view(torch.int32))
     assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(m_dev, m2))
     gh = [synth.as_numpy(t) for t in g]

@@ -1,4 +1,6 @@
 """The launch shapes of the step around the edges of their tiles, bit-exact against the oracle.
+The Python calls lend scratch memory to large steps with momentum, which then run as two launches; the
+one-pass kernels of that size are run through the C ABI, as a captured step runs them.
 With packed_out from about 2^20 coordinates on: a pack launch over all workers, then vote and
 update (256 coordinates a pack block with momentum, 1,024 without, 1,024 to 4,096 a vote block,
 padding to 128; fixed adders up to 16 workers, pointer tables of 16 and 64).  In one pass: the
@@ -329,6 +331,73 @@ def test_large_step_while_another_thread_captures(ss):
 class _Handle:
     def __init__(self, stream):
         self.cuda_stream = stream.cuda_stream
+
+
+def _pointers(ts):
+    import ctypes
+    return (ctypes.c_void_p * len(ts))(*[t.data_ptr() for t in ts]) if ts is not None else None
+
+
+def _drawn_step(d, M, dtype, momentum, scale):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d + M)
+    g = [(torch.randn(d, device=DEV, generator=gen) * scale).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+         for _ in range(M)]
+    m = [torch.randn(d, device=DEV, generator=gen) * 0.3 for _ in range(M)] if momentum else None
+    x = torch.randn(d, device=DEV, generator=gen) * 0.05
+    return g, m, x, [synth.as_numpy(t).copy() for t in m] if momentum else None, synth.as_numpy(x).copy()
+
+
+def _beyond_cache(M, dtype, momentum, extra):
+    """coordinates whose gradients and momentum are 2^28 bytes and a little: the smallest step of a streaming shape"""
+    size = (2 if dtype == "bf16" else 4) + (8 if momentum else 0)
+    return -(-(1 << 28) // (M * size)) + extra
+
+
+@pytest.mark.parametrize("M,dtype,momentum,extra,flags", [
+    (2, "f32", True, 1, 3), (7, "f32", True, 2047, 0), (7, "f32", True, 0, 2), (9, "f32", True, 511, 1), (16, "f32", True, 77, 0),
+    (2, "bf16", True, 2049, 0), (3, "bf16", True, 31, 2), (4, "bf16", True, 513, 1), (5, "bf16", True, 0, 0),
+    (8, "bf16", True, 127, 3), (9, "bf16", True, 255, 2), (12, "bf16", True, 5, 0), (23, "bf16", True, 33, 1),
+    (2, "f32", False, 2047, 2), (4, "f32", False, 1, 0), (7, "f32", False, 65, 0), (9, "f32", False, 333, 2),
+])
+def test_one_pass_step_beyond_the_cache(ss, oracle, M, dtype, momentum, extra, flags):
+    import ctypes
+    d = _beyond_cache(M, dtype, momentum, extra)
+    g, m, x, m_np, x_np = _drawn_step(d, M, dtype, momentum, 1.0)
+    voted = dirty_bits(ss, d)
+    sums = torch.full((d,), 99, dtype=torch.int8, device=DEV)
+    rc = ss.load_library().ss_signum_vote_step_ex(
+        _pointers(g), int(dtype == "bf16"), _pointers(m), M, 0.9, 1e-4, x.data_ptr(), voted.data_ptr(), None,
+        sums.data_ptr() if flags != 1 else None, d, flags, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    want = oracle.signum_vote_step_ex([synth.as_numpy(t) for t in g], m_np, 0.9, 1e-4, x_np, flags)
+    assert np.array_equal(bits_np(voted), want[0])
+    if flags != 1:
+        assert np.array_equal(sums.cpu().numpy(), want[2])
+    for w in range(M if momentum else 0):
+        assert_same_floats(m[w], m_np[w], "m[%d]" % w)
+    assert_same_floats(x, x_np, "x")
+
+
+@pytest.mark.parametrize("M,dtype,momentum,extra,quorum", [
+    (2, "f32", True, 1, 1), (7, "f32", True, 2047, 3), (9, "f32", True, 511, 2), (3, "bf16", True, 513, 2),
+    (4, "bf16", True, 0, 1), (5, "bf16", True, 129, 2), (8, "bf16", True, 511, 9), (13, "bf16", True, 33, 2),
+    (2, "bf16", False, 1023, 1), (9, "f32", False, 7, 4),
+])
+def test_one_pass_ternary_step_beyond_the_cache(ss, oracle, M, dtype, momentum, extra, quorum):
+    import ctypes
+    d = _beyond_cache(M, dtype, momentum, extra)
+    g, m, x, m_np, x_np = _drawn_step(d, M, dtype, momentum, 0.3)
+    neg, zero = dirty_bits(ss, d), dirty_bits(ss, d)
+    rc = ss.load_library().ss_signum_vote_step_ternary(
+        _pointers(g), int(dtype == "bf16"), _pointers(m), M, 0.9, 0.1, quorum, 1e-4, x.data_ptr(), neg.data_ptr(),
+        zero.data_ptr(), d, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    want_neg, want_zero = oracle.signum_vote_step_ternary([synth.as_numpy(t) for t in g], m_np, 0.9, 0.1, quorum, 1e-4, x_np)
+    assert np.array_equal(bits_np(neg), want_neg) and np.array_equal(bits_np(zero), want_zero)
+    for w in range(M if momentum else 0):
+        assert_same_floats(m[w], m_np[w], "m[%d]" % w)
+    assert_same_floats(x, x_np, "x")
 
 
 def _large_step(ss, extra):
