@@ -122,6 +122,8 @@ constexpr int kLdsPerUnitKB = 160;   // what the reservations below assume; chec
 // One pass -> two launches, us: fp32, M = 7: 0.7 M 12.2 -> 14.4, 1.1 M 22.9 -> 19.4, 4.4 M 70 -> 66,
 // 25.6 M 386 -> 358; M = 16: 1.1 M 48 -> 40, 25.6 M 871 -> 780; M = 2: 1.1 M 8.7 -> 8.9, 4.4 M 27.0 -> 25.8,
 // 25.6 M 138 -> 129; bf16, M = 8: 1.1 M 21.8 -> 19.8, 25.6 M 388 -> 341; M = 2: 4.4 M 22.8 -> 23.2, 25.6 M 120 -> 115.
+// Every step of a fixed number of workers that is large enough for a streaming shape is past this line, so those shapes
+// see packed_out with more than 22 workers only (d < 2^20), step_bf16_kernel never.
 inline bool split_pays(int M, size_t d) {
     return M >= 2 && d >= ((size_t)1 << 20) && d * (size_t)M >= ((size_t)1 << (M >= 4 ? 23 : 24));
 }
@@ -209,14 +211,14 @@ int launch_step_shape(ss::StepArgs<NPTR> &a, size_t d, hipStream_t stream) {
     return launch(ss::step_kernel<MT, NPTR, BLOCK, BW, R, HOLD_KB, LOADS_FIRST, HAS_M, G>, grid, 0, stream, a, BLOCK);
 }
 
-template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB>
+template <int MT, int NPTR, int BLOCK, int BW, int HOLD_KB>
 int launch_octets(ss::StepArgs<NPTR> &a, size_t d, hipStream_t stream) {
-    const Tiling t = make_tiling(d, R, true, BLOCK, 2 * ss::kQuad);
+    const Tiling t = make_tiling(d, 1, true, BLOCK, 2 * ss::kQuad);
     a.n_tiles = t.n_tiles;
     a.words_total = t.words_total;
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    return launch(ss::step_bf16_kernel<MT, NPTR, BLOCK, BW, R, HOLD_KB>, grid, 0, stream, a, BLOCK);
+    return launch(ss::step_bf16_kernel<MT, NPTR, BLOCK, BW, HOLD_KB>, grid, 0, stream, a, BLOCK);
 }
 
 // what distinguishes the variants of the step (see ss_step_flags)
@@ -253,9 +255,9 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
                 // one-wave blocks, fewer of them per unit the more loads each has out.  Against two workers a
                 // stage in quads, us: 25.6 M M = 3 57.1 / 59.2, 7 88.3 / 94.2, 8 98.1 / 102.0, 12 129 / 136, 16 160 / 166;
                 // 138 M M = 2 (390 M) 713 / 776, 5 386 / 403, 8 529 / 531, 12 696 / 733, 16 872 / 925
-                if constexpr (kBf16 && MT > 0 && MT <= 3) return launch_octets<MT, NPTR, 64, 4, 1, 10>(a, d, stream);
-                else if constexpr (kBf16 && MT > 0 && MT <= 6) return launch_octets<MT, NPTR, 64, 8, 1, 16>(a, d, stream);
-                else if constexpr (kBf16) return launch_octets<MT, NPTR, 64, 8, 1, MT == 16 ? 24 : 20>(a, d, stream);
+                if constexpr (kBf16 && MT > 0 && MT <= 3) return launch_octets<MT, NPTR, 64, 4, 10>(a, d, stream);
+                else if constexpr (kBf16 && MT > 0 && MT <= 6) return launch_octets<MT, NPTR, 64, 8, 16>(a, d, stream);
+                else if constexpr (kBf16) return launch_octets<MT, NPTR, 64, 8, MT == 16 ? 24 : 20>(a, d, stream);
                 // fp32: four loads per lane make up for the missing momentum stream
                 else return launch_step_shape<MT, NPTR, 256, 2, 2, 64, true, false, G>(a, d, stream);
             } else if constexpr (!kBf16) {

@@ -19,7 +19,8 @@
 //    unit (4-6 MB over the chip, the bandwidth-delay product) saturate HBM; more
 //    only lengthens the memory system's queues and mixes more DRAM rows into
 //    them, and the rate drops by 3-10 % - the more streams (workers) the worse.
-//    For large d the kernel therefore takes one or two workers per stage and
+//    For large d the kernel therefore takes one or two workers per stage (bf16
+//    gradients alone, which are short: up to eight, in step_bf16_kernel) and
 //    the block reserves LDS that it never uses (HOLD_KB), which caps the blocks
 //    that share a compute unit: e.g. 96 KB leaves room for one 512-thread block
 //    in a unit's 160 KB, 64 KB for two 256-thread blocks, 40 KB for four of 128.
@@ -234,45 +235,34 @@ __global__ __launch_bounds__(BLOCK) void step_kernel(const StepArgs<NPTR> a) {
 // The whole step for bf16 gradients without momentum.  The quad geometry would load 64 bits of gradient a
 // lane; here a lane loads 128 bits, an octet of coordinates, and counts its votes in two words of byte
 // counters.  x stays in quads - two per lane, whole kilobytes per wave - and what a lane needs of
-// its quads' votes comes from the octets' lanes by two lane reads at the end.
-template <int NW, int R, int NPTR>
-__device__ __forceinline__ void octet_stage(const StepArgs<NPTR> &a, int w0, const size_t (&o)[R], uint32_t (&lo)[R],
-                                            uint32_t (&hi)[R], int lane) {
-    u32x4 gv[R][NW];    // eight bf16, the lower coordinate in the lower half of a word
+// its quads' votes comes from the octets' lanes by two lane reads at the end.  Per-worker bits are not
+// written here: a step of this size that wants them runs as two launches.
+template <int NW, int NPTR>
+__device__ __forceinline__ void octet_stage(const StepArgs<NPTR> &a, int w0, size_t o, uint32_t &lo, uint32_t &hi) {
+    u32x4 gv[NW];    // eight bf16, the lower coordinate in the lower half of a word
 #pragma unroll
-    for (int j = 0; j < NW; ++j) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) gv[r][j] = ld_stream(reinterpret_cast<const u32x4 *>(a.p.g[w0 + j]) + o[r]);
-    }
+    for (int j = 0; j < NW; ++j) gv[j] = ld_stream(reinterpret_cast<const u32x4 *>(a.p.g[w0 + j]) + o);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < NW; ++j) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const uint32_t byte = neg_byte_bf16(gv[r][j]);
-            lo[r] += spread_nibble(byte & 0xFu);
-            hi[r] += spread_nibble(byte >> 4);
-            if (a.write_packed) {
-                const uint32_t word = combine4(byte, lane);
-                if ((lane & 3) == 0) a.p.packed[w0 + j][o[r] >> 2] = word;
-            }
-        }
+        const uint32_t byte = neg_byte_bf16(gv[j]);
+        lo += spread_nibble(byte & 0xFu);
+        hi += spread_nibble(byte >> 4);
     }
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int NMAX, int R, int NPTR>
-__device__ __forceinline__ void octet_rest(const StepArgs<NPTR> &a, int w0, int n, const size_t (&o)[R], uint32_t (&lo)[R],
-                                           uint32_t (&hi)[R], int lane) {
+template <int NMAX, int NPTR>
+__device__ __forceinline__ void octet_rest(const StepArgs<NPTR> &a, int w0, int n, size_t o, uint32_t &lo, uint32_t &hi) {
     if (n == NMAX) {
-        octet_stage<NMAX, R>(a, w0, o, lo, hi, lane);
+        octet_stage<NMAX>(a, w0, o, lo, hi);
     } else if constexpr (NMAX > 1) {
-        octet_rest<NMAX - 1, R>(a, w0, n, o, lo, hi, lane);
+        octet_rest<NMAX - 1>(a, w0, n, o, lo, hi);
     }
 }
 
-// BW, R, HOLD_KB as for step_kernel; a tile is R rows of BLOCK octets
-template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB>
+// BW, HOLD_KB as for step_kernel; a tile is one row of BLOCK octets
+template <int MT, int NPTR, int BLOCK, int BW, int HOLD_KB>
 __global__ __launch_bounds__(BLOCK) void step_bf16_kernel(const StepArgs<NPTR> a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.p.packed[0]);
     const int tid = threadIdx.x;
@@ -281,50 +271,43 @@ __global__ __launch_bounds__(BLOCK) void step_bf16_kernel(const StepArgs<NPTR> a
     const int T = M / 2 + 1;
     const size_t tile = blockIdx.x;
     if (tile < a.n_tiles) {
-        size_t o[R];
-        uint32_t lo[R], hi[R];
-        f32x4 xv[R][2];
+        const size_t o = tile * BLOCK + tid;
+        f32x4 *const xq = reinterpret_cast<f32x4 *>(a.x) + 2 * (o - lane) + lane;    // quads xq[0] and xq[64]
+        uint32_t lo = 0, hi = 0;
+        f32x4 xv[2];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            o[r] = (tile * R + r) * BLOCK + tid;
-            lo[r] = hi[r] = 0;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) xv[r][h] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + 2 * (o[r] - lane) + 64 * h + lane);
-        }
+        for (int h = 0; h < 2; ++h) xv[h] = ld_stream(xq + 64 * h);
         int w0 = 0;
-        for (; w0 + BW <= M; w0 += BW) octet_stage<BW, R>(a, w0, o, lo, hi, lane);
+        for (; w0 + BW <= M; w0 += BW) octet_stage<BW>(a, w0, o, lo, hi);
         if constexpr (MT > 0) {
-            if constexpr (MT % BW != 0) octet_stage<MT % BW, R>(a, w0, o, lo, hi, lane);
+            if constexpr (MT % BW != 0) octet_stage<MT % BW>(a, w0, o, lo, hi);
         } else {
-            octet_rest<BW - 1, R>(a, w0, M - w0, o, lo, hi, lane);
+            octet_rest<BW - 1>(a, w0, M - w0, o, lo, hi);
         }
+        const uint32_t byte = vote_nibble(lo, T) | (vote_nibble(hi, T) << 4);
+        const uint32_t word = combine4(byte, lane);
+        if ((lane & 3) == 0) a.voted[o >> 2] = word;
+        if (a.sums) reinterpret_cast<uint64_t *>(a.sums)[o] = sums_word(lo, M) | ((uint64_t)sums_word(hi, M) << 32);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const uint32_t byte = vote_nibble(lo[r], T) | (vote_nibble(hi[r], T) << 4);
-            const uint32_t word = combine4(byte, lane);
-            if ((lane & 3) == 0) a.voted[o[r] >> 2] = word;
-            if (a.sums) reinterpret_cast<uint64_t *>(a.sums)[o[r]] = sums_word(lo[r], M) | ((uint64_t)sums_word(hi[r], M) << 32);
+        for (int h = 0; h < 2; ++h) {
+            // quad `lane` of half h lies in the octet of lane 32 h + lane / 2
+            const int from = 32 * h + (lane >> 1);
+            f32x4 v = xv[h];
+            if (a.sum_update) {
+                const uint32_t l = (uint32_t)__shfl((int)lo, from, 64), u = (uint32_t)__shfl((int)hi, from, 64);
+                const uint32_t counts = (lane & 1) ? u : l;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                // quad `lane` of half h lies in the octet of lane 32 h + lane / 2
-                const int from = 32 * h + (lane >> 1);
-                f32x4 v = xv[r][h];
-                if (a.sum_update) {
-                    const uint32_t l = (uint32_t)__shfl((int)lo[r], from, 64), u = (uint32_t)__shfl((int)hi[r], from, 64);
-                    const uint32_t counts = (lane & 1) ? u : l;
+                for (int c = 0; c < 4; ++c) v[c] = step_sum(v[c], a.delta, sum_at(counts, c, M));
+            } else {
+                const uint32_t nib = (uint32_t)__shfl((int)byte, from, 64) >> ((lane & 1) * 4);
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) v[c] = step_sum(v[c], a.delta, sum_at(counts, c, M));
-                } else {
-                    const uint32_t nib = (uint32_t)__shfl((int)byte, from, 64) >> ((lane & 1) * 4);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) v[c] = step(v[c], a.delta, (nib >> c) & 1u);
-                }
-                st_stream(reinterpret_cast<f32x4 *>(a.x) + 2 * (o[r] - lane) + 64 * h + lane, v);
+                for (int c = 0; c < 4; ++c) v[c] = step(v[c], a.delta, (nib >> c) & 1u);
             }
+            st_stream(xq + 64 * h, v);
         }
         return;
     }
-    step_tail<false, Bf16Grad>(a, M, a.n_tiles * (size_t)(R * BLOCK * 2 * kQuad) + (tile - a.n_tiles) * BLOCK + tid, lane);
+    step_tail<false, Bf16Grad>(a, M, a.n_tiles * (size_t)(BLOCK * 2 * kQuad) + (tile - a.n_tiles) * BLOCK + tid, lane);
 }
 
 // ---------------------------------------------------------------- pack ----
