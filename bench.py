@@ -225,7 +225,7 @@ def main():
     t1 = time.perf_counter()
     wall_ms = (t1 - t0) * 1e3 / args.steps
     avg_kernel_ms = e_begin.elapsed_time(e_end) / args.steps
-    # spread of single launches, each between its own event pair (adds a few us per launch)
+    # spread of single steps, each between its own event pair (adds a few us per step)
     n_single = min(args.steps, 50)
     starts = [torch.cuda.Event(enable_timing=True) for _ in range(n_single)]
     stops = [torch.cuda.Event(enable_timing=True) for _ in range(n_single)]
@@ -238,8 +238,8 @@ def main():
 
     bytes_per_launch = bytes_per_coordinate(kernel, cfg) * d
     achieved = bytes_per_launch / (avg_kernel_ms * 1e-3) / 1e9
-    extra = {"kernel_ms_avg": avg_kernel_ms, "single_launch_ms_min": kernel_ms[0],
-             "single_launch_ms_median": kernel_ms[len(kernel_ms) // 2],
+    extra = {"kernel_ms_avg": avg_kernel_ms, "single_step_ms_min": kernel_ms[0],
+             "single_step_ms_median": kernel_ms[len(kernel_ms) // 2],
              "algorithmic_bytes_per_launch": bytes_per_launch,
              "algorithmic_bytes_per_coordinate": bytes_per_coordinate(kernel, cfg),
              "library_source_digest": library_source_digest()}

@@ -177,10 +177,14 @@ STEP_SUM_UPDATE = 2
 
 
 def signum_vote_step(g, m, beta, delta, x, voted, packed_out=None, d=None, stream=None):
-    """ss_signum_vote_step: the whole step for M = len(g) workers in one pass.
+    """ss_signum_vote_step: the whole step for M = len(g) workers in one call.
     g: list of gradients; m: list of momentum buffers or None.
-    A large step without packed_out borrows up to 128 MiB from torch's allocator
-    for the length of the call (ss_signum_vote_step_scratch), where it can."""
+    A large step with momentum and without packed_out borrows up to 128 MiB from
+    torch's caching allocator for the length of the call
+    (ss_signum_vote_step_scratch).  It does so on torch's own streams, outside of
+    capture, and while a gigabyte of device memory stays free beside it; otherwise
+    it runs in one pass, with the same results.  The allocator keeps such a block
+    for each stream until it needs the memory (torch.cuda.empty_cache)."""
     _check("ss_signum_vote_step", (_marshal or _native()).signum_vote_step(
         g, m, beta, delta, x, voted, packed_out, None, 0, d, stream))
     return voted
@@ -188,7 +192,7 @@ def signum_vote_step(g, m, beta, delta, x, voted, packed_out=None, d=None, strea
 
 def signum_vote_step_ex(g, m, beta, delta, x, voted, packed_out=None, sums_out=None, flags=None, d=None,
                         stream=None):
-    """ss_signum_vote_step_ex (flags None: the plain step)"""
+    """ss_signum_vote_step_ex (flags None: the plain step); borrows memory as signum_vote_step does"""
     _check("ss_signum_vote_step_ex", (_marshal or _native()).signum_vote_step(
         g, m, beta, delta, x, voted, packed_out, sums_out, int(flags or 0), d, stream))
     return voted
@@ -245,6 +249,7 @@ def ternary_apply(x, neg, zero, delta, d=None, stream=None):
 
 
 def signum_vote_step_ternary(g, m, beta, tau, quorum, delta, x, voted_neg, voted_zero, d=None, stream=None):
-    """ss_signum_vote_step_ternary: the whole step with abstention in one pass"""
+    """ss_signum_vote_step_ternary: the whole step with abstention in one call
+    (borrows memory as signum_vote_step does)"""
     _check("ss_signum_vote_step_ternary", (_marshal or _native()).signum_vote_step_ternary(
         g, m, beta, tau, quorum, delta, x, voted_neg, voted_zero, d, stream))

@@ -130,7 +130,8 @@ inline bool split_pays(int M, size_t d) {
 
 // A launch may have at most 2^32 - 1 threads, which a shape with one row of quads a lane reaches at 2^34
 // coordinates.  Up to half of that every shape is safe, the blocks of a tail included; a step over a longer vector
-// runs over parts of this many coordinates, and kernels that are not cut take a shape of two rows.
+// runs over parts of this many coordinates, the ternary step and sigma take two rows there, and the other calls end
+// at the limit itself.
 constexpr size_t kOneRowMaxD = (size_t)1 << 33;
 // no step is longer (nor fits: 4 bytes of x alone are 275 GB)
 constexpr size_t kStepMaxD = (size_t)1 << 36;
@@ -155,7 +156,9 @@ inline size_t scratch_slab(int M, size_t d, size_t bytes) {
 // 27.2 -> 27.2; M = 8 bf16 4.4 M (352 MB) 72 -> 65; M = 7 fp32 25.6 M 376 -> 357; M = 16 138 M 4,620 -> 4,170; M = 4 bf16
 // 8.0 M (320 MB) 64.7 -> 63.5; M = 3 fp32 8.0 M (288 MB) 60.4 -> 59.5; M = 2 fp32 12 M (288 MB) 65.8 -> 65.7,
 // 60 M 319 -> 294, bf16 17.6 M (352 MB) 77.6 -> 82.1, 60 M (1.2 GB) 263 -> 259.  Where a step takes less than ~40 us the
-// first allocation on a stream (~20 us, once) is not worth what is gained.
+// first allocation on a stream (~20 us, once) is not worth what is gained.  A lender that asks the device for its free
+// memory at each call pays 6-9 us of host time for it, which a step behind queued work hides: alone, M = 8 bf16 6.5 M takes
+// 112 us where the same launches without the question take 104.
 inline bool scratch_pays(int M, size_t d, size_t worker_bytes) {
     return d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 5 ? 28 : M >= 3 ? 29 : 30));
 }
@@ -328,8 +331,10 @@ int launch_pack(int n, const void *const *g, ss_dtype gdt, float *const *m, uint
     else return launch_pack_shape(ss::pack_kernel<NPTR, 128, 2, false, ss::F32Grad>, a, n, 128, 2, 4, stream);
 }
 
-// Vote and update from packed bits.  Four rows per block and four blocks per unit; from 2^28
-// coordinates on one row and no cap (d = 400 M, M = 8: 563 us against 590; d = 138 M, M = 16: 213 against 203).
+// Vote and update from packed bits.  Four rows per block and three blocks per unit (40 KB and the vote's own 0.5 KB
+// of LDS; the count planes' 3.5 KB and 36 make it four).  A step with packed_out, three against four blocks of the
+// fixed-M kernels, us: 25.6 M M = 7 355.6 / 356.3, M = 16 771 / 775, 60 M M = 8 940 / 941, 138 M M = 16 4,301 / 4,312.
+// From 2^28 coordinates on one row and no cap (d = 400 M, M = 8: 563 us against 590; d = 138 M, M = 16: 213 against 203).
 template <int MT, bool COUNTS>
 int launch_vote_apply(const uint32_t *const *packed, int M, uint32_t *voted, float *x, float delta, StepVariant var,
                       size_t d, hipStream_t stream) {
@@ -414,7 +419,10 @@ int launch_vote_any(const uint32_t *const *packed, int M, uint32_t *voted, size_
     if (word_lanes(M, d)) return launch(ss::vote_word_kernel, (4 * a.n_vec + 63) / 64, 0, stream, a, 64);
     const size_t grid = (a.n_vec + kVoteWave - 1) / kVoteWave;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    // 25.6 M: 14.5 us against 15.3 for four-wave blocks, 1.1 M 5.2 / 5.5
+    // one-wave blocks (25.6 M, M = 24: 14.5 us against 15.3 for four-wave blocks), with more LDS held back, so fewer of
+    // them per unit, from 2^26 coordinates on.  us, 8 against 16 KB: M = 20 25.6 M 13.8 / 15.1, 40 M 21.3 / 22.1,
+    // 67 M 31.4 / 31.8, 138 M 64.6 / 63.6, 390 M 171 / 165; M = 64 25.6 M 37.9 / 39.4, 40 M 58.6 / 59.7, 67 M 93.9 / 93.1,
+    // 138 M 193 / 189, 390 M 523 / 500; M = 24 and 33 alike
     if (d >= kLargeD / 4) return launch(ss::vote_kernel_any<kVoteWave, 16>, grid, 0, stream, a, kVoteWave);
     return launch(ss::vote_kernel_any<kVoteWave, 8>, grid, 0, stream, a, kVoteWave);
 }
@@ -784,6 +792,9 @@ int ss_welford_update(const void *g, ss_dtype gdt, float *mean, float *m2, uint6
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    // the cap of welford_update_kernel, us with against without: fp32 4.4 M 15.7 / 15.4, 8.8 M 29.1 / 29.2, 12 M 38.6 / 38.4,
+    // 16 M 50.1 / 50.7, 20 M 62.9 / 63.2, 25.6 M 80.1 / 81.4, 60 M 182 / 190; bf16 4.4 M 13.7 / 13.5, 12 M 34.5 / 34.7,
+    // 17.6 M 49.7 / 50.7, 60 M 164 / 170
     if (d >= ((size_t)1 << 24) && caps_apply()) {
         if (gdt == SS_F32) return launch(ss::welford_update_kernel<8, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
         return launch(ss::welford_update_kernel<8, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);

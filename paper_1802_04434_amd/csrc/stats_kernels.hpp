@@ -34,9 +34,9 @@ __device__ __forceinline__ void welford1(float g, float n, float &mean, float &m
     m2 = m2 + p;
 }
 
-// One-wave blocks as apply_kernel (see there).  Five streams: with HOLD_KB = 8 twenty waves share a unit
-// instead of 32, us against no cap and against blocks of four waves as launched before: 25.6 M
-// coordinates 80.6 / 81.5 / 82.2, 138 M 422 / 433 / 452, 600 M 1,926 / 1,964 / 1,978; 4.4 M 16.7 / 16.2 / 16.5.
+// One-wave blocks as sum_apply_kernel and copy_kernel (see there).  Five streams: with HOLD_KB = 8 twenty
+// waves share a unit instead of 32, us against no cap and against blocks of four waves as launched before:
+// 25.6 M coordinates 80.6 / 81.5 / 82.2, 138 M 422 / 433 / 452, 600 M 1,926 / 1,964 / 1,978; 4.4 M 16.7 / 16.2 / 16.5.
 template <int HOLD_KB, typename G>
 __global__ __launch_bounds__(kWave) void welford_update_kernel(const WelfordArgs a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, reinterpret_cast<uint32_t *>(a.mean));
