@@ -303,11 +303,49 @@ template <int NPTR>
 int launch_pack_shape(void (*kernel)(ss::PackArgs<NPTR>), ss::PackArgs<NPTR> &a, int n, int block, int rows, int per_lane,
                       hipStream_t stream) {
     const Tiling t = make_tiling(a.d, rows, true, block, per_lane);
-    a.n_tiles = t.n_tiles;
-    a.words_total = t.words_total;
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
+    a.n_tiles = (uint32_t)t.n_tiles;
+    a.words_total = t.words_total;
     return launch(kernel, grid, 0, stream, a, block, n);
+}
+
+// Runs of tiles that a die takes at a time (see die_tile): half a megabyte where vectors of up to some tens of millions of
+// coordinates are streamed, for in-place kernels that fit the caches a quarter.
+//
+// With momentum, shapes of pack_kernel (us, fp32 unless said):
+//   below 2^28 bytes        written lines left to the L2, quarters.  In order / quarter / half: 17.6 M M = 1 34.2 / 32.6 / 32.9,
+//                           4.4 M M = 2 17.7 / 17.4 / 17.4, bf16 17.6 M M = 1 29.0 / 27.4 / 27.8; written through 1.1 M M = 7 16.5
+//                           against 15.8
+//   up to 2^25 coordinates  written through, halves.  To the L2 in order / to the L2 halves / through in order / through
+//                           halves: 25.6 M M = 7 322 / 319 / 320 / 316, M = 1 48.4 / 46.7 / 47.1 / 46.6, 4.4 M M = 8 65.7 / 64.3 /
+//                           64.7 / 63.8, bf16 54.8 / 54.1 / 53.8 / 53.3
+//   above                   written through, in order, 7 KB held back: 21 waves a unit, 42 KB of loads in flight.  Through halves
+//                           without / in order without / in order with: 60 M M = 4 426 / 427 / 421, 138 M M = 4
+//                           982 / 986 / 968, 400 M M = 2 1,438 / 1,477 / 1,437, bf16 1,200 / 1,235 / 1,192
+template <int NPTR, typename G>
+int launch_pack_momentum(ss::PackArgs<NPTR> &a, int n, hipStream_t stream) {
+    constexpr size_t kBytes = sizeof(typename G::elem) + 2 * sizeof(float);
+    if (a.d * (size_t)n * kBytes < ((size_t)1 << 28))
+        return launch_pack_shape(ss::pack_kernel<NPTR, 64, 1, 0, ss::kStream, 8, true, G>, a, n, 64, 1, 4, stream);
+    if (a.d < ((size_t)1 << 25) || !caps_apply())
+        return launch_pack_shape(ss::pack_kernel<NPTR, 64, 1, 0, ss::kThrough, 9, true, G>, a, n, 64, 1, 4, stream);
+    return launch_pack_shape(ss::pack_kernel<NPTR, 64, 1, 7, ss::kThrough, 0, true, G>, a, n, 64, 1, 4, stream);
+}
+
+// Gradients only, one stream that is only read: two rows a wave and half a megabyte a die up to where the runs stop paying,
+// which is later in fp32.  In order / in runs, us: fp32 4.4 M M = 8 25.2 / 22.6, 25.6 M M = 1 17.3 / 15.9, M = 7 115 / 111, 60 M
+// M = 4 152 / 150, 400 M M = 2 512 / 519 (two waves of two rows in order 509); bf16 17.6 M M = 2 13.3 / 12.3, 25.6 M M = 1
+// 9.8 / 9.2, 60 M M = 4 79.6 / 80.2, 138 M M = 4 180 / 182.
+template <int NPTR>
+int launch_pack_sign(ss_dtype gdt, ss::PackArgs<NPTR> &a, int n, hipStream_t stream) {
+    if (gdt == SS_BF16) {
+        if (a.d < ((size_t)1 << 25)) return launch_pack_shape(ss::pack_bf16_kernel<NPTR, 64, 2, 8>, a, n, 64, 2, 8, stream);
+        return launch_pack_shape(ss::pack_bf16_kernel<NPTR, 64, 2, 0>, a, n, 64, 2, 8, stream);
+    }
+    if (a.d < ((size_t)1 << 27))
+        return launch_pack_shape(ss::pack_kernel<NPTR, 64, 2, 0, ss::kStream, 8, false, ss::F32Grad>, a, n, 64, 2, 4, stream);
+    return launch_pack_shape(ss::pack_kernel<NPTR, 128, 2, 0, ss::kStream, 0, false, ss::F32Grad>, a, n, 128, 2, 4, stream);
 }
 
 template <int NPTR>
@@ -319,23 +357,19 @@ int launch_pack(int n, const void *const *g, ss_dtype gdt, float *const *m, uint
     a.omb = 1.0f - beta;
     a.warmup = (flags & SS_STEP_WARMUP) ? 1 : 0;
     a.d = d;
-    if (m) {
-        if (gdt == SS_F32) return launch_pack_shape(ss::pack_kernel<NPTR, 64, 1, true, ss::F32Grad>, a, n, 64, 1, 4, stream);
-        return launch_pack_shape(ss::pack_kernel<NPTR, 64, 1, true, ss::Bf16Grad>, a, n, 64, 1, 4, stream);
-    }
-    if (gdt == SS_BF16) return launch_pack_shape(ss::pack_bf16_kernel<NPTR, 64, 2>, a, n, 64, 2, 8, stream);
-    // fp32 gradients only: one worker at d = 25.6 M 16.2 us with four rows of 256 threads against 17.6
-    // with two of 128; several workers the other way round (d = 25.6 M, M = 8 130 against 127 us,
-    // d = 138 M, M = 16 1.55 against 1.39 ms)
-    if constexpr (NPTR == 1) return launch_pack_shape(ss::pack_kernel<1, 256, 4, false, ss::F32Grad>, a, n, 256, 4, 4, stream);
-    else return launch_pack_shape(ss::pack_kernel<NPTR, 128, 2, false, ss::F32Grad>, a, n, 128, 2, 4, stream);
+    if (!m) return launch_pack_sign<NPTR>(gdt, a, n, stream);
+    if (gdt == SS_F32) return launch_pack_momentum<NPTR, ss::F32Grad>(a, n, stream);
+    return launch_pack_momentum<NPTR, ss::Bf16Grad>(a, n, stream);
 }
 
-// Vote and update from packed bits.  Four rows per block and three blocks per unit (40 KB and the vote's own 0.5 KB
-// of LDS; the count planes' 3.5 KB and 36 make it four).  A step with packed_out, three against four blocks of the
-// fixed-M kernels, us: 25.6 M M = 7 355.6 / 356.3, M = 16 771 / 775, 60 M M = 8 940 / 941, 138 M M = 16 4,301 / 4,312.
-// From 2^28 coordinates on one row and no cap (d = 400 M, M = 8: 563 us against 590; d = 138 M, M = 16: 213 against 203).
-template <int MT, bool COUNTS>
+// Vote and update from packed bits.  A fixed number of workers: blocks of two waves with four rows each, five of them and 40 KB
+// of x in flight to a unit.  Both launches of a step against four waves of four rows, three blocks a unit (us): 1.1 M M = 7
+// 19.5 / 21.1, 4.4 M 64.8 / 64.2, 25.6 M 348.2 / 351.8, 60 M M = 2 287.4 / 289.8, 138 M M = 4 1,146 / 1,162; one row and no cap:
+// 19.7, 64.8, 353, 304, 1,212.  One wave that votes on a word a lane and hands it on by ds_bpermute: 20.6, 67.2, 348.4,
+// 287.3, 1,140.
+// Any number of workers is added up batch by batch, and the longer a block waits for its votes the more waves a unit
+// wants: four waves of four rows, three blocks (count planes four), and from 2^28 coordinates on one row and no cap.
+template <int MT, int P>
 int launch_vote_apply(const uint32_t *const *packed, int M, uint32_t *voted, float *x, float delta, StepVariant var,
                       size_t d, hipStream_t stream) {
     constexpr int NPTR = MT > 0 ? MT : SS_MAX_WORKERS;
@@ -349,24 +383,28 @@ int launch_vote_apply(const uint32_t *const *packed, int M, uint32_t *voted, flo
     a.sum_update = (var.flags & SS_STEP_SUM_UPDATE) ? 1 : 0;
     a.d = d;
     a.words_total = ss_packed_bytes(d) / 4;
-    const bool large = d >= kLargeD;
-    const size_t words = large ? 32 : 128;
+    const size_t words = MT > 0 ? 64 : d >= kLargeD ? 32 : 128;
     const size_t grid = (a.words_total + words - 1) / words;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    if (large) return launch(ss::vote_apply_kernel<MT, NPTR, 1, 0, COUNTS>, grid, 0, stream, a);
-    return launch(ss::vote_apply_kernel<MT, NPTR, 4, 40 - (COUNTS ? 4 : 0), COUNTS>, grid, 0, stream, a);
+    if constexpr (MT > 0) return launch(ss::vote_apply_kernel<MT, NPTR, P, 128, 4, 31>, grid, 0, stream, a, 128);
+    else if (d >= kLargeD) return launch(ss::vote_apply_kernel<MT, NPTR, P, 256, 1, 0>, grid, 0, stream, a);
+    else return launch(ss::vote_apply_kernel<MT, NPTR, P, 256, 4, (P > 0 ? 36 : 40)>, grid, 0, stream, a);
 }
 
 int dispatch_vote_apply(const uint32_t *const *packed, int M, uint32_t *voted, float *x, float delta, StepVariant var,
                         size_t d, hipStream_t stream) {
-    if (var.sums || (var.flags & SS_STEP_SUM_UPDATE))
-        return launch_vote_apply<0, true>(packed, M, voted, x, delta, var, d, stream);
+    if (var.sums || (var.flags & SS_STEP_SUM_UPDATE)) {
+        const int planes = count_planes(M);
+        if (planes <= 3) return launch_vote_apply<0, 3>(packed, M, voted, x, delta, var, d, stream);
+        if (planes <= 5) return launch_vote_apply<0, 5>(packed, M, voted, x, delta, var, d, stream);
+        return launch_vote_apply<0, 7>(packed, M, voted, x, delta, var, d, stream);
+    }
 #define SS_CASE(n) \
-    case n: return launch_vote_apply<n, false>(packed, M, voted, x, delta, var, d, stream)
+    case n: return launch_vote_apply<n, 0>(packed, M, voted, x, delta, var, d, stream)
     switch (M) {
         SS_CASE(2); SS_CASE(3); SS_CASE(4); SS_CASE(5); SS_CASE(6); SS_CASE(7); SS_CASE(8);
         SS_CASE(9); SS_CASE(10); SS_CASE(11); SS_CASE(12); SS_CASE(13); SS_CASE(14); SS_CASE(15); SS_CASE(16);
-        default: return launch_vote_apply<0, false>(packed, M, voted, x, delta, var, d, stream);
+        default: return launch_vote_apply<0, 0>(packed, M, voted, x, delta, var, d, stream);
     }
 #undef SS_CASE
 }
@@ -479,7 +517,7 @@ int dispatch_ternary(ss::TernaryStepArgs &a, ss_dtype gdt, bool has_m, size_t d,
     return launch_ternary<false, VOTE, ss::Bf16Grad>(a, d, stream);
 }
 
-// answer and update from the planes a pack launch left in a.neg_out / a.zero_out; shapes as launch_vote_apply
+// answer and update from the planes a pack launch left in a.neg_out / a.zero_out
 int launch_quorum_apply(const ss::TernaryStepArgs &t, uint32_t *voted_neg, uint32_t *voted_zero, float *x, size_t d,
                         hipStream_t stream) {
     ss::QuorumApplyArgs a;

@@ -38,6 +38,29 @@ __device__ __forceinline__ void st_stream(T *p, T v) {
     __builtin_nontemporal_store(v, p);
 }
 
+// A block's own part of a buffer as a buffer descriptor: the base is the same for the whole block and sits in
+// scalar registers, a lane adds a 32-bit byte offset.  What lies at or beyond `bytes` reads as zero and is
+// not written.  Kernels that write where they have read are 1-2 % faster with it than with a 64-bit address a lane
+// (pack of 138 M coordinates, M = 4 968 us against 979, 400 M, M = 2 1,437 / 1,464); kernels that only read are as much slower
+// (a wave lives for ~2 us and the descriptors lengthen its start) and keep addresses.
+typedef __amdgpu_buffer_rsrc_t Window;
+__device__ __forceinline__ Window window(const void *base, size_t from, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(static_cast<const char *>(base)) + from, 0, (int)bytes, 0x00020000);
+}
+
+// Cache policies of stores (bits of the instruction: 2 = nt, 16 = sc1).  kStream leaves a written line to the L2 to
+// write back; kThrough sends it on at once, which large vectors prefer by 1-3 % (25.6 M, M = 7 324 us against 326, 138 M, M = 4
+// 986 / 991) and vectors that the memory-side cache holds do not (1.1 M, M = 7 16.1 / 15.3).
+constexpr int kStream = 2, kThrough = 18;
+
+__device__ __forceinline__ f32x4 ld_quad(Window w, uint32_t off) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(w, (int)off, 0, kStream));
+}
+template <int STORE>
+__device__ __forceinline__ void st_quad(Window w, uint32_t off, f32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), w, (int)off, 0, STORE);
+}
+
 // bf16 -> fp32 is exact: the bf16 pattern is the upper half of the fp32
 __device__ __forceinline__ float widen_bf16(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
@@ -46,6 +69,7 @@ struct F32Grad {
     static __device__ __forceinline__ f32x4 load4(const void *base, size_t quad) {
         return ld_stream(reinterpret_cast<const f32x4 *>(base) + quad);
     }
+    static __device__ __forceinline__ f32x4 load4(Window w, uint32_t quad) { return ld_quad(w, quad * 16); }
     static __device__ __forceinline__ float load1(const void *base, size_t i) {
         return reinterpret_cast<const float *>(base)[i];
     }
@@ -53,11 +77,16 @@ struct F32Grad {
 
 struct Bf16Grad {
     typedef uint16_t elem;
-    static __device__ __forceinline__ f32x4 load4(const void *base, size_t quad) {
-        u16x4 r = ld_stream(reinterpret_cast<const u16x4 *>(base) + quad);
+    static __device__ __forceinline__ f32x4 widen(u16x4 r) {
         f32x4 o;
         o.x = widen_bf16(r.x); o.y = widen_bf16(r.y); o.z = widen_bf16(r.z); o.w = widen_bf16(r.w);
         return o;
+    }
+    static __device__ __forceinline__ f32x4 load4(const void *base, size_t quad) {
+        return widen(ld_stream(reinterpret_cast<const u16x4 *>(base) + quad));
+    }
+    static __device__ __forceinline__ f32x4 load4(Window w, uint32_t quad) {
+        return widen(__builtin_bit_cast(u16x4, __builtin_amdgcn_raw_buffer_load_b64(w, (int)(quad * 8), 0, kStream)));
     }
     static __device__ __forceinline__ float load1(const void *base, size_t i) {
         return widen_bf16(reinterpret_cast<const uint16_t *>(base)[i]);
@@ -130,6 +159,17 @@ __device__ __forceinline__ void reserve_lds(bool never, uint32_t *sink) {
             sink[threadIdx.x] = hold[threadIdx.x ^ 1];
         }
     }
+}
+
+// Which tile a block takes.  Blocks go to the eight compute dies (XCDs) in turn, so block b and b + 8 share one.  With
+// CHUNK > 0 a die takes 2^CHUNK neighbouring tiles before the next one's turn; what does not fill eight
+// such runs is taken in order.
+template <uint32_t CHUNK>
+__device__ __forceinline__ uint32_t die_tile(uint32_t block, uint32_t n_tiles) {
+    if constexpr (CHUNK == 0) return block;
+    if (block >= (n_tiles >> (CHUNK + 3) << (CHUNK + 3))) return block;
+    const uint32_t turn = block >> 3;
+    return ((turn >> CHUNK << 3 | (block & 7u)) << CHUNK) | (turn & ((1u << CHUNK) - 1u));
 }
 
 // kernel argument block: M device pointers by value (no table in memory)

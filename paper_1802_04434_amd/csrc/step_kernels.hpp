@@ -323,8 +323,8 @@ struct PackArgs {
     PackWorker w[NPTR];  // blockIdx.y selects the worker
     float beta, omb;
     int warmup;          // Theorem 3 warm-up: signs come from g while m is still updated
+    uint32_t n_tiles;    // blocks on the vector path, R rows of BLOCK * 4 coordinates each
     size_t d;
-    size_t n_tiles;      // blocks on the vector path, R rows of BLOCK * 4 coordinates each
     size_t words_total;  // words of a packed buffer including zero padding
 };
 
@@ -355,44 +355,56 @@ __device__ __forceinline__ void pack_tail(const PackArgs<NPTR> &a, const PackWor
 // where M launches have M.
 //
 // With momentum a block is ONE wave with one row: the dispatcher refills a finished wave's slot at
-// once, where a block of four holds its slots until its slowest wave is done.  Measured against
-// 256 threads of one / four rows, none with a cap on the resident blocks (the cap that step_kernel
-// needs for its 2M + 1 streams gains nothing here): d = 25.6 M, M = 7 fp32 320 us against 332 / 342
-// (6,780 GB/s), d = 138 M, M = 16 3.94 ms against 4.11 / 4.44 (6,816 GB/s), d = 400 M, M = 8 bf16
-// 4.89 ms against 5.00 / 5.52; 1.1 M, M = 7 15.4 us against 15.8 / 16.1.  Without momentum there is
-// one stream and a lane wants more rows in flight; the host's launch_pack has those shapes.
-template <int NPTR, int BLOCK, int R, bool HAS_M, typename G>
+// once, where a block of four holds its slots until its slowest wave is done (d = 138 M, M = 16, us: 3,938 against 4,106
+// for four waves of one row and 4,435 for four rows; two rows a wave, neighbouring or eight apart: 4-8 % slower).
+// HOLD_KB, STORE and CHUNK are chosen by the host's launch_pack_momentum: d = 25.6 M, M = 7 315 us (6,890 GB/s) where
+// 64-bit addresses, the L2's own write-back and tiles in order gave 327, d = 138 M, M = 4 968 (6,935 GB/s) / 1,001,
+// d = 400 M, M = 2 bf16 1,192 / 1,214.
+template <int NPTR, int BLOCK, int R, int HOLD_KB, int STORE, uint32_t CHUNK, bool HAS_M, typename G>
 __global__ __launch_bounds__(BLOCK) void pack_kernel(const PackArgs<NPTR> a) {
+    reserve_lds<HOLD_KB>(a.d == ~(size_t)0 /* the host rejects such a d */, a.w[0].packed);
     const PackWorker w = a.w[NPTR == 1 ? 0 : blockIdx.y];
-    const int tid = threadIdx.x;
+    constexpr uint32_t kCoords = R * BLOCK * kQuad;
+    const uint32_t tid = threadIdx.x;
     const int lane = tid & 63;
-    const size_t tile = blockIdx.x;
-    if (tile < a.n_tiles) {
-        size_t q[R];
-        f32x4 gv[R], mv[R];
+    if (blockIdx.x < a.n_tiles) {
+        const size_t tile = die_tile<CHUNK>(blockIdx.x, a.n_tiles);
+        uint32_t *const out = w.packed + tile * (kCoords / 32);
+        if constexpr (HAS_M) {
+            const Window gw = window(w.g, tile * (kCoords * sizeof(typename G::elem)), kCoords * sizeof(typename G::elem));
+            const Window mw = window(w.m, tile * (kCoords * sizeof(float)), kCoords * sizeof(float));
+            f32x4 gv[R], mv[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            q[r] = (tile * R + r) * BLOCK + tid;
-            gv[r] = G::load4(w.g, q[r]);
-            if (HAS_M) mv[r] = ld_stream(reinterpret_cast<const f32x4 *>(w.m) + q[r]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            f32x4 v = gv[r];
-            if (HAS_M) {
-                v.x = momentum(a.beta, a.omb, mv[r].x, v.x);
-                v.y = momentum(a.beta, a.omb, mv[r].y, v.y);
-                v.z = momentum(a.beta, a.omb, mv[r].z, v.z);
-                v.w = momentum(a.beta, a.omb, mv[r].w, v.w);
-                st_stream(reinterpret_cast<f32x4 *>(w.m) + q[r], v);
+            for (int r = 0; r < R; ++r) {
+                gv[r] = G::load4(gw, r * BLOCK + tid);
+                mv[r] = ld_quad(mw, (r * BLOCK + tid) * 16);
             }
-            const uint32_t word = combine8(neg_nibble((HAS_M && a.warmup) ? gv[r] : v), lane);
-            if ((lane & 7) == 0) w.packed[q[r] >> 3] = word;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                f32x4 v;
+                v.x = momentum(a.beta, a.omb, mv[r].x, gv[r].x);
+                v.y = momentum(a.beta, a.omb, mv[r].y, gv[r].y);
+                v.z = momentum(a.beta, a.omb, mv[r].z, gv[r].z);
+                v.w = momentum(a.beta, a.omb, mv[r].w, gv[r].w);
+                st_quad<STORE>(mw, (r * BLOCK + tid) * 16, v);
+                const uint32_t word = combine8(neg_nibble(a.warmup ? gv[r] : v), lane);
+                if ((lane & 7) == 0) out[(r * BLOCK + tid) >> 3] = word;
+            }
+        } else {
+            f32x4 gv[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) gv[r] = G::load4(w.g, (tile * R + r) * BLOCK + tid);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const uint32_t word = combine8(neg_nibble(gv[r]), lane);
+                if ((lane & 7) == 0) out[(r * BLOCK + tid) >> 3] = word;
+            }
         }
         return;
     }
-    pack_tail<HAS_M, G>(a, w, a.n_tiles * (size_t)(R * BLOCK * kQuad) + (tile - a.n_tiles) * BLOCK + tid, lane);
+    pack_tail<HAS_M, G>(a, w, a.n_tiles * (size_t)kCoords + (size_t)(blockIdx.x - a.n_tiles) * BLOCK + tid, lane);
 }
 
 // pack_kernel for bf16 gradients without momentum: a lane loads 128 bits - eight coordinates, one
@@ -400,29 +412,27 @@ __global__ __launch_bounds__(BLOCK) void pack_kernel(const PackArgs<NPTR> a) {
 // loads to 64 bits and doubles their number: d = 25.6 M, M = 8 68 us (6,390 GB/s) against 78 with
 // four rows of 256 threads and quads, d = 138 M, M = 16 720 us against 833, one worker at 25.6 M
 // 9.8 against 10.8.
-template <int NPTR, int BLOCK, int R>
+template <int NPTR, int BLOCK, int R, uint32_t CHUNK>
 __global__ __launch_bounds__(BLOCK) void pack_bf16_kernel(const PackArgs<NPTR> a) {
     const PackWorker w = a.w[NPTR == 1 ? 0 : blockIdx.y];
-    const int tid = threadIdx.x;
+    constexpr uint32_t kCoords = R * BLOCK * 2 * kQuad;
+    const uint32_t tid = threadIdx.x;
     const int lane = tid & 63;
-    const size_t tile = blockIdx.x;
-    if (tile < a.n_tiles) {
-        size_t o[R];    // octet of coordinates
+    if (blockIdx.x < a.n_tiles) {
+        const size_t tile = die_tile<CHUNK>(blockIdx.x, a.n_tiles);
         u32x4 gv[R];    // eight bf16, the lower coordinate in the lower half of a word
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            o[r] = (tile * R + r) * BLOCK + tid;
-            gv[r] = ld_stream(reinterpret_cast<const u32x4 *>(w.g) + o[r]);
-        }
+        for (int r = 0; r < R; ++r) gv[r] = ld_stream(reinterpret_cast<const u32x4 *>(w.g) + (tile * R + r) * BLOCK + tid);
         __builtin_amdgcn_sched_barrier(0);
+        uint32_t *const out = w.packed + tile * (kCoords / 32);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const uint32_t word = combine4(neg_byte_bf16(gv[r]), lane);
-            if ((lane & 3) == 0) w.packed[o[r] >> 2] = word;
+            if ((lane & 3) == 0) out[(r * BLOCK + tid) >> 2] = word;
         }
         return;
     }
-    pack_tail<false, Bf16Grad>(a, w, a.n_tiles * (size_t)(R * BLOCK * 2 * kQuad) + (tile - a.n_tiles) * BLOCK + tid, lane);
+    pack_tail<false, Bf16Grad>(a, w, a.n_tiles * (size_t)kCoords + (size_t)(blockIdx.x - a.n_tiles) * BLOCK + tid, lane);
 }
 
 }  // namespace ss

@@ -260,72 +260,72 @@ struct VoteApplyArgs {
     const uint32_t *packed[NPTR];
     uint32_t *voted;
     float *x;
-    int8_t *sums;         // COUNTS only, may be NULL: per-coordinate sum of signs
+    int8_t *sums;         // with count planes only, may be NULL: per-coordinate sum of signs
     float delta;
     int M;
-    int sum_update;       // COUNTS only: x <- x - delta * (sum of signs) instead of its sign
+    int sum_update;       // with count planes only: x <- x - delta * (sum of signs) instead of its sign
     size_t d;
     size_t words_total;   // words of a packed buffer including zero padding
 };
 
 // MT workers at compile time; MT == 0: a.M at run time, added into binary count planes.
-// COUNTS (with MT == 0): the planes themselves go through LDS, for the sums and the sum update.
-// A block owns R rows of 1024 coordinates: its first 32 R lanes vote on a word each.  Bound by HBM:
-// 8.125 + M / 8 bytes per coordinate; d = 25.6 M, M = 7: 34.5 us (6,650 GB/s) where the two
-// launches take 5.4 + 33.2 us and a gap.  HOLD_KB caps the blocks per compute unit.
-template <int MT, int NPTR, int R, int HOLD_KB, bool COUNTS>
-__global__ __launch_bounds__(kBlock) void vote_apply_kernel(const VoteApplyArgs<NPTR> a) {
+// P > 0 (with MT == 0): the P planes themselves go through LDS, for the sums and the sum update.
+// A block owns R rows of BLOCK quads; its first lanes vote on a word each.  Bound by HBM: 8.125 + M / 8 bytes per
+// coordinate.  HOLD_KB caps the blocks per compute unit; the shapes are launch_vote_apply's.
+template <int MT, int NPTR, int P, int BLOCK, int R, int HOLD_KB>
+__global__ __launch_bounds__(BLOCK) void vote_apply_kernel(const VoteApplyArgs<NPTR> a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.voted);
-    constexpr int kWords = 32 * R;   // voted words of a block
-    constexpr int kShared = COUNTS ? kPlanes : 1;
-    __shared__ uint32_t vote[kShared][kWords];   // the voted words; COUNTS: the count planes
+    constexpr int kRowCoords = BLOCK * kQuad;
+    constexpr int kCoords = R * kRowCoords;
+    constexpr int kWords = kCoords / 32;   // voted words of a block
+    static_assert(kWords <= BLOCK, "a lane votes on one word");
+    __shared__ uint32_t vote[P > 0 ? P : 1][kWords];   // the voted words, or the count planes
     const int tid = threadIdx.x;
     const size_t wi = (size_t)blockIdx.x * kWords + tid;
-    const size_t base = (size_t)blockIdx.x * (R * kRowCoords);
-    const bool full = base + (size_t)(R * kRowCoords) <= a.d;
+    const size_t base = (size_t)blockIdx.x * kCoords;
+    const bool full = base + kCoords <= a.d;
     const bool votes = tid < kWords && wi < a.words_total;
     uint32_t in[MT > 0 ? MT : 1];
     if (MT > 0 && votes) {
 #pragma unroll
         for (int w = 0; w < MT; ++w) in[w] = a.packed[w][wi];
     }
+    const Window xw = window(a.x, base * sizeof(float), full ? kCoords * sizeof(float) : 0);
     f32x4 xv[R];
-    f32x4 *const xq = reinterpret_cast<f32x4 *>(a.x + base) + tid;
-    if (full) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) xv[r] = ld_stream(xq + r * kBlock);
-    }
+    for (int r = 0; r < R; ++r) xv[r] = ld_quad(xw, (r * BLOCK + tid) * 16);
     __builtin_amdgcn_sched_barrier(0);
     if (votes) {
         uint32_t ge;
         if constexpr (MT > 0) {
             ge = majority_word<MT>(in);
         } else {
+            constexpr int N = P > 0 ? P : kPlanes;
             const int T = a.M / 2 + 1;
-            uint32_t plane[kPlanes];
-            count_words<kPlanes, 8>(a.packed, a.M, wi, plane);
+            uint32_t plane[N];
+            count_words<N, 8>(a.packed, a.M, wi, plane);
             ge = 0xFFFFFFFFu;
 #pragma unroll
-            for (int k = 0; k < kPlanes; ++k) ge = ge_step(ge, plane[k], T, k);
-            if constexpr (COUNTS) {
+            for (int k = 0; k < N; ++k) ge = ge_step(ge, plane[k], T, k);
+            if constexpr (P > 0) {
 #pragma unroll
-                for (int k = 0; k < kPlanes; ++k) vote[k][tid] = plane[k];
+                for (int k = 0; k < P; ++k) vote[k][tid] = plane[k];
             }
         }
         ge &= live_mask(wi, a.d);
         a.voted[wi] = ge;
-        if constexpr (!COUNTS) vote[0][tid] = ge;
+        if constexpr (P == 0) vote[0][tid] = ge;
     }
     __syncthreads();
     if (full) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int word = r * 32 + (tid >> 3), shift = (tid & 7) * 4;
+            const int word = r * (kRowCoords / 32) + (tid >> 3), shift = (tid & 7) * 4;
             f32x4 v = xv[r];
-            if constexpr (COUNTS) {
+            if constexpr (P > 0) {
                 uint32_t counts = 0;
 #pragma unroll
-                for (int k = 0; k < kPlanes; ++k) counts += spread_nibble((vote[k][word] >> shift) & 0xFu) << k;
+                for (int k = 0; k < P; ++k) counts += spread_nibble((vote[k][word] >> shift) & 0xFu) << k;
                 if (a.sum_update) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c) v[c] = step_sum(v[c], a.delta, sum_at(counts, c, a.M));
@@ -335,22 +335,22 @@ __global__ __launch_bounds__(kBlock) void vote_apply_kernel(const VoteApplyArgs<
                     for (int c = 0; c < 4; ++c) v[c] = step(v[c], a.delta, (nib >> c) & 1u);
                 }
                 if (a.sums)
-                    st_stream(reinterpret_cast<uint32_t *>(a.sums + base) + tid + r * kBlock, sums_word(counts, a.M));
+                    st_stream(reinterpret_cast<uint32_t *>(a.sums + base) + r * BLOCK + tid, sums_word(counts, a.M));
             } else {
                 const uint32_t nib = vote[0][word] >> shift;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) v[c] = step(v[c], a.delta, (nib >> c) & 1u);
             }
-            st_stream(xq + r * kBlock, v);
+            st_quad<kThrough>(xw, (r * BLOCK + tid) * 16, v);
         }
         return;
     }
     // the last block: one coordinate per lane
-    for (int i = tid; base + i < a.d; i += kBlock) {
-        if constexpr (COUNTS) {
+    for (int i = tid; base + i < a.d; i += BLOCK) {
+        if constexpr (P > 0) {
             int count = 0;
 #pragma unroll
-            for (int k = 0; k < kPlanes; ++k) count += (int)((vote[k][i >> 5] >> (i & 31)) & 1u) << k;
+            for (int k = 0; k < P; ++k) count += (int)((vote[k][i >> 5] >> (i & 31)) & 1u) << k;
             const int S = a.M - 2 * count;
             a.x[base + i] = a.sum_update ? step_sum(a.x[base + i], a.delta, S) : step(a.x[base + i], a.delta, S < 0);
             if (a.sums) a.sums[base + i] = (int8_t)S;

@@ -1,0 +1,80 @@
+"""The streaming kernels at the edges of their tiles, of the runs of tiles that a compute die takes, and on both
+sides of the sizes at which a launch shape changes, bit-exact against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from test_gpu_parity import DEV, assert_same_floats, bits_np, dirty_bits, make_grad, make_momentum
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ss():
+    import paper_1802_04434_amd as lib
+    lib.load_library()
+    return lib
+
+
+def draw(seed, d, dtype, scale):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    t = torch.randn(d, device=DEV, generator=gen).mul_(scale)
+    t[::17] = 0.0
+    t[5::23] = -0.0
+    return t.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+
+
+# A wave's tile is 256 coordinates with momentum, 512 (fp32) or 1,024 (bf16) without; eight dies take 256 tiles each in
+# turn as long as there are so many, the rest goes in order.
+RUNS = [(1 << 19) + e for e in (-256, -1, 0, 255, 257)] + [(1 << 20) + e for e in (-1, 0, 513)] + [(1 << 21) + e for e in (-1, 1025)] + \
+       [255, 256, 511, 1025, 8 * 1024 + 3]
+
+
+@pytest.mark.parametrize("momentum", [True, False])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_pack_around_runs_of_tiles(ss, oracle, dtype, momentum):
+    rng = np.random.default_rng(3)
+    for d in RUNS:
+        g = make_grad(rng, d, dtype, scale=0.5)
+        m = make_momentum(rng, d) if momentum else None
+        m_dev = torch.from_numpy(m).to(DEV) if momentum else None
+        packed = dirty_bits(ss, d)
+        ss.signum_pack(g.to(DEV), m_dev, 0.9, packed)
+        want = oracle.signum_pack(synth.as_numpy(g), m, 0.9)
+        assert np.array_equal(bits_np(packed), want), d
+        if momentum:
+            assert_same_floats(m_dev, m, "m, d = %d" % d)
+
+
+# 2^28 bytes of gradient and momentum (12 and 10 a coordinate), then 2^25 coordinates
+@pytest.mark.parametrize("d,dtype", [((1 << 28) // 12, "f32"), ((1 << 28) // 12 + 1, "f32"), ((1 << 28) // 10 + 513, "bf16"),
+                                     ((1 << 25) - 3, "f32"), ((1 << 25) + 300, "f32"), ((1 << 25) + 255, "bf16")])
+def test_pack_on_both_sides_of_a_launch_shape(ss, oracle, d, dtype):
+    g, m_dev = draw(d, d, dtype, 0.5), draw(d + 1, d, "f32", 0.3)
+    m = synth.as_numpy(m_dev).copy()
+    packed = dirty_bits(ss, d)
+    ss.signum_pack(g, m_dev, 0.9, packed)
+    want = oracle.signum_pack(synth.as_numpy(g), m, 0.9)
+    assert np.array_equal(bits_np(packed), want)
+    assert_same_floats(m_dev, m, "m")
+
+
+# vote and update: a block's 2,048 (any number of workers: 4,096) coordinates, by fixed adders and by count planes
+@pytest.mark.parametrize("extra", [0, 1, 31, 2047, 4095])
+@pytest.mark.parametrize("M,flags", [(8, 0), (16, 0), (20, 0), (9, 2), (33, 2)])
+def test_vote_and_update_around_a_tile(ss, oracle, M, flags, extra):
+    d = (1 << 20) + extra
+    g = [draw(w, d, "bf16", 0.5) for w in range(M)]
+    x_dev = draw(99, d, "f32", 0.05)
+    x = synth.as_numpy(x_dev).copy()
+    voted, packed = dirty_bits(ss, d), [dirty_bits(ss, d) for _ in range(M)]
+    sums = torch.full((d,), 77, dtype=torch.int8, device=DEV) if flags else None
+    ss.signum_vote_step_ex(g, None, 0.9, 1e-4, x_dev, voted, packed, sums, flags)
+    want, want_packed, want_sums = oracle.signum_vote_step_ex([synth.as_numpy(t) for t in g], None, 0.9, 1e-4, x, flags)
+    assert np.array_equal(bits_np(voted), want)
+    assert all(np.array_equal(bits_np(packed[w]), want_packed[w]) for w in range(M))
+    assert_same_floats(x_dev, x, "x")
+    if flags:
+        assert np.array_equal(sums.cpu().numpy(), want_sums)
