@@ -103,29 +103,30 @@ inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = s
 // ------------------------------------------------------------------------
 // Launch shapes of the step kernel (see step_kernels.hpp for the reasoning).
 //   streaming shape, several workers and more data than the 256 MB memory-side cache holds: one or
-//     two workers at a time, and a reservation of LDS that no kernel touches, sized so that the
-//     wanted number of blocks fits in a compute unit's LDS
-//   latency shape, everything smaller: one-wave blocks that issue the loads of up to eight workers
-//     at once, no cap
-// The line between them, by graph replay over three sets of buffers (us, latency against streaming
-// shape): fp32 M = 7 1.1 M coordinates (92 MB) 19.1 / 22.8, 2.2 M 37.4 / 39.6, 4.4 M 72.2 / 72.1,
-// 12 M 194 / 184; M = 2 4.4 M 25.0 / 27.8; M = 16 1.1 M 42.4 / 47.6, 2.2 M (422 MB) 85 / 84; bf16 M = 8
-// 2.2 M 35.4 / 36.8; gradients only: fp32 M = 7 4.4 M (123 MB) 27.6 / 29.9, 12 M (336 MB) 72.9 / 72.0,
-// bf16 M = 8 4.4 M 19.2 / 22.9, 12 M (192 MB) 48.6 / 52.2.
-inline bool streams(int M, size_t d, size_t worker_bytes) { return d * (size_t)M * worker_bytes >= ((size_t)1 << 28); }
-constexpr int kLdsPerUnitKB = 160;   // what the reservations below assume; checked against the device
+//     a few workers at a time, and a reservation of LDS that no kernel touches, sized so that the
+//     wanted number of blocks fits in the 160 KB of a gfx950 compute unit
+//   latency shape, everything smaller: the loads of up to eight workers at once, no cap
+// The line between them, bytes of gradients and momentum (us, latency against streaming shape): with momentum fp32 1.1 M
+// M = 12 (158 MB) 29.9 / 29.2, 2.2 M M = 7 (185 MB) 36.4 / 34.6, 4.4 M M = 4 (211 MB) 41.8 / 40.3, 1.1 M M = 16 (211 MB) 39.6 / 37.0,
+// 4.4 M M = 5 (264 MB) 51.9 / 47.5, bf16 2.2 M M = 8 (176 MB) 35.0 / 35.3, 12 M M = 2 (240 MB) 55.1 / 52.1; without it the
+// streaming shapes pay from 2^28 bytes on.
+inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
+    return d * (size_t)M * worker_bytes >= (has_m ? (size_t)5 << 25 : (size_t)1 << 28);
+}
 
 // Given packed_out buffers, the step runs as two launches - pack_kernel over all workers, then vote
-// and update - from 2^20 coordinates and this many gradient elements on.  The one-pass kernel that
-// also writes the bits keeps 2M + 1 buffers open and stays at 6.1 TB/s; the two launches reach 6.4-6.8
-// but cost a second launch and tail (~2.5 us), which small and latency-bound steps do not earn back.
-// One pass -> two launches, us: fp32, M = 7: 0.7 M 12.2 -> 14.4, 1.1 M 22.9 -> 19.4, 4.4 M 70 -> 66,
-// 25.6 M 386 -> 358; M = 16: 1.1 M 48 -> 40, 25.6 M 871 -> 780; M = 2: 1.1 M 8.7 -> 8.9, 4.4 M 27.0 -> 25.8,
-// 25.6 M 138 -> 129; bf16, M = 8: 1.1 M 21.8 -> 19.8, 25.6 M 388 -> 341; M = 2: 4.4 M 22.8 -> 23.2, 25.6 M 120 -> 115.
-// Every step of a fixed number of workers that is large enough for a streaming shape is past this line, so those shapes
-// see packed_out with more than 22 workers only (d < 2^20), step_bf16_kernel never.
-inline bool split_pays(int M, size_t d) {
-    return M >= 2 && d >= ((size_t)1 << 20) && d * (size_t)M >= ((size_t)1 << (M >= 4 ? 23 : 24));
+// and update - from here on.  A one-pass kernel keeps 2M + 1 buffers open; the two launches stream three at a time, but
+// cost a second launch and tail (~2.5 us) and read the bits again.  One pass / two launches, us, bytes of gradients and
+// momentum: M = 2 fp32 8.8 M 45.1 / 48.7, 25.6 M 124.7 / 125.6, 60 M 287 / 290; M = 3 8.8 M 61.5 / 63.7, 25.6 M (920 MB)
+// 171.1 / 170.4, bf16 8.8 M 54.2 / 57.5, 138 M (4.2 GB) 802 / 787; M = 4 17.6 M (845 MB) 149.2 / 149.6, 25.6 M (1.2 GB) 217 / 214;
+// M = 5 8.8 M (528 MB) 94.0 / 94.3, 25.6 M (1.5 GB) 265 / 260; M = 7 2.2 M (185 MB) 35.4 / 35.4, 4.4 M (370 MB) 65.1 / 64.9, 6.6 M
+// 95.6 / 93.3; M = 9 1.1 M (119 MB) 23.1 / 24.0; M = 16 1.1 M (211 MB) 38.8 / 37.7; bf16 M = 8 4.4 M 65.5 / 62.1.
+// Without momentum: M = 2 fp32 8.8 M 23.7 / 27.9, 25.6 M 71.3 / 65.2, M = 8 25.6 M 177 / 162.  step_bf16_kernel, which writes no
+// bits, starts beyond this line.
+inline bool split_pays(int M, size_t d, bool has_m, size_t worker_bytes) {
+    if (M < 2 || d < ((size_t)1 << 20)) return false;
+    if (has_m) return M >= 3 && d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 8 ? 27 : M >= 6 ? 28 : 30));
+    return d * (size_t)M >= ((size_t)1 << (M >= 4 ? 23 : 25));
 }
 
 // A launch may have at most 2^32 - 1 threads, which a shape with one row of quads a lane reaches at 2^34
@@ -152,24 +153,16 @@ inline size_t scratch_slab(int M, size_t d, size_t bytes) {
     return std::min(room, ((d + parts - 1) / parts + 8191) / 8192 * 8192);
 }
 
-// One pass -> two launches with scratch, us: M = 5 fp32 2.2 M coordinates (132 MB of gradients and momentum)
-// 27.2 -> 27.2; M = 8 bf16 4.4 M (352 MB) 72 -> 65; M = 7 fp32 25.6 M 376 -> 357; M = 16 138 M 4,620 -> 4,170; M = 4 bf16
-// 8.0 M (320 MB) 64.7 -> 63.5; M = 3 fp32 8.0 M (288 MB) 60.4 -> 59.5; M = 2 fp32 12 M (288 MB) 65.8 -> 65.7,
-// 60 M 319 -> 294, bf16 17.6 M (352 MB) 77.6 -> 82.1, 60 M (1.2 GB) 263 -> 259.  Where a step takes less than ~40 us the
+// One pass / two launches with scratch, us: M = 3 fp32 138 M 904 / 908, bf16 791 / 787; M = 4 bf16 17.6 M (704 MB of gradients and
+// momentum) 128.6 / 128.7, 25.6 M (1.0 GB) 186.0 / 184.3, 138 M 1,011 / 989, fp32 25.6 M 214.2 / 214.3; M = 5 fp32 8.8 M (528 MB)
+// 93.4 / 94.3, 25.6 M 263.5 / 259.7; M = 7 4.4 M (370 MB) 64.0 / 64.9, 6.6 M (551 MB) 94.8 / 93.3, 25.6 M 362 / 350; M = 8 bf16 4.4 M
+// (352 MB) 63.6 / 62.1, 6.6 M 93.8 / 89.5; M = 12 fp32 2.2 M (317 MB) 57.4 / 53.7; M = 16 bf16 2.2 M (352 MB) 65.9 / 58.8, fp32 138 M
+// 4,520 / 4,060.  Where a step takes less than ~40 us the
 // first allocation on a stream (~20 us, once) is not worth what is gained.  A lender that asks the device for its free
 // memory at each call pays 6-9 us of host time for it, which a step behind queued work hides: alone, M = 8 bf16 6.5 M takes
 // 112 us where the same launches without the question take 104.
 inline bool scratch_pays(int M, size_t d, size_t worker_bytes) {
-    return d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 5 ? 28 : M >= 3 ? 29 : 30));
-}
-
-// LDS of one compute unit of the current device, in KB; 0 if the runtime will not say.  A pure
-// query: nothing is remembered between calls.
-inline int lds_per_unit_kb() {
-    int dev = 0, bytes = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&bytes, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess) return 0;
-    return bytes / 1024;
+    return M >= 4 && d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 5 ? 28 : 30));
 }
 
 // up to here sum_apply and copy keep four-wave blocks (see vote_apply_kernels.hpp)
@@ -179,9 +172,6 @@ constexpr size_t kCachedD = (size_t)1 << 21;
 // blocks per unit, roughly 24 KB of loads in flight, which an LDS reservation enforces) is 3-7 % faster
 // than four rows
 constexpr size_t kLargeD = (size_t)1 << 28;
-
-// the reservations are sized for a unit with kLdsPerUnitKB of LDS: on anything else, no cap
-inline bool caps_apply() { return lds_per_unit_kb() == kLdsPerUnitKB; }
 
 template <int NPTR>
 void fill_step_args(ss::StepArgs<NPTR> &a, int M, const void *const *g, float *const *m, uint32_t *const *packed,
@@ -204,24 +194,24 @@ void fill_step_args(ss::StepArgs<NPTR> &a, int M, const void *const *g, float *c
     a.d = d;
 }
 
-template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB, bool LOADS_FIRST, bool HAS_M, typename G>
+template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB, bool NEAR, int STORE, uint32_t CHUNK, bool HAS_M, typename G>
 int launch_step_shape(ss::StepArgs<NPTR> &a, size_t d, hipStream_t stream) {
     const Tiling t = make_tiling(d, R, true, BLOCK);
-    a.n_tiles = t.n_tiles;
-    a.words_total = t.words_total;
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    return launch(ss::step_kernel<MT, NPTR, BLOCK, BW, R, HOLD_KB, LOADS_FIRST, HAS_M, G>, grid, 0, stream, a, BLOCK);
+    a.n_tiles = (uint32_t)t.n_tiles;
+    a.words_total = t.words_total;
+    return launch(ss::step_kernel<MT, NPTR, BLOCK, BW, R, HOLD_KB, NEAR, STORE, CHUNK, HAS_M, G>, grid, 0, stream, a, BLOCK);
 }
 
-template <int MT, int NPTR, int BLOCK, int BW, int HOLD_KB>
+template <int MT, int NPTR, int BLOCK, int BW, int HOLD_KB, int STORE>
 int launch_octets(ss::StepArgs<NPTR> &a, size_t d, hipStream_t stream) {
     const Tiling t = make_tiling(d, 1, true, BLOCK, 2 * ss::kQuad);
-    a.n_tiles = t.n_tiles;
-    a.words_total = t.words_total;
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    return launch(ss::step_bf16_kernel<MT, NPTR, BLOCK, BW, HOLD_KB>, grid, 0, stream, a, BLOCK);
+    a.n_tiles = (uint32_t)t.n_tiles;
+    a.words_total = t.words_total;
+    return launch(ss::step_bf16_kernel<MT, NPTR, BLOCK, BW, HOLD_KB, STORE>, grid, 0, stream, a, BLOCK);
 }
 
 // what distinguishes the variants of the step (see ss_step_flags)
@@ -241,47 +231,49 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
     a.sum_update = (var.flags & SS_STEP_SUM_UPDATE) ? 1 : 0;
     a.sums = var.sums;
     constexpr bool kBf16 = std::is_same<G, ss::Bf16Grad>::value;
+    using ss::kStream;
+    using ss::kThrough;
     if constexpr (MT == 1) {
-        // a single worker is two or three streams whatever the shape: no cap; from 2^25 coordinates on
-        // one-wave blocks (138 M: 460 us against 500, without momentum 257 / 284, bf16 217 / 236; 60 M:
-        // 200 / 208, 112 / 122, 97 / 100; at 25.6 M 87 / 86, 51 / 51, 43 / 43)
-        if (d >= ((size_t)1 << 25)) return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, HAS_M, G>(a, d, stream);
-        return launch_step_shape<1, NPTR, 256, 1, 2, 0, false, HAS_M, G>(a, d, stream);
+        // One worker: one-wave blocks; from 2^24 coordinates on written through and with a cap.  us, as below 2^24 /
+        // capped / four waves of two rows: with momentum fp32 8.8 M 28.6 / 29.2 / 29.1, 17.6 M 55.8 / 54.7 / 57.2, 25.6 M 79.9 /
+        // 77.8 / 82.2, 138 M 433 / 410 / 477, bf16 25.6 M 72.1 / 70.2 / 73.2; without fp32 17.6 M 33.0 / 33.1 / 33.8, 25.6 M
+        // 46.8 / 46.8 / 48.3, 60 M 108 / 106 / 116, bf16 138 M 206 / 201 / 226
+        if (d >= ((size_t)1 << 24)) return launch_step_shape<1, NPTR, 64, 1, 1, HAS_M ? 10 : 6, false, kThrough, 0, HAS_M, G>(a, d, stream);
+        return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kStream, 8, HAS_M, G>(a, d, stream);
     } else {
-        // Streaming shapes.  Each keeps roughly 16-24 KB of loads in flight per compute unit (see
-        // step_kernels.hpp) and was picked by measurement among block sizes 64-1024, 1-8 workers per
-        // stage, 1-8 rows and 1-5 blocks per unit, with the workloads' own buffer placement.  The
-        // reservations only mean what they should on a part with the LDS size they were sized for.
-        if (streams(M, d, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0)) && lds_per_unit_kb() == kLdsPerUnitKB) {
-            if constexpr (!HAS_M) {
-                // gradients only.  bf16 (step_bf16_kernel): the workers' loads out together, eight at most, from
-                // one-wave blocks, fewer of them per unit the more loads each has out.  Against two workers a
-                // stage in quads, us: 25.6 M M = 3 57.1 / 59.2, 7 88.3 / 94.2, 8 98.1 / 102.0, 12 129 / 136, 16 160 / 166;
-                // 138 M M = 2 (390 M) 713 / 776, 5 386 / 403, 8 529 / 531, 12 696 / 733, 16 872 / 925
-                if constexpr (kBf16 && MT > 0 && MT <= 3) return launch_octets<MT, NPTR, 64, 4, 10>(a, d, stream);
-                else if constexpr (kBf16 && MT > 0 && MT <= 6) return launch_octets<MT, NPTR, 64, 8, 16>(a, d, stream);
-                else if constexpr (kBf16) return launch_octets<MT, NPTR, 64, 8, MT == 16 ? 24 : 20>(a, d, stream);
-                // fp32: four loads per lane make up for the missing momentum stream
-                else return launch_step_shape<MT, NPTR, 256, 2, 2, 64, true, false, G>(a, d, stream);
-            } else if constexpr (!kBf16) {
-                // fp32: one 512-thread block per unit, one worker and one row at a time
-                return launch_step_shape<MT, NPTR, 512, 1, 1, 96, true, true, G>(a, d, stream);
+        if (streams(M, d, HAS_M, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0))) {
+            // Streaming shapes: one-wave blocks of one row, written through, tiles in order.
+            if constexpr (HAS_M) {
+                // One worker a stage and 11 to 14 waves a unit, the fewer the more workers.  KB held back and us, against the
+                // shapes of one to four larger blocks a unit that were used before: fp32 13: 12 M M = 3 82.5 / 87.2, 25.6 M M = 2
+                // 122.5 / 134, M = 4 215.6 / 232, 138 M M = 2 647 / 733, M = 4 1,151 / 1,250; 14 (13): M = 5 261.7 (261.8) / 277,
+                // M = 9 454.7 (456.9) / 479, M = 16 805 (830) / 840; bf16 11: M = 3 147.2 / 165.6, 138 M M = 2 565 / 674, M = 4 993 / 1,123;
+                // 13 (11): M = 7 307.0 (308.9) / 314.9, M = 16 683 (708) / 696, 60 M M = 8 822 (830) / 860.  Runs of tiles a die: 5-10 %
+                // slower in each.
+                constexpr int kHold = (MT > 0 && MT < 5 ? 13 : 14) - (kBf16 ? (MT > 0 && MT < 5 ? 2 : 1) : 0);
+                return launch_step_shape<MT, NPTR, 64, 1, 1, kHold, false, kThrough, 0, true, G>(a, d, stream);
+            } else if constexpr (kBf16) {
+                // step_bf16_kernel: the workers' loads out together, eight at most, fewer blocks per unit the more loads
+                // each has out.  us, 25.6 M unless said: M = 2 138 M 248 / 296 (four-wave blocks of two rows before), M = 3 60 M 126.8 /
+                // 145.9, M = 4 63.2 / 65.0, 7 86.8, 8 96.3, 12 128, 16 160.7; written through or not M = 4 138 M 337 / 340, M = 8
+                // 60 M 224.8 / 223.2, M = 16 161.5 / 163.2
+                if constexpr (MT > 0 && MT <= 6) return launch_octets<MT, NPTR, 64, 8, MT == 2 ? 10 : MT == 3 ? 13 : 16, kThrough>(a, d, stream);
+                else return launch_octets<MT, NPTR, 64, 8, MT == 16 ? 24 : 20, MT == 16 ? kThrough : kStream>(a, d, stream);
             } else {
-                // bf16 gradients (a wave's gradient load is half as long): from four workers on, four
-                // 128-thread blocks per unit that take two workers at a time; below that, two
-                // 256-thread blocks with two rows, the loads left to the compiler's own interleaving
-                if (M >= 4) return launch_step_shape<MT, NPTR, 128, 2, 1, 40, true, true, G>(a, d, stream);
-                return launch_step_shape<MT, NPTR, 256, 1, 2, 64, false, true, G>(a, d, stream);
+                // fp32: four workers a stage make up for the missing momentum stream.  us, against two four-wave blocks a unit before:
+                // 25.6 M M = 3 76.4 / 83.1, 4 91.8 / 94.6, 7 135.4 / 145.5, 8 153.8 / 160.1, 9 169.0 / 178.3, 16 279.8 / 288.5, 138 M
+                // M = 2 319 / 345, M = 7 734 / 806
+                return launch_step_shape<MT, NPTR, 64, 4, 1, MT == 2 ? 11 : 13, false, kThrough, 0, false, G>(a, d, stream);
             }
         }
-        // Latency shape.  Four waves a block, two or four rows where a worker or three leave room for them
-        // and the compiler's order of the loads (what this was before): d = 272,474 fp32 M = 7 6.2 us
-        // against 5.5, M = 3 3.7 / 2.8, M = 16 13.5 / 11.0, M = 15 13.6 / 10.6 (its last seven workers are
-        // one stage now); 10,007 M = 3 2.8 / 2.2.  Sixteen workers' gradients alone keep four waves
-        // (272,474: 5.6 against 5.8; 700,001: 9.2 against 9.6).
+        // Latency shape: the loads of up to eight workers go out together, nothing is held back, buffers are addressed
+        // without arithmetic, a die takes runs of 64 (from 2^20 coordinates on 256) tiles.  us, against descriptors / no runs: 10,007 M = 16
+        // 3.2 / 3.4 / 3.2, 272,474 M = 7 5.8 / 6.1 / 6.7, M = 16 11.2 / 11.4 / 15.4, M = 9 7.2 / 7.2 / 8.3, 700,001 M = 7 12.4 / 12.6 /
+        // 13.3, 1.1 M M = 7 (runs of 256) 18.4 / 18.6 / 19.6, M = 16 38.8 / 38.8 / 43.7, 4.4 M M = 4 - / 42.1 / 44.3, gradients alone
+        // 272,474 M = 16 6.0 / 6.0 / 6.5, 8.8 M M = 4 34.3 / 34.2 / 35.6
         constexpr int BW = MT > 0 && MT < 8 ? MT : 8;
-        constexpr int B = !HAS_M && MT == 16 ? 256 : 64;
-        return launch_step_shape<MT, NPTR, B, BW, 1, 0, true, HAS_M, G>(a, d, stream);
+        if (d < ((size_t)1 << 20)) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, 6, HAS_M, G>(a, d, stream);
+        return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, 8, HAS_M, G>(a, d, stream);
     }
 }
 
@@ -328,7 +320,7 @@ int launch_pack_momentum(ss::PackArgs<NPTR> &a, int n, hipStream_t stream) {
     constexpr size_t kBytes = sizeof(typename G::elem) + 2 * sizeof(float);
     if (a.d * (size_t)n * kBytes < ((size_t)1 << 28))
         return launch_pack_shape(ss::pack_kernel<NPTR, 64, 1, 0, ss::kStream, 8, true, G>, a, n, 64, 1, 4, stream);
-    if (a.d < ((size_t)1 << 25) || !caps_apply())
+    if (a.d < ((size_t)1 << 25))
         return launch_pack_shape(ss::pack_kernel<NPTR, 64, 1, 0, ss::kThrough, 9, true, G>, a, n, 64, 1, 4, stream);
     return launch_pack_shape(ss::pack_kernel<NPTR, 64, 1, 7, ss::kThrough, 0, true, G>, a, n, 64, 1, 4, stream);
 }
@@ -439,7 +431,7 @@ int launch_vote_fixed(const uint32_t *const *packed, uint32_t *voted, size_t d, 
     a.d = d;
     a.n_vec = ss_packed_bytes(d) / 16;
     constexpr int kHold = M >= 8 ? 20 : 8;
-    const bool waves = M >= 4 && caps_apply() && d >= (M >= 12 ? kLargeD / 2 : kLargeD);
+    const bool waves = M >= 4 && d >= (M >= 12 ? kLargeD / 2 : kLargeD);
     const size_t block = waves ? kVoteWave : ss::kBlock;
     const size_t grid = (a.n_vec + block - 1) / block;
     if (grid > kMaxGrid) return SS_ERR_ARG;
@@ -487,7 +479,7 @@ template <bool HAS_M, bool VOTE, typename G>
 int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     constexpr bool kBf16 = std::is_same<G, ss::Bf16Grad>::value;
     if constexpr (VOTE) {
-        if ((a.M >= 2 && streams(a.M, d, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0)) && caps_apply()) || d >= kOneRowMaxD) {
+        if ((a.M >= 2 && streams(a.M, d, HAS_M, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0))) || d >= kOneRowMaxD) {
             if constexpr (!HAS_M) {
                 return launch_ternary_shape<64, 8, 2, 10, true, false, true, G>(a, d, stream);
             } else {
@@ -622,7 +614,7 @@ int ss_sign_apply(float *x, const uint32_t *bits, float delta, size_t d, void *h
     if (!aligned16(x) || !aligned16(bits)) return SS_ERR_ALIGN;
     Span spans[2] = {span(x, d * sizeof(float), true), span(bits, ss_packed_words(d) * 4, false)};
     if (written_spans_overlap(spans, 2)) return SS_ERR_ARG;
-    const bool large = d >= kLargeD && caps_apply();   // then one row per block, six blocks per unit
+    const bool large = d >= kLargeD;   // then one row per block, six blocks per unit
     const Tiling t = make_tiling(d, large ? 1 : 4, false);
     ss::ApplyArgs a;
     a.x = x;
@@ -688,7 +680,7 @@ static int vote_step_impl(const void *const *g, ss_dtype gdt, float *const *m, i
     // of the vector at a time as it has room for; otherwise one pass.  Same results, bit for bit.
     const size_t slab = scratch && !packed_out ? scratch_slab(M, d, scratch_bytes) : 0;
     const bool lent = slab >= kScratchMinSlab;
-    const bool two = lent || (packed_out && split_pays(M, d));
+    const bool two = lent || (packed_out && split_pays(M, d, m != nullptr, grad_bytes(gdt) + (m ? 2 * sizeof(float) : 0)));
     const size_t part = lent ? slab : std::min(d, kOneRowMaxD);
     if (!lent && part == d)
         return step_part(two, g, gdt, m, M, beta, delta, x, voted, packed_out, StepVariant{flags, sums_out}, d, stream);
@@ -770,7 +762,7 @@ int ss_vote_sum(const uint32_t *const *packed, int M, int8_t *sums, size_t d, vo
     // beyond cache-resident sizes two blocks per unit instead of four (the tile in LDS already
     // limits them to four): +3 % at d = 138 M, +9 % at 1.5 G
     constexpr int kVoteSumHoldKB = 24;
-    const bool capped = d >= ((size_t)1 << 27) && caps_apply();
+    const bool capped = d >= ((size_t)1 << 27);
     switch (count_planes(M)) {
         case 1: return capped ? launch(ss::vote_sum_kernel<1, kVoteSumHoldKB>, grid, 0, stream, a)
                               : launch(ss::vote_sum_kernel<1, 0>, grid, 0, stream, a);
@@ -833,7 +825,7 @@ int ss_welford_update(const void *g, ss_dtype gdt, float *mean, float *m2, uint6
     // the cap of welford_update_kernel, us with against without: fp32 4.4 M 15.7 / 15.4, 8.8 M 29.1 / 29.2, 12 M 38.6 / 38.4,
     // 16 M 50.1 / 50.7, 20 M 62.9 / 63.2, 25.6 M 80.1 / 81.4, 60 M 182 / 190; bf16 4.4 M 13.7 / 13.5, 12 M 34.5 / 34.7,
     // 17.6 M 49.7 / 50.7, 60 M 164 / 170
-    if (d >= ((size_t)1 << 24) && caps_apply()) {
+    if (d >= ((size_t)1 << 24)) {
         if (gdt == SS_F32) return launch(ss::welford_update_kernel<8, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
         return launch(ss::welford_update_kernel<8, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
     }
@@ -990,7 +982,7 @@ int ss_quorum_vote(const uint32_t *const *neg, const uint32_t *const *zero, int 
         return launch(ss::quorum_word_kernel<7>, blocks, 0, stream, a, 64);
     }
     // beyond cache-resident sizes two blocks per unit instead of eight: +2-4 % at d = 138 M, +9 % at 1.5 G
-    const bool capped = d >= ((size_t)1 << 27) && caps_apply();
+    const bool capped = d >= ((size_t)1 << 27);
     switch (count_planes(M)) {
         case 1: return capped ? launch(ss::quorum_vote_kernel<1, kVoteHoldKB>, grid, 0, stream, a)
                               : launch(ss::quorum_vote_kernel<1, 0>, grid, 0, stream, a);
@@ -1017,7 +1009,7 @@ int ss_ternary_apply(float *x, const uint32_t *neg, const uint32_t *zero, float 
     Span spans[3] = {span(x, d * sizeof(float), true), span(neg, ss_packed_words(d) * 4, false),
                      span(zero, ss_packed_words(d) * 4, false)};
     if (written_spans_overlap(spans, 3)) return SS_ERR_ARG;
-    const bool large = d >= kLargeD && caps_apply();   // then two rows per block, four blocks per unit
+    const bool large = d >= kLargeD;   // then two rows per block, four blocks per unit
     const Tiling t = make_tiling(d, large ? 2 : 4, false);
     ss::TernaryApplyArgs a;
     a.x = x;

@@ -61,6 +61,22 @@ __device__ __forceinline__ void st_quad(Window w, uint32_t off, f32x4 v) {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), w, (int)off, 0, STORE);
 }
 
+// A tile's quad at byte offset `off`, through a descriptor, or - NEAR, for buffers of less than 4 GiB - at a 32-bit
+// offset from the buffer's own base, which costs the wave no arithmetic per buffer: launches of a few
+// microseconds are as long as their waves' first instructions take.
+template <bool NEAR>
+__device__ __forceinline__ f32x4 ld_tile(const void *base, size_t tile, uint32_t tile_bytes, uint32_t off) {
+    if constexpr (NEAR)
+        return ld_stream(reinterpret_cast<const f32x4 *>(static_cast<const char *>(base) + (uint32_t)((uint32_t)tile * tile_bytes + off)));
+    else return ld_quad(window(base, tile * tile_bytes, tile_bytes), off);
+}
+template <bool NEAR, int STORE>
+__device__ __forceinline__ void st_tile(float *base, size_t tile, uint32_t tile_bytes, uint32_t off, f32x4 v) {
+    if constexpr (NEAR)
+        st_stream(reinterpret_cast<f32x4 *>(reinterpret_cast<char *>(base) + (uint32_t)((uint32_t)tile * tile_bytes + off)), v);
+    else st_quad<STORE>(window(base, tile * tile_bytes, tile_bytes), off, v);
+}
+
 // bf16 -> fp32 is exact: the bf16 pattern is the upper half of the fp32
 __device__ __forceinline__ float widen_bf16(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
@@ -70,6 +86,10 @@ struct F32Grad {
         return ld_stream(reinterpret_cast<const f32x4 *>(base) + quad);
     }
     static __device__ __forceinline__ f32x4 load4(Window w, uint32_t quad) { return ld_quad(w, quad * 16); }
+    template <bool NEAR>
+    static __device__ __forceinline__ f32x4 load_tile(const void *base, size_t tile, uint32_t tile_bytes, uint32_t quad) {
+        return ld_tile<NEAR>(base, tile, tile_bytes, quad * 16);
+    }
     static __device__ __forceinline__ float load1(const void *base, size_t i) {
         return reinterpret_cast<const float *>(base)[i];
     }
@@ -87,6 +107,12 @@ struct Bf16Grad {
     }
     static __device__ __forceinline__ f32x4 load4(Window w, uint32_t quad) {
         return widen(__builtin_bit_cast(u16x4, __builtin_amdgcn_raw_buffer_load_b64(w, (int)(quad * 8), 0, kStream)));
+    }
+    template <bool NEAR>
+    static __device__ __forceinline__ f32x4 load_tile(const void *base, size_t tile, uint32_t tile_bytes, uint32_t quad) {
+        if constexpr (NEAR)
+            return widen(ld_stream(reinterpret_cast<const u16x4 *>(static_cast<const char *>(base) + (uint32_t)((uint32_t)tile * tile_bytes + quad * 8))));
+        else return load4(window(base, tile * tile_bytes, tile_bytes), quad);
     }
     static __device__ __forceinline__ float load1(const void *base, size_t i) {
         return widen_bf16(reinterpret_cast<const uint16_t *>(base)[i]);
@@ -167,9 +193,9 @@ __device__ __forceinline__ void reserve_lds(bool never, uint32_t *sink) {
 template <uint32_t CHUNK>
 __device__ __forceinline__ uint32_t die_tile(uint32_t block, uint32_t n_tiles) {
     if constexpr (CHUNK == 0) return block;
-    if (block >= (n_tiles >> (CHUNK + 3) << (CHUNK + 3))) return block;
     const uint32_t turn = block >> 3;
-    return ((turn >> CHUNK << 3 | (block & 7u)) << CHUNK) | (turn & ((1u << CHUNK) - 1u));
+    const uint32_t tile = ((turn >> CHUNK << 3 | (block & 7u)) << CHUNK) | (turn & ((1u << CHUNK) - 1u));
+    return block < (n_tiles >> (CHUNK + 3) << (CHUNK + 3)) ? tile : block;
 }
 
 // kernel argument block: M device pointers by value (no table in memory)

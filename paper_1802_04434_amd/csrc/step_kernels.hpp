@@ -19,16 +19,14 @@
 //    unit (4-6 MB over the chip, the bandwidth-delay product) saturate HBM; more
 //    only lengthens the memory system's queues and mixes more DRAM rows into
 //    them, and the rate drops by 3-10 % - the more streams (workers) the worse.
-//    For large d the kernel therefore takes one or two workers per stage (bf16
-//    gradients alone, which are short: up to eight, in step_bf16_kernel) and
-//    the block reserves LDS that it never uses (HOLD_KB), which caps the blocks
-//    that share a compute unit: e.g. 96 KB leaves room for one 512-thread block
-//    in a unit's 160 KB, 64 KB for two 256-thread blocks, 40 KB for four of 128.
-//    The host picks the shape (launch_step_m in api.hip).
+//    For large d the kernel therefore takes one worker per stage (gradients alone, which are
+//    short: up to eight) from one-wave blocks and the block reserves LDS that it never
+//    uses (HOLD_KB), which caps the blocks that share a compute unit: 13 KB leave room
+//    for eleven waves in a unit's 160 KB.  The host picks the shape (launch_step_m in api.hip).
 //  * A tile costs (number of stages) x (one memory latency); the x load goes out
 //    with the first stage's loads and the x store overlaps the next tile.
 //    Small d is latency bound instead: there the loads of up to eight workers
-//    go out together from one-wave blocks, and nothing is held back.
+//    go out together, and nothing is held back.
 #pragma once
 #include "common.hpp"
 
@@ -45,8 +43,8 @@ struct StepArgs {
     int warmup;          // Theorem 3 warm-up: signs come from g while m is still updated
     int sum_update;      // Section 4 "(good)": x <- x - delta * (sum of signs) instead of its sign
     int8_t *sums;        // may be NULL: per-coordinate sum of signs
+    uint32_t n_tiles;    // blocks on the vector path
     size_t d;            // coordinates
-    size_t n_tiles;      // blocks on the vector path (R rows of kRowCoords coordinates each)
     size_t words_total;  // words of a packed buffer including zero padding
 };
 
@@ -82,23 +80,22 @@ __device__ __forceinline__ int sum_at(uint32_t counts, int k, int M) {
     return M - 2 * (int)((counts >> (8 * k)) & 0xFFu);
 }
 
-// One stage of the vector path: NW consecutive workers starting at w0, R rows.  With
-// LOADS_FIRST every load of the stage is issued before anything waits for one of them;
-// without it the compiler interleaves (for two rows it starts the second row's loads
-// when the first row's momentum has arrived, which keeps fewer bytes in flight).
-template <int NW, int R, int BLOCK, bool LOADS_FIRST, bool HAS_M, typename G, int NPTR>
-__device__ __forceinline__ void step_stage(const StepArgs<NPTR> &a, int w0, const size_t (&q)[R],
-                                           uint32_t (&counts)[R], int lane) {
+// One stage of the vector path: NW consecutive workers starting at w0, the R rows of a tile.
+// Every load of the stage is issued before anything waits for one of them.
+template <int NW, int R, int BLOCK, bool NEAR, int STORE, bool HAS_M, typename G, int NPTR>
+__device__ __forceinline__ void step_stage(const StepArgs<NPTR> &a, int w0, size_t tile, uint32_t tid, uint32_t (&counts)[R]) {
+    constexpr uint32_t kCoords = R * BLOCK * kQuad;
+    constexpr uint32_t kGrad = kCoords * sizeof(typename G::elem), kFloat = kCoords * sizeof(float);
     f32x4 gv[R][NW], mv[R][NW];
 #pragma unroll
     for (int j = 0; j < NW; ++j) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            gv[r][j] = G::load4(a.p.g[w0 + j], q[r]);
-            if (HAS_M) mv[r][j] = ld_stream(reinterpret_cast<const f32x4 *>(a.p.m[w0 + j]) + q[r]);
+            gv[r][j] = G::template load_tile<NEAR>(a.p.g[w0 + j], tile, kGrad, r * BLOCK + tid);
+            if (HAS_M) mv[r][j] = ld_tile<NEAR>(a.p.m[w0 + j], tile, kFloat, (r * BLOCK + tid) * 16);
         }
     }
-    if (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < NW; ++j) {
 #pragma unroll
@@ -110,28 +107,27 @@ __device__ __forceinline__ void step_stage(const StepArgs<NPTR> &a, int w0, cons
                 v.y = momentum(a.beta, a.omb, m0.y, v.y);
                 v.z = momentum(a.beta, a.omb, m0.z, v.z);
                 v.w = momentum(a.beta, a.omb, m0.w, v.w);
-                st_stream(reinterpret_cast<f32x4 *>(a.p.m[w0 + j]) + q[r], v);
+                st_tile<NEAR, STORE>(a.p.m[w0 + j], tile, kFloat, (r * BLOCK + tid) * 16, v);
             }
             // Algorithm 2 votes with sign(m); a warm-up iteration with sign(g)
             const uint32_t nib = neg_nibble((HAS_M && a.warmup) ? gv[r][j] : v);
             counts[r] += spread_nibble(nib);
             if (a.write_packed) {
-                const uint32_t word = combine8(nib, lane);
-                if ((lane & 7) == 0) a.p.packed[w0 + j][q[r] >> 3] = word;
+                const uint32_t word = combine8(nib, tid & 63);
+                if ((tid & 7) == 0) a.p.packed[w0 + j][tile * (kCoords / 32) + ((r * BLOCK + tid) >> 3)] = word;
             }
         }
     }
-    if (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // the n <= NMAX workers that the full stages leave over, as one stage of exactly that size
-template <int NMAX, int R, int BLOCK, bool LOADS_FIRST, bool HAS_M, typename G, int NPTR>
-__device__ __forceinline__ void step_rest(const StepArgs<NPTR> &a, int w0, int n, const size_t (&q)[R],
-                                          uint32_t (&counts)[R], int lane) {
+template <int NMAX, int R, int BLOCK, bool NEAR, int STORE, bool HAS_M, typename G, int NPTR>
+__device__ __forceinline__ void step_rest(const StepArgs<NPTR> &a, int w0, int n, size_t tile, uint32_t tid, uint32_t (&counts)[R]) {
     if (n == NMAX) {
-        step_stage<NMAX, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, q, counts, lane);
+        step_stage<NMAX, R, BLOCK, NEAR, STORE, HAS_M, G>(a, w0, tile, tid, counts);
     } else if constexpr (NMAX > 1) {
-        step_rest<NMAX - 1, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, n, q, counts, lane);
+        step_rest<NMAX - 1, R, BLOCK, NEAR, STORE, HAS_M, G>(a, w0, n, tile, tid, counts);
     }
 }
 
@@ -180,31 +176,32 @@ __device__ __forceinline__ void step_tail(const StepArgs<NPTR> &a, int M, size_t
 // R      : rows per block
 // HOLD_KB: kilobytes of LDS the block reserves and never uses, which caps how
 //          many blocks share a compute unit (0: no cap)
-template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB, bool LOADS_FIRST, bool HAS_M, typename G>
+// NEAR   : buffers of less than 4 GiB, addressed without arithmetic (ld_tile);  STORE: policy of the stores of m
+//          and x otherwise;  CHUNK: log2 of the tiles that a die takes at a time (die_tile)
+template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB, bool NEAR, int STORE, uint32_t CHUNK, bool HAS_M, typename G>
 __global__ __launch_bounds__(BLOCK) void step_kernel(const StepArgs<NPTR> a) {
-    const int tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x;
     const int lane = tid & 63;
     const int M = MT > 0 ? MT : a.M;
     const int T = M / 2 + 1;
-    const size_t tile = blockIdx.x;
+    constexpr uint32_t kCoords = R * BLOCK * kQuad;
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0 /* the host rejects such a d */, a.p.packed[0]);
 
-    if (tile < a.n_tiles) {
-        size_t q[R];
+    if (blockIdx.x < a.n_tiles) {
+        const size_t tile = die_tile<CHUNK>(blockIdx.x, a.n_tiles);
         uint32_t counts[R];
         f32x4 xv[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            q[r] = (tile * R + r) * BLOCK + tid;
             counts[r] = 0;
-            xv[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + q[r]);
+            xv[r] = ld_tile<NEAR>(a.x, tile, kCoords * sizeof(float), (r * BLOCK + tid) * 16);
         }
         int w0 = 0;
-        for (; w0 + BW <= M; w0 += BW) step_stage<BW, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, q, counts, lane);
+        for (; w0 + BW <= M; w0 += BW) step_stage<BW, R, BLOCK, NEAR, STORE, HAS_M, G>(a, w0, tile, tid, counts);
         if constexpr (MT > 0) {
-            if constexpr (MT % BW != 0) step_stage<MT % BW, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, q, counts, lane);
+            if constexpr (MT % BW != 0) step_stage<MT % BW, R, BLOCK, NEAR, STORE, HAS_M, G>(a, w0, tile, tid, counts);
         } else if constexpr (BW > 1) {
-            step_rest<BW - 1, R, BLOCK, LOADS_FIRST, HAS_M, G>(a, w0, M - w0, q, counts, lane);
+            step_rest<BW - 1, R, BLOCK, NEAR, STORE, HAS_M, G>(a, w0, M - w0, tile, tid, counts);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -221,15 +218,15 @@ __global__ __launch_bounds__(BLOCK) void step_kernel(const StepArgs<NPTR> a) {
                 v.z = step(v.z, a.delta, nib & 4u);
                 v.w = step(v.w, a.delta, nib & 8u);
             }
-            st_stream(reinterpret_cast<f32x4 *>(a.x) + q[r], v);
-            if (a.sums) reinterpret_cast<uint32_t *>(a.sums)[q[r]] = sums_word(counts[r], M);
+            st_tile<NEAR, STORE>(a.x, tile, kCoords * sizeof(float), (r * BLOCK + tid) * 16, v);
+            if (a.sums) reinterpret_cast<uint32_t *>(a.sums)[tile * (kCoords / 4) + r * BLOCK + tid] = sums_word(counts[r], M);
             const uint32_t word = combine8(nib, lane);
-            if ((lane & 7) == 0) a.voted[q[r] >> 3] = word;
+            if ((lane & 7) == 0) a.voted[tile * (kCoords / 32) + ((r * BLOCK + tid) >> 3)] = word;
         }
         return;
     }
 
-    step_tail<HAS_M, G>(a, M, a.n_tiles * (size_t)(R * BLOCK * kQuad) + (tile - a.n_tiles) * BLOCK + tid, lane);
+    step_tail<HAS_M, G>(a, M, a.n_tiles * (size_t)kCoords + (size_t)(blockIdx.x - a.n_tiles) * BLOCK + tid, lane);
 }
 
 // The whole step for bf16 gradients without momentum.  The quad geometry would load 64 bits of gradient a
@@ -262,21 +259,22 @@ __device__ __forceinline__ void octet_rest(const StepArgs<NPTR> &a, int w0, int 
 }
 
 // BW, HOLD_KB as for step_kernel; a tile is one row of BLOCK octets
-template <int MT, int NPTR, int BLOCK, int BW, int HOLD_KB>
+template <int MT, int NPTR, int BLOCK, int BW, int HOLD_KB, int STORE>
 __global__ __launch_bounds__(BLOCK) void step_bf16_kernel(const StepArgs<NPTR> a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.p.packed[0]);
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
+    const uint32_t tid = threadIdx.x;
+    const uint32_t lane = tid & 63;
     const int M = MT > 0 ? MT : a.M;
     const int T = M / 2 + 1;
-    const size_t tile = blockIdx.x;
-    if (tile < a.n_tiles) {
-        const size_t o = tile * BLOCK + tid;
-        f32x4 *const xq = reinterpret_cast<f32x4 *>(a.x) + 2 * (o - lane) + lane;    // quads xq[0] and xq[64]
+    constexpr uint32_t kCoords = BLOCK * 2 * kQuad;
+    if (blockIdx.x < a.n_tiles) {
+        const size_t o = blockIdx.x * (size_t)BLOCK + tid;
+        const Window xw = window(a.x, blockIdx.x * (size_t)(kCoords * sizeof(float)), kCoords * sizeof(float));
+        const uint32_t xo = (2 * (tid - lane) + lane) * 16;    // this lane's quads lie here and a kilobyte further
         uint32_t lo = 0, hi = 0;
         f32x4 xv[2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) xv[h] = ld_stream(xq + 64 * h);
+        for (int h = 0; h < 2; ++h) xv[h] = ld_quad(xw, xo + 1024 * h);
         int w0 = 0;
         for (; w0 + BW <= M; w0 += BW) octet_stage<BW>(a, w0, o, lo, hi);
         if constexpr (MT > 0) {
@@ -303,11 +301,11 @@ __global__ __launch_bounds__(BLOCK) void step_bf16_kernel(const StepArgs<NPTR> a
 #pragma unroll
                 for (int c = 0; c < 4; ++c) v[c] = step(v[c], a.delta, (nib >> c) & 1u);
             }
-            st_stream(xq + 64 * h, v);
+            st_quad<STORE>(xw, xo + 1024 * h, v);
         }
         return;
     }
-    step_tail<false, Bf16Grad>(a, M, a.n_tiles * (size_t)(BLOCK * 2 * kQuad) + (tile - a.n_tiles) * BLOCK + tid, lane);
+    step_tail<false, Bf16Grad>(a, M, a.n_tiles * (size_t)kCoords + (size_t)(blockIdx.x - a.n_tiles) * BLOCK + tid, lane);
 }
 
 // ---------------------------------------------------------------- pack ----

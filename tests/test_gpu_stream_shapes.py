@@ -78,3 +78,48 @@ def test_vote_and_update_around_a_tile(ss, oracle, M, flags, extra):
     assert_same_floats(x_dev, x, "x")
     if flags:
         assert np.array_equal(sums.cpu().numpy(), want_sums)
+
+
+# One pass.  Runs of 64 tiles of 256 coordinates a die below 2^20 coordinates, of 256 above; the streaming shapes begin at
+# 5 x 2^25 bytes of gradients and momentum (2^28 without momentum), one worker's at 2^24 coordinates.
+STEPS = [((1 << 17) - 1, 7, "f32", True), ((1 << 17) + 77, 16, "bf16", True), ((1 << 17) + 255, 1, "f32", True),
+         ((1 << 18) + 256, 9, "f32", True), ((1 << 20) - 1, 3, "bf16", False), ((1 << 20) + 300, 6, "f32", False),
+         ((5 << 25) // 84 - 1, 7, "f32", True), ((5 << 25) // 84 + 1, 7, "f32", True), ((5 << 25) // 24 + 255, 2, "f32", True),
+         ((5 << 25) // 40 + 3, 4, "bf16", True), ((5 << 25) // 90 + 257, 9, "bf16", True), ((1 << 28) // 28 + 511, 7, "f32", False),
+         ((1 << 28) // 8 + 300, 2, "f32", False), ((1 << 28) // 4 + 513, 2, "bf16", False), ((1 << 28) // 6 + 1, 3, "bf16", False),
+         ((1 << 24) - 1, 1, "bf16", True), ((1 << 24) + 1, 1, "f32", True), ((1 << 24) + 257, 1, "bf16", False)]
+
+
+@pytest.mark.parametrize("d,M,dtype,momentum", STEPS)
+def test_one_pass_around_runs_and_rules(ss, oracle, d, M, dtype, momentum):
+    g = [draw(d + w, d, dtype, 0.5) for w in range(M)]
+    m_dev = [draw(d - w, d, "f32", 0.3) for w in range(M)] if momentum else None
+    x_dev = draw(7, d, "f32", 0.05)
+    m, x = [synth.as_numpy(t).copy() for t in m_dev] if momentum else None, synth.as_numpy(x_dev).copy()
+    voted = dirty_bits(ss, d)
+    ss.signum_vote_step(g, m_dev, 0.9, 1e-4, x_dev, voted)
+    want = oracle.signum_vote_step([synth.as_numpy(t) for t in g], m, 0.9, 1e-4, x, threads=16)
+    assert np.array_equal(bits_np(voted), want)
+    for w in range(M if momentum else 0):
+        assert_same_floats(m_dev[w], m[w], "m[%d]" % w)
+    assert_same_floats(x_dev, x, "x")
+
+
+# with packed_out, on both sides of the line from which two launches pay: 2^30 bytes for three workers, 2^27 for eight
+@pytest.mark.parametrize("d,M,dtype,momentum", [((1 << 30) // 36 - 3, 3, "f32", True), ((1 << 30) // 36 + 3, 3, "f32", True),
+                                                ((1 << 27) // 80 - 1, 8, "bf16", True), ((1 << 27) // 80 + 1, 8, "bf16", True),
+                                                ((1 << 25) // 2 - 1, 2, "bf16", False), ((1 << 25) // 2 + 1, 2, "bf16", False),
+                                                ((1 << 24) + 300, 2, "f32", True)])
+def test_packed_out_on_both_sides_of_two_launches(ss, oracle, d, M, dtype, momentum):
+    g = [draw(d + w, d, dtype, 0.5) for w in range(M)]
+    m_dev = [draw(d - w, d, "f32", 0.3) for w in range(M)] if momentum else None
+    x_dev = draw(7, d, "f32", 0.05)
+    m, x = [synth.as_numpy(t).copy() for t in m_dev] if momentum else None, synth.as_numpy(x_dev).copy()
+    voted, packed = dirty_bits(ss, d), [dirty_bits(ss, d) for _ in range(M)]
+    ss.signum_vote_step(g, m_dev, 0.9, 1e-4, x_dev, voted, packed)
+    want, want_packed = oracle.signum_vote_step([synth.as_numpy(t) for t in g], m, 0.9, 1e-4, x, want_packed=True, threads=16)
+    assert np.array_equal(bits_np(voted), want)
+    assert all(np.array_equal(bits_np(packed[w]), want_packed[w]) for w in range(M))
+    for w in range(M if momentum else 0):
+        assert_same_floats(m_dev[w], m[w], "m[%d]" % w)
+    assert_same_floats(x_dev, x, "x")
