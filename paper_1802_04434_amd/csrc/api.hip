@@ -458,44 +458,51 @@ int launch_vote_any(const uint32_t *const *packed, int M, uint32_t *voted, size_
 }
 
 // launch helpers of the ternary (vote with abstention) kernels
-template <int BLOCK, int BW, int R, int HOLD_KB, bool LOADS_FIRST, bool HAS_M, bool VOTE, typename G>
+template <int BW, int R, int HOLD_KB, bool NEAR, int STORE, uint32_t CHUNK, bool HAS_M, bool VOTE, typename G>
 int launch_ternary_shape(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     // the step is one grid over all workers' votes, the pack one row of the grid per worker
-    const Tiling t = make_tiling(d, R, true, BLOCK);
-    a.n_tiles = t.n_tiles;
-    a.words_total = t.words_total;
+    const Tiling t = make_tiling(d, R, true, ss::kWave);
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    return launch(ss::ternary_step_kernel<BLOCK, BW, R, HOLD_KB, LOADS_FIRST, HAS_M, VOTE, G>, grid, 0, stream, a, BLOCK, VOTE ? 1 : a.M);
+    a.n_tiles = (uint32_t)t.n_tiles;
+    a.words_total = t.words_total;
+    return launch(ss::ternary_step_kernel<BW, R, HOLD_KB, NEAR, STORE, CHUNK, HAS_M, VOTE, G>, grid, 0, stream, a, ss::kWave, VOTE ? 1 : a.M);
 }
 
-// The ternary kernel takes any M at run time.  Below the line of streams() it runs one-wave blocks with
-// the loads of up to eight workers out first (d = 272,474: fp32 M = 7 6.0 us against 11.3 with two rows of
-// 256 threads and one worker at a time, M = 12 9.1 / 17.7, without momentum M = 7 3.7 / 9.3; 1.1 M, M = 7
-// 18.9 / 25.2; one worker at 60 M 185 / 200).  Above it, gradients only, the same with two rows and about
-// fifteen blocks per unit (138 M: fp32 M = 7 845 us against 902 for two workers a stage and 1,320 for one,
-// bf16 M = 8 550 / 649 / 1,010; 17.6 M: 109 / 118 / 172 and 73 / 87 / 132).
+// The ternary kernel takes any M at run time; its shapes follow the binary step's (launch_step_m, launch_pack_momentum,
+// launch_pack_sign).
 template <bool HAS_M, bool VOTE, typename G>
 int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     constexpr bool kBf16 = std::is_same<G, ss::Bf16Grad>::value;
+    constexpr size_t kBytes = sizeof(typename G::elem) + (HAS_M ? 2 * sizeof(float) : 0);
+    using ss::kStream;
+    using ss::kThrough;
     if constexpr (VOTE) {
-        if ((a.M >= 2 && streams(a.M, d, HAS_M, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0))) || d >= kOneRowMaxD) {
-            if constexpr (!HAS_M) {
-                return launch_ternary_shape<64, 8, 2, 10, true, false, true, G>(a, d, stream);
+        // two rows where a row a lane has too many threads
+        if (d >= kOneRowMaxD) return launch_ternary_shape<1, 2, 13, false, kThrough, 0, HAS_M, true, G>(a, d, stream);
+        if (a.M == 1 ? d >= ((size_t)1 << 24) : streams(a.M, d, HAS_M, kBytes)) {
+            // us, KB held back: with momentum fp32 11 / 13 / 16: 25.6 M M = 1 80.8 / 84.7 / 92.4, M = 2 125.7 / 133.3 / 146.4, M = 4 217.9 /
+            // 219.9 / 235.7, M = 7 367.9 / 360.6 / 375.2, M = 16 868 / 840 / 831, bf16 11 / 12 / 14: M = 3 151.3 / 157.5 / 172.8, M = 8
+            // 60 M 840 / 832 / 887; gradients alone 10 / 13: fp32 M = 3 80.2 / 83.1, M = 7 143.2 / 137.6, bf16 M = 7 90.3 / 115.4.
+            // Before (blocks of two to four waves, or eight workers a stage without momentum): M = 2 143, M = 7 387, bf16 60 M 861, fp32
+            // gradients M = 7 152.6, bf16 92.4.
+            if constexpr (HAS_M) {
+                if (a.M < 5) return launch_ternary_shape<1, 1, 11, false, kThrough, 0, true, true, G>(a, d, stream);
+                return launch_ternary_shape<1, 1, kBf16 ? 12 : 13, false, kThrough, 0, true, true, G>(a, d, stream);
             } else {
-                // bf16 gradients with momentum, from four workers on: the binary step's shape for that case
-                if (kBf16 && a.M >= 4) return launch_ternary_shape<128, 2, 1, 40, true, true, true, G>(a, d, stream);
-                // otherwise two blocks per unit, one worker at a time (the one-block-per-unit shape of
-                // the binary step measured 7 % slower here)
-                return launch_ternary_shape<256, 1, 2, 64, false, true, true, G>(a, d, stream);
+                if (a.M < (kBf16 ? 4 : 5)) return launch_ternary_shape<4, 1, kBf16 ? 7 : 10, false, kThrough, 0, false, true, G>(a, d, stream);
+                return launch_ternary_shape<4, 1, kBf16 ? 10 : 13, false, kThrough, 0, false, true, G>(a, d, stream);
             }
         }
-        return launch_ternary_shape<64, 8, 1, 0, true, HAS_M, true, G>(a, d, stream);
+        if (d < ((size_t)1 << 20)) return launch_ternary_shape<8, 1, 0, true, kStream, 6, HAS_M, true, G>(a, d, stream);
+        return launch_ternary_shape<8, 1, 0, true, kStream, 8, HAS_M, true, G>(a, d, stream);
     } else if constexpr (HAS_M) {
-        // one worker's ternary pack: pack_kernel's shape
-        return launch_ternary_shape<64, 1, 1, 0, true, true, false, G>(a, d, stream);
+        if (d * (size_t)a.M * kBytes < ((size_t)1 << 28)) return launch_ternary_shape<1, 1, 0, false, kStream, 8, true, false, G>(a, d, stream);
+        if (d < ((size_t)1 << 25)) return launch_ternary_shape<1, 1, 0, false, kThrough, 9, true, false, G>(a, d, stream);
+        return launch_ternary_shape<1, 1, 7, false, kThrough, 0, true, false, G>(a, d, stream);
     } else {
-        return launch_ternary_shape<256, 1, 2, 0, false, false, false, G>(a, d, stream);
+        if (d < ((size_t)1 << 27)) return launch_ternary_shape<1, 2, 0, false, kStream, 8, false, false, G>(a, d, stream);
+        return launch_ternary_shape<1, 2, 0, false, kStream, 0, false, false, G>(a, d, stream);
     }
 }
 
@@ -530,10 +537,10 @@ int launch_quorum_apply(const ss::TernaryStepArgs &t, uint32_t *voted_neg, uint3
     if (grid > kMaxGrid) return SS_ERR_ARG;
     const int planes = count_planes(t.M);
     if (planes <= 3)
-        return large ? launch(ss::quorum_apply_kernel<3, 1, 0>, grid, 0, stream, a) : launch(ss::quorum_apply_kernel<3, 4, 39>, grid, 0, stream, a);
+        return large ? launch(ss::quorum_apply_kernel<3, 8, 1, 0>, grid, 0, stream, a) : launch(ss::quorum_apply_kernel<3, 8, 4, 30>, grid, 0, stream, a);
     if (planes <= 5)
-        return large ? launch(ss::quorum_apply_kernel<5, 1, 0>, grid, 0, stream, a) : launch(ss::quorum_apply_kernel<5, 4, 39>, grid, 0, stream, a);
-    return large ? launch(ss::quorum_apply_kernel<7, 1, 0>, grid, 0, stream, a) : launch(ss::quorum_apply_kernel<7, 4, 39>, grid, 0, stream, a);
+        return large ? launch(ss::quorum_apply_kernel<5, 8, 1, 0>, grid, 0, stream, a) : launch(ss::quorum_apply_kernel<5, 8, 4, 30>, grid, 0, stream, a);
+    return large ? launch(ss::quorum_apply_kernel<7, 8, 1, 0>, grid, 0, stream, a) : launch(ss::quorum_apply_kernel<7, 8, 4, 30>, grid, 0, stream, a);
 }
 
 }  // namespace

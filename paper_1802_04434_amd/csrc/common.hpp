@@ -23,6 +23,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 
+constexpr int kWave = 64;            // threads of the one-wave blocks
 constexpr int kBlock = 256;          // threads per block unless a kernel is launched with its own
 constexpr int kQuad = 4;             // coordinates per lane per row
 constexpr int kRowCoords = kBlock * kQuad;   // 1024

@@ -31,8 +31,8 @@ struct TernaryStepArgs {
     float beta, omb, delta, tau;
     int M;
     int quorum;
+    uint32_t n_tiles;
     size_t d;
-    size_t n_tiles;
     size_t words_total;
 };
 
@@ -46,23 +46,25 @@ __device__ __forceinline__ float step_ternary(float x, float delta, uint32_t ans
     return (answer & 2u) ? x : ((answer & 1u) ? x + delta : x - delta);
 }
 
-// One stage of the vector path: NW consecutive workers starting at w0, R rows (as step_stage
-// of the binary kernel: with LOADS_FIRST every load of the stage is out before the first wait)
-template <int NW, int R, bool LOADS_FIRST, bool HAS_M, bool VOTE, typename G>
-__device__ __forceinline__ void ternary_stage(const TernaryStepArgs &a, int w0, const size_t (&q)[R],
-                                              uint32_t (&n_neg)[R], uint32_t (&n_zero)[R], int lane) {
-    uint32_t *const neg_out = VOTE ? nullptr : a.neg_out + w0 * a.plane_stride;
-    uint32_t *const zero_out = VOTE ? nullptr : a.zero_out + w0 * a.plane_stride;
+// One stage of the vector path: NW consecutive workers starting at w0, the R rows of a wave's tile (as step_stage of the
+// binary kernel)
+template <int NW, int R, bool NEAR, int STORE, bool HAS_M, bool VOTE, typename G>
+__device__ __forceinline__ void ternary_stage(const TernaryStepArgs &a, int w0, size_t tile, uint32_t lane,
+                                              uint32_t (&n_neg)[R], uint32_t (&n_zero)[R]) {
+    constexpr uint32_t kCoords = R * kWave * kQuad;
+    constexpr uint32_t kGrad = kCoords * sizeof(typename G::elem), kFloat = kCoords * sizeof(float);
     f32x4 gv[R][NW], mv[R][NW];
 #pragma unroll
     for (int j = 0; j < NW; ++j) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            gv[r][j] = G::load4(a.g[w0 + j], q[r]);
-            if (HAS_M) mv[r][j] = ld_stream(reinterpret_cast<const f32x4 *>(a.m[w0 + j]) + q[r]);
+            // what is only read has 64-bit addresses
+            if (HAS_M || VOTE) gv[r][j] = G::template load_tile<NEAR>(a.g[w0 + j], tile, kGrad, r * kWave + lane);
+            else gv[r][j] = G::load4(a.g[w0 + j], (tile * R + r) * kWave + lane);
+            if (HAS_M) mv[r][j] = ld_tile<NEAR>(a.m[w0 + j], tile, kFloat, (r * kWave + lane) * 16);
         }
     }
-    if (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < NW; ++j) {
 #pragma unroll
@@ -74,7 +76,7 @@ __device__ __forceinline__ void ternary_stage(const TernaryStepArgs &a, int w0, 
                 v.y = momentum(a.beta, a.omb, m0.y, v.y);
                 v.z = momentum(a.beta, a.omb, m0.z, v.z);
                 v.w = momentum(a.beta, a.omb, m0.w, v.w);
-                st_stream(reinterpret_cast<f32x4 *>(a.m[w0 + j]) + q[r], v);
+                st_tile<NEAR, STORE>(a.m[w0 + j], tile, kFloat, (r * kWave + lane) * 16, v);
             }
             uint32_t zero_nib = 0, neg_nib = 0;
 #pragma unroll
@@ -90,56 +92,51 @@ __device__ __forceinline__ void ternary_stage(const TernaryStepArgs &a, int w0, 
                 const uint32_t nw = combine8(neg_nib, lane);
                 const uint32_t zw = combine8(zero_nib, lane);
                 if ((lane & 7) == 0) {
-                    neg_out[q[r] >> 3] = nw;
-                    zero_out[q[r] >> 3] = zw;
+                    const size_t word = w0 * a.plane_stride + tile * (kCoords / 32) + ((r * kWave + lane) >> 3);
+                    a.neg_out[word] = nw;
+                    a.zero_out[word] = zw;
                 }
             }
         }
     }
-    if (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // the n <= NMAX workers that the full stages leave over, as one stage of exactly that size
-template <int NMAX, int R, bool LOADS_FIRST, bool HAS_M, bool VOTE, typename G>
-__device__ __forceinline__ void ternary_rest(const TernaryStepArgs &a, int w0, int n, const size_t (&q)[R],
-                                             uint32_t (&n_neg)[R], uint32_t (&n_zero)[R], int lane) {
+template <int NMAX, int R, bool NEAR, int STORE, bool HAS_M, bool VOTE, typename G>
+__device__ __forceinline__ void ternary_rest(const TernaryStepArgs &a, int w0, int n, size_t tile, uint32_t lane,
+                                             uint32_t (&n_neg)[R], uint32_t (&n_zero)[R]) {
     if (n == NMAX) {
-        ternary_stage<NMAX, R, LOADS_FIRST, HAS_M, VOTE, G>(a, w0, q, n_neg, n_zero, lane);
+        ternary_stage<NMAX, R, NEAR, STORE, HAS_M, VOTE, G>(a, w0, tile, lane, n_neg, n_zero);
     } else if constexpr (NMAX > 1) {
-        ternary_rest<NMAX - 1, R, LOADS_FIRST, HAS_M, VOTE, G>(a, w0, n, q, n_neg, n_zero, lane);
+        ternary_rest<NMAX - 1, R, NEAR, STORE, HAS_M, VOTE, G>(a, w0, n, tile, lane, n_neg, n_zero);
     }
 }
 
-// BLOCK threads per block, BW workers per stage (what M leaves over is one smaller stage), R rows
-// per block, HOLD_KB of LDS reserved to cap the blocks per compute unit, LOADS_FIRST as in the
-// binary step kernel
-template <int BLOCK, int BW, int R, int HOLD_KB, bool LOADS_FIRST, bool HAS_M, bool VOTE, typename G>
-__global__ __launch_bounds__(BLOCK) void ternary_step_kernel(const TernaryStepArgs a) {
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
+// One-wave blocks.  VOTE: the whole step; otherwise worker blockIdx.y's pack.  BW workers per stage (what M leaves over
+// is one smaller stage), R rows per block, HOLD_KB of LDS reserved to cap the blocks per compute unit; NEAR, STORE and
+// CHUNK as step_kernel's
+template <int BW, int R, int HOLD_KB, bool NEAR, int STORE, uint32_t CHUNK, bool HAS_M, bool VOTE, typename G>
+__global__ __launch_bounds__(kWave) void ternary_step_kernel(const TernaryStepArgs a) {
+    const uint32_t lane = threadIdx.x;
     const int M = a.M;
-    const size_t tile = blockIdx.x;
+    constexpr uint32_t kCoords = R * kWave * kQuad;
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0 /* the host rejects such a d */, VOTE ? a.voted_neg : a.neg_out);
 
-    if (tile < a.n_tiles) {
-        size_t q[R];
+    if (blockIdx.x < a.n_tiles) {
+        const size_t tile = die_tile<CHUNK>(blockIdx.x, a.n_tiles);
         uint32_t n_neg[R], n_zero[R];
         f32x4 xv[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            q[r] = (tile * R + r) * BLOCK + tid;
             n_neg[r] = 0;
             n_zero[r] = 0;
-            if (VOTE) xv[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + q[r]);
+            if (VOTE) xv[r] = ld_tile<NEAR>(a.x, tile, kCoords * sizeof(float), (r * kWave + lane) * 16);
         }
         if constexpr (VOTE) {
             int w0 = 0;
-            for (; w0 + BW <= M; w0 += BW) ternary_stage<BW, R, LOADS_FIRST, HAS_M, true, G>(a, w0, q, n_neg, n_zero, lane);
-            if constexpr (BW > 1) ternary_rest<BW - 1, R, LOADS_FIRST, HAS_M, true, G>(a, w0, M - w0, q, n_neg, n_zero, lane);
-        } else {
-            ternary_stage<1, R, LOADS_FIRST, HAS_M, false, G>(a, blockIdx.y, q, n_neg, n_zero, lane);
-        }
-        if (VOTE) {
+            for (; w0 + BW <= M; w0 += BW) ternary_stage<BW, R, NEAR, STORE, HAS_M, true, G>(a, w0, tile, lane, n_neg, n_zero);
+            if constexpr (BW > 1) ternary_rest<BW - 1, R, NEAR, STORE, HAS_M, true, G>(a, w0, M - w0, tile, lane, n_neg, n_zero);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 uint32_t neg_nib = 0, zero_nib = 0;
@@ -152,20 +149,23 @@ __global__ __launch_bounds__(BLOCK) void ternary_step_kernel(const TernaryStepAr
                     zero_nib |= ((ans >> 1) & 1u) << c;
                     v[c] = step_ternary(v[c], a.delta, ans);
                 }
-                st_stream(reinterpret_cast<f32x4 *>(a.x) + q[r], v);
+                st_tile<NEAR, STORE>(a.x, tile, kCoords * sizeof(float), (r * kWave + lane) * 16, v);
                 const uint32_t nw = combine8(neg_nib, lane);
                 const uint32_t zw = combine8(zero_nib, lane);
                 if ((lane & 7) == 0) {
-                    a.voted_neg[q[r] >> 3] = nw;
-                    a.voted_zero[q[r] >> 3] = zw;
+                    const size_t word = tile * (kCoords / 32) + ((r * kWave + lane) >> 3);
+                    a.voted_neg[word] = nw;
+                    a.voted_zero[word] = zw;
                 }
             }
+        } else {
+            ternary_stage<1, R, NEAR, STORE, HAS_M, false, G>(a, blockIdx.y, tile, lane, n_neg, n_zero);
         }
         return;
     }
 
     // scalar path: what does not fill a tile, and the zero padding words
-    const size_t i = a.n_tiles * (size_t)(R * BLOCK * kQuad) + (tile - a.n_tiles) * BLOCK + tid;
+    const size_t i = a.n_tiles * (size_t)kCoords + (size_t)(blockIdx.x - a.n_tiles) * kWave + lane;
     const bool in = i < a.d;
     const size_t word = i >> 5;
     const bool writes_word = (lane & 31) == 0 && word < a.words_total;
@@ -386,7 +386,7 @@ struct QuorumApplyArgs {
 };
 
 // P planes of the counts, as quorum_vote_kernel.  A block owns R rows of 1024 coordinates.
-template <int P, int R, int HOLD_KB>
+template <int P, int NB, int R, int HOLD_KB>
 __global__ __launch_bounds__(kBlock) void quorum_apply_kernel(const QuorumApplyArgs a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.voted_neg);
     constexpr int kWords = 32 * R;
@@ -396,14 +396,12 @@ __global__ __launch_bounds__(kBlock) void quorum_apply_kernel(const QuorumApplyA
     const size_t base = (size_t)blockIdx.x * (R * kRowCoords);
     const bool full = base + (size_t)(R * kRowCoords) <= a.d;
     f32x4 xv[R];
-    f32x4 *const xq = reinterpret_cast<f32x4 *>(a.x + base) + tid;
-    if (full) {
+    const Window xw = window(a.x, base * sizeof(float), full ? R * kRowCoords * sizeof(float) : 0);
 #pragma unroll
-        for (int r = 0; r < R; ++r) xv[r] = ld_stream(xq + r * kBlock);
-    }
+    for (int r = 0; r < R; ++r) xv[r] = ld_quad(xw, (r * kBlock + tid) * 16);
     if (tid < kWords && wi < a.words_total) {
         uint32_t is_neg, not_plus;
-        quorum_word<P, kQuorumBatch>([&](int w) { return a.neg + w * a.plane_stride + wi; },
+        quorum_word<P, NB>([&](int w) { return a.neg + w * a.plane_stride + wi; },
                                      [&](int w) { return a.zero + w * a.plane_stride + wi; }, a.M, a.quorum, is_neg, not_plus);
         const uint32_t live = live_mask(wi, a.d);
         const uint32_t neg = is_neg & live, zero = not_plus & ~is_neg & live;
@@ -421,7 +419,7 @@ __global__ __launch_bounds__(kBlock) void quorum_apply_kernel(const QuorumApplyA
             f32x4 v = xv[r];
 #pragma unroll
             for (int c = 0; c < 4; ++c) v[c] = step_ternary(v[c], a.delta, ((nn >> c) & 1u) | (((zn >> c) & 1u) << 1));
-            st_stream(xq + r * kBlock, v);
+            st_quad<kThrough>(xw, (r * kBlock + tid) * 16, v);
         }
         return;
     }

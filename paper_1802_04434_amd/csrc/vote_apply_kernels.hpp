@@ -475,7 +475,6 @@ __global__ __launch_bounds__(64) void vote_sum_word_kernel(const VoteSumArgs a) 
 // 186 / 194, 801 / 842; sigma 32.2 / 33.7, 166 / 176, 714 / 777.  Cached vectors like fewer, larger blocks
 // (1.1 M: copy 2.3 / 2.8, sum apply 2.9 / 3.3).  The kernels that read shared words of bits (apply, ternary
 // apply) gain nothing from it: 25.6 M 33.4 against 33.1 and 34.0 against 33.4.
-constexpr int kWave = 64;
 constexpr int kWaveCoords = kWave * kQuad;
 
 struct SumApplyArgs {

@@ -123,3 +123,38 @@ def test_packed_out_on_both_sides_of_two_launches(ss, oracle, d, M, dtype, momen
     for w in range(M if momentum else 0):
         assert_same_floats(m_dev[w], m[w], "m[%d]" % w)
     assert_same_floats(x_dev, x, "x")
+
+
+# the ternary step in one pass (through the C ABI nothing is lent): both sides of the rules on size and on the workers, and a
+# pack of planes around the runs of tiles
+@pytest.mark.parametrize("d,M,dtype,momentum", [((1 << 24) + 257, 1, "f32", True), ((5 << 25) // 48 + 3, 4, "f32", True),
+                                                ((5 << 25) // 60 + 255, 5, "f32", True), ((5 << 25) // 60 - 9, 5, "f32", True),
+                                                ((5 << 25) // 60 + 1, 6, "bf16", True), ((1 << 28) // 6 + 1, 3, "bf16", False),
+                                                ((1 << 28) // 8 + 511, 4, "bf16", False), ((1 << 28) // 16 + 77, 4, "f32", False),
+                                                ((1 << 20) + 300, 9, "f32", True), ((1 << 17) + 5, 9, "bf16", True)])
+def test_one_pass_ternary_around_rules(ss, oracle, d, M, dtype, momentum):
+    g = [draw(d + w, d, dtype, 0.2) for w in range(M)]
+    m_dev = [draw(d - w, d, "f32", 0.2) for w in range(M)] if momentum else None
+    x_dev = draw(7, d, "f32", 0.05)
+    m, x = [synth.as_numpy(t).copy() for t in m_dev] if momentum else None, synth.as_numpy(x_dev).copy()
+    neg, zero = dirty_bits(ss, d), dirty_bits(ss, d)
+    ss.signum_vote_step_ternary(g, m_dev, 0.9, 0.1, 2, 1e-4, x_dev, neg, zero)
+    want_neg, want_zero = oracle.signum_vote_step_ternary([synth.as_numpy(t) for t in g], m, 0.9, 0.1, 2, 1e-4, x)
+    assert np.array_equal(bits_np(neg), want_neg) and np.array_equal(bits_np(zero), want_zero)
+    for w in range(M if momentum else 0):
+        assert_same_floats(m_dev[w], m[w], "m[%d]" % w)
+    assert_same_floats(x_dev, x, "x")
+
+
+@pytest.mark.parametrize("d,dtype,momentum", [((1 << 19) + 257, "f32", True), ((1 << 20) - 1, "bf16", False),
+                                              ((1 << 28) // 12 + 255, "f32", True), ((1 << 25) + 3, "bf16", True)])
+def test_ternary_pack_around_rules(ss, oracle, d, dtype, momentum):
+    g = draw(d, d, dtype, 0.2)
+    m_dev = draw(d + 1, d, "f32", 0.2) if momentum else None
+    m = synth.as_numpy(m_dev).copy() if momentum else None
+    neg, zero = dirty_bits(ss, d), dirty_bits(ss, d)
+    ss.signum_pack_ternary(g, m_dev, 0.9, 0.1, neg, zero)
+    want_neg, want_zero = oracle.signum_pack_ternary(synth.as_numpy(g), m, 0.9, 0.1)
+    assert np.array_equal(bits_np(neg), want_neg) and np.array_equal(bits_np(zero), want_zero)
+    if momentum:
+        assert_same_floats(m_dev, m, "m")
