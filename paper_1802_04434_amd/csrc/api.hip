@@ -165,13 +165,21 @@ inline bool scratch_pays(int M, size_t d, size_t worker_bytes) {
     return M >= 4 && d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 5 ? 28 : 30));
 }
 
-// up to here sum_apply and copy keep four-wave blocks (see vote_apply_kernels.hpp)
-constexpr size_t kCachedD = (size_t)1 << 21;
-
-// apply and vote-and-update: from about a gigabyte per array on, one row per block (apply: with six
-// blocks per unit, roughly 24 KB of loads in flight, which an LDS reservation enforces) is 3-7 % faster
-// than four rows
+// any-M vote and update, and answer and update: from about a gigabyte of x on, one row per block is 3-7 % faster than four
 constexpr size_t kLargeD = (size_t)1 << 28;
+
+// the updates alone (see ApplyShape): two rows a wave up to here
+constexpr size_t kApplySmall = (size_t)1 << 23;
+
+template <typename Args>
+int launch_apply(void (*small)(Args), void (*large)(Args), Args a, void *hip_stream) {
+    const bool two_rows = a.d < kApplySmall || a.d >= kOneRowMaxD;   // beyond, a row a lane has too many threads
+    const Tiling t = make_tiling(a.d, two_rows ? 2 : 1, false, ss::kWave);
+    const size_t grid = t.n_tiles + t.tail_blocks;
+    if (grid > kMaxGrid) return SS_ERR_ARG;
+    a.n_tiles = (uint32_t)t.n_tiles;
+    return launch(two_rows ? small : large, grid, 0, static_cast<hipStream_t>(hip_stream), a, ss::kWave);
+}
 
 template <int NPTR>
 void fill_step_args(ss::StepArgs<NPTR> &a, int M, const void *const *g, float *const *m, uint32_t *const *packed,
@@ -337,6 +345,9 @@ int launch_pack_sign(ss_dtype gdt, ss::PackArgs<NPTR> &a, int n, hipStream_t str
     }
     if (a.d < ((size_t)1 << 27))
         return launch_pack_shape(ss::pack_kernel<NPTR, 64, 2, 0, ss::kStream, 8, false, ss::F32Grad>, a, n, 64, 2, 4, stream);
+    // two rows a lane have too many threads for the longest vectors
+    if (a.d >= kOneRowMaxD)
+        return launch_pack_shape(ss::pack_kernel<NPTR, 256, 4, 0, ss::kStream, 0, false, ss::F32Grad>, a, n, 256, 4, 4, stream);
     return launch_pack_shape(ss::pack_kernel<NPTR, 128, 2, 0, ss::kStream, 0, false, ss::F32Grad>, a, n, 128, 2, 4, stream);
 }
 
@@ -621,19 +632,7 @@ int ss_sign_apply(float *x, const uint32_t *bits, float delta, size_t d, void *h
     if (!aligned16(x) || !aligned16(bits)) return SS_ERR_ALIGN;
     Span spans[2] = {span(x, d * sizeof(float), true), span(bits, ss_packed_words(d) * 4, false)};
     if (written_spans_overlap(spans, 2)) return SS_ERR_ARG;
-    const bool large = d >= kLargeD;   // then one row per block, six blocks per unit
-    const Tiling t = make_tiling(d, large ? 1 : 4, false);
-    ss::ApplyArgs a;
-    a.x = x;
-    a.bits = bits;
-    a.delta = delta;
-    a.d = d;
-    a.n_tiles = t.n_tiles;
-    const size_t grid = t.n_tiles + t.tail_blocks;
-    if (grid > kMaxGrid) return SS_ERR_ARG;
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (large) return launch(ss::apply_kernel<1, 24, true>, grid, 0, stream, a);
-    return launch(ss::apply_kernel<4, 0, false>, grid, 0, stream, a);
+    return launch_apply(ss::apply_kernel<true>, ss::apply_kernel<false>, ss::ApplyArgs{x, bits, delta, 0, d}, hip_stream);
 }
 
 // the step over a vector, or a part of one, that every launch shape covers
@@ -794,19 +793,7 @@ int ss_sum_apply(float *x, const int8_t *sums, float delta, size_t d, void *hip_
     if (!aligned16(x) || !aligned16(sums)) return SS_ERR_ALIGN;
     Span spans[2] = {span(x, d * sizeof(float), true), span(sums, d, false)};
     if (written_spans_overlap(spans, 2)) return SS_ERR_ARG;
-    const bool small = d < kCachedD;
-    const Tiling t = make_tiling(d, small ? 4 : 1, false, small ? ss::kBlock : ss::kWave);
-    ss::SumApplyArgs a;
-    a.x = x;
-    a.sums = sums;
-    a.delta = delta;
-    a.d = d;
-    a.n_tiles = t.n_tiles;
-    const size_t grid = t.n_tiles + t.tail_blocks;
-    if (grid > kMaxGrid) return SS_ERR_ARG;
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (small) return launch(ss::sum_apply_kernel<ss::kBlock, 4>, grid, 0, stream, a);
-    return launch(ss::sum_apply_kernel<ss::kWave, 1>, grid, 0, stream, a, ss::kWave);
+    return launch_apply(ss::sum_apply_kernel<true>, ss::sum_apply_kernel<false>, ss::SumApplyArgs{x, sums, delta, 0, d}, hip_stream);
 }
 
 int ss_welford_update(const void *g, ss_dtype gdt, float *mean, float *m2, uint64_t n, size_t d, void *hip_stream) {
@@ -819,25 +806,19 @@ int ss_welford_update(const void *g, ss_dtype gdt, float *mean, float *m2, uint6
                      span(m2, d * sizeof(float), true)};
     if (written_spans_overlap(spans, 3)) return SS_ERR_ARG;
     const Tiling t = make_tiling(d, 1, false, ss::kWave);
-    ss::WelfordArgs a;
-    a.g = g;
-    a.mean = mean;
-    a.m2 = m2;
-    a.n = (float)n;
-    a.d = d;
-    a.n_tiles = t.n_tiles;
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
+    const ss::WelfordArgs a{g, mean, m2, (float)n, (uint32_t)t.n_tiles, d};
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    // the cap of welford_update_kernel, us with against without: fp32 4.4 M 15.7 / 15.4, 8.8 M 29.1 / 29.2, 12 M 38.6 / 38.4,
-    // 16 M 50.1 / 50.7, 20 M 62.9 / 63.2, 25.6 M 80.1 / 81.4, 60 M 182 / 190; bf16 4.4 M 13.7 / 13.5, 12 M 34.5 / 34.7,
-    // 17.6 M 49.7 / 50.7, 60 M 164 / 170
+    // Runs of half a megabyte a die while a cache may hold something, from 2^24 coordinates on written through, in order, with 14 waves
+    // a unit.  us, in order before / runs / capped: fp32 4.4 M 15.7 / 14.9 / 16.3, 8.8 M 28.9 / 27.9 / 28.8, 17.6 M 55.7 / 55.4 / 54.4,
+    // 60 M 184 / 184 / 178; bf16 4.4 M 14.1 / 13.6 / 13.4, 8.8 M 25.9 / 25.4 / 25.8, 17.6 M 50.5 / 50.1 / 48.7
     if (d >= ((size_t)1 << 24)) {
-        if (gdt == SS_F32) return launch(ss::welford_update_kernel<8, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
-        return launch(ss::welford_update_kernel<8, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
+        if (gdt == SS_F32) return launch(ss::welford_update_kernel<11, ss::kThrough, 0, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
+        return launch(ss::welford_update_kernel<11, ss::kThrough, 0, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
     }
-    if (gdt == SS_F32) return launch(ss::welford_update_kernel<0, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
-    return launch(ss::welford_update_kernel<0, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
+    if (gdt == SS_F32) return launch(ss::welford_update_kernel<0, ss::kStream, 9, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
+    return launch(ss::welford_update_kernel<0, ss::kStream, 9, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
 }
 
 int ss_welford_sigma(const float *m2, uint64_t n, float *sigma, size_t d, void *hip_stream) {
@@ -849,17 +830,13 @@ int ss_welford_sigma(const float *m2, uint64_t n, float *sigma, size_t d, void *
     if (written_spans_overlap(spans, 2)) return SS_ERR_ARG;
     const bool two_rows = d >= kOneRowMaxD;
     const Tiling t = make_tiling(d, two_rows ? 2 : 1, false, ss::kWave);
-    ss::SigmaArgs a;
-    a.m2 = m2;
-    a.sigma = sigma;
-    a.n = (float)n;
-    a.d = d;
-    a.n_tiles = t.n_tiles;
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
+    const ss::SigmaArgs a{m2, sigma, (float)n, (uint32_t)t.n_tiles, d};
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (two_rows) return launch(ss::welford_sigma_kernel<2>, grid, 0, stream, a, ss::kWave);
-    return launch(ss::welford_sigma_kernel<1>, grid, 0, stream, a, ss::kWave);
+    if (two_rows) return launch(ss::welford_sigma_kernel<2, ss::kThrough>, grid, 0, stream, a, ss::kWave);
+    if (d >= ((size_t)1 << 24)) return launch(ss::welford_sigma_kernel<1, ss::kThrough>, grid, 0, stream, a, ss::kWave);
+    return launch(ss::welford_sigma_kernel<1, ss::kStream>, grid, 0, stream, a, ss::kWave);
 }
 
 size_t ss_density_workspace_bytes(void) { return sizeof(ss::DensityScratch); }
@@ -1016,20 +993,8 @@ int ss_ternary_apply(float *x, const uint32_t *neg, const uint32_t *zero, float 
     Span spans[3] = {span(x, d * sizeof(float), true), span(neg, ss_packed_words(d) * 4, false),
                      span(zero, ss_packed_words(d) * 4, false)};
     if (written_spans_overlap(spans, 3)) return SS_ERR_ARG;
-    const bool large = d >= kLargeD;   // then two rows per block, four blocks per unit
-    const Tiling t = make_tiling(d, large ? 2 : 4, false);
-    ss::TernaryApplyArgs a;
-    a.x = x;
-    a.neg = neg;
-    a.zero = zero;
-    a.delta = delta;
-    a.d = d;
-    a.n_tiles = t.n_tiles;
-    const size_t grid = t.n_tiles + t.tail_blocks;
-    if (grid > kMaxGrid) return SS_ERR_ARG;
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (large) return launch(ss::ternary_apply_kernel<2, 40, true>, grid, 0, stream, a);
-    return launch(ss::ternary_apply_kernel<4, 0, false>, grid, 0, stream, a);
+    return launch_apply(ss::ternary_apply_kernel<true>, ss::ternary_apply_kernel<false>,
+                        ss::TernaryApplyArgs{x, neg, zero, delta, 0, d}, hip_stream);
 }
 
 static int ternary_step_impl(const void *const *g, ss_dtype gdt, float *const *m, int M, float beta, float tau, int quorum,
@@ -1127,14 +1092,10 @@ int ss_stream_copy(void *dst, const void *src, size_t nbytes, void *hip_stream) 
     Span spans[2] = {span(dst, nbytes, true), span(src, nbytes, false)};
     if (written_spans_overlap(spans, 2)) return SS_ERR_ARG;
     const size_t n_vec = nbytes / 16;
-    const bool small = nbytes < 2 * sizeof(float) * kCachedD;
-    const size_t per_block = small ? ss::kBlock * 2 : ss::kWave;
-    const size_t grid = (n_vec + per_block - 1) / per_block;
+    const size_t grid = (n_vec + ss::kWave - 1) / ss::kWave;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     const ss::CopyArgs a{static_cast<ss::f32x4 *>(dst), static_cast<const ss::f32x4 *>(src), n_vec};
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (small) return launch(ss::copy_kernel<ss::kBlock, 2>, grid, 0, stream, a);
-    return launch(ss::copy_kernel<ss::kWave, 1>, grid, 0, stream, a, ss::kWave);
+    return launch(ss::copy_kernel, grid, 0, static_cast<hipStream_t>(hip_stream), a, ss::kWave);
 }
 
 }  // extern "C"

@@ -20,8 +20,8 @@ struct WelfordArgs {
     float *mean;
     float *m2;
     float n;          // index of this gradient, 1-based, as fp32
+    uint32_t n_tiles;
     size_t d;
-    size_t n_tiles;
 };
 
 // delta = g - mean; mean <- mean + delta / n; m2 <- m2 + delta * (g - mean)
@@ -34,19 +34,19 @@ __device__ __forceinline__ void welford1(float g, float n, float &mean, float &m
     m2 = m2 + p;
 }
 
-// One-wave blocks as sum_apply_kernel and copy_kernel (see there).  Five streams: with HOLD_KB = 8 twenty
-// waves share a unit instead of 32, us against no cap and against blocks of four waves as launched before:
-// 25.6 M coordinates 80.6 / 81.5 / 82.2, 138 M 422 / 433 / 452, 600 M 1,926 / 1,964 / 1,978; 4.4 M 16.7 / 16.2 / 16.5.
-template <int HOLD_KB, typename G>
+// One-wave blocks of one row.  Five streams; the shapes are the host's (ss_welford_update), us, now / before (addresses a
+// lane, the L2's own write-back): 25.6 M coordinates 77.6 / 80.0, 138 M 411 / 427, 390 M 1,148 / 1,197, bf16 138 M 366 / 384.
+template <int HOLD_KB, int STORE, uint32_t CHUNK, typename G>
 __global__ __launch_bounds__(kWave) void welford_update_kernel(const WelfordArgs a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, reinterpret_cast<uint32_t *>(a.mean));
-    const int tid = threadIdx.x;
-    const size_t tile = blockIdx.x;
-    if (tile < a.n_tiles) {
-        const size_t q = tile * kWave + tid;
-        const f32x4 gv = G::load4(a.g, q);
-        f32x4 mean = ld_stream(reinterpret_cast<const f32x4 *>(a.mean) + q);
-        f32x4 m2 = ld_stream(reinterpret_cast<const f32x4 *>(a.m2) + q);
+    constexpr uint32_t kGrad = kWaveCoords * sizeof(typename G::elem), kFloat = kWaveCoords * sizeof(float);
+    const uint32_t lane = threadIdx.x;
+    if (blockIdx.x < a.n_tiles) {
+        const size_t tile = die_tile<CHUNK>(blockIdx.x, a.n_tiles);
+        const Window mean_w = window(a.mean, tile * kFloat, kFloat), m2_w = window(a.m2, tile * kFloat, kFloat);
+        const f32x4 gv = G::load4(window(a.g, tile * kGrad, kGrad), lane);
+        f32x4 mean = ld_quad(mean_w, lane * 16);
+        f32x4 m2 = ld_quad(m2_w, lane * 16);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -55,11 +55,11 @@ __global__ __launch_bounds__(kWave) void welford_update_kernel(const WelfordArgs
             mean[c] = mean_c;
             m2[c] = m2_c;
         }
-        st_stream(reinterpret_cast<f32x4 *>(a.mean) + q, mean);
-        st_stream(reinterpret_cast<f32x4 *>(a.m2) + q, m2);
+        st_quad<STORE>(mean_w, lane * 16, mean);
+        st_quad<STORE>(m2_w, lane * 16, m2);
         return;
     }
-    const size_t i = a.n_tiles * (size_t)kWaveCoords + (tile - a.n_tiles) * kWave + tid;
+    const size_t i = a.n_tiles * (size_t)kWaveCoords + (size_t)(blockIdx.x - a.n_tiles) * kWave + lane;
     if (i < a.d) {
         float mean = a.mean[i], m2 = a.m2[i];
         welford1(G::load1(a.g, i), a.n, mean, m2);
@@ -72,8 +72,8 @@ struct SigmaArgs {
     const float *m2;
     float *sigma;
     float n;
+    uint32_t n_tiles;
     size_t d;
-    size_t n_tiles;
 };
 
 __device__ __forceinline__ float sigma1(float m2, float n) {
@@ -81,15 +81,19 @@ __device__ __forceinline__ float sigma1(float m2, float n) {
     return __builtin_sqrtf(var);
 }
 
-// R rows: one, but for vectors whose one-row grid would have 2^32 threads
-template <int R>
+// R rows: one, but for vectors whose one-row grid would have 2^32 threads.  Read by address; written through (138 M 163.7 us
+// against 167.7, 390 M 458 / 466) unless the vector is small enough for a cache to hold what the next kernel reads: update,
+// sigma and the two densities at 1.1 M 19.7 / 18.6, at 4.4 M 39.1 / 38.0, at 17.6 M 107.2 / 108.6.
+template <int R, int STORE>
 __global__ __launch_bounds__(kWave) void welford_sigma_kernel(const SigmaArgs a) {
-    const int tid = threadIdx.x;
+    constexpr uint32_t kCoords = R * kWaveCoords;
+    const uint32_t lane = threadIdx.x;
     const size_t tile = blockIdx.x;
     if (tile < a.n_tiles) {
+        const Window to = window(a.sigma, tile * (kCoords * sizeof(float)), kCoords * sizeof(float));
         f32x4 v[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.m2) + (tile * R + r) * kWave + tid);
+        for (int r = 0; r < R; ++r) v[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.m2) + (tile * R + r) * kWave + lane);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             f32x4 s;
@@ -97,11 +101,11 @@ __global__ __launch_bounds__(kWave) void welford_sigma_kernel(const SigmaArgs a)
             s.y = sigma1(v[r].y, a.n);
             s.z = sigma1(v[r].z, a.n);
             s.w = sigma1(v[r].w, a.n);
-            st_stream(reinterpret_cast<f32x4 *>(a.sigma) + (tile * R + r) * kWave + tid, s);
+            st_quad<STORE>(to, (r * kWave + lane) * 16, s);
         }
         return;
     }
-    const size_t i = a.n_tiles * (size_t)(R * kWaveCoords) + (tile - a.n_tiles) * kWave + tid;
+    const size_t i = a.n_tiles * (size_t)kCoords + (tile - a.n_tiles) * kWave + lane;
     if (i < a.d) a.sigma[i] = sigma1(a.m2[i], a.n);
 }
 

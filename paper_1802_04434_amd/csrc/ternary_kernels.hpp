@@ -436,38 +436,39 @@ struct TernaryApplyArgs {
     const uint32_t *neg;
     const uint32_t *zero;
     float delta;
+    uint32_t n_tiles;
     size_t d;
-    size_t n_tiles;
 };
 
-template <int R, int HOLD_KB, bool LOADS_FIRST>
-__global__ __launch_bounds__(kBlock) void ternary_apply_kernel(const TernaryApplyArgs a) {
-    reserve_lds<HOLD_KB>(a.d == ~(size_t)0, reinterpret_cast<uint32_t *>(a.x));
-    const int tid = threadIdx.x;
-    const size_t tile = blockIdx.x;
-    if (tile < a.n_tiles) {
-        size_t q[R];
-        f32x4 xv[R];
-        uint32_t nw[R], zw[R];
+// in the shapes of apply_kernel
+template <bool SMALL>
+__global__ __launch_bounds__(kWave) void ternary_apply_kernel(const TernaryApplyArgs a) {
+    using S = ApplyShape<SMALL>;
+    const uint32_t lane = threadIdx.x;
+    if (blockIdx.x < a.n_tiles) {
+        const size_t tile = die_tile<S::kChunk>(blockIdx.x, a.n_tiles);
+        const size_t first = tile * (S::kCoords / 32);
+        const Window xw = window(a.x, tile * (S::kCoords * sizeof(float)), S::kCoords * sizeof(float));
+        f32x4 xv[S::kRows];
+        uint32_t nw[S::kRows], zw[S::kRows];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            q[r] = (tile * R + r) * kBlock + tid;
-            xv[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + q[r]);
-            nw[r] = a.neg[q[r] >> 3];
-            zw[r] = a.zero[q[r] >> 3];
+        for (int r = 0; r < S::kRows; ++r) {
+            nw[r] = a.neg[first + ((r * kWave + lane) >> 3)];
+            zw[r] = a.zero[first + ((r * kWave + lane) >> 3)];
+            xv[r] = ld_quad(xw, (r * kWave + lane) * 16);
         }
-        if (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const uint32_t nn = nw[r] >> ((tid & 7) * 4), zn = zw[r] >> ((tid & 7) * 4);
+        for (int r = 0; r < S::kRows; ++r) {
+            const uint32_t nn = nw[r] >> ((lane & 7) * 4), zn = zw[r] >> ((lane & 7) * 4);
             f32x4 v = xv[r];
 #pragma unroll
             for (int c = 0; c < 4; ++c) v[c] = step_ternary(v[c], a.delta, ((nn >> c) & 1u) | (((zn >> c) & 1u) << 1));
-            st_stream(reinterpret_cast<f32x4 *>(a.x) + q[r], v);
+            st_quad<S::kStore>(xw, (r * kWave + lane) * 16, v);
         }
         return;
     }
-    const size_t i = a.n_tiles * (size_t)(R * kRowCoords) + (tile - a.n_tiles) * kBlock + tid;
+    const size_t i = a.n_tiles * (size_t)S::kCoords + (size_t)(blockIdx.x - a.n_tiles) * kWave + lane;
     if (i < a.d) {
         const uint32_t ans = ((a.neg[i >> 5] >> (i & 31)) & 1u) | (((a.zero[i >> 5] >> (i & 31)) & 1u) << 1);
         a.x[i] = step_ternary(a.x[i], a.delta, ans);

@@ -204,45 +204,58 @@ __global__ __launch_bounds__(64) void vote_word_kernel(const VoteArgs<64> a) {
 
 // --------------------------------------------------------------- apply ----
 
+// The updates from bits, from sums and from an answer with abstentions stream x in place, 8 bytes a coordinate, and read
+// little beside it.  One-wave blocks: two rows, the L2 writing back and a quarter or half of a megabyte a die while a vector
+// fits the caches (kApplySmall), one row written through in the same runs beyond.  us, two rows / one row / blocks of four
+// waves as launched before: apply 1.1 M 2.4 / 3.3 / 2.9, 4.4 M 6.7 / 7.2 / 7.2, 8.8 M 12.0 / 12.0 / 12.7, 25.6 M 32.2 / 31.5 / 33.0,
+// 138 M 170 / 165 / 171, 390 M 486 / 465 / 482; sums 1.1 M 2.6 / 3.3 / 3.2, 25.6 M 35.6 / 35.1 / 35.7, 138 M 188 / 184 / 188;
+// answers 1.1 M 2.7 / 3.5, 25.6 M 32.9 / 31.9 / 32.7, 138 M 172 / 166 / 170.
+constexpr int kWaveCoords = kWave * kQuad;
+template <bool SMALL>
+struct ApplyShape {
+    static constexpr int kRows = SMALL ? 2 : 1;
+    static constexpr int kStore = SMALL ? kStream : kThrough;
+    static constexpr uint32_t kChunk = SMALL ? 8 : 9;
+    static constexpr uint32_t kCoords = kRows * kWaveCoords;
+};
+
 struct ApplyArgs {
     float *x;
     const uint32_t *bits;
     float delta;
+    uint32_t n_tiles;   // blocks on the vector path
     size_t d;
-    size_t n_tiles;   // blocks on the vector path, R rows each
 };
 
-// R rows per block, HOLD_KB of LDS reserved (caps the blocks per compute unit), LOADS_FIRST: every
-// load of the block is issued before the first result is waited for
-template <int R, int HOLD_KB, bool LOADS_FIRST>
-__global__ __launch_bounds__(kBlock) void apply_kernel(const ApplyArgs a) {
-    reserve_lds<HOLD_KB>(a.d == ~(size_t)0, reinterpret_cast<uint32_t *>(a.x));
-    const int tid = threadIdx.x;
-    const size_t tile = blockIdx.x;
-    if (tile < a.n_tiles) {
-        size_t q[R];
-        f32x4 xv[R];
-        uint32_t word[R];
+template <bool SMALL>
+__global__ __launch_bounds__(kWave) void apply_kernel(const ApplyArgs a) {
+    using S = ApplyShape<SMALL>;
+    const uint32_t lane = threadIdx.x;
+    if (blockIdx.x < a.n_tiles) {
+        const size_t tile = die_tile<S::kChunk>(blockIdx.x, a.n_tiles);
+        const uint32_t *const bits = a.bits + tile * (S::kCoords / 32);
+        const Window xw = window(a.x, tile * (S::kCoords * sizeof(float)), S::kCoords * sizeof(float));
+        f32x4 xv[S::kRows];
+        uint32_t word[S::kRows];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            q[r] = (tile * R + r) * kBlock + tid;
-            xv[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + q[r]);
-            word[r] = a.bits[q[r] >> 3];   // 8 lanes share a word
+        for (int r = 0; r < S::kRows; ++r) {
+            word[r] = bits[(r * kWave + lane) >> 3];   // 8 lanes share a word
+            xv[r] = ld_quad(xw, (r * kWave + lane) * 16);
         }
-        if (LOADS_FIRST) __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const uint32_t nib = word[r] >> ((tid & 7) * 4);
+        for (int r = 0; r < S::kRows; ++r) {
+            const uint32_t nib = word[r] >> ((lane & 7) * 4);
             f32x4 v = xv[r];
             v.x = step(v.x, a.delta, nib & 1u);
             v.y = step(v.y, a.delta, nib & 2u);
             v.z = step(v.z, a.delta, nib & 4u);
             v.w = step(v.w, a.delta, nib & 8u);
-            st_stream(reinterpret_cast<f32x4 *>(a.x) + q[r], v);
+            st_quad<S::kStore>(xw, (r * kWave + lane) * 16, v);
         }
         return;
     }
-    const size_t i = a.n_tiles * (size_t)(R * kRowCoords) + (tile - a.n_tiles) * kBlock + tid;
+    const size_t i = a.n_tiles * (size_t)S::kCoords + (size_t)(blockIdx.x - a.n_tiles) * kWave + lane;
     if (i < a.d) {
         const bool neg = (a.bits[i >> 5] >> (i & 31)) & 1u;
         a.x[i] = step(a.x[i], a.delta, neg);
@@ -468,49 +481,43 @@ __global__ __launch_bounds__(64) void vote_sum_word_kernel(const VoteSumArgs a) 
         if (wi * 32 + i < a.d) a.sums[wi * 32 + i] = (int8_t)(out[i >> 2] >> (8 * (i & 3)));
 }
 
-// sum_apply, copy, and Welford's update and sigma (stats_kernels.hpp) run as one-wave blocks of one row on
-// vectors that no cache holds: a finished wave's slot is refilled at once, and no cap on the resident
-// blocks is needed.  Against blocks of four waves with one to four rows, capped at some sizes, as launched
-// before (us): copy 25.6 M floats 32.1 / 33.9, 138 M 168 / 174, 600 M 719 / 738; sum apply 35.9 / 37.4,
-// 186 / 194, 801 / 842; sigma 32.2 / 33.7, 166 / 176, 714 / 777.  Cached vectors like fewer, larger blocks
-// (1.1 M: copy 2.3 / 2.8, sum apply 2.9 / 3.3).  The kernels that read shared words of bits (apply, ternary
-// apply) gain nothing from it: 25.6 M 33.4 against 33.1 and 34.0 against 33.4.
-constexpr int kWaveCoords = kWave * kQuad;
-
 struct SumApplyArgs {
     float *x;
     const int8_t *sums;
     float delta;
+    uint32_t n_tiles;
     size_t d;
-    size_t n_tiles;
 };
 
-template <int BLOCK, int R>
-__global__ __launch_bounds__(BLOCK) void sum_apply_kernel(const SumApplyArgs a) {
-    const int tid = threadIdx.x;
-    const size_t tile = blockIdx.x;
-    if (tile < a.n_tiles) {
-        size_t q[R];
-        f32x4 xv[R];
-        uint32_t sw[R];
+// in the shapes of apply_kernel
+template <bool SMALL>
+__global__ __launch_bounds__(kWave) void sum_apply_kernel(const SumApplyArgs a) {
+    using S = ApplyShape<SMALL>;
+    const uint32_t lane = threadIdx.x;
+    if (blockIdx.x < a.n_tiles) {
+        const size_t tile = die_tile<S::kChunk>(blockIdx.x, a.n_tiles);
+        const uint32_t *const sums = reinterpret_cast<const uint32_t *>(a.sums + tile * S::kCoords);
+        const Window xw = window(a.x, tile * (S::kCoords * sizeof(float)), S::kCoords * sizeof(float));
+        f32x4 xv[S::kRows];
+        uint32_t sw[S::kRows];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            q[r] = (tile * R + r) * BLOCK + tid;
-            xv[r] = ld_stream(reinterpret_cast<const f32x4 *>(a.x) + q[r]);
-            sw[r] = ld_stream(reinterpret_cast<const uint32_t *>(a.sums) + q[r]);
+        for (int r = 0; r < S::kRows; ++r) {
+            sw[r] = ld_stream(sums + r * kWave + lane);
+            xv[r] = ld_quad(xw, (r * kWave + lane) * 16);
         }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
+        for (int r = 0; r < S::kRows; ++r) {
             f32x4 v = xv[r];
             v.x = step_sum(v.x, a.delta, (int)(int8_t)(sw[r] & 0xFFu));
             v.y = step_sum(v.y, a.delta, (int)(int8_t)((sw[r] >> 8) & 0xFFu));
             v.z = step_sum(v.z, a.delta, (int)(int8_t)((sw[r] >> 16) & 0xFFu));
             v.w = step_sum(v.w, a.delta, (int)(int8_t)(sw[r] >> 24));
-            st_stream(reinterpret_cast<f32x4 *>(a.x) + q[r], v);
+            st_quad<S::kStore>(xw, (r * kWave + lane) * 16, v);
         }
         return;
     }
-    const size_t i = a.n_tiles * (size_t)(R * BLOCK * kQuad) + (tile - a.n_tiles) * BLOCK + tid;
+    const size_t i = a.n_tiles * (size_t)S::kCoords + (size_t)(blockIdx.x - a.n_tiles) * kWave + lane;
     if (i < a.d) a.x[i] = step_sum(a.x[i], a.delta, (int)a.sums[i]);
 }
 
@@ -522,16 +529,14 @@ struct CopyArgs {
     size_t n_vec;
 };
 
-template <int BLOCK, int R>
-__global__ __launch_bounds__(BLOCK) void copy_kernel(const CopyArgs a) {
-    const size_t base = (size_t)blockIdx.x * (BLOCK * R) + threadIdx.x;
-    f32x4 v[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-        if (base + r * BLOCK < a.n_vec) v[r] = ld_stream(a.src + base + r * BLOCK);
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-        if (base + r * BLOCK < a.n_vec) st_stream(a.dst + base + r * BLOCK, v[r]);
+// One row a wave, read by address and written through: 1.1 M floats 2.4 us against 2.6 for the L2's own write-back (and
+// four-wave blocks of two rows), 60 M 71.8 / 73.2, 138 M 164.3 / 167.1, 390 M 465 / 469.
+__global__ __launch_bounds__(kWave) void copy_kernel(const CopyArgs a) {
+    const size_t first = blockIdx.x * (size_t)kWave;
+    const size_t left = a.n_vec - first;
+    const uint32_t lane = threadIdx.x;
+    const Window to = window(a.dst, first * 16, left < kWave ? (uint32_t)left * 16 : kWave * 16);
+    if (lane < left) st_quad<kThrough>(to, lane * 16, ld_stream(a.src + first + lane));
 }
 
 }  // namespace ss

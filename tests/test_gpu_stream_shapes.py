@@ -158,3 +158,35 @@ def test_ternary_pack_around_rules(ss, oracle, d, dtype, momentum):
     assert np.array_equal(bits_np(neg), want_neg) and np.array_equal(bits_np(zero), want_zero)
     if momentum:
         assert_same_floats(m_dev, m, "m")
+
+
+# updates alone, statistics and the copy: two rows a wave below 2^23 coordinates, one above, runs of 256 and 512 tiles a die
+@pytest.mark.parametrize("d", [1, 511, 513, (1 << 20) - 1, (1 << 20) + 515, (1 << 23) - 1, (1 << 23) + 257, (1 << 24) + 300])
+def test_updates_and_statistics_around_rules(ss, oracle, d):
+    x0, words = draw(d, d, "f32", 0.05), ss.packed_bytes(d) // 4
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d)
+    neg = torch.randint(-2**31, 2**31, (words,), dtype=torch.int32, device=DEV, generator=gen)
+    zero = torch.randint(-2**31, 2**31, (words,), dtype=torch.int32, device=DEV, generator=gen)
+    sums = torch.randint(-64, 65, (d,), dtype=torch.int8, device=DEV, generator=gen)
+    bits = [bits_np(t) for t in (neg, zero)]
+    for call, want in ((lambda x: ss.sign_apply(x, neg, 1e-3), lambda x: oracle.sign_apply(x, bits[0], 1e-3)),
+                       (lambda x: ss.sum_apply(x, sums, 1e-3), lambda x: oracle.sum_apply(x, sums.cpu().numpy(), 1e-3)),
+                       (lambda x: ss.ternary_apply(x, neg, zero, 1e-3), lambda x: oracle.ternary_apply(x, bits[0], bits[1], 1e-3))):
+        x_dev, x = x0.clone(), synth.as_numpy(x0).copy()
+        call(x_dev)
+        want(x)
+        assert_same_floats(x_dev, x, "x")
+    for dtype in ("f32", "bf16"):
+        g, mean_dev, m2_dev = draw(d + 1, d, dtype, 0.5), draw(d + 2, d, "f32", 0.2), draw(d + 3, d, "f32", 0.5).square_()
+        mean, m2 = synth.as_numpy(mean_dev).copy(), synth.as_numpy(m2_dev).copy()
+        ss.welford_update(g, mean_dev, m2_dev, 7)
+        oracle.welford_update(synth.as_numpy(g), mean, m2, 7)
+        assert_same_floats(mean_dev, mean, "mean")
+        assert_same_floats(m2_dev, m2, "m2")
+    sigma = torch.full((d,), 9.0, device=DEV)
+    ss.welford_sigma(m2_dev, 7, sigma)
+    assert_same_floats(sigma, oracle.welford_sigma(m2, 7), "sigma")
+    to = torch.full((d + 8,), 9.0, device=DEV)
+    ss.stream_copy(to, x0, d // 4 * 16)
+    assert torch.equal(to[:d // 4 * 4].view(torch.int32), x0[:d // 4 * 4].view(torch.int32)) and bool((to[d // 4 * 4:] == 9).all())

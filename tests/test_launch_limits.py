@@ -103,7 +103,31 @@ def check_refused_steps(rec):
     assert rc == -6 and len(launches) == 1
 
 
-CHECKS = {f.__name__: f for f in (check_large_steps, check_ordinary_steps, check_refused_steps)}
+def check_other_calls(rec):
+    # calls that are not cut go up to the limit of the shape that they take for the longest vectors
+    f, size, vp = ctypes.c_float, ctypes.c_size_t, ctypes.c_void_p
+    d = (1 << 36) - 4096                                # a quarter of a terabyte of gradients
+    for bf16 in (0, 1):
+        rec.shim.record_anew(-1)
+        assert rec.lib.ss_signum_pack(vp(rec.buffer(4 * d)), bf16, None, f(0.9), vp(rec.buffer(d // 8)), size(d), None) == 0
+        assert len(rec.launches()) == 1 and threads(rec.launches()[0]) < 1 << 32
+    d = (1 << 34) - 4096
+    m, words = rec.buffer(4 * d), d // 8
+    rec.shim.record_anew(-1)
+    assert rec.lib.ss_signum_pack(vp(rec.buffer(4 * d)), 0, vp(m), f(0.9), vp(rec.buffer(words)), size(d), None) == 0
+    assert rec.lib.ss_welford_update(vp(rec.buffer(4 * d)), 0, vp(m), vp(rec.buffer(4 * d)), size(3), size(d), None) == 0
+    assert rec.lib.ss_stream_copy(vp(m), vp(rec.buffer(4 * d)), size(4 * d), None) == 0
+    d = (1 << 35) - 4096
+    x, bits = vp(rec.buffer(4 * d)), vp(rec.buffer(d // 8))
+    assert rec.lib.ss_sign_apply(x, bits, f(0.1), size(d), None) == 0
+    assert rec.lib.ss_sum_apply(x, vp(rec.buffer(d)), f(0.1), size(d), None) == 0
+    assert rec.lib.ss_ternary_apply(x, bits, vp(rec.buffer(d // 8)), f(0.1), size(d), None) == 0
+    assert rec.lib.ss_welford_sigma(x, size(3), vp(rec.buffer(4 * d)), size(d), None) == 0
+    assert rec.lib.ss_signum_pack_ternary(vp(rec.buffer(4 * d)), 0, None, f(0.9), f(0.1), bits, vp(rec.buffer(d // 8)), size(d), None) == 0
+    assert len(rec.launches()) == 8 and all(0 < threads(t) < 1 << 32 for t in rec.launches())
+
+
+CHECKS = {f.__name__: f for f in (check_large_steps, check_ordinary_steps, check_refused_steps, check_other_calls)}
 
 
 @pytest.fixture(scope="module")
