@@ -421,17 +421,20 @@ int launch_two(const void *const *g, ss_dtype gdt, float *const *m, int M, float
     return dispatch_vote_apply(packed, M, voted, x, delta, var, d, stream);
 }
 
-// The votes read M buffers at once and are launched as four-wave blocks without a cap up to about
-// 2^27 coordinates.  Above that one-wave blocks, from four workers on, with a cap that leaves fewer waves
-// the more loads each has out (138 M: M = 16 50.0 us against 51.9, 24 70.5 / 75.9, but 8 27.0 / 26.7;
-// 390 M: M = 4 39.4 / 41.6, 8 71.0 / 75.8, 12 100 / 108, 16 132 / 142, 24 188 / 206, but 2 24.0 / 23.1).
-constexpr int kVoteWave = 64;
-// One word a lane instead of four (the *_word_kernels) up to here.  us, word against 128-bit lanes: sums
-// M = 16 10,007 coordinates 3.0 / 5.2, 4.4 M 4.4 / 6.2, 17.6 M 10.0 / 11.4, M = 7 1.1 M 3.0 / 3.8, 4.4 M 4.0 / 4.2, 8.8 M
-// 5.2 / 4.9; quorum M = 16 10,007 2.7 / 5.0, 4.4 M 5.2 / 7.5, 17.6 M 12.6 / 15.8, 40 M 34 / 30, M = 4 4.4 M 2.9 / 3.1, 8.8 M
-// 3.8 / 3.7; vote M = 24 10,007 3.1 / 4.5, 8.8 M 7.1 / 7.5, 17.6 M 12.0 / 11.7.
-inline bool word_lanes(int M, size_t d) { return d < ((size_t)1 << (M >= 9 ? 24 : 22)); }
-constexpr int kVoteHoldKB = 64;   // ss_quorum_vote: two four-wave blocks per unit
+// The votes, sums and quorum votes read M (2 M) buffers at once, in one-wave blocks.  Up to some tens of millions of coordinates
+// nothing is held back and a die takes an eighth of a megabyte of every buffer at a time; beyond, tiles go in order with a cap that
+// leaves fewer waves the more loads each has out.  us, runs / in order and capped / four-wave blocks without runs as launched
+// before: vote M = 3 390 M 31.9 / 32.5 / 32.6, M = 7 25.6 M 5.0 / 5.3 / 5.4, 138 M 23.7 / 24.4 / 25.0, M = 8 17.6 M 4.0 / 4.4 / 5.0, 138 M
+// 26.4 / 26.8 / 27.8, 390 M 71.0 / 67.9 / 75, M = 16 8.8 M 4.1 / 5.1 / 5.4, 25.6 M 9.3 / 11.1 / 11.1, 40 M 14.7 / 15.3 / 15.5, 138 M
+// 48.3 / 46.7 / 52, M = 24 (any) 25.6 M 14.2 / 16.0 / 16.4, 40 M 20.9 / 22.3 / 23.0, 138 M 69.6 / 68.4 / 76.
+constexpr uint32_t kVoteChunk = 7;
+constexpr size_t kVoteRuns = (size_t)1 << 26;   // runs below, capped from here on
+
+// One word a lane instead of four (the *_word_kernels) up to `end`, with up to eight workers a third of it.  us, word / 128-bit lanes: sums
+// M = 16 4.4 M coordinates 4.2 / 5.7, 8.8 M 6.0 / 6.5, 17.6 M 12.7 / 9.9, M = 7 4.4 M 4.0 / 3.7; quorum M = 16 8.8 M 7.6 / 8.5, 17.6 M 17.2 /
+// 14.0, M = 3 4.4 M 2.8 / 2.7; vote M = 24 4.4 M 5.0 / 5.5, 8.8 M 7.1 / 6.6.
+constexpr size_t kSumWords = (size_t)3 << 22, kVoteWords = (size_t)3 << 21;
+inline bool word_lanes(int M, size_t d, size_t end) { return d < (M >= 9 ? end : end / 3); }
 
 template <int M>
 int launch_vote_fixed(const uint32_t *const *packed, uint32_t *voted, size_t d, hipStream_t stream) {
@@ -441,13 +444,20 @@ int launch_vote_fixed(const uint32_t *const *packed, uint32_t *voted, size_t d, 
     a.M = M;
     a.d = d;
     a.n_vec = ss_packed_bytes(d) / 16;
-    constexpr int kHold = M >= 8 ? 20 : 8;
-    const bool waves = M >= 4 && d >= (M >= 12 ? kLargeD / 2 : kLargeD);
-    const size_t block = waves ? kVoteWave : ss::kBlock;
+    // Up to three workers, little to wait for: four-wave blocks, and from 2^26 coordinates on runs (8.8 M M = 3 2.4 us in runs against 2.3,
+    // 25.6 M 3.3 / 3.1, 390 M 30.9 / 31.6).  Up to eleven the cap pays later.
+    const bool few = M < 4 && d < kVoteRuns;
+    const size_t block = few ? ss::kBlock : ss::kWave;
     const size_t grid = (a.n_vec + block - 1) / block;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    if (waves) return launch(ss::vote_kernel<M, kVoteWave, kHold>, grid, 0, stream, a, kVoteWave);
-    return launch(ss::vote_kernel<M, ss::kBlock, 0>, grid, 0, stream, a);
+    if constexpr (M < 4) {
+        if (few) return launch(ss::vote_kernel<M, ss::kBlock, 0, 0>, grid, 0, stream, a);
+        if (d < ((size_t)1 << 34)) return launch(ss::vote_kernel<M, ss::kWave, 0, kVoteChunk>, grid, 0, stream, a, ss::kWave);
+        return launch(ss::vote_kernel<M, ss::kWave, 0, 0>, grid, 0, stream, a, ss::kWave);
+    } else {
+        if (d < (M < 12 ? kVoteRuns << 2 : kVoteRuns)) return launch(ss::vote_kernel<M, ss::kWave, 0, kVoteChunk>, grid, 0, stream, a, ss::kWave);
+        return launch(ss::vote_kernel<M, ss::kWave, M >= 8 ? 20 : 8, 0>, grid, 0, stream, a, ss::kWave);
+    }
 }
 
 int launch_vote_any(const uint32_t *const *packed, int M, uint32_t *voted, size_t d, hipStream_t stream) {
@@ -457,15 +467,40 @@ int launch_vote_any(const uint32_t *const *packed, int M, uint32_t *voted, size_
     a.M = M;
     a.d = d;
     a.n_vec = ss_packed_bytes(d) / 16;
-    if (word_lanes(M, d)) return launch(ss::vote_word_kernel, (4 * a.n_vec + 63) / 64, 0, stream, a, 64);
-    const size_t grid = (a.n_vec + kVoteWave - 1) / kVoteWave;
+    if (word_lanes(M, d, kVoteWords)) return launch(ss::vote_word_kernel, (4 * a.n_vec + 63) / 64, 0, stream, a, 64);
+    const size_t grid = (a.n_vec + ss::kWave - 1) / ss::kWave;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    // one-wave blocks (25.6 M, M = 24: 14.5 us against 15.3 for four-wave blocks), with more LDS held back, so fewer of
-    // them per unit, from 2^26 coordinates on.  us, 8 against 16 KB: M = 20 25.6 M 13.8 / 15.1, 40 M 21.3 / 22.1,
-    // 67 M 31.4 / 31.8, 138 M 64.6 / 63.6, 390 M 171 / 165; M = 64 25.6 M 37.9 / 39.4, 40 M 58.6 / 59.7, 67 M 93.9 / 93.1,
-    // 138 M 193 / 189, 390 M 523 / 500; M = 24 and 33 alike
-    if (d >= kLargeD / 4) return launch(ss::vote_kernel_any<kVoteWave, 16>, grid, 0, stream, a, kVoteWave);
-    return launch(ss::vote_kernel_any<kVoteWave, 8>, grid, 0, stream, a, kVoteWave);
+    if (d < kVoteRuns) return launch(ss::vote_kernel_any<0, kVoteChunk>, grid, 0, stream, a, ss::kWave);
+    return launch(ss::vote_kernel_any<16, 0>, grid, 0, stream, a, ss::kWave);
+}
+
+// sums: in runs the L2 writes back, beyond they are written through with 7 KB held back beside the tile's 9.  us, runs / capped / before:
+// M = 3 17.6 M 4.5 / 4.5 / 5.3, 390 M 88.9 / 82.7 / 89.4, M = 7 25.6 M 7.3 / 10.5 / 9.3, 138 M 44.3 / 43.6 / 47.2, M = 16 17.6 M 9.9 /
+// 11.5 / 12.7, 40 M 21.6 / 23.4 / 23.7, 138 M 69.6 / 68.7 / 72.2, 390 M 193 / 184.5 / 192
+template <int P>
+int launch_vote_sum(const ss::VoteSumArgs &a, size_t grid, hipStream_t stream) {
+    if (a.d < kVoteRuns) return launch(ss::vote_sum_kernel<P, 0, ss::kStream, kVoteChunk - 1>, grid, 0, stream, a, ss::kWave);
+    return launch(ss::vote_sum_kernel<P, 7, ss::kThrough, 0>, grid, 0, stream, a, ss::kWave);
+}
+
+// quorum: us, runs / capped (26 KB; up to four workers 16) / four-wave blocks, four workers a batch: M = 7 4.4 M 3.6 / 3.6 / 4.1, 17.6 M 7.4 /
+// 8.7 / 7.6, 138 M 47.2 / 46.1 / 50.7, M = 16 17.6 M 13.8 / 16.8 / 15.8, 25.6 M 19.5 / 23.1 / 20.9, 60 M 44.2 / - / 46.0, 138 M 100.8 /
+// 95.8 / 104-115, 390 M 284 / 268 / 279, M = 24 25.6 M 27.9 / 33.1 / 30.4; M = 3 17.6 M 4.5 / 4.5 / 4.3, 25.6 M 5.7 / 6.5 / 5.6, 138 M
+// 24.0 / 24.5 / 28.0, 390 M 62.4 / 60.6 / 70.2
+template <int P>
+int launch_quorum_vote(const ss::QuorumVoteArgs &a, hipStream_t stream) {
+    const bool few = P <= 2 && a.d < kVoteRuns;
+    const size_t block = few ? ss::kBlock : ss::kWave;
+    const size_t grid = (a.n_vec + block - 1) / block;
+    if (grid > kMaxGrid) return SS_ERR_ARG;
+    if constexpr (P <= 2) {
+        if (few) return launch(ss::quorum_vote_kernel<P, ss::kBlock, 0, 0>, grid, 0, stream, a);
+        return launch(ss::quorum_vote_kernel<P, ss::kWave, 16, 0>, grid, 0, stream, a, ss::kWave);
+    } else {
+        if (a.d < kVoteRuns) return launch(ss::quorum_vote_kernel<P, ss::kWave, 0, kVoteChunk>, grid, 0, stream, a, ss::kWave);
+        if (a.M <= 4) return launch(ss::quorum_vote_kernel<P, ss::kWave, 16, 0>, grid, 0, stream, a, ss::kWave);
+        return launch(ss::quorum_vote_kernel<P, ss::kWave, 26, 0>, grid, 0, stream, a, ss::kWave);
+    }
 }
 
 // launch helpers of the ternary (vote with abstention) kernels
@@ -755,35 +790,24 @@ int ss_vote_sum(const uint32_t *const *packed, int M, int8_t *sums, size_t d, vo
     a.M = M;
     a.d = d;
     a.n_vec = ss_packed_bytes(d) / 16;
-    const size_t grid = (a.n_vec + ss::kBlock - 1) / ss::kBlock;
+    const size_t grid = (a.n_vec + ss::kWave - 1) / ss::kWave;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (word_lanes(M, d)) {
+    if (word_lanes(M, d, kSumWords)) {
         const size_t blocks = (4 * a.n_vec + 63) / 64;
         const int planes = count_planes(M);
         if (planes <= 3) return launch(ss::vote_sum_word_kernel<3>, blocks, 0, stream, a, 64);
         if (planes <= 5) return launch(ss::vote_sum_word_kernel<5>, blocks, 0, stream, a, 64);
         return launch(ss::vote_sum_word_kernel<7>, blocks, 0, stream, a, 64);
     }
-    // beyond cache-resident sizes two blocks per unit instead of four (the tile in LDS already
-    // limits them to four): +3 % at d = 138 M, +9 % at 1.5 G
-    constexpr int kVoteSumHoldKB = 24;
-    const bool capped = d >= ((size_t)1 << 27);
     switch (count_planes(M)) {
-        case 1: return capped ? launch(ss::vote_sum_kernel<1, kVoteSumHoldKB>, grid, 0, stream, a)
-                              : launch(ss::vote_sum_kernel<1, 0>, grid, 0, stream, a);
-        case 2: return capped ? launch(ss::vote_sum_kernel<2, kVoteSumHoldKB>, grid, 0, stream, a)
-                              : launch(ss::vote_sum_kernel<2, 0>, grid, 0, stream, a);
-        case 3: return capped ? launch(ss::vote_sum_kernel<3, kVoteSumHoldKB>, grid, 0, stream, a)
-                              : launch(ss::vote_sum_kernel<3, 0>, grid, 0, stream, a);
-        case 4: return capped ? launch(ss::vote_sum_kernel<4, kVoteSumHoldKB>, grid, 0, stream, a)
-                              : launch(ss::vote_sum_kernel<4, 0>, grid, 0, stream, a);
-        case 5: return capped ? launch(ss::vote_sum_kernel<5, kVoteSumHoldKB>, grid, 0, stream, a)
-                              : launch(ss::vote_sum_kernel<5, 0>, grid, 0, stream, a);
-        case 6: return capped ? launch(ss::vote_sum_kernel<6, kVoteSumHoldKB>, grid, 0, stream, a)
-                              : launch(ss::vote_sum_kernel<6, 0>, grid, 0, stream, a);
-        default: return capped ? launch(ss::vote_sum_kernel<7, kVoteSumHoldKB>, grid, 0, stream, a)
-                               : launch(ss::vote_sum_kernel<7, 0>, grid, 0, stream, a);
+        case 1: return launch_vote_sum<1>(a, grid, stream);
+        case 2: return launch_vote_sum<2>(a, grid, stream);
+        case 3: return launch_vote_sum<3>(a, grid, stream);
+        case 4: return launch_vote_sum<4>(a, grid, stream);
+        case 5: return launch_vote_sum<5>(a, grid, stream);
+        case 6: return launch_vote_sum<6>(a, grid, stream);
+        default: return launch_vote_sum<7>(a, grid, stream);
     }
 }
 
@@ -955,33 +979,22 @@ int ss_quorum_vote(const uint32_t *const *neg, const uint32_t *const *zero, int 
     a.quorum = quorum > M + 1 ? M + 1 : quorum;   // any quorum above M can never be met: same answers
     a.d = d;
     a.n_vec = ss_packed_bytes(d) / 16;
-    const size_t grid = (a.n_vec + ss::kBlock - 1) / ss::kBlock;
-    if (grid > kMaxGrid) return SS_ERR_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (word_lanes(M, d)) {
+    if (word_lanes(M, d, kSumWords)) {
         const size_t blocks = (4 * a.n_vec + 63) / 64;
         const int planes = count_planes(M);
         if (planes <= 3) return launch(ss::quorum_word_kernel<3>, blocks, 0, stream, a, 64);
         if (planes <= 5) return launch(ss::quorum_word_kernel<5>, blocks, 0, stream, a, 64);
         return launch(ss::quorum_word_kernel<7>, blocks, 0, stream, a, 64);
     }
-    // beyond cache-resident sizes two blocks per unit instead of eight: +2-4 % at d = 138 M, +9 % at 1.5 G
-    const bool capped = d >= ((size_t)1 << 27);
     switch (count_planes(M)) {
-        case 1: return capped ? launch(ss::quorum_vote_kernel<1, kVoteHoldKB>, grid, 0, stream, a)
-                              : launch(ss::quorum_vote_kernel<1, 0>, grid, 0, stream, a);
-        case 2: return capped ? launch(ss::quorum_vote_kernel<2, kVoteHoldKB>, grid, 0, stream, a)
-                              : launch(ss::quorum_vote_kernel<2, 0>, grid, 0, stream, a);
-        case 3: return capped ? launch(ss::quorum_vote_kernel<3, kVoteHoldKB>, grid, 0, stream, a)
-                              : launch(ss::quorum_vote_kernel<3, 0>, grid, 0, stream, a);
-        case 4: return capped ? launch(ss::quorum_vote_kernel<4, kVoteHoldKB>, grid, 0, stream, a)
-                              : launch(ss::quorum_vote_kernel<4, 0>, grid, 0, stream, a);
-        case 5: return capped ? launch(ss::quorum_vote_kernel<5, kVoteHoldKB>, grid, 0, stream, a)
-                              : launch(ss::quorum_vote_kernel<5, 0>, grid, 0, stream, a);
-        case 6: return capped ? launch(ss::quorum_vote_kernel<6, kVoteHoldKB>, grid, 0, stream, a)
-                              : launch(ss::quorum_vote_kernel<6, 0>, grid, 0, stream, a);
-        default: return capped ? launch(ss::quorum_vote_kernel<7, kVoteHoldKB>, grid, 0, stream, a)
-                               : launch(ss::quorum_vote_kernel<7, 0>, grid, 0, stream, a);
+        case 1: return launch_quorum_vote<1>(a, stream);
+        case 2: return launch_quorum_vote<2>(a, stream);
+        case 3: return launch_quorum_vote<3>(a, stream);
+        case 4: return launch_quorum_vote<4>(a, stream);
+        case 5: return launch_quorum_vote<5>(a, stream);
+        case 6: return launch_quorum_vote<6>(a, stream);
+        default: return launch_quorum_vote<7>(a, stream);
     }
 }
 

@@ -224,7 +224,7 @@ struct QuorumVoteArgs {
 //     answer "-"  iff  S <= -Q  iff  t >= M + Q
 //     answer  0   iff  |S| < Q  iff  M - Q < t < M + Q
 // which are two comparisons of t with constants, done from the lowest plane up.
-constexpr int kQuorumBatch = 4;    // workers (two planes each) whose words are loaded together
+constexpr int kQuorumBatch = 8;    // workers (two planes each) whose words are loaded together
 
 __device__ __forceinline__ u32x4 splat(uint32_t v) { return u32x4{v, v, v, v}; }
 
@@ -240,14 +240,14 @@ __device__ __forceinline__ u32x4 planes_ge(const u32x4 (&t)[N], int c) {
 }
 
 // NB workers' planes loaded together (no test between the loads), then counted
-template <int P, int NB>
-__device__ __forceinline__ void quorum_batch(const uint32_t *const *neg, const uint32_t *const *zero, size_t u,
+template <int P, int NB, typename At>
+__device__ __forceinline__ void quorum_batch(const uint32_t *const *neg, const uint32_t *const *zero, const At &at,
                                              u32x4 (&n)[P], u32x4 (&z)[P]) {
     u32x4 nw[NB], zw[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-        nw[j] = ld_stream(reinterpret_cast<const u32x4 *>(neg[j]) + u);
-        zw[j] = ld_stream(reinterpret_cast<const u32x4 *>(zero[j]) + u);
+        nw[j] = at.load(neg[j]);
+        zw[j] = at.load(zero[j]);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -265,27 +265,33 @@ __device__ __forceinline__ void quorum_batch(const uint32_t *const *neg, const u
     }
 }
 
+// the m <= NMAX workers that the full batches leave over, as one batch of exactly that size
+template <int P, int NMAX, typename At>
+__device__ __forceinline__ void quorum_rest(const uint32_t *const *neg, const uint32_t *const *zero, int m, const At &at,
+                                            u32x4 (&n)[P], u32x4 (&z)[P]) {
+    if (m == NMAX) {
+        quorum_batch<P, NMAX>(neg, zero, at, n, z);
+    } else if constexpr (NMAX > 1) {
+        quorum_rest<P, NMAX - 1>(neg, zero, m, at, n, z);
+    }
+}
+
 // P = number of binary planes of n and z (M < 2^P); t = 2 n + z <= 2 M needs one more.
 // HOLD_KB: LDS reserved to cap the blocks per compute unit.
-template <int P, int HOLD_KB>
-__global__ __launch_bounds__(kBlock) void quorum_vote_kernel(const QuorumVoteArgs a) {
+template <int P, int BLOCK, int HOLD_KB, uint32_t CHUNK>
+__global__ __launch_bounds__(BLOCK) void quorum_vote_kernel(const QuorumVoteArgs a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.voted_neg);
     constexpr int kCountPlanes = P;
     constexpr int kTotalPlanes = P + 1;
-    static_assert(kQuorumBatch == 4, "the remainder switch below lists 1 .. 3");
-    const size_t u = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    const Group<CHUNK, BLOCK> at(a.n_vec);
+    const size_t u = at.u;
     if (u >= a.n_vec) return;
     u32x4 n[kCountPlanes], z[kCountPlanes];
 #pragma unroll
     for (int k = 0; k < kCountPlanes; ++k) n[k] = z[k] = splat(0u);
     int w0 = 0;
-    for (; w0 + kQuorumBatch <= a.M; w0 += kQuorumBatch) quorum_batch<P, kQuorumBatch>(a.neg + w0, a.zero + w0, u, n, z);
-    switch (a.M - w0) {
-        case 1: quorum_batch<P, 1>(a.neg + w0, a.zero + w0, u, n, z); break;
-        case 2: quorum_batch<P, 2>(a.neg + w0, a.zero + w0, u, n, z); break;
-        case 3: quorum_batch<P, 3>(a.neg + w0, a.zero + w0, u, n, z); break;
-        default: break;
-    }
+    for (; w0 + kQuorumBatch <= a.M; w0 += kQuorumBatch) quorum_batch<P, kQuorumBatch>(a.neg + w0, a.zero + w0, at, n, z);
+    quorum_rest<P, kQuorumBatch - 1>(a.neg + w0, a.zero + w0, a.M - w0, at, n, z);
     // t = 2 n + z
     u32x4 t[kTotalPlanes];
     t[0] = z[0];

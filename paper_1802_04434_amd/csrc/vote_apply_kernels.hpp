@@ -78,28 +78,38 @@ __device__ __forceinline__ uint32_t live_mask(size_t wi, size_t d) {
     return (1u << (unsigned)(d - lo)) - 1u;
 }
 
-template <int M, int BLOCK, int HOLD_KB>
+// Which 128-bit group of words a lane takes.  With runs of tiles a die (CHUNK > 0) the buffers are shorter than
+// 4 GiB and are addressed by 32-bit offsets.
+template <uint32_t CHUNK, int BLOCK = kWave>
+struct Group {
+    size_t u;
+    __device__ __forceinline__ explicit Group(size_t n_vec)
+        : u(die_tile<CHUNK>(blockIdx.x, (uint32_t)(n_vec / BLOCK)) * (size_t)BLOCK + threadIdx.x) {}
+    __device__ __forceinline__ u32x4 load(const uint32_t *base) const {
+        if constexpr (CHUNK > 0)
+            return ld_stream(reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(base) + (uint32_t)((uint32_t)u * 16u)));
+        else return ld_stream(reinterpret_cast<const u32x4 *>(base) + u);
+    }
+};
+
+template <int M, int BLOCK, int HOLD_KB, uint32_t CHUNK>
 __global__ __launch_bounds__(BLOCK) void vote_kernel(const VoteArgs<M> a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.voted);
-    const size_t u = (size_t)blockIdx.x * BLOCK + threadIdx.x;
+    const Group<CHUNK, BLOCK> at(a.n_vec);
+    const size_t u = at.u;
     if (u >= a.n_vec) return;
     u32x4 in[M];
 #pragma unroll
-    for (int w = 0; w < M; ++w) in[w] = ld_stream(reinterpret_cast<const u32x4 *>(a.packed[w]) + u);
+    for (int w = 0; w < M; ++w) in[w] = at.load(a.packed[w]);
+    if constexpr (CHUNK > 0) __builtin_amdgcn_sched_barrier(0);
     uint32_t col[M];
     u32x4 out;
 #pragma unroll
-    for (int w = 0; w < M; ++w) col[w] = in[w].x;
-    out.x = majority_word<M>(col) & live_mask(4 * u + 0, a.d);
+    for (int c = 0; c < 4; ++c) {
 #pragma unroll
-    for (int w = 0; w < M; ++w) col[w] = in[w].y;
-    out.y = majority_word<M>(col) & live_mask(4 * u + 1, a.d);
-#pragma unroll
-    for (int w = 0; w < M; ++w) col[w] = in[w].z;
-    out.z = majority_word<M>(col) & live_mask(4 * u + 2, a.d);
-#pragma unroll
-    for (int w = 0; w < M; ++w) col[w] = in[w].w;
-    out.w = majority_word<M>(col) & live_mask(4 * u + 3, a.d);
+        for (int w = 0; w < M; ++w) col[w] = in[w][c];
+        out[c] = majority_word<M>(col) & live_mask(4 * u + c, a.d);
+    }
     st_stream(reinterpret_cast<u32x4 *>(a.voted) + u, out);
 }
 
@@ -109,11 +119,11 @@ constexpr int kPlanes = 7;   // counts up to 64 < 2^7
 
 // NB workers' 128-bit groups loaded together (no test between the loads: all NB are in flight
 // before the first is used), then rippled into the P count planes with half adders
-template <int P, int NB>
-__device__ __forceinline__ void ripple_batch(const uint32_t *const *packed, size_t u, u32x4 (&plane)[P]) {
+template <int P, int NB, uint32_t CHUNK>
+__device__ __forceinline__ void ripple_batch(const uint32_t *const *packed, const Group<CHUNK> &at, u32x4 (&plane)[P]) {
     u32x4 in[NB];
 #pragma unroll
-    for (int j = 0; j < NB; ++j) in[j] = ld_stream(reinterpret_cast<const u32x4 *>(packed[j]) + u);
+    for (int j = 0; j < NB; ++j) in[j] = at.load(packed[j]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
@@ -128,33 +138,34 @@ __device__ __forceinline__ void ripple_batch(const uint32_t *const *packed, size
 }
 
 // all M workers: full batches of NB, then the remaining 1 .. NB-1 as one batch of exactly that size
-template <int P, int NB>
-__device__ __forceinline__ void ripple_all(const uint32_t *const *packed, int M, size_t u, u32x4 (&plane)[P]) {
+template <int P, int NB, uint32_t CHUNK>
+__device__ __forceinline__ void ripple_all(const uint32_t *const *packed, int M, const Group<CHUNK> &at, u32x4 (&plane)[P]) {
     static_assert(NB == 8, "the remainder switch below lists 1 .. 7");
     int w0 = 0;
-    for (; w0 + NB <= M; w0 += NB) ripple_batch<P, NB>(packed + w0, u, plane);
+    for (; w0 + NB <= M; w0 += NB) ripple_batch<P, NB>(packed + w0, at, plane);
     switch (M - w0) {
-        case 1: ripple_batch<P, 1>(packed + w0, u, plane); break;
-        case 2: ripple_batch<P, 2>(packed + w0, u, plane); break;
-        case 3: ripple_batch<P, 3>(packed + w0, u, plane); break;
-        case 4: ripple_batch<P, 4>(packed + w0, u, plane); break;
-        case 5: ripple_batch<P, 5>(packed + w0, u, plane); break;
-        case 6: ripple_batch<P, 6>(packed + w0, u, plane); break;
-        case 7: ripple_batch<P, 7>(packed + w0, u, plane); break;
+        case 1: ripple_batch<P, 1>(packed + w0, at, plane); break;
+        case 2: ripple_batch<P, 2>(packed + w0, at, plane); break;
+        case 3: ripple_batch<P, 3>(packed + w0, at, plane); break;
+        case 4: ripple_batch<P, 4>(packed + w0, at, plane); break;
+        case 5: ripple_batch<P, 5>(packed + w0, at, plane); break;
+        case 6: ripple_batch<P, 6>(packed + w0, at, plane); break;
+        case 7: ripple_batch<P, 7>(packed + w0, at, plane); break;
         default: break;
     }
 }
 
-template <int BLOCK, int HOLD_KB>
-__global__ __launch_bounds__(BLOCK) void vote_kernel_any(const VoteArgs<64> a) {
+template <int HOLD_KB, uint32_t CHUNK>
+__global__ __launch_bounds__(kWave) void vote_kernel_any(const VoteArgs<64> a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.voted);
-    const size_t u = (size_t)blockIdx.x * BLOCK + threadIdx.x;
+    const Group<CHUNK> at(a.n_vec);
+    const size_t u = at.u;
     if (u >= a.n_vec) return;
     const int T = a.M / 2 + 1;
     u32x4 plane[kPlanes];
 #pragma unroll
     for (int k = 0; k < kPlanes; ++k) plane[k] = u32x4{0, 0, 0, 0};
-    ripple_all<kPlanes, 8>(a.packed, a.M, u, plane);
+    ripple_all<kPlanes, 8>(a.packed, a.M, at, plane);
     u32x4 ge = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
 #pragma unroll
     for (int k = 0; k < kPlanes; ++k) ge = ((T >> k) & 1) ? (plane[k] & ge) : (plane[k] | ge);
@@ -395,20 +406,22 @@ constexpr int kVoteSumBatch = 8;           // workers whose words are loaded tog
 constexpr int kVoteSumLaneBytes = 128;     // a lane's 128 coordinates give 128 int8 sums
 constexpr int kVoteSumLdsStride = 144;     // ... kept 144 bytes apart in LDS (spreads the banks)
 
-// P = number of binary planes of the count of "-" votes: counts up to M < 2^P
-template <int P, int HOLD_KB>
-__global__ __launch_bounds__(kBlock) void vote_sum_kernel(const VoteSumArgs a) {
-    reserve_lds<HOLD_KB>(a.d == ~(size_t)0, reinterpret_cast<uint32_t *>(a.sums));   // on top of the tile below
-    __shared__ __align__(16) unsigned char tile[kBlock * kVoteSumLdsStride];
-    const int tid = threadIdx.x;
-    const size_t u = (size_t)blockIdx.x * kBlock + tid;
+// P = number of binary planes of the count of "-" votes: counts up to M < 2^P.  One-wave blocks; HOLD_KB of LDS on top of the tile,
+// STORE and CHUNK by the size of the vector (ss_vote_sum)
+template <int P, int HOLD_KB, int STORE, uint32_t CHUNK>
+__global__ __launch_bounds__(kWave) void vote_sum_kernel(const VoteSumArgs a) {
+    reserve_lds<HOLD_KB>(a.d == ~(size_t)0, reinterpret_cast<uint32_t *>(a.sums));
+    __shared__ __align__(16) unsigned char tile[kWave * kVoteSumLdsStride];
+    const uint32_t lane = threadIdx.x;
+    Group<CHUNK> at(a.n_vec);
+    const size_t base = (at.u - lane) * kVoteSumLaneBytes;
     // lanes beyond the last group (last block only) re-read the last group: their coordinates
     // lie at or beyond d and are never stored
-    const size_t ul = u < a.n_vec ? u : a.n_vec - 1;
+    if (at.u >= a.n_vec) at.u = a.n_vec - 1;
     u32x4 plane[P];
 #pragma unroll
     for (int k = 0; k < P; ++k) plane[k] = u32x4{0, 0, 0, 0};
-    ripple_all<P, kVoteSumBatch>(a.packed, a.M, ul, plane);
+    ripple_all<P, kVoteSumBatch>(a.packed, a.M, at, plane);
     // planes -> one int8 sum per coordinate: the lane's 128 sums go to LDS as eight 16-byte pieces
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -421,26 +434,23 @@ __global__ __launch_bounds__(kBlock) void vote_sum_kernel(const VoteSumArgs a) {
             for (int k = 0; k < P; ++k) counts += spread_nibble((plane[k][q >> 1] >> shift) & 0xFu) << k;
             piece[e] = sums_word(counts, a.M);
         }
-        *reinterpret_cast<u32x4 *>(tile + tid * kVoteSumLdsStride + 16 * q) = piece;
+        *reinterpret_cast<u32x4 *>(tile + lane * kVoteSumLdsStride + 16 * q) = piece;
     }
     __syncthreads();
-    // ... and leave in the order of the coordinates: a wave's store is 1024 contiguous bytes
-    const size_t base = (size_t)blockIdx.x * (kBlock * kVoteSumLaneBytes);
-    if (base + (size_t)kBlock * kVoteSumLaneBytes <= a.d) {      // every block but the last: no test per store
-        u32x4 piece[8];
+    // ... and leave in the order of the coordinates: a store is 1024 contiguous bytes
+    constexpr uint32_t kBytes = kWave * kVoteSumLaneBytes;
+    if (base + kBytes <= a.d) {      // every block but the last: no test per store
+        const Window to = window(a.sums, base, kBytes);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int c = j * kBlock + tid;              // 16-byte piece within the block's output
-            piece[j] = *reinterpret_cast<const u32x4 *>(tile + (c >> 3) * kVoteSumLdsStride + 16 * (c & 7));
+            const uint32_t c = j * kWave + lane;              // 16-byte piece within the block's output
+            st_quad<STORE>(to, c * 16, *reinterpret_cast<const f32x4 *>(tile + (c >> 3) * kVoteSumLdsStride + 16 * (c & 7)));
         }
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            st_stream(reinterpret_cast<u32x4 *>(a.sums + base + 16 * (size_t)(j * kBlock + tid)), piece[j]);
         return;
     }
 #pragma unroll 1
     for (int j = 0; j < 8; ++j) {
-        const int c = j * kBlock + tid;
+        const int c = j * kWave + lane;
         const u32x4 piece = *reinterpret_cast<const u32x4 *>(tile + (c >> 3) * kVoteSumLdsStride + 16 * (c & 7));
         const size_t first = base + 16 * (size_t)c;
         if (first + 16 <= a.d) {

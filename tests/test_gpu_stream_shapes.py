@@ -190,3 +190,39 @@ def test_updates_and_statistics_around_rules(ss, oracle, d):
     to = torch.full((d + 8,), 9.0, device=DEV)
     ss.stream_copy(to, x0, d // 4 * 16)
     assert torch.equal(to[:d // 4 * 4].view(torch.int32), x0[:d // 4 * 4].view(torch.int32)) and bool((to[d // 4 * 4:] == 9).all())
+
+
+# the server: a wave's tile is 8,192 coordinates, dies take 64 (sums) or 128 tiles in turn; one word a lane below 2^22 (from nine workers
+# on 3 x 2^22, votes of more than sixteen 3 x 2^21), no runs from 2^26 on
+@pytest.mark.parametrize("M", [2, 7, 12, 16, 24])
+@pytest.mark.parametrize("d", [(1 << 22) - 1, (1 << 22) + 8191, (1 << 23) + 31, (3 << 21) - 7, (3 << 21) + 7, (3 << 22) - 5, (3 << 22) + 8193,
+                               (1 << 26) - 3, (1 << 26) + 129])
+def test_server_around_rules(ss, oracle, M, d):
+    if d > 1 << 25 and M not in (2, 16):
+        M = {7: 3, 12: 11, 24: 17}[M]       # other counts of planes and batches left over
+    n = ss.packed_bytes(d) // 4
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d + M)
+    neg = [torch.randint(-2**31, 2**31, (n,), dtype=torch.int32, device=DEV, generator=gen) for _ in range(M)]
+    zero = [torch.randint(-2**31, 2**31, (n,), dtype=torch.int32, device=DEV, generator=gen) for _ in range(M)]
+    # the reference on the device, coordinate by coordinate of a sample of words, the ends included
+    at = torch.cat([torch.arange(0, min(n, 700), device=DEV), torch.arange(max(0, n - 700), n, device=DEV),
+                    torch.randint(0, n, (20_000,), device=DEV, generator=gen)])
+    k = torch.arange(32, device=DEV)
+
+    def bits(t):
+        return (t[at][:, None] >> k) & 1
+
+    live = at[:, None] * 32 + k < d
+    minus = sum(bits(t) for t in neg)
+    sums = torch.full((d + 16,), 99, dtype=torch.int8, device=DEV)
+    ss.vote_sum(neg, sums, d)
+    padded = torch.nn.functional.pad(sums[:d], (0, 32 * n - d))
+    assert torch.equal(padded[at[:, None] * 32 + k][live].long(), (M - 2 * minus)[live]) and bool((sums[d:] == 99).all())
+    voted = dirty_bits(ss, d)
+    ss.majority_vote(neg, voted, d)
+    assert torch.equal(bits(voted).bool(), (2 * minus > M) & live)
+    vn, vz = dirty_bits(ss, d), dirty_bits(ss, d)
+    ss.quorum_vote(neg, zero, 2, vn, vz, d)
+    total = M - sum(bits(z) for z in zero) - 2 * sum(bits(a) & ~bits(z) for a, z in zip(neg, zero))
+    assert torch.equal(bits(vn).bool(), (total <= -2) & live) and torch.equal(bits(vz).bool(), (total.abs() < 2) & live)
