@@ -123,7 +123,7 @@ int ss_sign_apply(float *x, const uint32_t *bits, float delta, size_t d,
  *   packed_out  out  NULL, or host array of M device pointers that receive
  *                    every worker's sign bits (ss_packed_bytes(d) bytes each)
  * Normally one kernel launch.  When packed_out is given, there are two workers or
- * more and d is large (from about 2^20 coordinates on), the call enqueues two
+ * more (with momentum three) and d is large (2^20 coordinates at least), the call enqueues two
  * launches that hand the signs over through packed_out, which is faster there; the
  * results are the same.  Should the runtime refuse the second launch (SS_ERR_HIP),
  * the first stays enqueued: the momentum buffers have then been advanced by this
@@ -201,7 +201,7 @@ int ss_signum_vote_step_ex(const void *const *g, ss_dtype gdt, float *const *m,
  * ss_signum_vote_step_ex for a caller that can lend device memory for the length
  * of the call: with it a large step runs as two launches that hand the workers'
  * bits over through that memory (over slabs of the vector, should it be small),
- * which is 3-10 % faster than one pass over all workers' buffers at once.  Results
+ * which is 1-12 % faster than one pass over all workers' buffers at once.  Results
  * are the same, bit for bit.
  *   scratch        work  scratch_bytes of device memory, 16-byte aligned, contents
  *                        immaterial before and after; it must stay untouched by others

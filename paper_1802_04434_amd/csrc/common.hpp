@@ -6,8 +6,8 @@
 //             one 128-bit access per fp32 buffer, one 64-bit access for bf16
 //   8 lanes   own 32 consecutive coordinates = one packed word
 //   wave      64 lanes = 256 coordinates = 8 packed words
-//   block     B threads = 4 B coordinates per row, R rows per block (B = 256 = kBlock where a
-//             kernel does not say otherwise; the step and pack kernels use 64-512)
+//   block     one wave (kWave) with one row of 256 coordinates or a few; B threads = 4 B coordinates
+//             per row where a kernel is launched with more
 // The coordinates that do not fill a whole tile go through a scalar path in
 // extra blocks at the end of the same grid (one coordinate per lane; there a
 // wave ballot is already in packed-word order).
@@ -24,7 +24,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWave = 64;            // threads of the one-wave blocks
-constexpr int kBlock = 256;          // threads per block unless a kernel is launched with its own
+constexpr int kBlock = 256;          // threads of the four-wave blocks
 constexpr int kQuad = 4;             // coordinates per lane per row
 constexpr int kRowCoords = kBlock * kQuad;   // 1024
 
