@@ -121,12 +121,15 @@ inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
 // 171.1 / 170.4, bf16 8.8 M 54.2 / 57.5, 138 M (4.2 GB) 802 / 787; M = 4 17.6 M (845 MB) 149.2 / 149.6, 25.6 M (1.2 GB) 217 / 214;
 // M = 5 8.8 M (528 MB) 94.0 / 94.3, 25.6 M (1.5 GB) 265 / 260; M = 7 2.2 M (185 MB) 35.4 / 35.4, 4.4 M (370 MB) 65.1 / 64.9, 6.6 M
 // 95.6 / 93.3; M = 9 1.1 M (119 MB) 23.1 / 24.0; M = 16 1.1 M (211 MB) 38.8 / 37.7; bf16 M = 8 4.4 M 65.5 / 62.1.
-// Without momentum: M = 2 fp32 8.8 M 23.7 / 27.9, 25.6 M 71.3 / 65.2, M = 8 25.6 M 177 / 162.  step_bf16_kernel, which writes no
-// bits, starts beyond this line.
+// Without momentum where the streaming shapes begin, bytes of gradients: fp32 M = 2 8.4 M (67 MB) 22.7 / 27.2, 33.5 M (268 MB) 83.2 /
+// 86.8 before the line and 92.3 / 88.4 behind it, 67 M 183 / 166, M = 4 4.2 M 17.6 / 21.8, 16.8 M 66.6 / 67.0, 33.6 M 122.4 / 125.1,
+// 134 M 503 / 493, M = 8 4.2 M 29.6 / 32.3, 8.4 M 57.7 / 58.1 and 61.7 / 57.0, 16.8 M 116 / 106, M = 16 4.2 M 53.2 / 54.2, 7.8 M
+// 111.8 / 93.0; bf16 M = 3 5.6 M 14.9 / 18.3, 41.7 M (250 MB) 91.7 / 94.5, M = 8 4.2 M 19.3 / 24.5, 15.7 M 64.3 / 65.6.
+// step_bf16_kernel, which writes no bits, starts at the same line.
 inline bool split_pays(int M, size_t d, bool has_m, size_t worker_bytes) {
     if (M < 2 || d < ((size_t)1 << 20)) return false;
-    if (has_m) return M >= 3 && d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 8 ? 27 : M >= 6 ? 28 : 30));
-    return d * (size_t)M >= ((size_t)1 << (M >= 4 ? 23 : 25));
+    if (!has_m) return streams(M, d, false, worker_bytes);
+    return M >= 3 && d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 8 ? 27 : M >= 6 ? 28 : 30));
 }
 
 // A launch may have at most 2^32 - 1 threads, which a shape with one row of quads a lane reaches at 2^34

@@ -105,11 +105,15 @@ def test_one_pass_around_runs_and_rules(ss, oracle, d, M, dtype, momentum):
     assert_same_floats(x_dev, x, "x")
 
 
-# with packed_out, on both sides of the line from which two launches pay: 2^30 bytes for three workers, 2^27 for eight
+# with packed_out, on both sides of the line from which two launches pay: 2^30 bytes for three workers, 2^27 for eight, 2^28
+# without momentum
 @pytest.mark.parametrize("d,M,dtype,momentum", [((1 << 30) // 36 - 3, 3, "f32", True), ((1 << 30) // 36 + 3, 3, "f32", True),
                                                 ((1 << 27) // 80 - 1, 8, "bf16", True), ((1 << 27) // 80 + 1, 8, "bf16", True),
                                                 ((1 << 25) // 2 - 1, 2, "bf16", False), ((1 << 25) // 2 + 1, 2, "bf16", False),
-                                                ((1 << 24) + 300, 2, "f32", True)])
+                                                ((1 << 24) + 300, 2, "f32", True),
+                                                ((1 << 28) // 4 - 1, 2, "bf16", False), ((1 << 28) // 4 + 129, 2, "bf16", False),
+                                                ((1 << 28) // 28, 7, "f32", False), ((1 << 28) // 28 + 1, 7, "f32", False),
+                                                ((1 << 28) // 32 - 255, 16, "bf16", False), ((1 << 20) + 4097, 33, "f32", False)])
 def test_packed_out_on_both_sides_of_two_launches(ss, oracle, d, M, dtype, momentum):
     g = [draw(d + w, d, dtype, 0.5) for w in range(M)]
     m_dev = [draw(d - w, d, "f32", 0.3) for w in range(M)] if momentum else None

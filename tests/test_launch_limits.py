@@ -93,6 +93,16 @@ def check_ordinary_steps(rec):
         assert rc == 0 and len(launches) == n and launches[0][3] == g, (d, M, packed, launches)
 
 
+def check_packed_out_without_momentum(rec):
+    # one pass while the cache holds the gradients (it is 2-30 % faster there), from 2^28 bytes on two launches
+    for bf16 in (0, 1):
+        for M in (2, 3, 4, 8, 16, 33):
+            line = -(-(1 << 28) // (M * (2 if bf16 else 4)))
+            for d, n in ((1 << 20, 1), (line // 2 + 1, 1), (line - 1, 1), (line, 2), (4 * line + 5, 2)):
+                rc, launches, _ = rec.step(d, M, bf16, False, packed=True)
+                assert rc == 0 and len(launches) == n, (bf16, M, d, launches)
+
+
 def check_refused_steps(rec):
     # more coordinates than any launch shape ever took
     for d in ((1 << 36) + 1, 1 << 40, 1 << 61):
@@ -127,7 +137,8 @@ def check_other_calls(rec):
     assert len(rec.launches()) == 8 and all(0 < threads(t) < 1 << 32 for t in rec.launches())
 
 
-CHECKS = {f.__name__: f for f in (check_large_steps, check_ordinary_steps, check_refused_steps, check_other_calls)}
+CHECKS = {f.__name__: f for f in (check_large_steps, check_ordinary_steps, check_packed_out_without_momentum, check_refused_steps,
+                                  check_other_calls)}
 
 
 @pytest.fixture(scope="module")
