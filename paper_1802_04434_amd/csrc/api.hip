@@ -156,16 +156,18 @@ inline size_t scratch_slab(int M, size_t d, size_t bytes) {
     return std::min(room, ((d + parts - 1) / parts + 8191) / 8192 * 8192);
 }
 
-// One pass / two launches with scratch, us: M = 3 fp32 138 M 904 / 908, bf16 791 / 787; M = 4 bf16 17.6 M (704 MB of gradients and
-// momentum) 128.6 / 128.7, 25.6 M (1.0 GB) 186.0 / 184.3, 138 M 1,011 / 989, fp32 25.6 M 214.2 / 214.3; M = 5 fp32 8.8 M (528 MB)
-// 93.4 / 94.3, 25.6 M 263.5 / 259.7; M = 7 4.4 M (370 MB) 64.0 / 64.9, 6.6 M (551 MB) 94.8 / 93.3, 25.6 M 362 / 350; M = 8 bf16 4.4 M
-// (352 MB) 63.6 / 62.1, 6.6 M 93.8 / 89.5; M = 12 fp32 2.2 M (317 MB) 57.4 / 53.7; M = 16 bf16 2.2 M (352 MB) 65.9 / 58.8, fp32 138 M
-// 4,520 / 4,060.  Where a step takes less than ~40 us the
-// first allocation on a stream (~20 us, once) is not worth what is gained.  A lender that asks the device for its free
-// memory at each call pays 6-9 us of host time for it, which a step behind queued work hides: alone, M = 8 bf16 6.5 M takes
-// 112 us where the same launches without the question take 104.
+// One pass / two launches with scratch, us behind queued work, MB of gradients and momentum: fp32 M = 4 805 MB 144 / 142, 1,074 188 /
+// 189, 2,147 372 / 369; M = 5 268 48.3 / 51.0, 537 93.4 / 93.9, 805 140 / 140, 1,074 186 / 183; M = 6 537 92.9 / 94.4, 805 137 / 137, 2,147
+// 359 / 357; M = 7 268 47.0 / 49.1, 537 90.4 / 93.1, 805 136 / 135, 2,147 354 / 352; M = 8 268 48.6 / 48.6, 403 70.7 / 69.1, 805 137 / 133;
+// M = 12 403 70.9 / 68.3; M = 16 268 51.5 / 48.5, 138 M 4,520 / 4,060; bf16 M = 4 1,074 195 / 193, 2,147 390 / 384; M = 5 537 97.6 / 98.0,
+// 805 146 / 141; M = 7 537 94.0 / 94.2, 805 140 / 137; M = 8 268 48.4 / 49.1, 524 94 / 90; M = 12 268 51.9 / 47.0.  Three workers
+// 389 / 387 at 2,147 MB, two 424 / 422 (bf16 444 / 447): never.  The step with abstentions takes the same lines: M = 4 1,074 191 / 192,
+// bf16 2,147 388 / 395, M = 7 805 138 / 137, M = 8 268 47.6 / 50.1, 403 70.5 / 69.7, bf16 268 51.2 / 50.1, M = 16 805 136 / 129.
+// A lender that asks the device for its free memory at each call, borrows and launches twice spends 10-15 us of host time on it,
+// which queued work hides: waited for after each step M = 5 268 MB takes 74.5 us where one pass takes 59.5, 1,080 MB 209 / 196.
 inline bool scratch_pays(int M, size_t d, size_t worker_bytes) {
-    return M >= 4 && d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 5 ? 28 : 30));
+    const int many = worker_bytes < 12 ? 5 : 6;    // bf16, fp32
+    return M >= 4 && d * (size_t)M * worker_bytes >= (size_t)(M >= 8 ? 1 : M >= many ? 3 : 4) << 28;
 }
 
 // any-M vote and update, and answer and update: from about a gigabyte of x on, one row per block is 3-7 % faster than four

@@ -163,7 +163,7 @@ def test_step_with_lent_scratch(ss, oracle, d, M, dtype, flags, sums, room):
 
 def test_large_step_on_streams_and_under_capture(ss):
     # the binding lends scratch on the step's own stream; a captured step takes one pass, and both agree
-    d, M = (1 << 28) // 60 + 12_345, 5
+    d, M = (1 << 30) // 60 + 12_345, 5
     gen = torch.Generator(device=DEV)
     gen.manual_seed(9)
     g = [torch.randn(d, device=DEV, generator=gen) for _ in range(M)]
@@ -292,7 +292,7 @@ def test_server_one_word_a_lane_and_four(ss, oracle, d, M):
 def test_large_step_while_another_thread_captures(ss):
     # the scratch that the binding lends is allocated beside an open capture, which goes on unharmed
     import threading
-    d, M = (1 << 28) // 60 + 77, 5
+    d, M = (1 << 30) // 60 + 77, 5
     gen = torch.Generator(device=DEV)
     gen.manual_seed(3)
     g = [torch.randn(d, device=DEV, generator=gen) for _ in range(M)]
@@ -402,7 +402,7 @@ def test_one_pass_ternary_step_beyond_the_cache(ss, oracle, M, dtype, momentum, 
 
 def _large_step(ss, extra):
     """a step for which scratch is lent; the call, binary or ternary, on fresh state and a stream, and its outputs"""
-    d, M = (1 << 28) // 60 + extra, 5
+    d, M = (1 << 30) // 60 + extra, 5
     gen = torch.Generator(device=DEV)
     gen.manual_seed(extra)
     g = [torch.randn(d, device=DEV, generator=gen) for _ in range(M)]

@@ -236,6 +236,19 @@ def test_abstention_entry_points_validate_arguments(lib):
     assert step(one, 9, None, 1, f(0.9), f(0.1), 1, f(0.1), a, a, a, 8, None) == -4
 
 
+def test_scratch_is_wanted_where_two_launches_are_faster(lib):
+    # gradient type, workers, bytes of gradients and momentum up to which one pass is as fast
+    for gdt, M, line in ((0, 4, 1 << 30), (1, 4, 1 << 30), (0, 5, 1 << 30), (1, 5, 3 << 28), (0, 6, 3 << 28), (1, 7, 3 << 28),
+                         (0, 7, 3 << 28), (0, 8, 1 << 28), (1, 8, 1 << 28), (0, 16, 1 << 28), (1, 64, 1 << 28)):
+        d = -(-line // (M * (10 if gdt else 12)))
+        for n, wanted in ((d - 1, False), (max(d, 1 << 20), True), (4 * d + (1 << 20), True)):
+            assert (lib.ss_step_scratch_bytes(gdt, 1, M, n) > 0) == wanted, (gdt, M, n)
+            assert (lib.ss_ternary_scratch_bytes(gdt, 1, M, n) > 0) == wanted, (gdt, M, n)
+    for M in (2, 3):
+        for d in (8_800_000, 138_357_544, 1 << 31):
+            assert lib.ss_step_scratch_bytes(0, 1, M, d) == 0 and lib.ss_ternary_scratch_bytes(1, 1, M, d) == 0
+
+
 def test_lent_scratch_is_bounded_and_validated(lib):
     for gdt in (0, 1):
         for M in (2, 3, 5, 7, 8, 16, 17, 64):
