@@ -123,12 +123,13 @@ int ss_sign_apply(float *x, const uint32_t *bits, float delta, size_t d,
  *   packed_out  out  NULL, or host array of M device pointers that receive
  *                    every worker's sign bits (ss_packed_bytes(d) bytes each)
  * Normally one kernel launch.  When packed_out is given, there are two workers or
- * more (with momentum three) and d is large (2^20 coordinates at least), the call enqueues two
- * launches that hand the signs over through packed_out, which is faster there; the
- * results are the same.  Should the runtime refuse the second launch (SS_ERR_HIP),
- * the first stays enqueued: the momentum buffers have then been advanced by this
- * step and x has not.  A vector of more than 2^33 coordinates is stepped part by
- * part, each as above; the parts before a refused launch stay enqueued.
+ * more (with momentum three) and d is large (2^20 coordinates at least, without
+ * momentum 2^28 bytes of gradients), the call enqueues two launches that hand the
+ * signs over through packed_out, which is faster there; the results are the same.
+ * Should the runtime refuse the second launch (SS_ERR_HIP), the first stays
+ * enqueued: the momentum buffers have then been advanced by this step and x has
+ * not.  A vector of more than 2^33 coordinates is stepped part by part, each as
+ * above; the parts before a refused launch stay enqueued.
  */
 int ss_signum_vote_step(const void *const *g, ss_dtype gdt, float *const *m,
                         int M, float beta, float delta, float *x,
@@ -199,16 +200,18 @@ int ss_signum_vote_step_ex(const void *const *g, ss_dtype gdt, float *const *m,
 
 /*
  * ss_signum_vote_step_ex for a caller that can lend device memory for the length
- * of the call: with it a large step runs as two launches that hand the workers'
- * bits over through that memory (over slabs of the vector, should it be small),
- * which is 1-12 % faster than one pass over all workers' buffers at once.  Results
- * are the same, bit for bit.
+ * of the call: with it a step over 2^20 coordinates or more runs as two launches
+ * that hand the workers' bits over through that memory (over slabs of the vector,
+ * should it be small), whatever M is.  Where ss_step_scratch_bytes names a size that
+ * is level with one pass over all workers' buffers at once or up to 9 % faster, the
+ * more the more workers; elsewhere it is level or, in smaller steps and with two or
+ * three workers, up to 8 % slower.  Results are the same, bit for bit.
  *   scratch        work  scratch_bytes of device memory, 16-byte aligned, contents
  *                        immaterial before and after; it must stay untouched by others
  *                        until the enqueued work has run.  NULL or too small to help:
  *                        one pass, as ss_signum_vote_step_ex.
- * ss_step_scratch_bytes is the size that helps (128 MiB at most), 0 where one pass
- * is as fast.  Everything else as for ss_signum_vote_step_ex; on SS_ERR_HIP the
+ * ss_step_scratch_bytes is the size that helps (128 MiB at most), 0 where lending
+ * does not.  Everything else as for ss_signum_vote_step_ex; on SS_ERR_HIP the
  * launches before the refused one stay enqueued.
  */
 size_t ss_step_scratch_bytes(ss_dtype gdt, int has_momentum, int M, size_t d);
