@@ -268,10 +268,11 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
             } else if constexpr (kBf16) {
                 // step_bf16_kernel: the workers' loads out together, eight at most, fewer blocks per unit the more loads
                 // each has out.  us, 25.6 M unless said: M = 2 138 M 248 / 296 (four-wave blocks of two rows before), M = 3 60 M 126.8 /
-                // 145.9, M = 4 63.2 / 65.0, 7 86.8, 8 96.3, 12 128, 16 160.7; written through or not M = 4 138 M 337 / 340, M = 8
-                // 60 M 224.8 / 223.2, M = 16 161.5 / 163.2
+                // 145.9, M = 4 63.2 / 65.0, 7 86.8, 8 96.3, 12 128, 16 160.7.  x left to the L2 / written through: M = 4 67 M 166 / 159,
+                // 134 M 331 / 322, M = 5 54 M 147 / 147, M = 7 38 M 132 / 133, 153 M 510 / 520, M = 8 34 M 128 / 129; beyond eight within 2 %
+                // either way, M = 9 30 M 126 / 123, M = 16 9.4 M 64.0 / 64.7, 34 M 211 / 210.
                 if constexpr (MT > 0 && MT <= 6) return launch_octets<MT, NPTR, 64, 8, MT == 2 ? 10 : MT == 3 ? 13 : 16, kThrough>(a, d, stream);
-                else return launch_octets<MT, NPTR, 64, 8, MT == 16 ? 24 : 20, MT == 16 ? kThrough : kStream>(a, d, stream);
+                else return launch_octets<MT, NPTR, 64, 8, MT == 16 ? 24 : 20, kStream>(a, d, stream);
             } else {
                 // fp32: four workers a stage make up for the missing momentum stream.  us, against two four-wave blocks a unit before:
                 // 25.6 M M = 3 76.4 / 83.1, 4 91.8 / 94.6, 7 135.4 / 145.5, 8 153.8 / 160.1, 9 169.0 / 178.3, 16 279.8 / 288.5, 138 M
@@ -435,11 +436,12 @@ int launch_two(const void *const *g, ss_dtype gdt, float *const *m, int M, float
 constexpr uint32_t kVoteChunk = 7;
 constexpr size_t kVoteRuns = (size_t)1 << 26;   // runs below, capped from here on
 
-// One word a lane instead of four (the *_word_kernels) up to `end`, with up to eight workers a third of it.  us, word / 128-bit lanes: sums
-// M = 16 4.4 M coordinates 4.2 / 5.7, 8.8 M 6.0 / 6.5, 17.6 M 12.7 / 9.9, M = 7 4.4 M 4.0 / 3.7; quorum M = 16 8.8 M 7.6 / 8.5, 17.6 M 17.2 /
-// 14.0, M = 3 4.4 M 2.8 / 2.7; vote M = 24 4.4 M 5.0 / 5.5, 8.8 M 7.1 / 6.6.
+// One word a lane instead of four (the *_word_kernels) up to here; sums and quorum votes of up to eight workers a third of it.  us,
+// word / 128-bit lanes: sums M = 16 4.4 M coordinates 4.2 / 5.7, 8.8 M 6.0 / 6.5, 17.6 M 12.7 / 9.9, M = 7 4.4 M 4.0 / 3.7; quorum
+// M = 16 8.8 M 7.6 / 8.5, 17.6 M 17.2 / 14.0, M = 3 4.4 M 2.8 / 2.7; vote (more than sixteen workers only) M = 24 4.4 M 5.0 / 5.5, 8.8 M
+// 7.1 / 6.6.
 constexpr size_t kSumWords = (size_t)3 << 22, kVoteWords = (size_t)3 << 21;
-inline bool word_lanes(int M, size_t d, size_t end) { return d < (M >= 9 ? end : end / 3); }
+inline bool sum_word_lanes(int M, size_t d) { return d < (M >= 9 ? kSumWords : kSumWords / 3); }
 
 template <int M>
 int launch_vote_fixed(const uint32_t *const *packed, uint32_t *voted, size_t d, hipStream_t stream) {
@@ -472,7 +474,7 @@ int launch_vote_any(const uint32_t *const *packed, int M, uint32_t *voted, size_
     a.M = M;
     a.d = d;
     a.n_vec = ss_packed_bytes(d) / 16;
-    if (word_lanes(M, d, kVoteWords)) return launch(ss::vote_word_kernel, (4 * a.n_vec + 63) / 64, 0, stream, a, 64);
+    if (d < kVoteWords) return launch(ss::vote_word_kernel, (4 * a.n_vec + 63) / 64, 0, stream, a, 64);
     const size_t grid = (a.n_vec + ss::kWave - 1) / ss::kWave;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     if (d < kVoteRuns) return launch(ss::vote_kernel_any<0, kVoteChunk>, grid, 0, stream, a, ss::kWave);
@@ -798,7 +800,7 @@ int ss_vote_sum(const uint32_t *const *packed, int M, int8_t *sums, size_t d, vo
     const size_t grid = (a.n_vec + ss::kWave - 1) / ss::kWave;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (word_lanes(M, d, kSumWords)) {
+    if (sum_word_lanes(M, d)) {
         const size_t blocks = (4 * a.n_vec + 63) / 64;
         const int planes = count_planes(M);
         if (planes <= 3) return launch(ss::vote_sum_word_kernel<3>, blocks, 0, stream, a, 64);
@@ -985,7 +987,7 @@ int ss_quorum_vote(const uint32_t *const *neg, const uint32_t *const *zero, int 
     a.d = d;
     a.n_vec = ss_packed_bytes(d) / 16;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (word_lanes(M, d, kSumWords)) {
+    if (sum_word_lanes(M, d)) {
         const size_t blocks = (4 * a.n_vec + 63) / 64;
         const int planes = count_planes(M);
         if (planes <= 3) return launch(ss::quorum_word_kernel<3>, blocks, 0, stream, a, 64);
