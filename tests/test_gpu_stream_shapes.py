@@ -1,5 +1,6 @@
 """The streaming kernels at the edges of their tiles, of the runs of tiles that a compute die takes, and on both
-sides of the sizes at which a launch shape changes, bit-exact against the oracle."""
+sides of the sizes at which a launch shape changes, bit-exact on every element: against the oracle, and for the server's calls
+and the longest vectors against torch's integer and exactly rounded arithmetic on the device."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +15,8 @@ pytestmark = pytest.mark.gpu
 def ss():
     import paper_1802_04434_amd as lib
     lib.load_library()
-    return lib
+    yield lib
+    torch.cuda.empty_cache()        # the longest vectors take a hundred gigabytes
 
 
 def draw(seed, d, dtype, scale):
@@ -59,6 +61,15 @@ def test_pack_on_both_sides_of_a_launch_shape(ss, oracle, d, dtype):
     want = oracle.signum_pack(synth.as_numpy(g), m, 0.9)
     assert np.array_equal(bits_np(packed), want)
     assert_same_floats(m_dev, m, "m")
+
+
+# without momentum: fp32 in runs and one-wave blocks below 2^27, bf16 below 2^25, in order beyond
+@pytest.mark.parametrize("d,dtype", [((1 << 27) - 513, "f32"), ((1 << 27) + 1027, "f32"), ((1 << 25) - 1, "bf16"), ((1 << 25) + 1025, "bf16")])
+def test_sign_pack_on_both_sides_of_a_launch_shape(ss, oracle, d, dtype):
+    g = draw(d, d, dtype, 0.5)
+    packed = dirty_bits(ss, d)
+    ss.signum_pack(g, None, 0.9, packed)
+    assert np.array_equal(bits_np(packed), oracle.signum_pack(synth.as_numpy(g), None, 0.9))
 
 
 # vote and update: a block's 2,048 (any number of workers: 4,096) coordinates, by fixed adders and by count planes
@@ -113,7 +124,8 @@ def test_one_pass_around_runs_and_rules(ss, oracle, d, M, dtype, momentum):
                                                 ((1 << 24) + 300, 2, "f32", True),
                                                 ((1 << 28) // 4 - 1, 2, "bf16", False), ((1 << 28) // 4 + 129, 2, "bf16", False),
                                                 ((1 << 28) // 28, 7, "f32", False), ((1 << 28) // 28 + 1, 7, "f32", False),
-                                                ((1 << 28) // 32 - 255, 16, "bf16", False), ((1 << 20) + 4097, 33, "f32", False)])
+                                                ((1 << 28) // 32 - 255, 16, "bf16", False), ((1 << 20) + 4097, 33, "f32", False),
+                                                ((1 << 27) + 1023, 2, "f32", False)])
 def test_packed_out_on_both_sides_of_two_launches(ss, oracle, d, M, dtype, momentum):
     g = [draw(d + w, d, dtype, 0.5) for w in range(M)]
     m_dev = [draw(d - w, d, "f32", 0.3) for w in range(M)] if momentum else None
@@ -151,7 +163,9 @@ def test_one_pass_ternary_around_rules(ss, oracle, d, M, dtype, momentum):
 
 
 @pytest.mark.parametrize("d,dtype,momentum", [((1 << 19) + 257, "f32", True), ((1 << 20) - 1, "bf16", False),
-                                              ((1 << 28) // 12 + 255, "f32", True), ((1 << 25) + 3, "bf16", True)])
+                                              ((1 << 28) // 12 + 255, "f32", True), ((1 << 25) + 3, "bf16", True),
+                                              ((1 << 27) - 1, "f32", False), ((1 << 27) + 513, "f32", False),
+                                              ((1 << 27) + 31, "bf16", False)])
 def test_ternary_pack_around_rules(ss, oracle, d, dtype, momentum):
     g = draw(d, d, dtype, 0.2)
     m_dev = draw(d + 1, d, "f32", 0.2) if momentum else None
@@ -196,37 +210,188 @@ def test_updates_and_statistics_around_rules(ss, oracle, d):
     assert torch.equal(to[:d // 4 * 4].view(torch.int32), x0[:d // 4 * 4].view(torch.int32)) and bool((to[d // 4 * 4:] == 9).all())
 
 
-# the server: a wave's tile is 8,192 coordinates, dies take 64 (sums) or 128 tiles in turn; one word a lane below 2^22 (from nine workers
-# on 3 x 2^22, votes of more than sixteen 3 x 2^21), no runs from 2^26 on
+# ---- the server, every coordinate against torch's own arithmetic on the device (the oracle is compared with the same calls at
+# smaller sizes)
+
+WORDS = 1 << 18         # words that are compared at a time
+
+
+def random_planes(d, M, n):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d + M)
+    return [[torch.randint(-2**31, 2**31, (n,), dtype=torch.int32, device=DEV, generator=gen) for _ in range(M)] for _ in range(2)]
+
+
+def check_server(ss, d, M, Q):
+    n = ss.packed_bytes(d) // 4
+    neg, zero = random_planes(d, M, n)
+    sums = torch.full((d + 16,), 99, dtype=torch.int8, device=DEV)      # no sum: |99| > M
+    ss.vote_sum(neg, sums, d)
+    voted, vn, vz = dirty_bits(ss, d), dirty_bits(ss, d), dirty_bits(ss, d)
+    ss.majority_vote(neg, voted, d)
+    ss.quorum_vote(neg, zero, Q, vn, vz, d)
+    assert bool((sums[d:] == 99).all())
+    sums = torch.nn.functional.pad(sums[:d], (0, 32 * n - d))
+    k = torch.arange(32, dtype=torch.int32, device=DEV)
+    for a in range(0, n, WORDS):
+        def bits(t):
+            return (t[a:a + WORDS, None] >> k) & 1
+
+        live = torch.arange(a, min(a + WORDS, n), device=DEV)[:, None] * 32 + k < d
+        minus, none, only_minus = (torch.zeros(live.shape, dtype=torch.int32, device=DEV) for _ in range(3))
+        for x, z in zip(neg, zero):
+            x, z = bits(x), bits(z)
+            minus += x
+            none += z
+            only_minus += x & ~z
+        assert torch.equal(sums[32 * a:32 * (a + WORDS)].view(-1, 32).int(), torch.where(live, M - 2 * minus, 0)), a
+        assert torch.equal(bits(voted).bool(), (2 * minus > M) & live), a
+        total = M - none - 2 * only_minus
+        assert torch.equal(bits(vn).bool(), (total <= -Q) & live) and torch.equal(bits(vz).bool(), (total.abs() < Q) & live), a
+
+
+# a wave's tile is 8,192 coordinates, dies take 64 (sums) or 128 tiles in turn; one word a lane below 2^22 (from nine workers
+# on 3 x 2^22, votes of more than sixteen 3 x 2^21), no runs from 2^26 on (votes of up to eleven workers 2^28)
 @pytest.mark.parametrize("M", [2, 7, 12, 16, 24])
 @pytest.mark.parametrize("d", [(1 << 22) - 1, (1 << 22) + 8191, (1 << 23) + 31, (3 << 21) - 7, (3 << 21) + 7, (3 << 22) - 5, (3 << 22) + 8193,
                                (1 << 26) - 3, (1 << 26) + 129])
-def test_server_around_rules(ss, oracle, M, d):
+def test_server_around_rules(ss, M, d):
     if d > 1 << 25 and M not in (2, 16):
         M = {7: 3, 12: 11, 24: 17}[M]       # other counts of planes and batches left over
-    n = ss.packed_bytes(d) // 4
+    check_server(ss, d, M, 2)
+
+
+# every count of planes in lanes of four words, in runs and beyond them: one plane (a single worker), two and three with the
+# caps of up to three, four and more workers, six and seven
+@pytest.mark.parametrize("M,d,Q", [(1, (1 << 22) + 8193, 1), (1, (1 << 26) + 129, 1), (4, (1 << 24) + 31, 1), (4, (1 << 26) + 129, 2),
+                                   (5, (1 << 26) + 8191, 3), (7, (1 << 26) + 129, 2), (33, (3 << 22) + 65, 4), (33, (1 << 26) + 1, 2),
+                                   (64, (3 << 22) + 8191, 9), (64, (1 << 26) + 129, 5)])
+def test_server_in_lanes_of_four_words(ss, M, d, Q):
+    check_server(ss, d, M, Q)
+
+
+# ---- the longest vectors: shapes that only they take, the reference in chunks on the device
+
+CHUNK = 1 << 28
+LONGEST = (1 << 33) + 1283      # from 2^33 on two rows (the pack: four) a wave
+
+
+def long_floats(d, seed, scale):
+    t = torch.empty(d, device=DEV)
     gen = torch.Generator(device=DEV)
-    gen.manual_seed(d + M)
-    neg = [torch.randint(-2**31, 2**31, (n,), dtype=torch.int32, device=DEV, generator=gen) for _ in range(M)]
-    zero = [torch.randint(-2**31, 2**31, (n,), dtype=torch.int32, device=DEV, generator=gen) for _ in range(M)]
-    # the reference on the device, coordinate by coordinate of a sample of words, the ends included
-    at = torch.cat([torch.arange(0, min(n, 700), device=DEV), torch.arange(max(0, n - 700), n, device=DEV),
-                    torch.randint(0, n, (20_000,), device=DEV, generator=gen)])
-    k = torch.arange(32, device=DEV)
+    gen.manual_seed(seed)
+    for a in range(0, d, CHUNK):
+        t[a:a + CHUNK].normal_(0, scale, generator=gen)
+    return t
 
-    def bits(t):
-        return (t[at][:, None] >> k) & 1
 
-    live = at[:, None] * 32 + k < d
-    minus = sum(bits(t) for t in neg)
-    sums = torch.full((d + 16,), 99, dtype=torch.int8, device=DEV)
-    ss.vote_sum(neg, sums, d)
-    padded = torch.nn.functional.pad(sums[:d], (0, 32 * n - d))
-    assert torch.equal(padded[at[:, None] * 32 + k][live].long(), (M - 2 * minus)[live]) and bool((sums[d:] == 99).all())
+def long_words(d, seed):
+    n = (d + 127) // 128 * 4
+    t = torch.empty(n, dtype=torch.int32, device=DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    for a in range(0, n, CHUNK):
+        t[a:a + CHUNK].random_(-2**31, 2**31, generator=gen)
+    return t
+
+
+def bits_of(words, a, n):
+    """the bits of coordinates a to a + n as booleans; a is a multiple of 32"""
+    k = torch.arange(32, dtype=torch.int32, device=DEV)
+    return ((words[a // 32:(a + n + 31) // 32, None] >> k) & 1).view(-1)[:n].bool()
+
+
+# runs of tiles with 32-bit offsets up to 2^34 coordinates, 64-bit ones beyond
+@pytest.mark.parametrize("d", [(1 << 34) - 33, (1 << 34) + 8193])
+def test_vote_over_the_longest_vectors(ss, d):
+    a, b, c = (long_words(d, seed) for seed in range(3))
     voted = dirty_bits(ss, d)
-    ss.majority_vote(neg, voted, d)
-    assert torch.equal(bits(voted).bool(), (2 * minus > M) & live)
-    vn, vz = dirty_bits(ss, d), dirty_bits(ss, d)
-    ss.quorum_vote(neg, zero, 2, vn, vz, d)
-    total = M - sum(bits(z) for z in zero) - 2 * sum(bits(a) & ~bits(z) for a, z in zip(neg, zero))
-    assert torch.equal(bits(vn).bool(), (total <= -2) & live) and torch.equal(bits(vz).bool(), (total.abs() < 2) & live)
+    for workers, vote in (([a], lambda x: x[0]), ([a, b], lambda x: x[0] & x[1]),
+                          ([a, b, c], lambda x: (x[0] & x[1]) | (x[2] & (x[0] ^ x[1])))):
+        voted.fill_(-1)
+        ss.majority_vote(workers, voted, d)
+        full = d // 32
+        for lo in range(0, full, CHUNK):
+            hi = min(lo + CHUNK, full)
+            assert torch.equal(voted[lo:hi], vote([t[lo:hi] for t in workers])), (len(workers), lo)
+        rest = vote([t[full:] for t in workers]).cpu()
+        rest[0] &= (1 << d % 32) - 1
+        rest[1:] = 0
+        assert torch.equal(voted[full:].cpu(), rest)
+
+
+def test_sign_pack_of_the_longest_vectors(ss):
+    d = LONGEST
+    g = long_floats(d, 5, 1.0)
+    packed = dirty_bits(ss, d)
+    ss.signum_pack(g, None, 0.9, packed)
+    for a in range(0, d, CHUNK):
+        n = min(CHUNK, d - a)
+        assert torch.equal(bits_of(packed, a, n), g[a:a + n] < 0), a
+    assert packed[d // 32].item() >> d % 32 == 0 and bool((packed[d // 32 + 1:] == 0).all())
+
+
+def test_updates_and_sigma_of_the_longest_vectors(ss):
+    d = LONGEST
+    x, delta = torch.zeros(d, device=DEV), 0.25                   # multiples of a quarter: every sum is exact
+    neg, zero = long_words(d, 1), long_words(d, 2)
+    ss.sign_apply(x, neg, delta)
+    ss.ternary_apply(x, neg, zero, 4 * delta)
+    sums = torch.empty(d, dtype=torch.int8, device=DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(3)
+    for a in range(0, d, CHUNK):
+        sums[a:a + CHUNK].random_(-64, 65, generator=gen)
+    ss.sum_apply(x, sums, 16 * delta)
+    for a in range(0, d, CHUNK):
+        n = min(CHUNK, d - a)
+        s = 1.0 - 2.0 * bits_of(neg, a, n).float()
+        want = -delta * s - 4 * delta * torch.where(bits_of(zero, a, n), 0.0, s) - 16 * delta * sums[a:a + n].float()
+        assert torch.equal(x[a:a + n], want), a
+    del sums, neg, zero
+    for a in range(0, d, CHUNK):                                  # squares, so that the root is exact
+        x[a:a + CHUNK].random_(0, 4096, generator=gen).square_()
+    sigma = torch.full((d,), 9.0, device=DEV)
+    ss.welford_sigma(x, 1, sigma)
+    for a in range(0, d, CHUNK):
+        assert torch.equal(sigma[a:a + CHUNK].square(), x[a:a + CHUNK]) and bool((sigma[a:a + CHUNK] >= 0).all()), a
+
+
+# the binary step runs part by part, the ternary one in two rows a wave; with momentum halved into zeros every value is exact
+@pytest.mark.parametrize("M,dtype,momentum", [(2, "f32", False), (2, "bf16", False), (1, "f32", True), (1, "bf16", True)])
+def test_steps_over_the_longest_vectors(ss, M, dtype, momentum):
+    d, delta, tau, quorum = LONGEST, 0.25, 0.5, M
+    g = []
+    for w in range(M):
+        t = torch.empty(d, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device=DEV)
+        gen = torch.Generator(device=DEV)
+        gen.manual_seed(w)
+        for a in range(0, d, CHUNK):
+            t[a:a + CHUNK].normal_(0, 1, generator=gen)
+        g.append(t)
+    m = [torch.zeros(d, device=DEV) for _ in range(M)] if momentum else None
+    x, neg, zero = torch.zeros(d, device=DEV), dirty_bits(ss, d), dirty_bits(ss, d)
+
+    def chunks():
+        for a in range(0, d, CHUNK):
+            n = min(CHUNK, d - a)
+            v = [t[a:a + n].float() * (0.5 if momentum else 1.0) for t in g]
+            if momentum:
+                assert torch.equal(m[0][a:a + n], v[0]), a
+                m[0][a:a + n] = 0
+            yield a, n, v
+
+    ss.signum_vote_step(g, m, 0.5, delta, x, neg)
+    for a, n, v in chunks():
+        minus = sum((t < 0).to(torch.int8) for t in v) >= M // 2 + 1
+        assert torch.equal(bits_of(neg, a, n), minus) and torch.equal(x[a:a + n], torch.where(minus, delta, -delta)), a
+        x[a:a + n] = 0
+    neg.fill_(-1)
+    ss.signum_vote_step_ternary(g, m, 0.5, tau, quorum, delta, x, neg, zero)
+    for a, n, v in chunks():
+        total = sum(torch.where(t.abs() < tau, 0, torch.where(t < 0, -1, 1)).to(torch.int8) for t in v)
+        minus, none = total <= -quorum, total.abs() < quorum
+        assert torch.equal(bits_of(neg, a, n), minus) and torch.equal(bits_of(zero, a, n), none), a
+        assert torch.equal(x[a:a + n], torch.where(none, 0.0, torch.where(minus, delta, -delta))), a
+    for t in (neg, zero):
+        assert t[d // 32].item() >> d % 32 == 0 and bool((t[d // 32 + 1:] == 0).all())
