@@ -1,11 +1,11 @@
 """GPU parity at vector sizes where the library changes launch shape.
 
 The kernels that stream one or a few buffers (pack, apply, Welford, copy, the
-stand-alone votes) take other tilings - fewer rows per block, a cap on the
-blocks per compute unit - once the vector is large (2^27, 2^28 or 2^30
+stand-alone votes) take other tilings - fewer rows per block, no runs of tiles,
+a cap on the blocks per compute unit - once the vector is large (2^23 to 2^28
 coordinates depending on the entry point).  The arithmetic is the same code;
 what changes is which block owns which coordinates and where the ragged end
-begins.  Each test runs one entry point just above its threshold, with a
+begins.  Each test runs one entry point beyond its last threshold, with a
 ragged end, and compares every output element with the CPU oracle.
 """
 import numpy as np
@@ -17,7 +17,7 @@ from test_gpu_parity import DEV, assert_same_floats, bits_np, dirty_bits
 
 pytestmark = pytest.mark.gpu
 
-D28 = (1 << 28) + 4099      # above the 2^28 threshold; d mod 1024 = 3, d mod 32 = 3
+D28 = (1 << 28) + 4099      # d mod 1024 = 3, d mod 32 = 3
 D27 = (1 << 27) + 77
 D30 = (1 << 30) + 33
 
@@ -157,7 +157,7 @@ def test_vote_sum_and_quorum_vote_large(ss, oracle, M):
     assert np.array_equal(bits_np(vz), want_z)
 
 
-# one-wave blocks with a cap from 2^28 coordinates on, from twelve workers on from 2^27; never for three
+# a cap from 2^28 coordinates on, from twelve workers on from 2^26; never for three
 @pytest.mark.parametrize("M,d", [(3, D30), (17, D30), (4, (1 << 28) + 1), (8, (1 << 28) + 8191), (11, (1 << 28) + 127),
                                  (8, (1 << 28) - 1), (12, (1 << 27) + 33), (16, (1 << 27) + 8193), (16, (1 << 27) - 129),
                                  (24, (1 << 26) + 65)])

@@ -251,8 +251,8 @@ def test_fused_equals_three_call_path(ss):
 
 @pytest.mark.parametrize("M,dtype", [(7, "f32"), (16, "f32"), (8, "bf16")])
 def test_fused_equals_three_call_path_streaming_shape(ss, M, dtype):
-    # with per-worker bits the call hands the signs over through packed_out, without them it takes one
-    # pass (M = 7 and 8: the latency shape) or, for M = 16, borrows scratch memory; the outputs must be
+    # M = 7 takes one pass with and without the workers' bits, in the streaming shape; with them M = 8 and 16 hand the
+    # signs over through packed_out, without them M = 16 borrows scratch memory; the outputs must be
     # those of M packs + vote + apply every time (ragged d, so the scalar tail takes part)
     d = 3 * (1 << 20) + 2048 + 77
     gen = torch.Generator(device=DEV)
@@ -440,8 +440,9 @@ def test_checkpoint_resume_is_bit_identical(ss):
 @pytest.mark.parametrize("M,dtype,momentum", [(2, "f32", True), (3, "bf16", True), (4, "f32", False),
                                               (9, "f32", True), (11, "bf16", False)])
 def test_fused_step_large_d_streaming_shape(ss, oracle, M, dtype, momentum):
-    # the first step in one pass (M = 3: the streaming shape, M = 2, 4, 11: the latency shape) or, M = 9, as two
-    # launches over borrowed scratch, the second through packed_out; ragged so that the scalar tail runs as well
+    # the first step in one pass (M = 2 and 3: the streaming shape, M = 4 and 11: the latency shape) or, M = 9, as two
+    # launches over borrowed scratch, the second with the workers' bits as well (M = 9: handed over through them);
+    # ragged so that the scalar tail runs too
     d = 9_000_000 + 1234 + 19
     cfg = synth.Config("large", 40 + M, d, M, dtype, 0.9 if momentum else None, 1e-4, 2, "normal", 0.1, 0.5)
     m = [np.zeros(d, np.float32) for _ in range(M)] if momentum else None
@@ -470,7 +471,7 @@ def test_fused_step_large_d_streaming_shape(ss, oracle, M, dtype, momentum):
 def test_fused_step_streaming_shape_any_worker_count(ss, oracle, M, dtype, momentum):
     # worker counts without a kernel of their own (the run-time-M kernel) and M = 6, with every kind of
     # gradient: the first step in one pass (M = 64: the streaming shape, beyond 2^28 bytes of gradients) or, M = 33,
-    # over borrowed scratch, the second through packed_out where d M is 2^23 or more; ragged d
+    # over borrowed scratch, the second with the workers' bits (M = 13, 33 and 64: handed over through them); ragged d
     d = (1 << 20) + 4096 + 333
     rng = np.random.default_rng(1000 + M)
     m = [make_momentum(rng, d) for _ in range(M)] if momentum else None

@@ -1,10 +1,11 @@
 """The launch shapes of the step around the edges of their tiles, bit-exact against the oracle.
 The Python calls lend scratch memory to large steps with momentum, which then run as two launches; the
 one-pass kernels of that size are run through the C ABI, as a captured step runs them.
-With packed_out from about 2^20 coordinates on: a pack launch over all workers, then vote and
-update (256 coordinates a pack block with momentum, 1,024 without, 1,024 to 4,096 a vote block,
-padding to 128; fixed adders up to 16 workers, pointer tables of 16 and 64).  In one pass: the
-stages of eight workers and what they leave over, and both sides of the size rules."""
+With packed_out: in one pass, and from the size rules on a pack launch over all workers, then vote and
+update (256 coordinates a pack block with momentum, 512 or 1,024 without, 2,048 or 4,096 a vote block,
+padding to 128; fixed adders up to 16 workers, pointer tables of 16 and 64).  In one pass: the stages of
+eight workers and what they leave over, and sizes beyond the size rules; both sides of each rule are in
+test_gpu_stream_shapes.py."""
 import numpy as np
 import pytest
 import torch
@@ -82,7 +83,8 @@ def test_small_step_with_workers_left_over(ss, oracle, d, M, momentum):
     ((1 << 28) // 84 - 5, 7, "f32", True), ((1 << 28) // 80 + 77, 8, "bf16", True),
 ])
 def test_step_on_both_sides_of_a_launch_shape(ss, oracle, d, M, dtype, momentum):
-    # one worker from 2^25 coordinates on; several workers at 2^28 bytes of gradients and momentum
+    # one worker beyond 2^24 coordinates; several workers at 2^28 bytes of gradients and momentum, where scratch is lent to
+    # eight and more
     rng = np.random.default_rng(d)
     g = [make_grad(rng, d, dtype, scale=0.5) for _ in range(M)]
     m = [make_momentum(rng, d) for _ in range(M)] if momentum else None
@@ -103,7 +105,7 @@ def test_step_on_both_sides_of_a_launch_shape(ss, oracle, d, M, dtype, momentum)
     ((1 << 28) // 28 + 511, 7, "f32", False), ((1 << 28) // 32 + 1, 16, "bf16", False), ((1 << 28) // 24 - 300, 2, "f32", True),
 ])
 def test_ternary_step(ss, oracle, d, M, dtype, momentum):
-    # stages of eight workers and what they leave over, and both sides of the 2^28-byte rule
+    # stages of eight workers and what they leave over, and the streaming shapes beyond 2^28 bytes
     rng = np.random.default_rng(d + M)
     g = [make_grad(rng, d, dtype, scale=0.2) for _ in range(M)]
     m = [make_momentum(rng, d) for _ in range(M)] if momentum else None
@@ -349,7 +351,7 @@ def _drawn_step(d, M, dtype, momentum, scale):
 
 
 def _beyond_cache(M, dtype, momentum, extra):
-    """coordinates whose gradients and momentum are 2^28 bytes and a little: the smallest step of a streaming shape"""
+    """coordinates whose gradients and momentum are 2^28 bytes and a little: a step of a streaming shape"""
     size = (2 if dtype == "bf16" else 4) + (8 if momentum else 0)
     return -(-(1 << 28) // (M * size)) + extra
 

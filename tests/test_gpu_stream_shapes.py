@@ -1,6 +1,8 @@
 """The streaming kernels at the edges of their tiles, of the runs of tiles that a compute die takes, and on both
 sides of the sizes at which a launch shape changes, bit-exact on every element: against the oracle, and for the server's calls
 and the longest vectors against torch's integer and exactly rounded arithmetic on the device."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -72,14 +74,17 @@ def test_sign_pack_on_both_sides_of_a_launch_shape(ss, oracle, d, dtype):
     assert np.array_equal(bits_np(packed), oracle.signum_pack(synth.as_numpy(g), None, 0.9))
 
 
-# vote and update: a block's 2,048 (any number of workers: 4,096) coordinates, by fixed adders and by count planes
-@pytest.mark.parametrize("extra", [0, 1, 31, 2047, 4095])
-@pytest.mark.parametrize("M,flags", [(8, 0), (16, 0), (20, 0), (9, 2), (33, 2)])
-def test_vote_and_update_around_a_tile(ss, oracle, M, flags, extra):
+# vote and update: a block's 2,048 (any number of workers: 4,096) coordinates, by fixed adders and by count planes, after a pack
+# over lent memory; with packed_out a step of this size takes one pass.  Without momentum, for which the binding lends nothing.
+@pytest.mark.parametrize("M,dtype,flags,extra", [(M, "bf16", flags, extra) for extra in (0, 1, 31, 2047, 4095)
+                                                 for M, flags in ((8, 0), (16, 0), (20, 0), (9, 2), (33, 2))] +
+                         [(M, "f32" if M % 2 else "bf16", 0, 2049 + M) for M in range(2, 16) if M != 8] +
+                         [(33, "f32", 0, 5), (64, "bf16", 0, 8191), (3, "f32", 2, 511), (16, "f32", 2, 4097)])
+def test_vote_and_update_around_a_tile(ss, oracle, M, dtype, flags, extra):
     d = (1 << 20) + extra
-    g = [draw(w, d, "bf16", 0.5) for w in range(M)]
+    g = [draw(w, d, dtype, 0.5) for w in range(M)]
     x_dev = draw(99, d, "f32", 0.05)
-    x = synth.as_numpy(x_dev).copy()
+    x_lent, x = x_dev.clone(), synth.as_numpy(x_dev).copy()
     voted, packed = dirty_bits(ss, d), [dirty_bits(ss, d) for _ in range(M)]
     sums = torch.full((d,), 77, dtype=torch.int8, device=DEV) if flags else None
     ss.signum_vote_step_ex(g, None, 0.9, 1e-4, x_dev, voted, packed, sums, flags)
@@ -87,6 +92,17 @@ def test_vote_and_update_around_a_tile(ss, oracle, M, flags, extra):
     assert np.array_equal(bits_np(voted), want)
     assert all(np.array_equal(bits_np(packed[w]), want_packed[w]) for w in range(M))
     assert_same_floats(x_dev, x, "x")
+    if flags:
+        assert np.array_equal(sums.cpu().numpy(), want_sums)
+        sums.fill_(77)
+    voted.fill_(-1)
+    lent = torch.empty(M * ss.packed_bytes(d), dtype=torch.uint8, device=DEV)
+    table = (ctypes.c_void_p * M)(*[t.data_ptr() for t in g])
+    assert ss.load_library().ss_signum_vote_step_scratch(
+        table, int(dtype == "bf16"), None, M, 0.9, 1e-4, x_lent.data_ptr(), voted.data_ptr(), sums.data_ptr() if flags else None,
+        lent.data_ptr(), lent.numel(), d, flags, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    assert np.array_equal(bits_np(voted), want)
+    assert_same_floats(x_lent, x, "x over lent memory")
     if flags:
         assert np.array_equal(sums.cpu().numpy(), want_sums)
 
@@ -116,12 +132,16 @@ def test_one_pass_around_runs_and_rules(ss, oracle, d, M, dtype, momentum):
     assert_same_floats(x_dev, x, "x")
 
 
-# with packed_out, on both sides of the line from which two launches pay: 2^30 bytes for three workers, 2^27 for eight, 2^28
-# without momentum
+# with packed_out, on both sides of the line from which two launches pay: 2^30 bytes for three to five workers, 2^28 for six and
+# seven, 2^27 for eight and more; 2^28 without momentum
 @pytest.mark.parametrize("d,M,dtype,momentum", [((1 << 30) // 36 - 3, 3, "f32", True), ((1 << 30) // 36 + 3, 3, "f32", True),
                                                 ((1 << 27) // 80 - 1, 8, "bf16", True), ((1 << 27) // 80 + 1, 8, "bf16", True),
                                                 ((1 << 25) // 2 - 1, 2, "bf16", False), ((1 << 25) // 2 + 1, 2, "bf16", False),
                                                 ((1 << 24) + 300, 2, "f32", True),
+                                                ((1 << 30) // 48 + 1025, 4, "f32", True), ((1 << 30) // 50 + 31, 5, "bf16", True),
+                                                ((1 << 28) // 72 - 1, 6, "f32", True), ((1 << 28) // 72 + 4095, 6, "f32", True),
+                                                ((1 << 28) // 70 + 255, 7, "bf16", True), ((1 << 27) // 90 + 129, 9, "bf16", True),
+                                                ((1 << 27) // 144 + (1 << 17), 12, "f32", True),
                                                 ((1 << 28) // 4 - 1, 2, "bf16", False), ((1 << 28) // 4 + 129, 2, "bf16", False),
                                                 ((1 << 28) // 28, 7, "f32", False), ((1 << 28) // 28 + 1, 7, "f32", False),
                                                 ((1 << 28) // 32 - 255, 16, "bf16", False), ((1 << 20) + 4097, 33, "f32", False),
