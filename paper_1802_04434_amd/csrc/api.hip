@@ -102,14 +102,14 @@ inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = s
 
 // ------------------------------------------------------------------------
 // Launch shapes of the step kernel (see step_kernels.hpp for the reasoning).
-//   streaming shape, several workers and more data than the 256 MB memory-side cache holds: one or
-//     a few workers at a time, and a reservation of LDS that no kernel touches, sized so that the
-//     wanted number of blocks fits in the 160 KB of a gfx950 compute unit
+//   streaming shape, several workers and more bytes than the line below: one or a few workers at a time, and a
+//     reservation of LDS that no kernel touches, sized so that the wanted number of blocks fits in the 160 KB of a
+//     gfx950 compute unit (the only one that the library is built for)
 //   latency shape, everything smaller: the loads of up to eight workers at once, no cap
-// The line between them, bytes of gradients and momentum (us, latency against streaming shape): with momentum fp32 1.1 M
-// M = 12 (158 MB) 29.9 / 29.2, 2.2 M M = 7 (185 MB) 36.4 / 34.6, 4.4 M M = 4 (211 MB) 41.8 / 40.3, 1.1 M M = 16 (211 MB) 39.6 / 37.0,
-// 4.4 M M = 5 (264 MB) 51.9 / 47.5, bf16 2.2 M M = 8 (176 MB) 35.0 / 35.3, 12 M M = 2 (240 MB) 55.1 / 52.1; without it the
-// streaming shapes pay from 2^28 bytes on.
+// The line between them, in bytes of gradients and momentum, where momentum counts twice, read and written, here and below.  us,
+// latency against streaming shape: with momentum fp32 1.1 M M = 12 (158 MB) 29.9 / 29.2, 2.2 M M = 7 (185 MB) 36.4 / 34.6, 4.4 M
+// M = 4 (211 MB) 41.8 / 40.3, 1.1 M M = 16 (211 MB) 39.6 / 37.0, 4.4 M M = 5 (264 MB) 51.9 / 47.5, bf16 2.2 M M = 8 (176 MB)
+// 35.0 / 35.3, 12 M M = 2 (240 MB) 55.1 / 52.1; without it the streaming shapes pay from 2^28 bytes on.
 inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
     return d * (size_t)M * worker_bytes >= (has_m ? (size_t)5 << 25 : (size_t)1 << 28);
 }
@@ -120,7 +120,9 @@ inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
 // momentum: M = 2 fp32 8.8 M 45.1 / 48.7, 25.6 M 124.7 / 125.6, 60 M 287 / 290; M = 3 8.8 M 61.5 / 63.7, 25.6 M (920 MB)
 // 171.1 / 170.4, bf16 8.8 M 54.2 / 57.5, 138 M (4.2 GB) 802 / 787; M = 4 17.6 M (845 MB) 149.2 / 149.6, 25.6 M (1.2 GB) 217 / 214;
 // M = 5 8.8 M (528 MB) 94.0 / 94.3, 25.6 M (1.5 GB) 265 / 260; M = 7 2.2 M (185 MB) 35.4 / 35.4, 4.4 M (370 MB) 65.1 / 64.9, 6.6 M
-// 95.6 / 93.3; M = 9 1.1 M (119 MB) 23.1 / 24.0; M = 16 1.1 M (211 MB) 38.8 / 37.7; bf16 M = 8 4.4 M 65.5 / 62.1.
+// 95.6 / 93.3; M = 9 1.1 M (119 MB) 23.1 / 24.0; M = 16 1.1 M (211 MB) 38.8 / 37.7; bf16 M = 8 4.4 M 65.5 / 62.1.  Up to the next
+// step of the rule M = 6 and 7 differ by type: 268 MB fp32 49.0 / 49.8 and 47.8 / 49.9, bf16 51.8 / 50.9 and 51.6 / 49.8, 537 MB
+// fp32 94.4 / 94.2 and 91.8 / 92.8, bf16 98.1 / 93.7 and 96.8 / 94.4.
 // Without momentum where the streaming shapes begin, bytes of gradients: fp32 M = 2 8.4 M (67 MB) 22.7 / 27.2, 33.5 M (268 MB) 83.2 /
 // 86.8 before the line and 92.3 / 88.4 behind it, 67 M 183 / 166, M = 4 4.2 M 17.6 / 21.8, 16.8 M 66.6 / 67.0, 33.6 M 122.4 / 125.1,
 // 134 M 503 / 493, M = 8 4.2 M 29.6 / 32.3, 8.4 M 57.7 / 58.1 and 61.7 / 57.0, 16.8 M 116 / 106, M = 16 4.2 M 53.2 / 54.2, 7.8 M
@@ -257,7 +259,7 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
         if (streams(M, d, HAS_M, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0))) {
             // Streaming shapes: one-wave blocks of one row, written through, tiles in order.
             if constexpr (HAS_M) {
-                // One worker a stage and 11 to 14 waves a unit, the fewer the more workers.  KB held back and us, against the
+                // One worker a stage and 10 to 14 waves a unit, the fewer the more workers.  KB held back and us, against the
                 // shapes of one to four larger blocks a unit that were used before: fp32 13: 12 M M = 3 82.5 / 87.2, 25.6 M M = 2
                 // 122.5 / 134, M = 4 215.6 / 232, 138 M M = 2 647 / 733, M = 4 1,151 / 1,250; 14 (13): M = 5 261.7 (261.8) / 277,
                 // M = 9 454.7 (456.9) / 479, M = 16 805 (830) / 840; bf16 11: M = 3 147.2 / 165.6, 138 M M = 2 565 / 674, M = 4 993 / 1,123;
@@ -341,8 +343,10 @@ int launch_pack_momentum(ss::PackArgs<NPTR> &a, int n, hipStream_t stream) {
 
 // Gradients only, one stream that is only read: two rows a wave and half a megabyte a die up to where the runs stop paying,
 // which is later in fp32.  In order / in runs, us: fp32 4.4 M M = 8 25.2 / 22.6, 25.6 M M = 1 17.3 / 15.9, M = 7 115 / 111, 60 M
-// M = 4 152 / 150, 400 M M = 2 512 / 519 (two waves of two rows in order 509); bf16 17.6 M M = 2 13.3 / 12.3, 25.6 M M = 1
-// 9.8 / 9.2, 60 M M = 4 79.6 / 80.2, 138 M M = 4 180 / 182.
+// M = 4 152 / 150, 400 M M = 2 512 / 519; bf16 17.6 M M = 2 13.3 / 12.3, 25.6 M M = 1 9.8 / 9.2, 60 M M = 4 79.6 / 80.2, 138 M
+// M = 4 180 / 182.  fp32 beyond 2^27, in order by two waves / in runs, a worker alone 134 M 82.8 / 80.7, 400 M 244.1 / 244.0, 537 M
+// 326.7 / 328.5, a step's pack and update M = 4 134 M 493.5 / 495.1, 400 M 1,519 / 1,550, M = 8 200 M 1,290 / 1,317; in order
+// by one wave within 0.8 % of two (134 M alone 84.4, otherwise level).
 template <int NPTR>
 int launch_pack_sign(ss_dtype gdt, ss::PackArgs<NPTR> &a, int n, hipStream_t stream) {
     if (gdt == SS_BF16) {
@@ -427,7 +431,9 @@ int launch_two(const void *const *g, ss_dtype gdt, float *const *m, int M, float
     return dispatch_vote_apply(packed, M, voted, x, delta, var, d, stream);
 }
 
-// The votes, sums and quorum votes read M (2 M) buffers at once, in one-wave blocks.  Up to some tens of millions of coordinates
+// The votes, sums and quorum votes read M (2 M) buffers at once, in one-wave blocks.  Figures here are over three sets of buffers in
+// turn, and one session's differ from another's by 3 %; over one set, which the memory-side cache keeps, runs and order are level
+// (M = 7 25.6 M vote 5.8 / 5.7, sums 7.7 / 7.6).  Up to some tens of millions of coordinates
 // nothing is held back and a die takes an eighth of a megabyte of every buffer at a time; beyond, tiles go in order with a cap that
 // leaves fewer waves the more loads each has out.  us, runs / in order and capped / four-wave blocks without runs as launched
 // before: vote M = 3 390 M 31.9 / 32.5 / 32.6, M = 7 25.6 M 5.0 / 5.3 / 5.4, 138 M 23.7 / 24.4 / 25.0, M = 8 17.6 M 4.0 / 4.4 / 5.0, 138 M

@@ -216,9 +216,8 @@ __global__ __launch_bounds__(64) void vote_word_kernel(const VoteArgs<64> a) {
 // --------------------------------------------------------------- apply ----
 
 // The updates from bits, from sums and from an answer with abstentions stream x in place, 8 bytes a coordinate, and read
-// little beside it.  One-wave blocks: two rows, the L2 writing back and a quarter or half of a megabyte a die while a vector
-// fits the caches (kApplySmall), one row written through in the same runs beyond.  us, two rows / one row / blocks of four
-// waves as launched before: apply 1.1 M 2.4 / 3.3 / 2.9, 4.4 M 6.7 / 7.2 / 7.2, 8.8 M 12.0 / 12.0 / 12.7, 25.6 M 32.2 / 31.5 / 33.0,
+// little beside it.  One-wave blocks in runs of half a megabyte a die: two rows, the L2 writing back while a vector fits
+// the caches (kApplySmall), one row written through beyond.  us, two rows / one row / blocks of four waves as launched before: apply 1.1 M 2.4 / 3.3 / 2.9, 4.4 M 6.7 / 7.2 / 7.2, 8.8 M 12.0 / 12.0 / 12.7, 25.6 M 32.2 / 31.5 / 33.0,
 // 138 M 170 / 165 / 171, 390 M 486 / 465 / 482; sums 1.1 M 2.6 / 3.3 / 3.2, 25.6 M 35.6 / 35.1 / 35.7, 138 M 188 / 184 / 188;
 // answers 1.1 M 2.7 / 3.5, 25.6 M 32.9 / 31.9 / 32.7, 138 M 172 / 166 / 170.
 constexpr int kWaveCoords = kWave * kQuad;
