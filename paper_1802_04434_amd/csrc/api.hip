@@ -432,8 +432,8 @@ int launch_two(const void *const *g, ss_dtype gdt, float *const *m, int M, float
 }
 
 // The votes, sums and quorum votes read M (2 M) buffers at once, in one-wave blocks.  Figures here are over three sets of buffers in
-// turn, and one session's differ from another's by 3 %; over one set, which the memory-side cache keeps, runs and order are level
-// (M = 7 25.6 M vote 5.8 / 5.7, sums 7.7 / 7.6).  Up to some tens of millions of coordinates
+// turn, and one session's differ from another's by 3 %; over one set, which the memory-side cache keeps, runs gain nothing on the
+// blocks before (M = 7 25.6 M vote 5.8 / 5.7, sums 7.7 / 7.6).  Up to some tens of millions of coordinates
 // nothing is held back and a die takes an eighth of a megabyte of every buffer at a time; beyond, tiles go in order with a cap that
 // leaves fewer waves the more loads each has out.  us, runs / in order and capped / four-wave blocks without runs as launched
 // before: vote M = 3 390 M 31.9 / 32.5 / 32.6, M = 7 25.6 M 5.0 / 5.3 / 5.4, 138 M 23.7 / 24.4 / 25.0, M = 8 17.6 M 4.0 / 4.4 / 5.0, 138 M
