@@ -219,7 +219,7 @@ struct QuorumVoteArgs {
 
 // Bit-sliced, like the binary vote: a lane holds 128 coordinates (four words)
 // of every plane.  The numbers of "-" votes (n) and of abstentions (z) are
-// counted into binary planes with a ripple of half adders per worker; then
+// counted into binary planes, a batch of workers at a time; then
 // t = 2 n + z is formed plane by plane, and since S = #plus - #minus = M - t,
 //     answer "-"  iff  S <= -Q  iff  t >= M + Q
 //     answer  0   iff  |S| < Q  iff  M - Q < t < M + Q
@@ -251,18 +251,9 @@ __device__ __forceinline__ void quorum_batch(const uint32_t *const *neg, const u
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        u32x4 cz = zw[j];
-        u32x4 cn = nw[j] & ~zw[j];   // an abstention is not a vote, whatever the other plane says
-#pragma unroll
-        for (int k = 0; k < P; ++k) {
-            const u32x4 tn = n[k] & cn, tz = z[k] & cz;
-            n[k] ^= cn;
-            z[k] ^= cz;
-            cn = tn;
-            cz = tz;
-        }
-    }
+    for (int j = 0; j < NB; ++j) nw[j] &= ~zw[j];   // an abstention is not a vote, whatever the other plane says
+    add_words<0>(n, nw);
+    add_words<0>(z, zw);
 }
 
 // the m <= NMAX workers that the full batches leave over, as one batch of exactly that size
@@ -333,17 +324,11 @@ __device__ __forceinline__ void quorum_word(At1 neg_at, At2 zero_at, int M, int 
         }
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-            uint32_t cz = w0 + j < M ? zw[j] : 0u;
-            uint32_t cn = w0 + j < M ? nw[j] & ~zw[j] : 0u;   // an abstention is not a vote
-#pragma unroll
-            for (int k = 0; k < P; ++k) {
-                const uint32_t tn = n[k] & cn, tz = z[k] & cz;
-                n[k] ^= cn;
-                z[k] ^= cz;
-                cn = tn;
-                cz = tz;
-            }
+            nw[j] = w0 + j < M ? nw[j] & ~zw[j] : 0u;   // an abstention is not a vote
+            zw[j] = w0 + j < M ? zw[j] : 0u;
         }
+        add_words<0>(n, nw);
+        add_words<0>(z, zw);
     }
     is_neg = not_plus = 0xFFFFFFFFu;
     uint32_t carry = 0;

@@ -13,12 +13,15 @@ namespace ss {
 // votes, and the count is compared with the constant threshold
 // T = floor(M/2)+1 plane by plane.  32 coordinates per ALU lane-operation.
 
-struct Sum2 { uint32_t sum, carry; };
-__device__ __forceinline__ Sum2 full_add(uint32_t a, uint32_t b, uint32_t c) {
-    const uint32_t ab = a ^ b;
+template <typename W>    // a word, or four of them
+struct Sum2 { W sum, carry; };
+template <typename W>
+__device__ __forceinline__ Sum2<W> full_add(W a, W b, W c) {
+    const W ab = a ^ b;
     return {ab ^ c, (a & b) | (ab & c)};
 }
-__device__ __forceinline__ Sum2 half_add(uint32_t a, uint32_t b) { return {a ^ b, a & b}; }
+template <typename W>
+__device__ __forceinline__ Sum2<W> half_add(W a, W b) { return {a ^ b, a & b}; }
 
 // count >= T decided from the least significant plane upwards:
 // ge_k = plane_k > T_k, or equal and ge_(k-1)
@@ -37,12 +40,12 @@ struct CsaLevel {
         uint32_t acc = w[0];
 #pragma unroll
         for (int j = 0; j < kFull; ++j) {
-            const Sum2 s = full_add(acc, w[1 + 2 * j], w[2 + 2 * j]);
+            const Sum2<uint32_t> s = full_add(acc, w[1 + 2 * j], w[2 + 2 * j]);
             acc = s.sum;
             next[j] = s.carry;
         }
         if constexpr (N % 2 == 0) {
-            const Sum2 s = half_add(acc, w[N - 1]);
+            const Sum2<uint32_t> s = half_add(acc, w[N - 1]);
             acc = s.sum;
             next[kFull] = s.carry;
         }
@@ -113,46 +116,63 @@ __global__ __launch_bounds__(BLOCK) void vote_kernel(const VoteArgs<M> a) {
     st_stream(reinterpret_cast<u32x4 *>(a.voted) + u, out);
 }
 
-// Any M up to SS_MAX_WORKERS: the count planes are kept in seven registers
-// and every word is added with a ripple of half adders.
+// Any M up to SS_MAX_WORKERS: the binary planes of the count are kept in registers and a batch of words
+// is added to them at a time.
 constexpr int kPlanes = 7;   // counts up to 64 < 2^7
 
+// N words of weight 2^K into the planes from K up (what would leave the last plane is zero: M < 2^P).  Two words a full adder, so
+// that eight words cost seven full adders and P - 3 half adders, two instructions each; a ripple of half adders
+// from the lowest plane up for every word by itself is 8 P of them.  us, ripple / this: vote M = 24 8.8 M coordinates 7.3 / 6.7, 40 M
+// 22.4 / 21.3, quorum votes M = 24 17.6 M 20.1 / 19.0, 138 M 147 / 141, M = 12 8.8 M 6.5 / 6.1; beyond, memory decides (390 M: level).
+template <int K, int P, int N, typename W>
+__device__ __forceinline__ void add_words(W (&plane)[P], const W (&w)[N]) {
+    if constexpr (K < P) {
+        W carry[(N + 1) / 2];
+        W acc = plane[K];
+#pragma unroll
+        for (int j = 0; j < N / 2; ++j) {
+            const Sum2<W> s = full_add(acc, w[2 * j], w[2 * j + 1]);
+            acc = s.sum;
+            carry[j] = s.carry;
+        }
+        if constexpr (N % 2 != 0) {
+            const Sum2<W> s = half_add(acc, w[N - 1]);
+            acc = s.sum;
+            carry[N / 2] = s.carry;
+        }
+        plane[K] = acc;
+        add_words<K + 1>(plane, carry);
+    }
+}
+
 // NB workers' 128-bit groups loaded together (no test between the loads: all NB are in flight
-// before the first is used), then rippled into the P count planes with half adders
+// before the first is used), then added
 template <int P, int NB, uint32_t CHUNK>
-__device__ __forceinline__ void ripple_batch(const uint32_t *const *packed, const Group<CHUNK> &at, u32x4 (&plane)[P]) {
+__device__ __forceinline__ void count_batch(const uint32_t *const *packed, const Group<CHUNK> &at, u32x4 (&plane)[P]) {
     u32x4 in[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) in[j] = at.load(packed[j]);
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        u32x4 carry = in[j];
-#pragma unroll
-        for (int k = 0; k < P; ++k) {
-            const u32x4 t = plane[k] & carry;
-            plane[k] ^= carry;
-            carry = t;
-        }
+    add_words<0>(plane, in);
+}
+
+// the m <= NMAX workers that the full batches leave over, as one batch of exactly that size
+template <int P, int NMAX, uint32_t CHUNK>
+__device__ __forceinline__ void count_rest(const uint32_t *const *packed, int m, const Group<CHUNK> &at, u32x4 (&plane)[P]) {
+    if (m == NMAX) {
+        count_batch<P, NMAX>(packed, at, plane);
+    } else if constexpr (NMAX > 1) {
+        count_rest<P, NMAX - 1>(packed, m, at, plane);
     }
 }
 
-// all M workers: full batches of NB, then the remaining 1 .. NB-1 as one batch of exactly that size
 template <int P, int NB, uint32_t CHUNK>
-__device__ __forceinline__ void ripple_all(const uint32_t *const *packed, int M, const Group<CHUNK> &at, u32x4 (&plane)[P]) {
-    static_assert(NB == 8, "the remainder switch below lists 1 .. 7");
+__device__ __forceinline__ void count_all(const uint32_t *const *packed, int M, const Group<CHUNK> &at, u32x4 (&plane)[P]) {
+#pragma unroll
+    for (int k = 0; k < P; ++k) plane[k] = u32x4{0, 0, 0, 0};
     int w0 = 0;
-    for (; w0 + NB <= M; w0 += NB) ripple_batch<P, NB>(packed + w0, at, plane);
-    switch (M - w0) {
-        case 1: ripple_batch<P, 1>(packed + w0, at, plane); break;
-        case 2: ripple_batch<P, 2>(packed + w0, at, plane); break;
-        case 3: ripple_batch<P, 3>(packed + w0, at, plane); break;
-        case 4: ripple_batch<P, 4>(packed + w0, at, plane); break;
-        case 5: ripple_batch<P, 5>(packed + w0, at, plane); break;
-        case 6: ripple_batch<P, 6>(packed + w0, at, plane); break;
-        case 7: ripple_batch<P, 7>(packed + w0, at, plane); break;
-        default: break;
-    }
+    for (; w0 + NB <= M; w0 += NB) count_batch<P, NB>(packed + w0, at, plane);
+    count_rest<P, NB - 1>(packed + w0, M - w0, at, plane);
 }
 
 template <int HOLD_KB, uint32_t CHUNK>
@@ -163,9 +183,7 @@ __global__ __launch_bounds__(kWave) void vote_kernel_any(const VoteArgs<64> a) {
     if (u >= a.n_vec) return;
     const int T = a.M / 2 + 1;
     u32x4 plane[kPlanes];
-#pragma unroll
-    for (int k = 0; k < kPlanes; ++k) plane[k] = u32x4{0, 0, 0, 0};
-    ripple_all<kPlanes, 8>(a.packed, a.M, at, plane);
+    count_all<kPlanes, 8>(a.packed, a.M, at, plane);
     u32x4 ge = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
 #pragma unroll
     for (int k = 0; k < kPlanes; ++k) ge = ((T >> k) & 1) ? (plane[k] & ge) : (plane[k] | ge);
@@ -187,15 +205,8 @@ __device__ __forceinline__ void count_words(const uint32_t *const *packed, int M
 #pragma unroll
         for (int j = 0; j < NB; ++j) word[j] = packed[w0 + j < M ? w0 + j : w0][wi];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            uint32_t carry = w0 + j < M ? word[j] : 0u;
-#pragma unroll
-            for (int k = 0; k < P; ++k) {
-                const uint32_t t = plane[k] & carry;
-                plane[k] ^= carry;
-                carry = t;
-            }
-        }
+        for (int j = 0; j < NB; ++j) word[j] = w0 + j < M ? word[j] : 0u;
+        add_words<0>(plane, word);
     }
 }
 
@@ -387,7 +398,7 @@ __global__ __launch_bounds__(BLOCK) void vote_apply_kernel(const VoteApplyArgs<N
 // ------------------------------------------------ "(good)": vote sums ----
 // Section 4's first scheme sends back the sum of the workers' signs instead of
 // its sign.  Bit-sliced like the vote: a lane loads 128 coordinates (four words)
-// of every worker with one 128-bit load and ripples them into the binary planes
+// of every worker with one 128-bit load and adds them into the binary planes
 // of the count of "-" votes; only at the end are the planes turned into one
 // int8 per coordinate.  A lane's 128 sums are contiguous in memory, so the block
 // passes them through LDS and stores them in coordinate order (a wave's store is
@@ -400,6 +411,43 @@ struct VoteSumArgs {
     size_t d;
     size_t n_vec;      // 128-bit groups of packed words, padding included
 };
+
+// The planes of a word's 32 counts as bytes: byte c of out[q] is the count of coordinate 4 q + c.  The four lowest planes are
+// transposed within every nibble (c[j] then holds the counts of the coordinates 4 i + j, one a nibble), nibbles are
+// widened to bytes and the planes above are put in, and four words of four bytes are transposed: some 45 instructions
+// for four planes where expanding each nibble of each plane by a multiplication took 200 and 32 multiplications.  With
+// add_words, sums, us before / now: M = 8 8.8 M coordinates 5.4 / 4.9, 40 M 16.1 / 15.5, M = 24 4.4 M 5.7 / 5.4, M = 12 17.6 M 7.8 / 7.4.
+template <int P>
+__device__ __forceinline__ void count_bytes(const uint32_t (&plane)[P], uint32_t (&out)[8]) {
+    const auto at = [&](int k) { return k < P ? plane[k < P ? k : 0] : 0u; };
+    const auto choose = [](uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); };
+    const uint32_t p0 = at(0), p1 = at(1), p2 = at(2), p3 = at(3);
+    const uint32_t a01 = choose(0x55555555u, p0, p1 << 1), b01 = choose(0x55555555u, p0 >> 1, p1);
+    const uint32_t a23 = choose(0x55555555u, p2, p3 << 1), b23 = choose(0x55555555u, p2 >> 1, p3);
+    const uint32_t c[4] = {choose(0x33333333u, a01, a23 << 2), choose(0x33333333u, b01, b23 << 2),
+                           choose(0x33333333u, a01 >> 2, a23), choose(0x33333333u, b01 >> 2, b23)};
+    uint32_t even[4], odd[4];     // byte b: coordinates 8 b + j and 8 b + 4 + j
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        even[j] = c[j] & 0x0F0F0F0Fu;
+        odd[j] = (c[j] >> 4) & 0x0F0F0F0Fu;
+#pragma unroll
+        for (int k = 4; k < P; ++k) {
+            even[j] |= (plane[k] << (k - j)) & (0x01010101u << k);
+            odd[j] |= (k - 4 >= j ? plane[k] << (k - 4 - j) : plane[k] >> (j + 4 - k)) & (0x01010101u << k);
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t(&v)[4] = h ? odd : even;
+        const uint32_t lo01 = __builtin_amdgcn_perm(v[1], v[0], 0x05010400u), hi01 = __builtin_amdgcn_perm(v[1], v[0], 0x07030602u);
+        const uint32_t lo23 = __builtin_amdgcn_perm(v[3], v[2], 0x05010400u), hi23 = __builtin_amdgcn_perm(v[3], v[2], 0x07030602u);
+        out[h] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
+        out[2 + h] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
+        out[4 + h] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
+        out[6 + h] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+    }
+}
 
 constexpr int kVoteSumBatch = 8;           // workers whose words are loaded together
 constexpr int kVoteSumLaneBytes = 128;     // a lane's 128 coordinates give 128 int8 sums
@@ -418,22 +466,21 @@ __global__ __launch_bounds__(kWave) void vote_sum_kernel(const VoteSumArgs a) {
     // lie at or beyond d and are never stored
     if (at.u >= a.n_vec) at.u = a.n_vec - 1;
     u32x4 plane[P];
-#pragma unroll
-    for (int k = 0; k < P; ++k) plane[k] = u32x4{0, 0, 0, 0};
-    ripple_all<P, kVoteSumBatch>(a.packed, a.M, at, plane);
+    count_all<P, kVoteSumBatch>(a.packed, a.M, at, plane);
     // planes -> one int8 sum per coordinate: the lane's 128 sums go to LDS as eight 16-byte pieces
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        u32x4 piece;
+    for (int w = 0; w < 4; ++w) {
+        uint32_t column[P], counts[8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int shift = 4 * ((q & 1) * 4 + e);     // nibble of word q / 2
-            uint32_t counts = 0;
+        for (int k = 0; k < P; ++k) column[k] = plane[k][w];
+        count_bytes(column, counts);
 #pragma unroll
-            for (int k = 0; k < P; ++k) counts += spread_nibble((plane[k][q >> 1] >> shift) & 0xFu) << k;
-            piece[e] = sums_word(counts, a.M);
+        for (int h = 0; h < 2; ++h) {
+            u32x4 piece;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) piece[e] = sums_word(counts[4 * h + e], a.M);
+            *reinterpret_cast<u32x4 *>(tile + lane * kVoteSumLdsStride + 16 * (2 * w + h)) = piece;
         }
-        *reinterpret_cast<u32x4 *>(tile + lane * kVoteSumLdsStride + 16 * q) = piece;
     }
     __syncthreads();
     // ... and leave in the order of the coordinates: a store is 1024 contiguous bytes
@@ -472,13 +519,9 @@ __global__ __launch_bounds__(64) void vote_sum_word_kernel(const VoteSumArgs a) 
     uint32_t plane[P];
     count_words<P, 16>(a.packed, a.M, wi, plane);
     uint32_t out[8];
+    count_bytes(plane, out);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        uint32_t counts = 0;
-#pragma unroll
-        for (int k = 0; k < P; ++k) counts += spread_nibble((plane[k] >> (4 * q)) & 0xFu) << k;
-        out[q] = sums_word(counts, a.M);
-    }
+    for (int q = 0; q < 8; ++q) out[q] = sums_word(out[q], a.M);
     if (wi * 32 + 32 <= a.d) {
         u32x4 *const to = reinterpret_cast<u32x4 *>(a.sums + wi * 32);
         to[0] = u32x4{out[0], out[1], out[2], out[3]};
