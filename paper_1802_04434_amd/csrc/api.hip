@@ -432,15 +432,16 @@ int launch_two(const void *const *g, ss_dtype gdt, float *const *m, int M, float
 }
 
 // The votes, sums and quorum votes read M (2 M) buffers at once, in one-wave blocks.  Figures here are over three sets of buffers in
-// turn, and one session's differ from another's by 3 %; over one set, which the memory-side cache keeps, runs gain nothing on the
-// blocks before (M = 7 25.6 M vote 5.8 / 5.7, sums 7.7 / 7.6).  Up to some tens of millions of coordinates
-// nothing is held back and a die takes an eighth of a megabyte of every buffer at a time; beyond, tiles go in order with a cap that
-// leaves fewer waves the more loads each has out.  us, runs / in order and capped / four-wave blocks without runs as launched
-// before: vote M = 3 390 M 31.9 / 32.5 / 32.6, M = 7 25.6 M 5.0 / 5.3 / 5.4, 138 M 23.7 / 24.4 / 25.0, M = 8 17.6 M 4.0 / 4.4 / 5.0, 138 M
-// 26.4 / 26.8 / 27.8, 390 M 71.0 / 67.9 / 75, M = 16 8.8 M 4.1 / 5.1 / 5.4, 25.6 M 9.3 / 11.1 / 11.1, 40 M 14.7 / 15.3 / 15.5, 138 M
-// 48.3 / 46.7 / 52, M = 24 (any) 25.6 M 14.2 / 16.0 / 16.4, 40 M 20.9 / 22.3 / 23.0, 138 M 69.6 / 68.4 / 76.
-constexpr uint32_t kVoteChunk = 7;
-constexpr size_t kVoteRuns = (size_t)1 << 26;   // runs below, capped from here on
+// turn, and one session's differ from another's by 3 %; where a rule was replaced, the figure in brackets is what it gave.  Up to some tens
+// of millions of coordinates nothing is held back and a die takes an eighth of a megabyte of every buffer at a time (kVoteChunk); where
+// twelve buffers and more are open, from 2^27 coordinates on half a megabyte (kVoteLongChunk) with a cap that leaves fewer waves the
+// more loads each has out; from 2^28 on tiles go in order, capped.  us, eighths / halves capped / in order capped: vote M = 7 138 M
+// 23.1 / 22.4 / 25.1, M = 9 110 M 23.1 / 23.3 / 24.0, 138 M 28.6 / 27.7 / 28.9, 390 M 78.7 / 75.2 / 75.0; M = 12 100 M 26.6 / - / 28.3, 138 M 36.5 / 35.1 /
+// 36.8, M = 16 80 M 28.0 / 28.5 / 30.1, 110 M 38.1 / 38.7 / 39.8, 138 M 47.6 / 46.0 / 50.2, 200 M 68.6 / 66.9 / 69.3, 390 M 134 / 130 / 129, 1,000 M 350 /
+// 344 / 327; M = 24 (any) 80 M 40.9 / 40.9 / 42.3, 138 M 70.2 / 67.2 / 72.1, 390 M 198 / 189 / 190, 1,000 M 520 / 508 / 489.  From Python: M = 16
+// 138 M 45.5 (48.5), M = 17 110 M 40.5 (43.6), M = 33 138 M 91.1 (97).
+constexpr uint32_t kVoteChunk = 7, kVoteLongChunk = 9;
+constexpr size_t kVoteRuns = (size_t)1 << 26, kVoteHalves = (size_t)1 << 27, kVoteInOrder = (size_t)1 << 28;
 
 // One word a lane instead of four (the *_word_kernels) up to here; sums and quorum votes of up to eight workers a third of it.  us,
 // word / 128-bit lanes: sums M = 16 4.4 M coordinates 4.2 / 5.7, 8.8 M 6.0 / 6.5, 17.6 M 12.7 / 9.9, M = 7 4.4 M 4.0 / 3.7; quorum
@@ -458,7 +459,7 @@ int launch_vote_fixed(const uint32_t *const *packed, uint32_t *voted, size_t d, 
     a.d = d;
     a.n_vec = ss_packed_bytes(d) / 16;
     // Up to three workers, little to wait for: four-wave blocks, and from 2^26 coordinates on runs (8.8 M M = 3 2.4 us in runs against 2.3,
-    // 25.6 M 3.3 / 3.1, 390 M 30.9 / 31.6).  Up to eleven the cap pays later.
+    // 25.6 M 3.3 / 3.1, 390 M 30.9 / 31.6).
     const bool few = M < 4 && d < kVoteRuns;
     const size_t block = few ? ss::kBlock : ss::kWave;
     const size_t grid = (a.n_vec + block - 1) / block;
@@ -468,7 +469,9 @@ int launch_vote_fixed(const uint32_t *const *packed, uint32_t *voted, size_t d, 
         if (d < ((size_t)1 << 34)) return launch(ss::vote_kernel<M, ss::kWave, 0, kVoteChunk>, grid, 0, stream, a, ss::kWave);
         return launch(ss::vote_kernel<M, ss::kWave, 0, 0>, grid, 0, stream, a, ss::kWave);
     } else {
-        if (d < (M < 12 ? kVoteRuns << 2 : kVoteRuns)) return launch(ss::vote_kernel<M, ss::kWave, 0, kVoteChunk>, grid, 0, stream, a, ss::kWave);
+        if (d < (M < 12 ? kVoteInOrder : kVoteHalves)) return launch(ss::vote_kernel<M, ss::kWave, 0, kVoteChunk>, grid, 0, stream, a, ss::kWave);
+        if constexpr (M >= 12)
+            if (d < kVoteInOrder) return launch(ss::vote_kernel<M, ss::kWave, 20, kVoteLongChunk>, grid, 0, stream, a, ss::kWave);
         return launch(ss::vote_kernel<M, ss::kWave, M >= 8 ? 20 : 8, 0>, grid, 0, stream, a, ss::kWave);
     }
 }
@@ -483,23 +486,37 @@ int launch_vote_any(const uint32_t *const *packed, int M, uint32_t *voted, size_
     if (d < kVoteWords) return launch(ss::vote_word_kernel, (4 * a.n_vec + 63) / 64, 0, stream, a, 64);
     const size_t grid = (a.n_vec + ss::kWave - 1) / ss::kWave;
     if (grid > kMaxGrid) return SS_ERR_ARG;
-    if (d < kVoteRuns) return launch(ss::vote_kernel_any<0, kVoteChunk>, grid, 0, stream, a, ss::kWave);
+    if (d < kVoteHalves) return launch(ss::vote_kernel_any<0, kVoteChunk>, grid, 0, stream, a, ss::kWave);
+    if (d < kVoteInOrder) return launch(ss::vote_kernel_any<16, kVoteLongChunk>, grid, 0, stream, a, ss::kWave);
     return launch(ss::vote_kernel_any<16, 0>, grid, 0, stream, a, ss::kWave);
 }
 
-// sums: in runs the L2 writes back, beyond they are written through with 7 KB held back beside the tile's 9.  us, runs / capped / before:
-// M = 3 17.6 M 4.5 / 4.5 / 5.3, 390 M 88.9 / 82.7 / 89.4, M = 7 25.6 M 7.3 / 10.5 / 9.3, 138 M 44.3 / 43.6 / 47.2, M = 16 17.6 M 9.9 /
-// 11.5 / 12.7, 40 M 21.6 / 23.4 / 23.7, 138 M 69.6 / 68.7 / 72.2, 390 M 193 / 184.5 / 192
+// Sums, in runs of 64 tiles a die.  Eight workers' words a batch and the sums written through; from 2^24 coordinates on four to seven
+// workers leave them to the L2 and more load four a batch; from kVoteRuns on 7 KB are held back beside the tile's 9, and from eight workers on
+// the runs go on to kVoteInOrder.  us, sums to the L2 / through: M = 2 13 M 4.6 / 4.2, 60 M 14.2 / 12.4, M = 7 8.8 M 4.8 / 4.2, 17.6 M 5.8 / 5.6, 25.6 M
+// 7.7 / 8.1, 60 M 20.5 / 21.5, M = 16 17.6 M 9.5 / 9.0; eight / four a batch: M = 5 25.6 M 6.7 / 7.3, M = 12 13 M 6.1 / 6.5, 25.6 M 12.0 / 10.9, M = 16
+// 25.6 M 14.8 / 12.4, M = 24 13 M 9.8 / 10.0, 17.6 M 13.9 / 13.4, 25.6 M 19.4 / 18.3, 60 M 41.8 / 41.9; beyond, in order / in runs: M = 7 138 M 43.3 / 43.6, M = 9
+// 80 M 32.6 / 32.1, M = 12 80 M 35.8 / 34.6, 138 M 57.9 / 56.8, M = 13 138 M 61.1 / 59.5, M = 33 138 M 121.5 / 118, 250 M 211 / 210, M = 24 1,000 M 646 / 652.
 template <int P>
 int launch_vote_sum(const ss::VoteSumArgs &a, size_t grid, hipStream_t stream) {
-    if (a.d < kVoteRuns) return launch(ss::vote_sum_kernel<P, 0, ss::kStream, kVoteChunk - 1>, grid, 0, stream, a, ss::kWave);
-    return launch(ss::vote_sum_kernel<P, 7, ss::kThrough, 0>, grid, 0, stream, a, ss::kWave);
+    using ss::kStream;
+    using ss::kThrough;
+    constexpr uint32_t kRun = kVoteChunk - 1;
+    if (a.d < kVoteRuns) {
+        if (P < 3 || a.d < ((size_t)1 << 24)) return launch(ss::vote_sum_kernel<P, 0, kThrough, kRun, 8>, grid, 0, stream, a, ss::kWave);
+        if constexpr (P == 3) return launch(ss::vote_sum_kernel<P, 0, kStream, kRun, 8>, grid, 0, stream, a, ss::kWave);
+        else if constexpr (P > 3) return launch(ss::vote_sum_kernel<P, 0, kThrough, kRun, 4>, grid, 0, stream, a, ss::kWave);
+    }
+    if constexpr (P > 3)
+        if (a.d < kVoteInOrder) return launch(ss::vote_sum_kernel<P, 7, kThrough, kRun, 8>, grid, 0, stream, a, ss::kWave);
+    return launch(ss::vote_sum_kernel<P, 7, kThrough, 0, 8>, grid, 0, stream, a, ss::kWave);
 }
 
-// quorum: us, runs / capped (26 KB; up to four workers 16) / four-wave blocks, four workers a batch: M = 7 4.4 M 3.6 / 3.6 / 4.1, 17.6 M 7.4 /
-// 8.7 / 7.6, 138 M 47.2 / 46.1 / 50.7, M = 16 17.6 M 13.8 / 16.8 / 15.8, 25.6 M 19.5 / 23.1 / 20.9, 60 M 44.2 / - / 46.0, 138 M 100.8 /
-// 95.8 / 104-115, 390 M 284 / 268 / 279, M = 24 25.6 M 27.9 / 33.1 / 30.4; M = 3 17.6 M 4.5 / 4.5 / 4.3, 25.6 M 5.7 / 6.5 / 5.6, 138 M
-// 24.0 / 24.5 / 28.0, 390 M 62.4 / 60.6 / 70.2
+// Quorum votes, us, eighths / halves capped / in order capped: M = 7 80 M 27.3 / 29.9 / 28.2, 138 M 47.6 / 45.0 / 46.2, 390 M 131 / 126 / 121; M = 16
+// 80 M 57.6 / 61.3 / 58.4, 110 M 78.5 / - / 79.8, 138 M 100 / 95.0 / 101, 220 M - / 150 / 153, 390 M 282 / 272 / 270; M = 24 110 M 114 / - / 119, 138 M 146 /
+// 139 / 146, 220 M - / 220 / 224.  Five to seven workers in halves: 138 M 34.7 (35.8), 39.5 (40.9), 45.0 (45.1), 220 M 53 (52), 61.6 (60.6), 70 (70):
+// not worth it.  Up to seven workers in eighths, eight / four a batch, M = 7 17.6 M 7.3 / 7.1, 25.6 M 9.8 / 9.5, 48 M 17.5 / 16.8, M = 6 48 M 15.3 / 14.6,
+// M = 5 17.6 M 5.9 / 6.2, 25.6 M 7.8 / 7.7.  Up to three workers four-wave blocks without runs, then 16 KB held back, in order, as for four.
 template <int P>
 int launch_quorum_vote(const ss::QuorumVoteArgs &a, hipStream_t stream) {
     const bool few = P <= 2 && a.d < kVoteRuns;
@@ -507,12 +524,17 @@ int launch_quorum_vote(const ss::QuorumVoteArgs &a, hipStream_t stream) {
     const size_t grid = (a.n_vec + block - 1) / block;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     if constexpr (P <= 2) {
-        if (few) return launch(ss::quorum_vote_kernel<P, ss::kBlock, 0, 0>, grid, 0, stream, a);
-        return launch(ss::quorum_vote_kernel<P, ss::kWave, 16, 0>, grid, 0, stream, a, ss::kWave);
+        if (few) return launch(ss::quorum_vote_kernel<P, ss::kBlock, 0, 0, 8>, grid, 0, stream, a);
+        return launch(ss::quorum_vote_kernel<P, ss::kWave, 16, 0, 8>, grid, 0, stream, a, ss::kWave);
     } else {
-        if (a.d < kVoteRuns) return launch(ss::quorum_vote_kernel<P, ss::kWave, 0, kVoteChunk>, grid, 0, stream, a, ss::kWave);
-        if (a.M <= 4) return launch(ss::quorum_vote_kernel<P, ss::kWave, 16, 0>, grid, 0, stream, a, ss::kWave);
-        return launch(ss::quorum_vote_kernel<P, ss::kWave, 26, 0>, grid, 0, stream, a, ss::kWave);
+        if (a.M == 4 && a.d >= kVoteRuns) return launch(ss::quorum_vote_kernel<P, ss::kWave, 16, 0, 8>, grid, 0, stream, a, ss::kWave);
+        if constexpr (P == 3) {
+            if (a.d >= ((size_t)5 << 22) && a.d < kVoteHalves) return launch(ss::quorum_vote_kernel<P, ss::kWave, 0, kVoteChunk, 4>, grid, 0, stream, a, ss::kWave);
+        } else {
+            if (a.d >= kVoteHalves && a.d < kVoteInOrder) return launch(ss::quorum_vote_kernel<P, ss::kWave, 26, kVoteLongChunk, 8>, grid, 0, stream, a, ss::kWave);
+        }
+        if (a.d < kVoteHalves) return launch(ss::quorum_vote_kernel<P, ss::kWave, 0, kVoteChunk, 8>, grid, 0, stream, a, ss::kWave);
+        return launch(ss::quorum_vote_kernel<P, ss::kWave, 26, 0, 8>, grid, 0, stream, a, ss::kWave);
     }
 }
 

@@ -224,8 +224,6 @@ struct QuorumVoteArgs {
 //     answer "-"  iff  S <= -Q  iff  t >= M + Q
 //     answer  0   iff  |S| < Q  iff  M - Q < t < M + Q
 // which are two comparisons of t with constants, done from the lowest plane up.
-constexpr int kQuorumBatch = 8;    // workers (two planes each) whose words are loaded together
-
 __device__ __forceinline__ u32x4 splat(uint32_t v) { return u32x4{v, v, v, v}; }
 
 // planes of (t >= c) for a constant c, t given by its N binary planes
@@ -268,8 +266,8 @@ __device__ __forceinline__ void quorum_rest(const uint32_t *const *neg, const ui
 }
 
 // P = number of binary planes of n and z (M < 2^P); t = 2 n + z <= 2 M needs one more.
-// HOLD_KB: LDS reserved to cap the blocks per compute unit.
-template <int P, int BLOCK, int HOLD_KB, uint32_t CHUNK>
+// HOLD_KB: LDS reserved to cap the blocks per compute unit; NB: workers (two planes each) whose words are loaded together.
+template <int P, int BLOCK, int HOLD_KB, uint32_t CHUNK, int NB>
 __global__ __launch_bounds__(BLOCK) void quorum_vote_kernel(const QuorumVoteArgs a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.voted_neg);
     constexpr int kCountPlanes = P;
@@ -281,8 +279,8 @@ __global__ __launch_bounds__(BLOCK) void quorum_vote_kernel(const QuorumVoteArgs
 #pragma unroll
     for (int k = 0; k < kCountPlanes; ++k) n[k] = z[k] = splat(0u);
     int w0 = 0;
-    for (; w0 + kQuorumBatch <= a.M; w0 += kQuorumBatch) quorum_batch<P, kQuorumBatch>(a.neg + w0, a.zero + w0, at, n, z);
-    quorum_rest<P, kQuorumBatch - 1>(a.neg + w0, a.zero + w0, a.M - w0, at, n, z);
+    for (; w0 + NB <= a.M; w0 += NB) quorum_batch<P, NB>(a.neg + w0, a.zero + w0, at, n, z);
+    quorum_rest<P, NB - 1>(a.neg + w0, a.zero + w0, a.M - w0, at, n, z);
     // t = 2 n + z
     u32x4 t[kTotalPlanes];
     t[0] = z[0];

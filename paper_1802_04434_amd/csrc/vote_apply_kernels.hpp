@@ -417,8 +417,14 @@ struct VoteSumArgs {
 // widened to bytes and the planes above are put in, and four words of four bytes are transposed: some 45 instructions
 // for four planes where expanding each nibble of each plane by a multiplication took 200 and 32 multiplications.  With
 // add_words, sums, us before / now: M = 8 8.8 M coordinates 5.4 / 4.9, 40 M 16.1 / 15.5, M = 24 4.4 M 5.7 / 5.4, M = 12 17.6 M 7.8 / 7.4.
+// A single plane is expanded by multiplications (M = 1 138 M 28.6 us, transposed 28.9).
 template <int P>
 __device__ __forceinline__ void count_bytes(const uint32_t (&plane)[P], uint32_t (&out)[8]) {
+    if constexpr (P == 1) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) out[q] = spread_nibble((plane[0] >> (4 * q)) & 0xFu);
+        return;
+    }
     const auto at = [&](int k) { return k < P ? plane[k < P ? k : 0] : 0u; };
     const auto choose = [](uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); };
     const uint32_t p0 = at(0), p1 = at(1), p2 = at(2), p3 = at(3);
@@ -449,13 +455,12 @@ __device__ __forceinline__ void count_bytes(const uint32_t (&plane)[P], uint32_t
     }
 }
 
-constexpr int kVoteSumBatch = 8;           // workers whose words are loaded together
 constexpr int kVoteSumLaneBytes = 128;     // a lane's 128 coordinates give 128 int8 sums
 constexpr int kVoteSumLdsStride = 144;     // ... kept 144 bytes apart in LDS (spreads the banks)
 
 // P = number of binary planes of the count of "-" votes: counts up to M < 2^P.  One-wave blocks; HOLD_KB of LDS on top of the tile,
-// STORE and CHUNK by the size of the vector (ss_vote_sum)
-template <int P, int HOLD_KB, int STORE, uint32_t CHUNK>
+// STORE, CHUNK and how many workers' words are loaded together (NB) by the size of the vector (launch_vote_sum)
+template <int P, int HOLD_KB, int STORE, uint32_t CHUNK, int NB>
 __global__ __launch_bounds__(kWave) void vote_sum_kernel(const VoteSumArgs a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, reinterpret_cast<uint32_t *>(a.sums));
     __shared__ __align__(16) unsigned char tile[kWave * kVoteSumLdsStride];
@@ -466,7 +471,7 @@ __global__ __launch_bounds__(kWave) void vote_sum_kernel(const VoteSumArgs a) {
     // lie at or beyond d and are never stored
     if (at.u >= a.n_vec) at.u = a.n_vec - 1;
     u32x4 plane[P];
-    count_all<P, kVoteSumBatch>(a.packed, a.M, at, plane);
+    count_all<P, NB>(a.packed, a.M, at, plane);
     // planes -> one int8 sum per coordinate: the lane's 128 sums go to LDS as eight 16-byte pieces
 #pragma unroll
     for (int w = 0; w < 4; ++w) {

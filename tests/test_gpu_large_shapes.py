@@ -157,7 +157,7 @@ def test_vote_sum_and_quorum_vote_large(ss, oracle, M):
     assert np.array_equal(bits_np(vz), want_z)
 
 
-# a cap from 2^28 coordinates on, from twelve workers on from 2^26; never for three
+# a cap from 2^28 coordinates on, from twelve workers on from 2^27; never for three
 @pytest.mark.parametrize("M,d", [(3, D30), (17, D30), (4, (1 << 28) + 1), (8, (1 << 28) + 8191), (11, (1 << 28) + 127),
                                  (8, (1 << 28) - 1), (12, (1 << 27) + 33), (16, (1 << 27) + 8193), (16, (1 << 27) - 129),
                                  (24, (1 << 26) + 65)])

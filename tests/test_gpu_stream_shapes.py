@@ -271,7 +271,7 @@ def check_server(ss, d, M, Q):
 
 
 # a wave's tile is 8,192 coordinates, dies take 64 (sums) or 128 tiles in turn; one word a lane below 2^22 (from nine workers
-# on 3 x 2^22, votes of more than sixteen 3 x 2^21), no runs from 2^26 on (votes of up to eleven workers 2^28)
+# on 3 x 2^22, votes of more than sixteen 3 x 2^21); 2^26 is where caps and orders begin to change
 @pytest.mark.parametrize("M", [2, 7, 12, 16, 24])
 @pytest.mark.parametrize("d", [(1 << 22) - 1, (1 << 22) + 8191, (1 << 23) + 31, (3 << 21) - 7, (3 << 21) + 7, (3 << 22) - 5, (3 << 22) + 8193,
                                (1 << 26) - 3, (1 << 26) + 129])
@@ -288,6 +288,16 @@ def test_server_around_rules(ss, M, d):
                                    (64, (3 << 22) + 8191, 9), (64, (1 << 26) + 129, 5)])
 def test_server_in_lanes_of_four_words(ss, M, d, Q):
     check_server(ss, d, M, Q)
+
+
+# The runs of 512 tiles and the rules of the larger vectors: votes of twelve workers and more and quorum votes of eight and more in runs from 2^27
+# to 2^28, sums of eight and more from 2^26 to 2^28; sums four a batch from 2^24 on, quorum votes of up to seven from 5 x 2^22.  The
+# first and the last coordinates, where the runs begin and end, and what does not fill a round of them.
+@pytest.mark.parametrize("M,d", [(5, (5 << 22) - 1), (6, (5 << 22) + 33), (7, (1 << 24) - 129), (9, (1 << 24) + 1), (13, (1 << 24) + 8193), (33, (1 << 24) + 31),
+                                 (9, (1 << 26) + 8191), (5, (1 << 27) - 1), (13, (1 << 27) + 4097), (20, (1 << 27) - 33), (17, (1 << 27) + 8193),
+                                 (8, (1 << 27) + 1), (12, (1 << 28) - 31), (17, (1 << 28) - 8193), (9, (1 << 28) + 129), (12, (1 << 28) + 1)])
+def test_server_in_long_runs(ss, M, d):
+    check_server(ss, d, M, 2)
 
 
 # ---- the longest vectors: shapes that only they take, the reference in chunks on the device
