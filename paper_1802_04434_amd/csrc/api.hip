@@ -106,12 +106,22 @@ inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = s
 //     reservation of LDS that no kernel touches, sized so that the wanted number of blocks fits in the 160 KB of a
 //     gfx950 compute unit (the only one that the library is built for)
 //   latency shape, everything smaller: the loads of up to eight workers at once, no cap
-// The line between them, in bytes of gradients and momentum, where momentum counts twice, read and written, here and below.  us,
-// latency against streaming shape: with momentum fp32 1.1 M M = 12 (158 MB) 29.9 / 29.2, 2.2 M M = 7 (185 MB) 36.4 / 34.6, 4.4 M
-// M = 4 (211 MB) 41.8 / 40.3, 1.1 M M = 16 (211 MB) 39.6 / 37.0, 4.4 M M = 5 (264 MB) 51.9 / 47.5, bf16 2.2 M M = 8 (176 MB)
-// 35.0 / 35.3, 12 M M = 2 (240 MB) 55.1 / 52.1; without it the streaming shapes pay from 2^28 bytes on.
+// With momentum the line between them is kKeepMost bytes of momentum and x written: up to there what a step writes is left in the
+// memory-side cache (kKeep), where the next step finds it unless much else has come between.  us over three states in turn, streaming and
+// through / streaming and kept / latency and kept: M = 9 2.0 M coordinates (80 MB written) 42.1 / 39.8 / 35.8, 2.2 M (88) 44.2 / 42.5 / 39.5, M = 7 2.8 M (90) 43.5 /
+// 41.4 / 39.5, M = 12 1.7 M (88) 43.8 / 42.0 / 40.0, M = 7 3.1 M (99) 46.4 / 45.0 / 45.5, M = 2 8.2 M (98) 41.6 / 41.4 / 43.2, M = 5 4.4 M (106) 48.0 / 48.7 / 51.5.
+// Below some 16 MB (one worker and bf16 gradients 24 MB, more than eight workers 32 MB) keeping costs 1-6 %: M = 7 400,001 (13) 7.8 / 7.3, 272,474
+// (9) 5.7 / 6.0, M = 16 400,001 (27) 15.3 / 15.8, 550,003 (37) 20.9 / 19.5, bf16 M = 8 400,001 (14) 7.6 / 8.0, 700,001 (25) 11.9 / 11.7, M = 4 900,001
+// (18) 8.7 / 8.9, 1.7 M (34) 15.3 / 14.9, M = 1 2.2 M (18) 8.35 / 8.5, 5.0 M (40) 17.2 / 16.3.
+// Without momentum, where x alone is written, the streaming shapes pay from 2^28 bytes of gradients on.
+constexpr size_t kKeepMost = (size_t)11 << 23;
+inline size_t step_written(int M, size_t d, bool has_m) { return d * sizeof(float) * (has_m ? M + 1 : 1); }
+inline bool step_keeps(int M, size_t d, bool has_m, bool bf16) {
+    const size_t written = step_written(M, d, has_m);
+    return written >= (size_t)(M > 8 ? 4 : bf16 || M == 1 ? 3 : 2) << 23 && written < kKeepMost;
+}
 inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
-    return d * (size_t)M * worker_bytes >= (has_m ? (size_t)5 << 25 : (size_t)1 << 28);
+    return has_m ? step_written(M, d, true) >= kKeepMost : d * (size_t)M * worker_bytes >= (size_t)1 << 28;
 }
 
 // Given packed_out buffers, the step runs as two launches - pack_kernel over all workers, then vote
@@ -120,8 +130,9 @@ inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
 // momentum: M = 2 fp32 8.8 M 45.1 / 48.7, 25.6 M 124.7 / 125.6, 60 M 287 / 290; M = 3 8.8 M 61.5 / 63.7, 25.6 M (920 MB)
 // 171.1 / 170.4, bf16 8.8 M 54.2 / 57.5, 138 M (4.2 GB) 802 / 787; M = 4 17.6 M (845 MB) 149.2 / 149.6, 25.6 M (1.2 GB) 217 / 214;
 // M = 5 8.8 M (528 MB) 94.0 / 94.3, 25.6 M (1.5 GB) 265 / 260; M = 7 2.2 M (185 MB) 35.4 / 35.4, 4.4 M (370 MB) 65.1 / 64.9, 6.6 M
-// 95.6 / 93.3; M = 9 1.1 M (119 MB) 23.1 / 24.0; M = 16 1.1 M (211 MB) 38.8 / 37.7; bf16 M = 8 4.4 M 65.5 / 62.1.  Up to the next
-// step of the rule M = 6 and 7 differ by type: 268 MB fp32 49.0 / 49.8 and 47.8 / 49.9, bf16 51.8 / 50.9 and 51.6 / 49.8, 537 MB
+// 95.6 / 93.3; bf16 M = 8 4.4 M 65.5 / 62.1.  From eight workers on they take over where the streaming shapes begin: one pass leaves
+// what it writes in the memory-side cache up to there, M = 8 2.0 M 33.6 / 37.2, bf16 2.4 M 34.4 / 38.5, M = 12 1.5 M 35.4 / 39.5, M = 16 1.1 M 35.2 /
+// 37.1.  Up to the next step of the rule M = 6 and 7 differ by type: 268 MB fp32 49.0 / 49.8 and 47.8 / 49.9, bf16 51.8 / 50.9 and 51.6 / 49.8, 537 MB
 // fp32 94.4 / 94.2 and 91.8 / 92.8, bf16 98.1 / 93.7 and 96.8 / 94.4.
 // Without momentum where the streaming shapes begin, bytes of gradients: fp32 M = 2 8.4 M (67 MB) 22.7 / 27.2, 33.5 M (268 MB) 83.2 /
 // 86.8 before the line and 92.3 / 88.4 behind it, 67 M 183 / 166, M = 4 4.2 M 17.6 / 21.8, 16.8 M 66.6 / 67.0, 33.6 M 122.4 / 125.1,
@@ -131,7 +142,8 @@ inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
 inline bool split_pays(int M, size_t d, bool has_m, size_t worker_bytes) {
     if (M < 2 || d < ((size_t)1 << 20)) return false;
     if (!has_m) return streams(M, d, false, worker_bytes);
-    return M >= 3 && d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 8 ? 27 : M >= 6 ? 28 : 30));
+    if (M >= 8) return streams(M, d, true, worker_bytes);
+    return M >= 3 && d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 6 ? 28 : 30));
 }
 
 // A launch may have at most 2^32 - 1 threads, which a shape with one row of quads a lane reaches at 2^34
@@ -246,13 +258,17 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
     a.sum_update = (var.flags & SS_STEP_SUM_UPDATE) ? 1 : 0;
     a.sums = var.sums;
     constexpr bool kBf16 = std::is_same<G, ss::Bf16Grad>::value;
+    using ss::kCached;
+    using ss::kKeep;
     using ss::kStream;
     using ss::kThrough;
+    const bool keep = step_keeps(M, d, HAS_M, kBf16);
     if constexpr (MT == 1) {
         // One worker: one-wave blocks; from 2^24 coordinates on written through and with a cap.  us, as below 2^24 /
         // capped / four waves of two rows: with momentum fp32 8.8 M 28.6 / 29.2 / 29.1, 17.6 M 55.8 / 54.7 / 57.2, 25.6 M 79.9 /
         // 77.8 / 82.2, 138 M 433 / 410 / 477, bf16 25.6 M 72.1 / 70.2 / 73.2; without fp32 17.6 M 33.0 / 33.1 / 33.8, 25.6 M
         // 46.8 / 46.8 / 48.3, 60 M 108 / 106 / 116, bf16 138 M 206 / 201 / 226
+        if (keep) return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kKeep, 8, HAS_M, G>(a, d, stream);
         if (d >= ((size_t)1 << 24)) return launch_step_shape<1, NPTR, 64, 1, 1, HAS_M ? 10 : 6, false, kThrough, 0, HAS_M, G>(a, d, stream);
         return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kStream, 8, HAS_M, G>(a, d, stream);
     } else {
@@ -279,6 +295,7 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
                 // fp32: four workers a stage make up for the missing momentum stream.  us, against two four-wave blocks a unit before:
                 // 25.6 M M = 3 76.4 / 83.1, 4 91.8 / 94.6, 7 135.4 / 145.5, 8 153.8 / 160.1, 9 169.0 / 178.3, 16 279.8 / 288.5, 138 M
                 // M = 2 319 / 345, M = 7 734 / 806
+                if (keep) return launch_step_shape<MT, NPTR, 64, 4, 1, MT == 2 ? 11 : 13, false, kKeep, 0, false, G>(a, d, stream);
                 return launch_step_shape<MT, NPTR, 64, 4, 1, MT == 2 ? 11 : 13, false, kThrough, 0, false, G>(a, d, stream);
             }
         }
@@ -288,7 +305,15 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
         // 13.3, 1.1 M M = 7 (runs of 256) 18.4 / 18.6 / 19.6, M = 16 38.8 / 38.8 / 43.7, 4.4 M M = 4 - / 42.1 / 44.3, gradients alone
         // 272,474 M = 16 6.0 / 6.0 / 6.5, 8.8 M M = 4 34.3 / 34.2 / 35.6
         constexpr int BW = MT > 0 && MT < 8 ? MT : 8;
-        if (d < ((size_t)1 << 20)) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, 6, HAS_M, G>(a, d, stream);
+        const bool small = d < ((size_t)1 << 20);
+        if (keep && small) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kKeep, 6, HAS_M, G>(a, d, stream);
+        if (keep) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kKeep, 8, HAS_M, G>(a, d, stream);
+        // Up to seven workers, whose loads are one stage, and 26 MB in all, written lines stay in every cache.  us, not / so: M = 3 400,001 4.6 /
+        // 4.2, 700,001 6.4 / 6.0, M = 4 bf16 400,001 5.0 / 4.6, M = 7 180,001 4.6 / 4.4, 272,474 5.75 / 5.55; more workers lose: M = 12 272,474 8.6 / 10.0.
+        if constexpr (MT > 0 && MT < 8 && HAS_M) {
+            if (small && d * (size_t)((kBf16 ? 6 : 8) * MT + 4) < ((size_t)25 << 20)) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kCached, 6, HAS_M, G>(a, d, stream);
+        }
+        if (small) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, 6, HAS_M, G>(a, d, stream);
         return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, 8, HAS_M, G>(a, d, stream);
     }
 }
@@ -556,12 +581,14 @@ template <bool HAS_M, bool VOTE, typename G>
 int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     constexpr bool kBf16 = std::is_same<G, ss::Bf16Grad>::value;
     constexpr size_t kBytes = sizeof(typename G::elem) + (HAS_M ? 2 * sizeof(float) : 0);
+    using ss::kKeep;
     using ss::kStream;
     using ss::kThrough;
     if constexpr (VOTE) {
         // two rows where a row a lane has too many threads
         if (d >= kOneRowMaxD) return launch_ternary_shape<1, 2, 13, false, kThrough, 0, HAS_M, true, G>(a, d, stream);
-        if (a.M == 1 ? d >= ((size_t)1 << 24) : streams(a.M, d, HAS_M, kBytes)) {
+        const bool keep = step_keeps(a.M, d, HAS_M, kBf16);
+        if (a.M == 1 ? d >= ((size_t)1 << 24) && !keep : streams(a.M, d, HAS_M, kBytes)) {
             // us, KB held back: with momentum fp32 11 / 13 / 16: 25.6 M M = 1 80.8 / 84.7 / 92.4, M = 2 125.7 / 133.3 / 146.4, M = 4 217.9 /
             // 219.9 / 235.7, M = 7 367.9 / 360.6 / 375.2, M = 16 868 / 840 / 831, bf16 11 / 12 / 14: M = 3 151.3 / 157.5 / 172.8, M = 8
             // 60 M 840 / 832 / 887; gradients alone 10 / 13: fp32 M = 3 80.2 / 83.1, M = 7 143.2 / 137.6, bf16 M = 7 90.3 / 115.4.
@@ -575,7 +602,10 @@ int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
                 return launch_ternary_shape<4, 1, kBf16 ? 10 : 13, false, kThrough, 0, false, true, G>(a, d, stream);
             }
         }
-        if (d < ((size_t)1 << 20)) return launch_ternary_shape<8, 1, 0, true, kStream, 6, HAS_M, true, G>(a, d, stream);
+        const bool small = d < ((size_t)1 << 20);
+        if (keep && small) return launch_ternary_shape<8, 1, 0, true, kKeep, 6, HAS_M, true, G>(a, d, stream);
+        if (keep) return launch_ternary_shape<8, 1, 0, true, kKeep, 8, HAS_M, true, G>(a, d, stream);
+        if (small) return launch_ternary_shape<8, 1, 0, true, kStream, 6, HAS_M, true, G>(a, d, stream);
         return launch_ternary_shape<8, 1, 0, true, kStream, 8, HAS_M, true, G>(a, d, stream);
     } else if constexpr (HAS_M) {
         if (d * (size_t)a.M * kBytes < ((size_t)1 << 28)) return launch_ternary_shape<1, 1, 0, false, kStream, 8, true, false, G>(a, d, stream);

@@ -108,7 +108,7 @@ def test_vote_and_update_around_a_tile(ss, oracle, M, dtype, flags, extra):
 
 
 # One pass.  Runs of 64 tiles of 256 coordinates a die below 2^20 coordinates, of 256 above; the streaming shapes begin at
-# 5 x 2^25 bytes of gradients and momentum (2^28 without momentum), one worker's at 2^24 coordinates.
+# 11 x 2^23 bytes of momentum and x written (2^28 bytes of gradients without momentum), one worker's at 2^24 coordinates.
 STEPS = [((1 << 17) - 1, 7, "f32", True), ((1 << 17) + 77, 16, "bf16", True), ((1 << 17) + 255, 1, "f32", True),
          ((1 << 18) + 256, 9, "f32", True), ((1 << 20) - 1, 3, "bf16", False), ((1 << 20) + 300, 6, "f32", False),
          ((5 << 25) // 84 - 1, 7, "f32", True), ((5 << 25) // 84 + 1, 7, "f32", True), ((5 << 25) // 24 + 255, 2, "f32", True),
@@ -132,8 +132,46 @@ def test_one_pass_around_runs_and_rules(ss, oracle, d, M, dtype, momentum):
     assert_same_floats(x_dev, x, "x")
 
 
+# Where what a step writes is left in the memory-side cache: both ends of that range (16, 24 or 32 MB, by workers and type, to 11 x 2^23
+# bytes of momentum and x), the small steps of up to seven workers whose lines stay in every cache (25 x 2^20 bytes in all), and the two
+# launches that packed_out takes beyond it.  Two steps in a row, binary and with abstentions: the second reads what the first left.
+MOST = 11 << 23
+KEPT = [((1 << 24) // 32 - 1, 7, "f32", True), ((1 << 24) // 32 + 1, 7, "f32", True), (MOST // 32 - 1, 7, "f32", True), (MOST // 32, 7, "f32", True),
+        ((3 << 23) // 36 + 1, 8, "bf16", True), (MOST // 36 - 255, 8, "bf16", True), (MOST // 36 + 1, 8, "f32", True),
+        ((1 << 25) // 52 + 1, 12, "f32", True), ((1 << 25) // 52 - 300, 12, "bf16", True), (MOST // 40 - 1, 9, "f32", True), (MOST // 12 + 257, 2, "bf16", True),
+        ((25 << 20) // 28 - 1, 3, "f32", True), ((25 << 20) // 28 + 33, 3, "f32", True), ((25 << 20) // 28 - 257, 4, "bf16", True), (10_007, 2, "f32", True),
+        ((3 << 23) // 8 + 1, 1, "f32", True), (MOST // 8 - 1, 1, "bf16", True), (MOST // 8 + 1, 1, "f32", True), (MOST // 4 - 1, 1, "f32", False),
+        ((1 << 24) // 4 + 1, 3, "f32", False), ((1 << 28) // 28 + 257, 7, "f32", False), ((1 << 28) // 64 + 1, 16, "f32", False), (MOST // 4 - 513, 4, "f32", False),
+        (MOST // 4 + 1, 4, "bf16", False)]
+
+
+@pytest.mark.parametrize("d,M,dtype,momentum", KEPT)
+def test_steps_that_leave_their_lines_in_the_caches(ss, oracle, d, M, dtype, momentum):
+    g = [draw(d + w, d, dtype, 0.5) for w in range(M)]
+    g_host = [synth.as_numpy(t) for t in g]
+    m0, x0 = [draw(d - w, d, "f32", 0.3) for w in range(M)] if momentum else None, draw(7, d, "f32", 0.05)
+    for kind in ("step", "packed", "ternary") if d * M < 20_000_000 else ("step", "ternary") if M < 7 else ("step",):
+        m_dev, x_dev = [t.clone() for t in m0] if momentum else None, x0.clone()
+        m, x = [synth.as_numpy(t).copy() for t in m0] if momentum else None, synth.as_numpy(x0).copy()
+        packed = [dirty_bits(ss, d) for _ in range(M)] if kind == "packed" else None
+        for _ in range(2):
+            voted, zero = dirty_bits(ss, d), dirty_bits(ss, d)
+            if kind == "ternary":
+                ss.signum_vote_step_ternary(g, m_dev, 0.9, 0.1, 2, 1e-4, x_dev, voted, zero)
+                want, want_zero = oracle.signum_vote_step_ternary(g_host, m, 0.9, 0.1, 2, 1e-4, x)
+                assert np.array_equal(bits_np(zero), want_zero)
+            else:
+                ss.signum_vote_step(g, m_dev, 0.9, 1e-4, x_dev, voted, packed)
+                want, want_packed = oracle.signum_vote_step(g_host, m, 0.9, 1e-4, x, want_packed=True, threads=16)
+                assert all(np.array_equal(bits_np(packed[w]), want_packed[w]) for w in range(M if packed else 0))
+            assert np.array_equal(bits_np(voted), want), kind
+        for w in range(M if momentum else 0):
+            assert_same_floats(m_dev[w], m[w], "%s m[%d]" % (kind, w))
+        assert_same_floats(x_dev, x, "%s x" % kind)
+
+
 # with packed_out, on both sides of the line from which two launches pay: 2^30 bytes for three to five workers, 2^28 for six and
-# seven, 2^27 for eight and more; 2^28 without momentum
+# seven, for eight and more where the streaming shapes begin; 2^28 without momentum
 @pytest.mark.parametrize("d,M,dtype,momentum", [((1 << 30) // 36 - 3, 3, "f32", True), ((1 << 30) // 36 + 3, 3, "f32", True),
                                                 ((1 << 27) // 80 - 1, 8, "bf16", True), ((1 << 27) // 80 + 1, 8, "bf16", True),
                                                 ((1 << 25) // 2 - 1, 2, "bf16", False), ((1 << 25) // 2 + 1, 2, "bf16", False),
