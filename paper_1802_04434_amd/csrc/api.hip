@@ -899,15 +899,22 @@ int ss_welford_update(const void *g, ss_dtype gdt, float *mean, float *m2, uint6
     if (grid > kMaxGrid) return SS_ERR_ARG;
     const ss::WelfordArgs a{g, mean, m2, (float)n, (uint32_t)t.n_tiles, d};
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    // Runs of half a megabyte a die while a cache may hold something, from 2^24 coordinates on written through, in order, with 14 waves
-    // a unit.  us, in order before / runs / capped: fp32 4.4 M 15.7 / 14.9 / 16.3, 8.8 M 28.9 / 27.9 / 28.8, 17.6 M 55.7 / 55.4 / 54.4,
-    // 60 M 184 / 184 / 178; bf16 4.4 M 14.1 / 13.6 / 13.4, 8.8 M 25.9 / 25.4 / 25.8, 17.6 M 50.5 / 50.1 / 48.7
-    if (d >= ((size_t)1 << 24)) {
-        if (gdt == SS_F32) return launch(ss::welford_update_kernel<11, ss::kThrough, 0, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
-        return launch(ss::welford_update_kernel<11, ss::kThrough, 0, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
+    // m2 is left in the memory-side cache (kKeep) for the next update and for sigma, the mean as long as both are not too much for it.
+    // In order, with 14 waves a unit; between 2^21 and 2^24 coordinates runs of half a megabyte a die.  us, update, sigma and two densities,
+    // everything written through / m2 and sigma kept / the mean too, in order: 1.1 M 18.3 / 17.1 / 16.5 (runs 17.7), 8.8 M 61.6 / 57.4 / 56.5
+    // (runs 55.7), 17.6 M 105.8 / 99.3 / 98.2 (runs 100.5), 30 M 169.2 / 158.1 / 156.9, 40 M 220.0 / 205.1 / 205.5, 48 M 261.6 / 243.8 / 251.0, 60 M 323 / 302 / 317, 138 M
+    // 742 / 736 / 742; m2 alone kept 60 M 303.6, 80 M 405.5 (428, with sigma 419.7), 138 M 715, 390 M 2,024 (2,059).
+    const bool runs = d >= ((size_t)1 << 21) && d < ((size_t)1 << 24), both = d < ((size_t)5 << 23);
+    using ss::kKeep;
+    using ss::kThrough;
+    if (gdt == SS_F32) {
+        if (runs) return launch(ss::welford_update_kernel<0, kKeep, 9, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
+        if (both) return launch(ss::welford_update_kernel<11, kKeep, 0, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
+        return launch(ss::welford_update_kernel<11, kThrough, 0, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
     }
-    if (gdt == SS_F32) return launch(ss::welford_update_kernel<0, ss::kStream, 9, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
-    return launch(ss::welford_update_kernel<0, ss::kStream, 9, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
+    if (runs) return launch(ss::welford_update_kernel<0, kKeep, 9, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
+    if (both) return launch(ss::welford_update_kernel<11, kKeep, 0, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
+    return launch(ss::welford_update_kernel<11, kThrough, 0, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
 }
 
 int ss_welford_sigma(const float *m2, uint64_t n, float *sigma, size_t d, void *hip_stream) {
@@ -924,11 +931,18 @@ int ss_welford_sigma(const float *m2, uint64_t n, float *sigma, size_t d, void *
     const ss::SigmaArgs a{m2, sigma, (float)n, (uint32_t)t.n_tiles, d};
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (two_rows) return launch(ss::welford_sigma_kernel<2, ss::kThrough>, grid, 0, stream, a, ss::kWave);
-    if (d >= ((size_t)1 << 24)) return launch(ss::welford_sigma_kernel<1, ss::kThrough>, grid, 0, stream, a, ss::kWave);
-    return launch(ss::welford_sigma_kernel<1, ss::kStream>, grid, 0, stream, a, ss::kWave);
+    // kept for the density that reads it next while the cache can hold all of it: 60 M 301.8 us of statistics against 303.6, 80 M 419.7 / 405.5
+    if (d >= ((size_t)1 << 26)) return launch(ss::welford_sigma_kernel<1, ss::kThrough>, grid, 0, stream, a, ss::kWave);
+    return launch(ss::welford_sigma_kernel<1, ss::kKeep>, grid, 0, stream, a, ss::kWave);
 }
 
 size_t ss_density_workspace_bytes(void) { return sizeof(ss::DensityScratch); }
+
+// Rows of a density tile: short tiles while the blocks are few, eight rows where their number, that is the tickets', counts, and six,
+// whose 48 KB do not line blocks up on the same channels, where memory decides.  us, 3 / 8 / 6 rows: 100,003 3.7 / 3.8 / 3.8, 272,474 4.15 / 4.8 / 4.6,
+// 700,001 4.9 / 5.0 / 4.8, 1.1 M 5.8 / 5.0 / 5.0, 4.4 M 8.2 / 7.3 / 7.6, 25.6 M 19.0 / 18.7 / 19.1, 60 M 37.2 / 37.8 / 37.1, 100 M 59.1 / 64.3 / 58.7, 390 M
+// 217 / 226 / 217; four 86.6 at 138 M, two of which the next two are loaded early 80.8, six 79.7.
+static int density_rows(size_t d) { return d < ((size_t)3 << 18) ? 3 : d < ((size_t)1 << 25) ? 8 : 6; }
 
 // `partials` is a device address: the caller's workspace, or the looked-up address of the array above
 static int density_impl(const float *v, size_t d, double *out, ss::DensityScratch *partials, hipStream_t stream) {
@@ -938,12 +952,15 @@ static int density_impl(const float *v, size_t d, double *out, ss::DensityScratc
     a.scratch = partials;
     a.d = d;
     a.n_rows = d / ((size_t)ss::kDensityThreads * ss::kQuad);
-    a.n_tiles = a.n_rows / ss::kDensityRows;
+    const int rows = density_rows(d);
+    a.n_tiles = a.n_rows / rows;
     // every block gets the same number of tiles (the last one possibly fewer): the grid is a
     // function of d alone, which is what fixes the order of the additions
     const size_t per_block = (a.n_tiles + ss::kDensityMaxBlocks - 1) / ss::kDensityMaxBlocks;
     const size_t grid = per_block ? (a.n_tiles + per_block - 1) / per_block : 1;
-    return launch(ss::density_kernel, grid, 0, stream, a, ss::kDensityThreads);
+    if (rows == 3) return launch(ss::density_kernel<3>, grid, 0, stream, a, ss::kDensityThreads);
+    if (rows == 6) return launch(ss::density_kernel<6>, grid, 0, stream, a, ss::kDensityThreads);
+    return launch(ss::density_kernel<8>, grid, 0, stream, a, ss::kDensityThreads);
 }
 
 int ss_density(const float *v, size_t d, double *out, void *workspace, void *hip_stream) {

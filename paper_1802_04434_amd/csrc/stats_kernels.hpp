@@ -6,7 +6,7 @@
 // Welford is pointwise and streams like the step kernels (20 bytes per
 // coordinate: read g, mean, m2; write mean, m2).  The density is two sums over
 // d elements: every term is exact in fp64, each lane accumulates its share in
-// fp64, waves and blocks reduce through shuffles and LDS, each block leaves
+// fp64, waves reduce by lane moves and blocks through LDS, each block leaves
 // its pair of sums in a scratch slot and the last block to finish adds the
 // slots.  Every addition happens in an order that depends on d alone, so the
 // result is the same bits on every run.
@@ -34,9 +34,9 @@ __device__ __forceinline__ void welford1(float g, float n, float &mean, float &m
     m2 = m2 + p;
 }
 
-// One-wave blocks of one row.  Five streams; the shapes are the host's (ss_welford_update), us, now / before (addresses a
-// lane, the L2's own write-back): 25.6 M coordinates 77.6 / 80.0, 138 M 411 / 427, 390 M 1,148 / 1,197, bf16 138 M 366 / 384.
-template <int HOLD_KB, int STORE, uint32_t CHUNK, typename G>
+// One-wave blocks of one row.  Five streams; the shapes and what is left in the memory-side cache for the next update, for sigma and
+// for the densities are the host's (ss_welford_update).
+template <int HOLD_KB, int STORE_MEAN, uint32_t CHUNK, typename G>
 __global__ __launch_bounds__(kWave) void welford_update_kernel(const WelfordArgs a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, reinterpret_cast<uint32_t *>(a.mean));
     constexpr uint32_t kGrad = kWaveCoords * sizeof(typename G::elem), kFloat = kWaveCoords * sizeof(float);
@@ -55,8 +55,8 @@ __global__ __launch_bounds__(kWave) void welford_update_kernel(const WelfordArgs
             mean[c] = mean_c;
             m2[c] = m2_c;
         }
-        st_quad<STORE>(mean_w, lane * 16, mean);
-        st_quad<STORE>(m2_w, lane * 16, m2);
+        st_quad<STORE_MEAN>(mean_w, lane * 16, mean);
+        st_quad<kKeep>(m2_w, lane * 16, m2);
         return;
     }
     const size_t i = a.n_tiles * (size_t)kWaveCoords + (size_t)(blockIdx.x - a.n_tiles) * kWave + lane;
@@ -81,9 +81,7 @@ __device__ __forceinline__ float sigma1(float m2, float n) {
     return __builtin_sqrtf(var);
 }
 
-// R rows: one, but for vectors whose one-row grid would have 2^32 threads.  Read by address; written through (138 M 163.7 us
-// against 167.7, 390 M 458 / 466) unless the vector is small enough for a cache to hold what the next kernel reads: update,
-// sigma and the two densities at 1.1 M 19.7 / 18.6, at 4.4 M 39.1 / 38.0, at 17.6 M 107.2 / 108.6.
+// R rows: one, but for vectors whose one-row grid would have 2^32 threads.  Read by address; the store policy is the host's (ss_welford_sigma).
 template <int R, int STORE>
 __global__ __launch_bounds__(kWave) void welford_sigma_kernel(const SigmaArgs a) {
     constexpr uint32_t kCoords = R * kWaveCoords;
@@ -110,10 +108,10 @@ __global__ __launch_bounds__(kWave) void welford_sigma_kernel(const SigmaArgs a)
 }
 
 // ------------------------------------------------------------- density ----
-// One launch, fixed summation order.  Block b owns tiles b, b + G, b + 2G, ... of kDensityRows rows of
-// kDensityThreads quads (G = gridDim.x <= kDensityMaxBlocks, a function of d alone); the rows left over
+// One launch, fixed summation order.  Block b owns tiles b, b + G, b + 2G, ... of R rows of
+// kDensityThreads quads (R and G = gridDim.x <= kDensityMaxBlocks, functions of d alone); the rows left over
 // go to the blocks one by one.  Each lane adds its elements in that order in fp64, lanes combine
-// through a shuffle tree, waves through LDS, and the block's two sums go to slot b of a scratch array.
+// through a tree of lane moves, waves through LDS, and the block's two sums go to slot b of a scratch array.
 // The block that takes the last ticket adds the G slots in a fixed order (whichever block it is),
 // writes the result and puts the ticket back to zero for the next call.  A vector of less than two
 // tiles is one block's, which needs neither slots nor ticket.
@@ -121,14 +119,14 @@ __global__ __launch_bounds__(kWave) void welford_sigma_kernel(const SigmaArgs a)
 // What does not fill a tile used to be added one coordinate a lane and turn, a chain of up to 32
 // dependent loads (us): d = 1,000 3.6 -> 2.2, 10,007 5.5 -> 2.7, 40,001 5.0 -> 4.4.  Dealing all rows out
 // evenly instead of whole tiles to 134 - 256 blocks costs 1 us at 4.4 M (more tickets) and gains
-// nothing at 25.6 M.
+// nothing at 25.6 M.  After its last element a block is a chain of dependent steps; lane moves for the shuffles through LDS, one wave instead
+// of eight after the waves' sums and one rounding for product and sum took 0.6 - 0.8 us off it: 272,474 5.6 -> 4.8, 4.4 M 8.0 -> 7.3, 25.6 M 19.3 -> 18.7.
 
 // Few, large blocks: the tickets are atomics on one address and cost about 11 ns each, one after
 // the other, at the very end of the launch (measured: 780 blocks of 256 threads 25 us at
 // d = 25.6 M, 223 blocks of 512 threads 18 us; a plain read of the same bytes 16 us).
 constexpr int kDensityMaxBlocks = 256;
 constexpr int kDensityThreads = 512;
-constexpr int kDensityRows = 8;          // rows of a tile, whose loads are issued together
 
 // layout of the scratch area: ticket counter, then one pair of sums per block
 struct DensityScratch {
@@ -146,35 +144,35 @@ struct DensityArgs {
     size_t n_rows;     // full rows, those of the tiles included
 };
 
+// the square of a 24-bit significand is exact, so that one rounding is what product and sum give
 __device__ __forceinline__ void accumulate(float v, double &l1, double &l2sq) {
     const double a = (double)__builtin_fabsf(v);
     l1 += a;
-    l2sq += a * a;     // exact product of two 24-bit significands
+    l2sq = __builtin_fma(a, a, l2sq);
 }
 
-// sum over the block of each lane's (s1, s2), in a fixed order; valid in thread 0
-__device__ __forceinline__ void block_sum(double &s1, double &s2, double (*part)[kDensityThreads / 64]) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        s1 += __shfl_down(s1, off, 64);
-        s2 += __shfl_down(s2, off, 64);
-    }
-    const int tid = threadIdx.x;
-    if ((tid & 63) == 0) {
-        part[0][tid >> 6] = s1;
-        part[1][tid >> 6] = s2;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        s1 = part[0][0];
-        s2 = part[1][0];
-#pragma unroll
-        for (int w = 1; w < kDensityThreads / 64; ++w) {
-            s1 += part[0][w];
-            s2 += part[1][w];
-        }
-    }
-    __syncthreads();
+// another lane's value, zero in the rows (of 16 lanes) that ROWS leaves out
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ double lane_move(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xF, false);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// sum over each eight lanes, in all of them
+__device__ __forceinline__ double sum8(double s) {
+    s += lane_move<0xB1 /* quad_perm [1,0,3,2] */>(s);
+    s += lane_move<0x4E /* quad_perm [2,3,0,1] */>(s);
+    return s + lane_move<0x141 /* row_half_mirror */>(s);
+}
+
+// sum over the wave, in lane 63
+__device__ __forceinline__ double sum_wave(double s) {
+    s = sum8(s);
+    s += lane_move<0x140 /* row_mirror */>(s);
+    s += lane_move<0x142 /* row_bcast:15 */, 0xA>(s);
+    return s + lane_move<0x143 /* row_bcast:31 */, 0xC>(s);
 }
 
 __device__ __forceinline__ void density_result(const DensityArgs &a, double s1, double s2) {
@@ -212,12 +210,13 @@ __device__ __forceinline__ void density_rest(const f32x4 *v, size_t row, size_t 
     }
 }
 
+// R rows of a tile, whose loads are issued together: see density_rows in api.hip
+template <int R>
 __global__ __launch_bounds__(kDensityThreads) void density_kernel(const DensityArgs a) {
-    constexpr int R = kDensityRows;
-    constexpr int B = kDensityThreads;
-    __shared__ double part[2][B / 64];
-    __shared__ int is_last;
-    const int tid = threadIdx.x;
+    constexpr int B = kDensityThreads, kWaves = B / 64;
+    static_assert(kWaves == 8, "sum8 adds the waves' sums");
+    __shared__ double part[2][kWaves];
+    const int tid = threadIdx.x, lane = tid & 63;
     const unsigned G = gridDim.x;
     double l1 = 0.0, l2sq = 0.0;
     const f32x4 *const v = reinterpret_cast<const f32x4 *>(a.v) + tid;
@@ -231,12 +230,22 @@ __global__ __launch_bounds__(kDensityThreads) void density_kernel(const DensityA
         const size_t i = a.d / kQuad * kQuad + tid;
         if (i < a.d) accumulate(a.v[i], l1, l2sq);
     }
-    block_sum(l1, l2sq, part);
+    l1 = sum_wave(l1);
+    l2sq = sum_wave(l2sq);
+    if (lane == 63) {
+        part[0][tid >> 6] = l1;
+        part[1][tid >> 6] = l2sq;
+    }
+    __syncthreads();
+    if (tid >= 64) return;
+    l1 = sum8(part[0][lane & (kWaves - 1)]);
+    l2sq = sum8(part[1][lane & (kWaves - 1)]);
     if (G == 1) {
-        if (tid == 0) density_result(a, l1, l2sq);
+        if (lane == 0) density_result(a, l1, l2sq);
         return;
     }
-    if (tid == 0) {
+    unsigned last = 0;
+    if (lane == 0) {
         // Publish the slot, then take a ticket.  The slot is written with device-scope stores
         // (they go through to where every compute die sees them) and the wave waits until they
         // have been performed before it issues the ticket's atomic; a device-wide release fence
@@ -245,21 +254,29 @@ __global__ __launch_bounds__(kDensityThreads) void density_kernel(const DensityA
         __hip_atomic_store(&a.scratch->partial[blockIdx.x][0], l1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&a.scratch->partial[blockIdx.x][1], l2sq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        is_last = __hip_atomic_fetch_add(&a.scratch->ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                  (unsigned long long)G - 1;
+        last = __hip_atomic_fetch_add(&a.scratch->ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned long long)G - 1;
     }
-    __syncthreads();
-    if (!is_last) return;
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    asm volatile("" ::: "memory");     // the loads below stay behind the ticket
     // every other block's slot was performed before its ticket, and this block's loads below are
     // device-scope loads issued after the last ticket came back
-    double s1 = 0.0, s2 = 0.0;
-    for (unsigned b = tid; b < G; b += B) {
-        s1 += __hip_atomic_load(&a.scratch->partial[b][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s2 += __hip_atomic_load(&a.scratch->partial[b][1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    constexpr int kSlots = kDensityMaxBlocks / 64;
+    double s1[kSlots], s2[kSlots];
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) {
+        const unsigned b = lane + 64 * k;
+        s1[k] = b < G ? __hip_atomic_load(&a.scratch->partial[b][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+        s2[k] = b < G ? __hip_atomic_load(&a.scratch->partial[b][1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
     }
-    block_sum(s1, s2, part);
-    if (tid == 0) {
-        density_result(a, s1, s2);
+#pragma unroll
+    for (int k = 1; k < kSlots; ++k) {
+        s1[0] += s1[k];
+        s2[0] += s2[k];
+    }
+    l1 = sum_wave(s1[0]);
+    l2sq = sum_wave(s2[0]);
+    if (lane == 63) {
+        density_result(a, l1, l2sq);
         __hip_atomic_store(&a.scratch->ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }

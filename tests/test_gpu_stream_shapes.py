@@ -268,6 +268,33 @@ def test_updates_and_statistics_around_rules(ss, oracle, d):
     assert torch.equal(to[:d // 4 * 4].view(torch.int32), x0[:d // 4 * 4].view(torch.int32)) and bool((to[d // 4 * 4:] == 9).all())
 
 
+# Update after update, sigma and the densities, each reading what the one before left in the caches: runs between 2^21 and 2^24 coordinates,
+# the mean kept up to 5 x 2^23, sigma up to 2^26; densities in tiles of three rows below 3 x 2^18 coordinates, eight below 2^25, six beyond, a
+# row being 2,048 coordinates: one tile less than a row, one and two tiles, a round of the most blocks.
+# A sum's error is at most its longest chain of additions (below 800) x 2^-53 = 9e-14.
+@pytest.mark.parametrize("d", [6 * 2048 - 1, 6 * 2048 + 3, (3 << 18) - 1, (3 << 18), (1 << 21) - 1, (1 << 21) + 2047, 256 * 8 * 2048 + 5, (1 << 24) + 1,
+                               (1 << 25) - 1, (1 << 25) + 6 * 2048 + 1, (5 << 23) + 257, (1 << 26) - 1, (1 << 26) + 4097])
+def test_statistics_in_a_row(ss, oracle, d):
+    mean_dev, m2_dev = draw(d + 2, d, "f32", 0.2), draw(d + 3, d, "f32", 0.5).square_()
+    mean, m2 = synth.as_numpy(mean_dev).copy(), synth.as_numpy(m2_dev).copy()
+    sigma, out, work = torch.full((d,), 9.0, device=DEV), torch.zeros(2, 4, dtype=torch.float64, device=DEV), ss.new_density_workspace(DEV)
+    g = [draw(d + 1, d, "f32", 0.5), draw(d + 4, d, "bf16", 0.5)]
+    for n, grad in ((7, g[0]), (8, g[1])):
+        ss.welford_update(grad, mean_dev, m2_dev, n)
+    ss.welford_sigma(m2_dev, 8, sigma)
+    ss.density(mean_dev, out[0], work)
+    ss.density(sigma, out[1], work)
+    for n, grad in ((7, g[0]), (8, g[1])):
+        oracle.welford_update(synth.as_numpy(grad), mean, m2, n)
+    assert_same_floats(mean_dev, mean, "mean")
+    assert_same_floats(m2_dev, m2, "m2")
+    want = oracle.welford_sigma(m2, 8)
+    assert_same_floats(sigma, want, "sigma")
+    assert int(work[0]) == 0
+    for got, v in zip(out[:, :3].cpu().tolist(), (mean, want)):
+        assert got == pytest.approx(oracle.density(v), rel=1e-12)
+
+
 # ---- the server, every coordinate against torch's own arithmetic on the device (the oracle is compared with the same calls at
 # smaller sizes)
 
