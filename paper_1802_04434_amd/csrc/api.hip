@@ -113,6 +113,10 @@ inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = s
 // Below some 16 MB (one worker and bf16 gradients 24 MB, more than eight workers 32 MB) keeping costs 1-6 %: M = 7 400,001 (13) 7.8 / 7.3, 272,474
 // (9) 5.7 / 6.0, M = 16 400,001 (27) 15.3 / 15.8, 550,003 (37) 20.9 / 19.5, bf16 M = 8 400,001 (14) 7.6 / 8.0, 700,001 (25) 11.9 / 11.7, M = 4 900,001
 // (18) 8.7 / 8.9, 1.7 M (34) 15.3 / 14.9, M = 1 2.2 M (18) 8.35 / 8.5, 5.0 M (40) 17.2 / 16.3.
+// Beyond kKeepMost of momentum and x the streaming shapes still keep x by itself, the buffer that the program reads next, up to as much: M = 1 17.6 M
+// 54.3 / 50.5, M = 2 8.8 M 45.0 / 42.9, 13 M 63.7 / 61.2, M = 4 17.6 M 150.5 / 143.3, 22 M 184.8 / 179, bf16 M = 3 13 M 75.9 / 71.3, M = 7 8.8 M 126.1 / 123,
+// 17.6 M 246 / 245.6, beyond it M = 4 25.6 M 217 / 218, M = 7 33 M 461 / 462; vote and update gain nothing (M = 8 bf16 6.6 M with the bits 90.9 / 90.1, 13 M
+// 173.9 / 173.3, M = 12 8.8 M 203 / 203).
 // Without momentum, where x alone is written, the streaming shapes pay from 2^28 bytes of gradients on.
 constexpr size_t kKeepMost = (size_t)11 << 23;
 inline size_t step_written(int M, size_t d, bool has_m) { return d * sizeof(float) * (has_m ? M + 1 : 1); }
@@ -221,14 +225,14 @@ void fill_step_args(ss::StepArgs<NPTR> &a, int M, const void *const *g, float *c
     a.d = d;
 }
 
-template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB, bool NEAR, int STORE, uint32_t CHUNK, bool HAS_M, typename G>
+template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB, bool NEAR, int STORE, int STORE_X, uint32_t CHUNK, bool HAS_M, typename G>
 int launch_step_shape(ss::StepArgs<NPTR> &a, size_t d, hipStream_t stream) {
     const Tiling t = make_tiling(d, R, true, BLOCK);
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     a.n_tiles = (uint32_t)t.n_tiles;
     a.words_total = t.words_total;
-    return launch(ss::step_kernel<MT, NPTR, BLOCK, BW, R, HOLD_KB, NEAR, STORE, CHUNK, HAS_M, G>, grid, 0, stream, a, BLOCK);
+    return launch(ss::step_kernel<MT, NPTR, BLOCK, BW, R, HOLD_KB, NEAR, STORE, STORE_X, CHUNK, HAS_M, G>, grid, 0, stream, a, BLOCK);
 }
 
 template <int MT, int NPTR, int BLOCK, int BW, int HOLD_KB, int STORE>
@@ -262,15 +266,17 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
     using ss::kKeep;
     using ss::kStream;
     using ss::kThrough;
-    const bool keep = step_keeps(M, d, HAS_M, kBf16);
+    const bool keep = step_keeps(M, d, HAS_M, kBf16), keep_x = step_written(M, d, false) < kKeepMost;
     if constexpr (MT == 1) {
-        // One worker: one-wave blocks; from 2^24 coordinates on written through and with a cap.  us, as below 2^24 /
+        // One worker: one-wave blocks; from 2^24 coordinates on, with momentum beyond kKeepMost, written through and with a cap.  us, as below 2^24 /
         // capped / four waves of two rows: with momentum fp32 8.8 M 28.6 / 29.2 / 29.1, 17.6 M 55.8 / 54.7 / 57.2, 25.6 M 79.9 /
         // 77.8 / 82.2, 138 M 433 / 410 / 477, bf16 25.6 M 72.1 / 70.2 / 73.2; without fp32 17.6 M 33.0 / 33.1 / 33.8, 25.6 M
         // 46.8 / 46.8 / 48.3, 60 M 108 / 106 / 116, bf16 138 M 206 / 201 / 226
-        if (keep) return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kKeep, 8, HAS_M, G>(a, d, stream);
-        if (d >= ((size_t)1 << 24)) return launch_step_shape<1, NPTR, 64, 1, 1, HAS_M ? 10 : 6, false, kThrough, 0, HAS_M, G>(a, d, stream);
-        return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kStream, 8, HAS_M, G>(a, d, stream);
+        if (keep) return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kKeep, kKeep, 8, HAS_M, G>(a, d, stream);
+        if constexpr (HAS_M)
+            if (keep_x && step_written(1, d, true) >= kKeepMost) return launch_step_shape<1, NPTR, 64, 1, 1, 10, false, kThrough, kKeep, 0, true, G>(a, d, stream);
+        if (d >= ((size_t)1 << 24)) return launch_step_shape<1, NPTR, 64, 1, 1, HAS_M ? 10 : 6, false, kThrough, kThrough, 0, HAS_M, G>(a, d, stream);
+        return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kStream, kStream, 8, HAS_M, G>(a, d, stream);
     } else {
         if (streams(M, d, HAS_M, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0))) {
             // Streaming shapes: one-wave blocks of one row, written through, tiles in order.
@@ -282,7 +288,8 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
                 // 13 (11): M = 7 307.0 (308.9) / 314.9, M = 16 683 (708) / 696, 60 M M = 8 822 (830) / 860.  Runs of tiles a die: 5-10 %
                 // slower in each.
                 constexpr int kHold = (MT > 0 && MT < 5 ? 13 : 14) - (kBf16 ? (MT > 0 && MT < 5 ? 2 : 1) : 0);
-                return launch_step_shape<MT, NPTR, 64, 1, 1, kHold, false, kThrough, 0, true, G>(a, d, stream);
+                if (keep_x) return launch_step_shape<MT, NPTR, 64, 1, 1, kHold, false, kThrough, kKeep, 0, true, G>(a, d, stream);
+                return launch_step_shape<MT, NPTR, 64, 1, 1, kHold, false, kThrough, kThrough, 0, true, G>(a, d, stream);
             } else if constexpr (kBf16) {
                 // step_bf16_kernel: the workers' loads out together, eight at most, fewer blocks per unit the more loads
                 // each has out.  us, 25.6 M unless said: M = 2 138 M 248 / 296 (four-wave blocks of two rows before), M = 3 60 M 126.8 /
@@ -295,8 +302,8 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
                 // fp32: four workers a stage make up for the missing momentum stream.  us, against two four-wave blocks a unit before:
                 // 25.6 M M = 3 76.4 / 83.1, 4 91.8 / 94.6, 7 135.4 / 145.5, 8 153.8 / 160.1, 9 169.0 / 178.3, 16 279.8 / 288.5, 138 M
                 // M = 2 319 / 345, M = 7 734 / 806
-                if (keep) return launch_step_shape<MT, NPTR, 64, 4, 1, MT == 2 ? 11 : 13, false, kKeep, 0, false, G>(a, d, stream);
-                return launch_step_shape<MT, NPTR, 64, 4, 1, MT == 2 ? 11 : 13, false, kThrough, 0, false, G>(a, d, stream);
+                if (keep_x) return launch_step_shape<MT, NPTR, 64, 4, 1, MT == 2 ? 11 : 13, false, kThrough, kKeep, 0, false, G>(a, d, stream);
+                return launch_step_shape<MT, NPTR, 64, 4, 1, MT == 2 ? 11 : 13, false, kThrough, kThrough, 0, false, G>(a, d, stream);
             }
         }
         // Latency shape: the loads of up to eight workers go out together, nothing is held back, buffers are addressed
@@ -306,15 +313,15 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
         // 272,474 M = 16 6.0 / 6.0 / 6.5, 8.8 M M = 4 34.3 / 34.2 / 35.6
         constexpr int BW = MT > 0 && MT < 8 ? MT : 8;
         const bool small = d < ((size_t)1 << 20);
-        if (keep && small) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kKeep, 6, HAS_M, G>(a, d, stream);
-        if (keep) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kKeep, 8, HAS_M, G>(a, d, stream);
+        if (keep && small) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kKeep, kKeep, 6, HAS_M, G>(a, d, stream);
+        if (keep) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kKeep, kKeep, 8, HAS_M, G>(a, d, stream);
         // Up to seven workers, whose loads are one stage, and 26 MB in all, written lines stay in every cache.  us, not / so: M = 3 400,001 4.6 /
         // 4.2, 700,001 6.4 / 6.0, M = 4 bf16 400,001 5.0 / 4.6, M = 7 180,001 4.6 / 4.4, 272,474 5.75 / 5.55; more workers lose: M = 12 272,474 8.6 / 10.0.
         if constexpr (MT > 0 && MT < 8 && HAS_M) {
-            if (small && d * (size_t)((kBf16 ? 6 : 8) * MT + 4) < ((size_t)25 << 20)) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kCached, 6, HAS_M, G>(a, d, stream);
+            if (small && d * (size_t)((kBf16 ? 6 : 8) * MT + 4) < ((size_t)25 << 20)) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kCached, kCached, 6, HAS_M, G>(a, d, stream);
         }
-        if (small) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, 6, HAS_M, G>(a, d, stream);
-        return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, 8, HAS_M, G>(a, d, stream);
+        if (small) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, kStream, 6, HAS_M, G>(a, d, stream);
+        return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, kStream, 8, HAS_M, G>(a, d, stream);
     }
 }
 
@@ -564,7 +571,7 @@ int launch_quorum_vote(const ss::QuorumVoteArgs &a, hipStream_t stream) {
 }
 
 // launch helpers of the ternary (vote with abstention) kernels
-template <int BW, int R, int HOLD_KB, bool NEAR, int STORE, uint32_t CHUNK, bool HAS_M, bool VOTE, typename G>
+template <int BW, int R, int HOLD_KB, bool NEAR, int STORE, int STORE_X, uint32_t CHUNK, bool HAS_M, bool VOTE, typename G>
 int launch_ternary_shape(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     // the step is one grid over all workers' votes, the pack one row of the grid per worker
     const Tiling t = make_tiling(d, R, true, ss::kWave);
@@ -572,7 +579,7 @@ int launch_ternary_shape(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     if (grid > kMaxGrid) return SS_ERR_ARG;
     a.n_tiles = (uint32_t)t.n_tiles;
     a.words_total = t.words_total;
-    return launch(ss::ternary_step_kernel<BW, R, HOLD_KB, NEAR, STORE, CHUNK, HAS_M, VOTE, G>, grid, 0, stream, a, ss::kWave, VOTE ? 1 : a.M);
+    return launch(ss::ternary_step_kernel<BW, R, HOLD_KB, NEAR, STORE, STORE_X, CHUNK, HAS_M, VOTE, G>, grid, 0, stream, a, ss::kWave, VOTE ? 1 : a.M);
 }
 
 // The ternary kernel takes any M at run time; its shapes follow the binary step's (launch_step_m, launch_pack_momentum,
@@ -586,34 +593,39 @@ int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     using ss::kThrough;
     if constexpr (VOTE) {
         // two rows where a row a lane has too many threads
-        if (d >= kOneRowMaxD) return launch_ternary_shape<1, 2, 13, false, kThrough, 0, HAS_M, true, G>(a, d, stream);
+        if (d >= kOneRowMaxD) return launch_ternary_shape<1, 2, 13, false, kThrough, kThrough, 0, HAS_M, true, G>(a, d, stream);
         const bool keep = step_keeps(a.M, d, HAS_M, kBf16);
-        if (a.M == 1 ? d >= ((size_t)1 << 24) && !keep : streams(a.M, d, HAS_M, kBytes)) {
+        if (a.M == 1 ? !keep && (d >= ((size_t)1 << 24) || step_written(1, d, HAS_M) >= kKeepMost) : streams(a.M, d, HAS_M, kBytes)) {
             // us, KB held back: with momentum fp32 11 / 13 / 16: 25.6 M M = 1 80.8 / 84.7 / 92.4, M = 2 125.7 / 133.3 / 146.4, M = 4 217.9 /
             // 219.9 / 235.7, M = 7 367.9 / 360.6 / 375.2, M = 16 868 / 840 / 831, bf16 11 / 12 / 14: M = 3 151.3 / 157.5 / 172.8, M = 8
             // 60 M 840 / 832 / 887; gradients alone 10 / 13: fp32 M = 3 80.2 / 83.1, M = 7 143.2 / 137.6, bf16 M = 7 90.3 / 115.4.
             // Before (blocks of two to four waves, or eight workers a stage without momentum): M = 2 143, M = 7 387, bf16 60 M 861, fp32
             // gradients M = 7 152.6, bf16 92.4.
-            if constexpr (HAS_M) {
-                if (a.M < 5) return launch_ternary_shape<1, 1, 11, false, kThrough, 0, true, true, G>(a, d, stream);
-                return launch_ternary_shape<1, 1, kBf16 ? 12 : 13, false, kThrough, 0, true, true, G>(a, d, stream);
-            } else {
-                if (a.M < (kBf16 ? 4 : 5)) return launch_ternary_shape<4, 1, kBf16 ? 7 : 10, false, kThrough, 0, false, true, G>(a, d, stream);
-                return launch_ternary_shape<4, 1, kBf16 ? 10 : 13, false, kThrough, 0, false, true, G>(a, d, stream);
-            }
+            const auto streaming = [&](auto x) {
+                constexpr int kX = decltype(x)::value;
+                if constexpr (HAS_M) {
+                    if (a.M < 5) return launch_ternary_shape<1, 1, 11, false, kThrough, kX, 0, true, true, G>(a, d, stream);
+                    return launch_ternary_shape<1, 1, kBf16 ? 12 : 13, false, kThrough, kX, 0, true, true, G>(a, d, stream);
+                } else {
+                    if (a.M < (kBf16 ? 4 : 5)) return launch_ternary_shape<4, 1, kBf16 ? 7 : 10, false, kThrough, kX, 0, false, true, G>(a, d, stream);
+                    return launch_ternary_shape<4, 1, kBf16 ? 10 : 13, false, kThrough, kX, 0, false, true, G>(a, d, stream);
+                }
+            };
+            if (step_written(a.M, d, false) < kKeepMost) return streaming(std::integral_constant<int, kKeep>());
+            return streaming(std::integral_constant<int, kThrough>());
         }
         const bool small = d < ((size_t)1 << 20);
-        if (keep && small) return launch_ternary_shape<8, 1, 0, true, kKeep, 6, HAS_M, true, G>(a, d, stream);
-        if (keep) return launch_ternary_shape<8, 1, 0, true, kKeep, 8, HAS_M, true, G>(a, d, stream);
-        if (small) return launch_ternary_shape<8, 1, 0, true, kStream, 6, HAS_M, true, G>(a, d, stream);
-        return launch_ternary_shape<8, 1, 0, true, kStream, 8, HAS_M, true, G>(a, d, stream);
+        if (keep && small) return launch_ternary_shape<8, 1, 0, true, kKeep, kKeep, 6, HAS_M, true, G>(a, d, stream);
+        if (keep) return launch_ternary_shape<8, 1, 0, true, kKeep, kKeep, 8, HAS_M, true, G>(a, d, stream);
+        if (small) return launch_ternary_shape<8, 1, 0, true, kStream, kStream, 6, HAS_M, true, G>(a, d, stream);
+        return launch_ternary_shape<8, 1, 0, true, kStream, kStream, 8, HAS_M, true, G>(a, d, stream);
     } else if constexpr (HAS_M) {
-        if (d * (size_t)a.M * kBytes < ((size_t)1 << 28)) return launch_ternary_shape<1, 1, 0, false, kStream, 8, true, false, G>(a, d, stream);
-        if (d < ((size_t)1 << 25)) return launch_ternary_shape<1, 1, 0, false, kThrough, 9, true, false, G>(a, d, stream);
-        return launch_ternary_shape<1, 1, 7, false, kThrough, 0, true, false, G>(a, d, stream);
+        if (d * (size_t)a.M * kBytes < ((size_t)1 << 28)) return launch_ternary_shape<1, 1, 0, false, kStream, kStream, 8, true, false, G>(a, d, stream);
+        if (d < ((size_t)1 << 25)) return launch_ternary_shape<1, 1, 0, false, kThrough, kThrough, 9, true, false, G>(a, d, stream);
+        return launch_ternary_shape<1, 1, 7, false, kThrough, kThrough, 0, true, false, G>(a, d, stream);
     } else {
-        if (d < ((size_t)1 << 27)) return launch_ternary_shape<1, 2, 0, false, kStream, 8, false, false, G>(a, d, stream);
-        return launch_ternary_shape<1, 2, 0, false, kStream, 0, false, false, G>(a, d, stream);
+        if (d < ((size_t)1 << 27)) return launch_ternary_shape<1, 2, 0, false, kStream, kStream, 8, false, false, G>(a, d, stream);
+        return launch_ternary_shape<1, 2, 0, false, kStream, kStream, 0, false, false, G>(a, d, stream);
     }
 }
 

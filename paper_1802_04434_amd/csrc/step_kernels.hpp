@@ -176,9 +176,9 @@ __device__ __forceinline__ void step_tail(const StepArgs<NPTR> &a, int M, size_t
 // R      : rows per block
 // HOLD_KB: kilobytes of LDS the block reserves and never uses, which caps how
 //          many blocks share a compute unit (0: no cap)
-// NEAR   : buffers of less than 4 GiB, addressed without arithmetic (ld_tile);  STORE: policy of the stores of m
-//          and x otherwise;  CHUNK: log2 of the tiles that a die takes at a time (die_tile)
-template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB, bool NEAR, int STORE, uint32_t CHUNK, bool HAS_M, typename G>
+// NEAR   : buffers of less than 4 GiB, addressed without arithmetic (ld_tile);  STORE, STORE_X: policies of the stores of m
+//          and of x;  CHUNK: log2 of the tiles that a die takes at a time (die_tile)
+template <int MT, int NPTR, int BLOCK, int BW, int R, int HOLD_KB, bool NEAR, int STORE, int STORE_X, uint32_t CHUNK, bool HAS_M, typename G>
 __global__ __launch_bounds__(BLOCK) void step_kernel(const StepArgs<NPTR> a) {
     const uint32_t tid = threadIdx.x;
     const int lane = tid & 63;
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(BLOCK) void step_kernel(const StepArgs<NPTR> a) {
                 v.z = step(v.z, a.delta, nib & 4u);
                 v.w = step(v.w, a.delta, nib & 8u);
             }
-            st_tile<NEAR, STORE>(a.x, tile, kCoords * sizeof(float), (r * BLOCK + tid) * 16, v);
+            st_tile<NEAR, STORE_X>(a.x, tile, kCoords * sizeof(float), (r * BLOCK + tid) * 16, v);
             if (a.sums) reinterpret_cast<uint32_t *>(a.sums)[tile * (kCoords / 4) + r * BLOCK + tid] = sums_word(counts[r], M);
             const uint32_t word = combine8(nib, lane);
             if ((lane & 7) == 0) a.voted[tile * (kCoords / 32) + ((r * BLOCK + tid) >> 3)] = word;
