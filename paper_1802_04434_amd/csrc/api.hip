@@ -110,9 +110,10 @@ inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = s
 // memory-side cache (kKeep), where the next step finds it unless much else has come between.  us over three states in turn, streaming and
 // through / streaming and kept / latency and kept: M = 9 2.0 M coordinates (80 MB written) 42.1 / 39.8 / 35.8, 2.2 M (88) 44.2 / 42.5 / 39.5, M = 7 2.8 M (90) 43.5 /
 // 41.4 / 39.5, M = 12 1.7 M (88) 43.8 / 42.0 / 40.0, M = 7 3.1 M (99) 46.4 / 45.0 / 45.5, M = 2 8.2 M (98) 41.6 / 41.4 / 43.2, M = 5 4.4 M (106) 48.0 / 48.7 / 51.5.
-// Below some 16 MB (one worker and bf16 gradients 24 MB, more than eight workers 32 MB) keeping costs 1-6 %: M = 7 400,001 (13) 7.8 / 7.3, 272,474
+// Below some 16 MB (one worker or bf16 gradients 24 MB, both 48 MB, more than eight workers 32 MB) keeping costs 1-6 %: M = 7 400,001 (13) 7.8 / 7.3, 272,474
 // (9) 5.7 / 6.0, M = 16 400,001 (27) 15.3 / 15.8, 550,003 (37) 20.9 / 19.5, bf16 M = 8 400,001 (14) 7.6 / 8.0, 700,001 (25) 11.9 / 11.7, M = 4 900,001
-// (18) 8.7 / 8.9, 1.7 M (34) 15.3 / 14.9, M = 1 2.2 M (18) 8.35 / 8.5, 5.0 M (40) 17.2 / 16.3.
+// (18) 8.7 / 8.9, 1.7 M (34) 15.3 / 14.9, M = 1 2.2 M (18) 8.35 / 8.5, 5.0 M (40) 17.2 / 16.3, bf16 4.4 M (35)
+// 13.9 / 14.7, 8.8 M (70) 26.2 / 26.1, 11 M (88) 32.1 / 30.2.
 // Beyond kKeepMost of momentum and x the streaming shapes still keep x by itself, the buffer that the program reads next, up to as much: M = 1 17.6 M
 // 54.3 / 50.5, M = 2 8.8 M 45.0 / 42.9, 13 M 63.7 / 61.2, M = 4 17.6 M 150.5 / 143.3, 22 M 184.8 / 179, bf16 M = 3 13 M 75.9 / 71.3, M = 7 8.8 M 126.1 / 123,
 // 17.6 M 246 / 245.6, beyond it M = 4 25.6 M 217 / 218, M = 7 33 M 461 / 462; vote and update gain nothing (M = 8 bf16 6.6 M with the bits 90.9 / 90.1, 13 M
@@ -122,7 +123,8 @@ constexpr size_t kKeepMost = (size_t)11 << 23;
 inline size_t step_written(int M, size_t d, bool has_m) { return d * sizeof(float) * (has_m ? M + 1 : 1); }
 inline bool step_keeps(int M, size_t d, bool has_m, bool bf16) {
     const size_t written = step_written(M, d, has_m);
-    return written >= (size_t)(M > 8 ? 4 : bf16 || M == 1 ? 3 : 2) << 23 && written < kKeepMost;
+    const size_t least = (size_t)(M > 8 ? 4 : M == 1 && bf16 ? 6 : bf16 || M == 1 ? 3 : 2) << 23;
+    return written >= least && written < kKeepMost;
 }
 inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
     return has_m ? step_written(M, d, true) >= kKeepMost : d * (size_t)M * worker_bytes >= (size_t)1 << 28;

@@ -132,7 +132,7 @@ def test_one_pass_around_runs_and_rules(ss, oracle, d, M, dtype, momentum):
     assert_same_floats(x_dev, x, "x")
 
 
-# Where what a step writes is left in the memory-side cache: both ends of that range (16, 24 or 32 MB, by workers and type, to 11 x 2^23
+# Where what a step writes is left in the memory-side cache: both ends of that range (16 to 48 MB, by workers and type, to 11 x 2^23
 # bytes of momentum and x), the small steps of up to seven workers whose lines stay in every cache (25 x 2^20 bytes in all), and the two
 # launches that packed_out takes beyond it.  Two steps in a row, binary and with abstentions: the second reads what the first left.
 MOST = 11 << 23
@@ -140,7 +140,7 @@ KEPT = [((1 << 24) // 32 - 1, 7, "f32", True), ((1 << 24) // 32 + 1, 7, "f32", T
         ((3 << 23) // 36 + 1, 8, "bf16", True), (MOST // 36 - 255, 8, "bf16", True), (MOST // 36 + 1, 8, "f32", True),
         ((1 << 25) // 52 + 1, 12, "f32", True), ((1 << 25) // 52 - 300, 12, "bf16", True), (MOST // 40 - 1, 9, "f32", True), (MOST // 12 + 257, 2, "bf16", True),
         ((25 << 20) // 28 - 1, 3, "f32", True), ((25 << 20) // 28 + 33, 3, "f32", True), ((25 << 20) // 28 - 257, 4, "bf16", True), (10_007, 2, "f32", True),
-        ((3 << 23) // 8 + 1, 1, "f32", True), (MOST // 8 - 1, 1, "bf16", True), (MOST // 8 + 1, 1, "f32", True), (MOST // 4 - 1, 1, "f32", False),
+        ((3 << 23) // 8 + 1, 1, "f32", True), ((3 << 24) // 8 - 1, 1, "bf16", True), (MOST // 8 - 1, 1, "bf16", True), (MOST // 8 + 300, 2, "f32", True), (MOST // 8 + 1, 1, "f32", True), (MOST // 4 - 1, 1, "f32", False),
         ((1 << 24) // 4 + 1, 3, "f32", False), ((1 << 28) // 28 + 257, 7, "f32", False), ((1 << 28) // 64 + 1, 16, "f32", False), (MOST // 4 - 513, 4, "f32", False),
         (MOST // 4 + 1, 4, "bf16", False)]
 
