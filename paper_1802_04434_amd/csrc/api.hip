@@ -114,12 +114,20 @@ inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = s
 // (9) 5.7 / 6.0, M = 16 400,001 (27) 15.3 / 15.8, 550,003 (37) 20.9 / 19.5, bf16 M = 8 400,001 (14) 7.6 / 8.0, 700,001 (25) 11.9 / 11.7, M = 4 900,001
 // (18) 8.7 / 8.9, 1.7 M (34) 15.3 / 14.9, M = 1 2.2 M (18) 8.35 / 8.5, 5.0 M (40) 17.2 / 16.3, bf16 4.4 M (35)
 // 13.9 / 14.7, 8.8 M (70) 26.2 / 26.1, 11 M (88) 32.1 / 30.2.
-// Beyond kKeepMost of momentum and x the streaming shapes still keep x by itself, the buffer that the program reads next, up to as much: M = 1 17.6 M
-// 54.3 / 50.5, M = 2 8.8 M 45.0 / 42.9, 13 M 63.7 / 61.2, M = 4 17.6 M 150.5 / 143.3, 22 M 184.8 / 179, bf16 M = 3 13 M 75.9 / 71.3, M = 7 8.8 M 126.1 / 123,
-// 17.6 M 246 / 245.6, beyond it M = 4 25.6 M 217 / 218, M = 7 33 M 461 / 462; vote and update gain nothing (M = 8 bf16 6.6 M with the bits 90.9 / 90.1, 13 M
-// 173.9 / 173.3, M = 12 8.8 M 203 / 203).
+// Beyond, the streaming shapes still keep the first kKeepX bytes of x, the buffer that the program reads next.  us, nothing kept / 64 MB / 84 MB / all of x, one state
+// again and again: M = 1 without momentum 25.6 M 47.1 / 45.3 / 44.5 / 43.9, 138 M 241.4 / 239.6 / 239.2 / 255, with 25.6 M 77.0 / 75.0 / 73.4 / 72.3, M = 2 25.6 M
+// 122.3 / 118.4 / 117.1 / 116.2, bf16 alone M = 8 25.6 M 96.5 / 92.6 / 90.9 / 89.5, 18 M 68.6 / 64.5 / 64.0 / 64.0; three states in turn, which is why it is not more: 47.0 / 45.4 /
+// 44.8 / 47.7, 243.0 / 241.6 / 244.1 / 253, 77.0 / 74.2 / 73.0 / 77.6, 122.3 / 118.0 / 116.8 / 122.3, 98.7 / 93.6 / 92.3 / 100.7, 69.8 / 64.7 / 64.0 / 64.0.  Gradients alone M = 7 25.6 M
+// 135.9 / 131.5 / 132.2 / 140.2, with abstentions M = 3 173.6 / 169.2 / 169.2 / 174.0.  The more other traffic, the less: M = 4 17.6 M with momentum 150.5 / - / 143.3, M = 7
+// 246 / - / 245.6, bf16 alone M = 16 25.6 M 166.1 / 162.6 / 162.6 / 169.9, M = 24 9 M level; vote and update gain nothing (M = 8 bf16 6.6 M with the bits 90.9 / - / 90.1,
+// M = 12 8.8 M 203 / - / 203).
 // Without momentum, where x alone is written, the streaming shapes pay from 2^28 bytes of gradients on.
-constexpr size_t kKeepMost = (size_t)11 << 23;
+constexpr size_t kKeepMost = (size_t)11 << 23, kKeepX = (size_t)9 << 23;
+// Tiles of x that are kept: none in a step that moves 2^31 bytes or more, where what is kept no longer waits for the next step but costs its way out, us without /
+// with 75 MB: M = 1 300 M 876 / 885, bf16 alone M = 2 380 M 672 / 682; below M = 1 alone 138 M 241.6 / 240.5, M = 2 60 M 282.5 / 279.1.
+inline uint32_t x_tiles_kept(int M, size_t d, size_t worker_bytes, size_t tile_bytes) {
+    return d * (M * worker_bytes + 2 * sizeof(float)) < (size_t)1 << 31 ? (uint32_t)(kKeepX / tile_bytes) : 0;
+}
 inline size_t step_written(int M, size_t d, bool has_m) { return d * sizeof(float) * (has_m ? M + 1 : 1); }
 inline bool step_keeps(int M, size_t d, bool has_m, bool bf16) {
     const size_t written = step_written(M, d, has_m);
@@ -233,7 +241,11 @@ int launch_step_shape(ss::StepArgs<NPTR> &a, size_t d, hipStream_t stream) {
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     a.n_tiles = (uint32_t)t.n_tiles;
+    a.x_kept = x_tiles_kept(a.M, d, sizeof(typename G::elem) + (HAS_M ? 2 * sizeof(float) : 0), R * BLOCK * sizeof(ss::f32x4));
     a.words_total = t.words_total;
+    // two policies in one kernel cost the sums 3-4 % (M = 3 gradients alone 40 M 121.1 us against 125.0, and see launch_octets)
+    if (STORE != STORE_X && (a.x_kept == 0 || a.sums || a.sum_update))
+        return launch(ss::step_kernel<MT, NPTR, BLOCK, BW, R, HOLD_KB, NEAR, STORE, STORE, CHUNK, HAS_M, G>, grid, 0, stream, a, BLOCK);
     return launch(ss::step_kernel<MT, NPTR, BLOCK, BW, R, HOLD_KB, NEAR, STORE, STORE_X, CHUNK, HAS_M, G>, grid, 0, stream, a, BLOCK);
 }
 
@@ -243,8 +255,11 @@ int launch_octets(ss::StepArgs<NPTR> &a, size_t d, hipStream_t stream) {
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     a.n_tiles = (uint32_t)t.n_tiles;
+    a.x_kept = x_tiles_kept(a.M, d, sizeof(uint16_t), 2 * BLOCK * sizeof(ss::f32x4));
     a.words_total = t.words_total;
-    return launch(ss::step_bf16_kernel<MT, NPTR, BLOCK, BW, HOLD_KB, STORE>, grid, 0, stream, a, BLOCK);
+    // two policies in one kernel cost the sums 4 % (M = 9 100 M 440 us against 459 with no tile kept)
+    if (a.x_kept == 0 || a.sums || a.sum_update) return launch(ss::step_bf16_kernel<MT, NPTR, BLOCK, BW, HOLD_KB, STORE, STORE>, grid, 0, stream, a, BLOCK);
+    return launch(ss::step_bf16_kernel<MT, NPTR, BLOCK, BW, HOLD_KB, STORE, ss::kKeep>, grid, 0, stream, a, BLOCK);
 }
 
 // what distinguishes the variants of the step (see ss_step_flags)
@@ -268,7 +283,7 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
     using ss::kKeep;
     using ss::kStream;
     using ss::kThrough;
-    const bool keep = step_keeps(M, d, HAS_M, kBf16), keep_x = step_written(M, d, false) < kKeepMost;
+    const bool keep = step_keeps(M, d, HAS_M, kBf16);
     if constexpr (MT == 1) {
         // One worker: one-wave blocks; from 2^24 coordinates on, with momentum beyond kKeepMost, written through and with a cap.  us, as below 2^24 /
         // capped / four waves of two rows: with momentum fp32 8.8 M 28.6 / 29.2 / 29.1, 17.6 M 55.8 / 54.7 / 57.2, 25.6 M 79.9 /
@@ -276,8 +291,8 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
         // 46.8 / 46.8 / 48.3, 60 M 108 / 106 / 116, bf16 138 M 206 / 201 / 226
         if (keep) return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kKeep, kKeep, 8, HAS_M, G>(a, d, stream);
         if constexpr (HAS_M)
-            if (keep_x && step_written(1, d, true) >= kKeepMost) return launch_step_shape<1, NPTR, 64, 1, 1, 10, false, kThrough, kKeep, 0, true, G>(a, d, stream);
-        if (d >= ((size_t)1 << 24)) return launch_step_shape<1, NPTR, 64, 1, 1, HAS_M ? 10 : 6, false, kThrough, kThrough, 0, HAS_M, G>(a, d, stream);
+            if (step_written(1, d, true) >= kKeepMost) return launch_step_shape<1, NPTR, 64, 1, 1, 10, false, kThrough, kKeep, 0, true, G>(a, d, stream);
+        if (d >= ((size_t)1 << 24)) return launch_step_shape<1, NPTR, 64, 1, 1, HAS_M ? 10 : 6, false, kThrough, kKeep, 0, HAS_M, G>(a, d, stream);
         return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kStream, kStream, 8, HAS_M, G>(a, d, stream);
     } else {
         if (streams(M, d, HAS_M, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0))) {
@@ -290,8 +305,7 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
                 // 13 (11): M = 7 307.0 (308.9) / 314.9, M = 16 683 (708) / 696, 60 M M = 8 822 (830) / 860.  Runs of tiles a die: 5-10 %
                 // slower in each.
                 constexpr int kHold = (MT > 0 && MT < 5 ? 13 : 14) - (kBf16 ? (MT > 0 && MT < 5 ? 2 : 1) : 0);
-                if (keep_x) return launch_step_shape<MT, NPTR, 64, 1, 1, kHold, false, kThrough, kKeep, 0, true, G>(a, d, stream);
-                return launch_step_shape<MT, NPTR, 64, 1, 1, kHold, false, kThrough, kThrough, 0, true, G>(a, d, stream);
+                return launch_step_shape<MT, NPTR, 64, 1, 1, kHold, false, kThrough, kKeep, 0, true, G>(a, d, stream);
             } else if constexpr (kBf16) {
                 // step_bf16_kernel: the workers' loads out together, eight at most, fewer blocks per unit the more loads
                 // each has out.  us, 25.6 M unless said: M = 2 138 M 248 / 296 (four-wave blocks of two rows before), M = 3 60 M 126.8 /
@@ -304,8 +318,7 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
                 // fp32: four workers a stage make up for the missing momentum stream.  us, against two four-wave blocks a unit before:
                 // 25.6 M M = 3 76.4 / 83.1, 4 91.8 / 94.6, 7 135.4 / 145.5, 8 153.8 / 160.1, 9 169.0 / 178.3, 16 279.8 / 288.5, 138 M
                 // M = 2 319 / 345, M = 7 734 / 806
-                if (keep_x) return launch_step_shape<MT, NPTR, 64, 4, 1, MT == 2 ? 11 : 13, false, kThrough, kKeep, 0, false, G>(a, d, stream);
-                return launch_step_shape<MT, NPTR, 64, 4, 1, MT == 2 ? 11 : 13, false, kThrough, kThrough, 0, false, G>(a, d, stream);
+                return launch_step_shape<MT, NPTR, 64, 4, 1, MT == 2 ? 11 : 13, false, kThrough, kKeep, 0, false, G>(a, d, stream);
             }
         }
         // Latency shape: the loads of up to eight workers go out together, nothing is held back, buffers are addressed
@@ -580,6 +593,7 @@ int launch_ternary_shape(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     a.n_tiles = (uint32_t)t.n_tiles;
+    a.x_kept = x_tiles_kept(a.M, d, sizeof(typename G::elem) + (HAS_M ? 2 * sizeof(float) : 0), R * ss::kWave * sizeof(ss::f32x4));
     a.words_total = t.words_total;
     return launch(ss::ternary_step_kernel<BW, R, HOLD_KB, NEAR, STORE, STORE_X, CHUNK, HAS_M, VOTE, G>, grid, 0, stream, a, ss::kWave, VOTE ? 1 : a.M);
 }
@@ -603,18 +617,13 @@ int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
             // 60 M 840 / 832 / 887; gradients alone 10 / 13: fp32 M = 3 80.2 / 83.1, M = 7 143.2 / 137.6, bf16 M = 7 90.3 / 115.4.
             // Before (blocks of two to four waves, or eight workers a stage without momentum): M = 2 143, M = 7 387, bf16 60 M 861, fp32
             // gradients M = 7 152.6, bf16 92.4.
-            const auto streaming = [&](auto x) {
-                constexpr int kX = decltype(x)::value;
-                if constexpr (HAS_M) {
-                    if (a.M < 5) return launch_ternary_shape<1, 1, 11, false, kThrough, kX, 0, true, true, G>(a, d, stream);
-                    return launch_ternary_shape<1, 1, kBf16 ? 12 : 13, false, kThrough, kX, 0, true, true, G>(a, d, stream);
-                } else {
-                    if (a.M < (kBf16 ? 4 : 5)) return launch_ternary_shape<4, 1, kBf16 ? 7 : 10, false, kThrough, kX, 0, false, true, G>(a, d, stream);
-                    return launch_ternary_shape<4, 1, kBf16 ? 10 : 13, false, kThrough, kX, 0, false, true, G>(a, d, stream);
-                }
-            };
-            if (step_written(a.M, d, false) < kKeepMost) return streaming(std::integral_constant<int, kKeep>());
-            return streaming(std::integral_constant<int, kThrough>());
+            if constexpr (HAS_M) {
+                if (a.M < 5) return launch_ternary_shape<1, 1, 11, false, kThrough, kKeep, 0, true, true, G>(a, d, stream);
+                return launch_ternary_shape<1, 1, kBf16 ? 12 : 13, false, kThrough, kKeep, 0, true, true, G>(a, d, stream);
+            } else {
+                if (a.M < (kBf16 ? 4 : 5)) return launch_ternary_shape<4, 1, kBf16 ? 7 : 10, false, kThrough, kKeep, 0, false, true, G>(a, d, stream);
+                return launch_ternary_shape<4, 1, kBf16 ? 10 : 13, false, kThrough, kKeep, 0, false, true, G>(a, d, stream);
+            }
         }
         const bool small = d < ((size_t)1 << 20);
         if (keep && small) return launch_ternary_shape<8, 1, 0, true, kKeep, kKeep, 6, HAS_M, true, G>(a, d, stream);

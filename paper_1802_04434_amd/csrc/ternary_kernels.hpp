@@ -32,6 +32,7 @@ struct TernaryStepArgs {
     int M;
     int quorum;
     uint32_t n_tiles;
+    uint32_t x_kept;       // as StepArgs'
     size_t d;
     size_t words_total;
 };
@@ -149,7 +150,8 @@ __global__ __launch_bounds__(kWave) void ternary_step_kernel(const TernaryStepAr
                     zero_nib |= ((ans >> 1) & 1u) << c;
                     v[c] = step_ternary(v[c], a.delta, ans);
                 }
-                st_tile<NEAR, STORE_X>(a.x, tile, kCoords * sizeof(float), (r * kWave + lane) * 16, v);
+                if (STORE == STORE_X || tile < a.x_kept) st_tile<NEAR, STORE_X>(a.x, tile, kCoords * sizeof(float), (r * kWave + lane) * 16, v);
+                else st_tile<NEAR, STORE>(a.x, tile, kCoords * sizeof(float), (r * kWave + lane) * 16, v);
                 const uint32_t nw = combine8(neg_nib, lane);
                 const uint32_t zw = combine8(zero_nib, lane);
                 if ((lane & 7) == 0) {

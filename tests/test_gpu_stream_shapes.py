@@ -145,6 +145,13 @@ KEPT = [((1 << 24) // 32 - 1, 7, "f32", True), ((1 << 24) // 32 + 1, 7, "f32", T
         (MOST // 4 + 1, 4, "bf16", False)]
 
 
+# Beyond, the first 9 x 2^23 bytes of x are kept and the rest is not: the line between tiles of 256 (bf16 gradients alone 512) coordinates
+# and the ragged end behind it.
+X = (9 << 23) // 4
+KEPT += [(MOST // 4 + 255, 1, "f32", False), (X + 3 * 256 + 77, 1, "bf16", True), (X - 1, 2, "f32", True), (X + 257, 4, "f32", False), (X + 511, 9, "bf16", False),
+         (X + 512 + 33, 8, "bf16", False), ((1 << 28) // 12 + 513, 6, "bf16", False)]
+
+
 @pytest.mark.parametrize("d,M,dtype,momentum", KEPT)
 def test_steps_that_leave_their_lines_in_the_caches(ss, oracle, d, M, dtype, momentum):
     g = [draw(d + w, d, dtype, 0.5) for w in range(M)]
