@@ -586,16 +586,15 @@ int launch_quorum_vote(const ss::QuorumVoteArgs &a, hipStream_t stream) {
 }
 
 // launch helpers of the ternary (vote with abstention) kernels
-template <int BW, int R, int HOLD_KB, bool NEAR, int STORE, int STORE_X, uint32_t CHUNK, bool HAS_M, bool VOTE, typename G>
+template <int BW, int R, int HOLD_KB, bool NEAR, int STORE, uint32_t CHUNK, bool HAS_M, bool VOTE, typename G>
 int launch_ternary_shape(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     // the step is one grid over all workers' votes, the pack one row of the grid per worker
     const Tiling t = make_tiling(d, R, true, ss::kWave);
     const size_t grid = t.n_tiles + t.tail_blocks;
     if (grid > kMaxGrid) return SS_ERR_ARG;
     a.n_tiles = (uint32_t)t.n_tiles;
-    a.x_kept = x_tiles_kept(a.M, d, sizeof(typename G::elem) + (HAS_M ? 2 * sizeof(float) : 0), R * ss::kWave * sizeof(ss::f32x4));
     a.words_total = t.words_total;
-    return launch(ss::ternary_step_kernel<BW, R, HOLD_KB, NEAR, STORE, STORE_X, CHUNK, HAS_M, VOTE, G>, grid, 0, stream, a, ss::kWave, VOTE ? 1 : a.M);
+    return launch(ss::ternary_step_kernel<BW, R, HOLD_KB, NEAR, STORE, CHUNK, HAS_M, VOTE, G>, grid, 0, stream, a, ss::kWave, VOTE ? 1 : a.M);
 }
 
 // The ternary kernel takes any M at run time; its shapes follow the binary step's (launch_step_m, launch_pack_momentum,
@@ -609,34 +608,39 @@ int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     using ss::kThrough;
     if constexpr (VOTE) {
         // two rows where a row a lane has too many threads
-        if (d >= kOneRowMaxD) return launch_ternary_shape<1, 2, 13, false, kThrough, kThrough, 0, HAS_M, true, G>(a, d, stream);
+        if (d >= kOneRowMaxD) return launch_ternary_shape<1, 2, 13, false, kThrough, 0, HAS_M, true, G>(a, d, stream);
         const bool keep = step_keeps(a.M, d, HAS_M, kBf16);
         if (a.M == 1 ? !keep && (d >= ((size_t)1 << 24) || step_written(1, d, HAS_M) >= kKeepMost) : streams(a.M, d, HAS_M, kBytes)) {
             // us, KB held back: with momentum fp32 11 / 13 / 16: 25.6 M M = 1 80.8 / 84.7 / 92.4, M = 2 125.7 / 133.3 / 146.4, M = 4 217.9 /
             // 219.9 / 235.7, M = 7 367.9 / 360.6 / 375.2, M = 16 868 / 840 / 831, bf16 11 / 12 / 14: M = 3 151.3 / 157.5 / 172.8, M = 8
             // 60 M 840 / 832 / 887; gradients alone 10 / 13: fp32 M = 3 80.2 / 83.1, M = 7 143.2 / 137.6, bf16 M = 7 90.3 / 115.4.
+            // One policy for all stores.  A second one for tiles of x that stay in the memory-side cache, as the binary step has, costs these
+            // kernels more than it saves.  us, one state again and again / twelve and more in turn, all through / 75 MB of x kept: M = 1
+            // gradients alone 60 M 117 / 135 and 117 / 138, bf16 96.5 / 110 and 96.5 / 113, M = 7 25.6 M 142.5 / 145 and 139 / 151, bf16 M = 8 25.6 M 97.4 / 103 and
+            // 96.5 / 107, with momentum M = 2 25.6 M 126.7 / 127.7 and 125.8 / 130.7, M = 7 8.0 M 117.8 / 117.9 and 117.6 / 120.9; M = 3 gradients alone 25.6 M 80.3 / 75.8 and
+            // 80.6 / 81.3 is the exception.
             // Before (blocks of two to four waves, or eight workers a stage without momentum): M = 2 143, M = 7 387, bf16 60 M 861, fp32
             // gradients M = 7 152.6, bf16 92.4.
             if constexpr (HAS_M) {
-                if (a.M < 5) return launch_ternary_shape<1, 1, 11, false, kThrough, kKeep, 0, true, true, G>(a, d, stream);
-                return launch_ternary_shape<1, 1, kBf16 ? 12 : 13, false, kThrough, kKeep, 0, true, true, G>(a, d, stream);
+                if (a.M < 5) return launch_ternary_shape<1, 1, 11, false, kThrough, 0, true, true, G>(a, d, stream);
+                return launch_ternary_shape<1, 1, kBf16 ? 12 : 13, false, kThrough, 0, true, true, G>(a, d, stream);
             } else {
-                if (a.M < (kBf16 ? 4 : 5)) return launch_ternary_shape<4, 1, kBf16 ? 7 : 10, false, kThrough, kKeep, 0, false, true, G>(a, d, stream);
-                return launch_ternary_shape<4, 1, kBf16 ? 10 : 13, false, kThrough, kKeep, 0, false, true, G>(a, d, stream);
+                if (a.M < (kBf16 ? 4 : 5)) return launch_ternary_shape<4, 1, kBf16 ? 7 : 10, false, kThrough, 0, false, true, G>(a, d, stream);
+                return launch_ternary_shape<4, 1, kBf16 ? 10 : 13, false, kThrough, 0, false, true, G>(a, d, stream);
             }
         }
         const bool small = d < ((size_t)1 << 20);
-        if (keep && small) return launch_ternary_shape<8, 1, 0, true, kKeep, kKeep, 6, HAS_M, true, G>(a, d, stream);
-        if (keep) return launch_ternary_shape<8, 1, 0, true, kKeep, kKeep, 8, HAS_M, true, G>(a, d, stream);
-        if (small) return launch_ternary_shape<8, 1, 0, true, kStream, kStream, 6, HAS_M, true, G>(a, d, stream);
-        return launch_ternary_shape<8, 1, 0, true, kStream, kStream, 8, HAS_M, true, G>(a, d, stream);
+        if (keep && small) return launch_ternary_shape<8, 1, 0, true, kKeep, 6, HAS_M, true, G>(a, d, stream);
+        if (keep) return launch_ternary_shape<8, 1, 0, true, kKeep, 8, HAS_M, true, G>(a, d, stream);
+        if (small) return launch_ternary_shape<8, 1, 0, true, kStream, 6, HAS_M, true, G>(a, d, stream);
+        return launch_ternary_shape<8, 1, 0, true, kStream, 8, HAS_M, true, G>(a, d, stream);
     } else if constexpr (HAS_M) {
-        if (d * (size_t)a.M * kBytes < ((size_t)1 << 28)) return launch_ternary_shape<1, 1, 0, false, kStream, kStream, 8, true, false, G>(a, d, stream);
-        if (d < ((size_t)1 << 25)) return launch_ternary_shape<1, 1, 0, false, kThrough, kThrough, 9, true, false, G>(a, d, stream);
-        return launch_ternary_shape<1, 1, 7, false, kThrough, kThrough, 0, true, false, G>(a, d, stream);
+        if (d * (size_t)a.M * kBytes < ((size_t)1 << 28)) return launch_ternary_shape<1, 1, 0, false, kStream, 8, true, false, G>(a, d, stream);
+        if (d < ((size_t)1 << 25)) return launch_ternary_shape<1, 1, 0, false, kThrough, 9, true, false, G>(a, d, stream);
+        return launch_ternary_shape<1, 1, 7, false, kThrough, 0, true, false, G>(a, d, stream);
     } else {
-        if (d < ((size_t)1 << 27)) return launch_ternary_shape<1, 2, 0, false, kStream, kStream, 8, false, false, G>(a, d, stream);
-        return launch_ternary_shape<1, 2, 0, false, kStream, kStream, 0, false, false, G>(a, d, stream);
+        if (d < ((size_t)1 << 27)) return launch_ternary_shape<1, 2, 0, false, kStream, 8, false, false, G>(a, d, stream);
+        return launch_ternary_shape<1, 2, 0, false, kStream, 0, false, false, G>(a, d, stream);
     }
 }
 

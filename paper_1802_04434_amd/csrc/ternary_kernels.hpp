@@ -32,7 +32,6 @@ struct TernaryStepArgs {
     int M;
     int quorum;
     uint32_t n_tiles;
-    uint32_t x_kept;       // as StepArgs'
     size_t d;
     size_t words_total;
 };
@@ -115,9 +114,9 @@ __device__ __forceinline__ void ternary_rest(const TernaryStepArgs &a, int w0, i
 }
 
 // One-wave blocks.  VOTE: the whole step; otherwise worker blockIdx.y's pack.  BW workers per stage (what M leaves over
-// is one smaller stage), R rows per block, HOLD_KB of LDS reserved to cap the blocks per compute unit; NEAR, STORE, STORE_X and
+// is one smaller stage), R rows per block, HOLD_KB of LDS reserved to cap the blocks per compute unit; NEAR, STORE and
 // CHUNK as step_kernel's
-template <int BW, int R, int HOLD_KB, bool NEAR, int STORE, int STORE_X, uint32_t CHUNK, bool HAS_M, bool VOTE, typename G>
+template <int BW, int R, int HOLD_KB, bool NEAR, int STORE, uint32_t CHUNK, bool HAS_M, bool VOTE, typename G>
 __global__ __launch_bounds__(kWave) void ternary_step_kernel(const TernaryStepArgs a) {
     const uint32_t lane = threadIdx.x;
     const int M = a.M;
@@ -150,8 +149,7 @@ __global__ __launch_bounds__(kWave) void ternary_step_kernel(const TernaryStepAr
                     zero_nib |= ((ans >> 1) & 1u) << c;
                     v[c] = step_ternary(v[c], a.delta, ans);
                 }
-                if (STORE == STORE_X || tile < a.x_kept) st_tile<NEAR, STORE_X>(a.x, tile, kCoords * sizeof(float), (r * kWave + lane) * 16, v);
-                else st_tile<NEAR, STORE>(a.x, tile, kCoords * sizeof(float), (r * kWave + lane) * 16, v);
+                st_tile<NEAR, STORE>(a.x, tile, kCoords * sizeof(float), (r * kWave + lane) * 16, v);
                 const uint32_t nw = combine8(neg_nib, lane);
                 const uint32_t zw = combine8(zero_nib, lane);
                 if ((lane & 7) == 0) {

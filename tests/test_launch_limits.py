@@ -14,7 +14,7 @@ ROOT = os.path.dirname(HERE)
 
 class Launch(ctypes.Structure):
     _fields_ = [("grid_x", ctypes.c_uint), ("grid_y", ctypes.c_uint), ("block_x", ctypes.c_uint),
-                ("reserved", ctypes.c_uint), ("first", ctypes.c_void_p)]
+                ("reserved", ctypes.c_uint), ("first", ctypes.c_void_p), ("kernel", ctypes.c_void_p)]
 
 
 class Recorder:

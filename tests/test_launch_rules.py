@@ -1,0 +1,79 @@
+"""Which kernel a step takes on each side of the rules on size, workers and type, without a GPU: the recorder of
+test_launch_limits notes the kernel of every launch, and its name holds the launch shape."""
+import ctypes
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+from test_launch_limits import Launch, Recorder, shim  # noqa: F401
+
+STREAM, KEEP, THROUGH = 2, 16, 18       # store policies: the L2 writes back, left in the memory-side cache, sent on
+
+PARAMETERS = {"step_kernel": "MT NPTR BLOCK BW R HOLD NEAR STORE STORE_X CHUNK HAS_M",
+              "step_bf16_kernel": "MT NPTR BLOCK BW HOLD STORE STORE_X",
+              "ternary_step_kernel": "BW R HOLD NEAR STORE CHUNK HAS_M VOTE"}
+
+
+class DlInfo(ctypes.Structure):
+    _fields_ = [("fname", ctypes.c_char_p), ("fbase", ctypes.c_void_p), ("sname", ctypes.c_char_p), ("saddr", ctypes.c_void_p)]
+
+
+def shape(symbol):
+    """kernel and, of those above, the launch shape as a dict"""
+    kernel = re.match(r"_ZN2ss(\d+)", symbol)
+    kernel = symbol[kernel.end():kernel.end() + int(kernel.group(1))]
+    values = [int(v) for v in re.findall(r"L[ijb](\d+)E", symbol)]
+    names = PARAMETERS.get(kernel, "").split()
+    assert not names or len(names) == len(values), symbol
+    return kernel, dict(zip(names, values))
+
+
+class Rules(Recorder):
+    def kernels(self):
+        p = ctypes.POINTER(Launch)()
+        n = self.shim.recorded(ctypes.byref(p))
+        info, symbols = DlInfo(), []
+        for i in range(n):
+            assert ctypes.CDLL(None).dladdr(ctypes.c_void_p(p[i].kernel), ctypes.byref(info)) and info.saddr == p[i].kernel
+            symbols.append(info.sname.decode())
+        return symbols
+
+    def step_shapes(self, d, M, bf16, momentum, **how):
+        rc, _, _ = self.step(d, M, bf16, momentum, **how)
+        assert rc == 0
+        return [shape(s) for s in self.kernels()]
+
+    def ternary_shapes(self, d, M, bf16, momentum):
+        f, vp, words = ctypes.c_float, ctypes.c_void_p, (d + 127) // 128 * 16
+        g = self.buffer(d * (2 if bf16 else 4))
+        m = self.table([self.buffer(4 * d) for _ in range(M)]) if momentum else None
+        self.shim.record_anew(-1)
+        assert self.lib.ss_signum_vote_step_ternary(self.table([g] * M), bf16, m, M, f(0.9), f(0.1), 2, f(0.1), vp(self.buffer(4 * d)),
+                                                    vp(self.buffer(words)), vp(self.buffer(words)), ctypes.c_size_t(d), None) == 0
+        return [shape(s) for s in self.kernels()]
+
+
+def check_ternary_steps_have_one_store_policy(rules):
+    # a second policy, for tiles of x that are kept, made these kernels 1-15 % slower
+    for M in (1, 2, 3, 4, 5, 7, 8, 16, 33, 64):
+        for bf16 in (0, 1):
+            for momentum in (True, False):
+                for d in (10_007, 700_001, 2_500_003, 8_000_001, 18_000_001, 25_557_032, 60_000_001, 400_000_001):
+                    (kernel, s), = rules.ternary_shapes(d, M, bf16, momentum)
+                    assert kernel == "ternary_step_kernel" and s["VOTE"] and s["STORE"] in (STREAM, KEEP, THROUGH), (M, d, s)
+
+
+CHECKS = {f.__name__: f for f in (check_ternary_steps_have_one_store_policy,)}
+
+
+@pytest.mark.parametrize("name", sorted(CHECKS))
+def test_rules(shim, name):  # noqa: F811
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), shim, name], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+if __name__ == "__main__":
+    CHECKS[sys.argv[2]](Rules(sys.argv[1]))
