@@ -279,7 +279,6 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
     a.sum_update = (var.flags & SS_STEP_SUM_UPDATE) ? 1 : 0;
     a.sums = var.sums;
     constexpr bool kBf16 = std::is_same<G, ss::Bf16Grad>::value;
-    using ss::kCached;
     using ss::kKeep;
     using ss::kStream;
     using ss::kThrough;
@@ -330,11 +329,9 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
         const bool small = d < ((size_t)1 << 20);
         if (keep && small) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kKeep, kKeep, 6, HAS_M, G>(a, d, stream);
         if (keep) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kKeep, kKeep, 8, HAS_M, G>(a, d, stream);
-        // Up to seven workers, whose loads are one stage, and 26 MB in all, written lines stay in every cache.  us, not / so: M = 3 400,001 4.6 /
-        // 4.2, 700,001 6.4 / 6.0, M = 4 bf16 400,001 5.0 / 4.6, M = 7 180,001 4.6 / 4.4, 272,474 5.75 / 5.55; more workers lose: M = 12 272,474 8.6 / 10.0.
-        if constexpr (MT > 0 && MT < 8 && HAS_M) {
-            if (small && d * (size_t)((kBf16 ? 6 : 8) * MT + 4) < ((size_t)25 << 20)) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kCached, kCached, 6, HAS_M, G>(a, d, stream);
-        }
+        // Written lines that stay in every cache (26 MB in all, up to seven workers, whose loads are one stage) lose: us, the same state again / three
+        // in turn / a hundred, to the L2 with nt against without: M = 7 272,474 4.7 / 5.4 / 6.2 against 4.7 / 6.0 / 9.5, M = 5 400,001 4.6 / 5.6 / 6.3 against
+        // 4.6 / 6.1 / 8.9, M = 3 700,001 4.9 / 6.0 / 6.7 against 4.9 / 6.4 / 8.0.
         if (small) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, kStream, 6, HAS_M, G>(a, d, stream);
         return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, kStream, 8, HAS_M, G>(a, d, stream);
     }

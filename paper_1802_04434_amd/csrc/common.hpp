@@ -51,10 +51,10 @@ __device__ __forceinline__ Window window(const void *base, size_t from, uint32_t
 
 // Cache policies of stores (bits of the instruction: 2 = nt, 16 = sc1).  kStream leaves a written line to the L2 to write back,
 // kThrough sends it on at once; nt also keeps it out of the 256 MB memory-side cache.  kKeep sends it on and leaves it there, for
-// the next step or kernel that reads it; kCached leaves it to every cache.  Updating a vector in place (nt loads, which find what is there and do not crowd it out),
+// the next step or kernel that reads it.  Updating a vector in place (nt loads, which find what is there and do not crowd it out),
 // us, kStream / kThrough / kKeep: the same 4.4 M coordinates again 6.8 / 7.0 / 6.2, 25.6 M 31.3 / 31.0 / 28.4, 60 M (240 MB) 72.0 / 70.4 / 65.0; too much for
 // the cache, twelve vectors of 8.8 M in turn 12.1 / 11.9 / 12.2, of 138 M 163.4 / 161.5 / 164.3.
-constexpr int kCached = 0, kStream = 2, kKeep = 16, kThrough = 18;
+constexpr int kStream = 2, kKeep = 16, kThrough = 18;
 
 __device__ __forceinline__ f32x4 ld_quad(Window w, uint32_t off) {
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(w, (int)off, 0, kStream));
@@ -76,13 +76,9 @@ __device__ __forceinline__ f32x4 ld_tile(const void *base, size_t tile, uint32_t
 template <bool NEAR, int STORE>
 __device__ __forceinline__ void st_tile(float *base, size_t tile, uint32_t tile_bytes, uint32_t off, f32x4 v) {
     if constexpr (!NEAR) st_quad<STORE>(window(base, tile * tile_bytes, tile_bytes), off, v);
-    // addresses know nt or nothing: the other policies take a descriptor of the whole buffer, made while the loads are out
-    else if constexpr (STORE != kStream && STORE != kCached) st_quad<STORE>(window(base, 0, 0xFFFFFFFFu), (uint32_t)tile * tile_bytes + off, v);
-    else {
-        f32x4 *const to = reinterpret_cast<f32x4 *>(reinterpret_cast<char *>(base) + (uint32_t)((uint32_t)tile * tile_bytes + off));
-        if constexpr (STORE == kStream) st_stream(to, v);
-        else *to = v;
-    }
+    // addresses know nt: the other policies take a descriptor of the whole buffer, made while the loads are out
+    else if constexpr (STORE != kStream) st_quad<STORE>(window(base, 0, 0xFFFFFFFFu), (uint32_t)tile * tile_bytes + off, v);
+    else st_stream(reinterpret_cast<f32x4 *>(reinterpret_cast<char *>(base) + (uint32_t)((uint32_t)tile * tile_bytes + off)), v);
 }
 
 // bf16 -> fp32 is exact: the bf16 pattern is the upper half of the fp32
