@@ -106,10 +106,15 @@ inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = s
 //     reservation of LDS that no kernel touches, sized so that the wanted number of blocks fits in the 160 KB of a
 //     gfx950 compute unit (the only one that the library is built for)
 //   latency shape, everything smaller: the loads of up to eight workers at once, no cap
-// With momentum the line between them is kKeepMost bytes of momentum and x written: up to there what a step writes is left in the
-// memory-side cache (kKeep), where the next step finds it unless much else has come between.  us over three states in turn, streaming and
-// through / streaming and kept / latency and kept: M = 9 2.0 M coordinates (80 MB written) 42.1 / 39.8 / 35.8, 2.2 M (88) 44.2 / 42.5 / 39.5, M = 7 2.8 M (90) 43.5 /
-// 41.4 / 39.5, M = 12 1.7 M (88) 43.8 / 42.0 / 40.0, M = 7 3.1 M (99) 46.4 / 45.0 / 45.5, M = 2 8.2 M (98) 41.6 / 41.4 / 43.2, M = 5 4.4 M (106) 48.0 / 48.7 / 51.5.
+// The line between them, in bytes of gradients and momentum, where momentum counts twice, read and written, here and below.  With momentum it is
+// 5 x 2^25, us, latency / streaming with x kept (kKeepX), the same state again and twelve and more in turn: M = 2 7.2 M coordinates 37.3 / 34.4 and 38.8 / 37.5, M = 4 3.6 M
+// 33.3 / 31.5 and 34.7 / 32.5, M = 7 2.05 M 32.2 / 31.3 and 34.0 / 33.2, 2.8 M 45.0 / 42.8 and 45.5 / 43.0, M = 12 1.2 M 31.7 / 29.7 and 33.8 / 31.2, M = 16 900,000 32.3 / 33.4
+// and 34.3 / 34.5, 1.3 M 46.7 / 43.0 and 48.1 / 43.2, bf16 M = 8 2.2 M 33.0 / 32.8 and 35.0 / 35.0, M = 16 1.3 M 37.7 / 35.8 and 40.8 / 37.4.  Without momentum it is 2^28.
+// The latency shape with all lines kept (kKeep) is faster on the far side as long as nothing else comes between the steps, and slower as soon as
+// something does.  us, kept / streaming, one state, three in turn, twelve and more, and one state behind a 600 MB copy (copy and step): M = 4 4.4 M 36.3 / 39.0, 36.9 / 39.2,
+// 44.6 / 39.4, 155.0 / 152.9; M = 7 2.2 M 29.9 / 33.4, 31.4 / 34.4, 38.6 / 34.7, 149.7 / 147.4; M = 16 1.1 M 34.8 / 37.6, 35.4 / 37.5, 44.0 / 37.6, 155.3 / 150.1; M = 33 650,000
+// 41.1 / 42.7, 43.1 / 42.9, 54.1 / 42.9, 164.6 / 154.6.
+// With momentum, what a step of the latency shape writes is left in the memory-side cache (kKeep), where the next step finds it unless much else has come between.
 // Below some 16 MB (one worker or bf16 gradients 24 MB, both 48 MB, more than eight workers 32 MB) keeping costs 1-6 %: M = 7 400,001 (13) 7.8 / 7.3, 272,474
 // (9) 5.7 / 6.0, M = 16 400,001 (27) 15.3 / 15.8, 550,003 (37) 20.9 / 19.5, bf16 M = 8 400,001 (14) 7.6 / 8.0, 700,001 (25) 11.9 / 11.7, M = 4 900,001
 // (18) 8.7 / 8.9, 1.7 M (34) 15.3 / 14.9, M = 1 2.2 M (18) 8.35 / 8.5, 5.0 M (40) 17.2 / 16.3, bf16 4.4 M (35)
@@ -135,7 +140,7 @@ inline bool step_keeps(int M, size_t d, bool has_m, bool bf16) {
     return written >= least && written < kKeepMost;
 }
 inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
-    return has_m ? step_written(M, d, true) >= kKeepMost : d * (size_t)M * worker_bytes >= (size_t)1 << 28;
+    return d * (size_t)M * worker_bytes >= (has_m ? (size_t)5 << 25 : (size_t)1 << 28);
 }
 
 // Given packed_out buffers, the step runs as two launches - pack_kernel over all workers, then vote
@@ -144,10 +149,11 @@ inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
 // momentum: M = 2 fp32 8.8 M 45.1 / 48.7, 25.6 M 124.7 / 125.6, 60 M 287 / 290; M = 3 8.8 M 61.5 / 63.7, 25.6 M (920 MB)
 // 171.1 / 170.4, bf16 8.8 M 54.2 / 57.5, 138 M (4.2 GB) 802 / 787; M = 4 17.6 M (845 MB) 149.2 / 149.6, 25.6 M (1.2 GB) 217 / 214;
 // M = 5 8.8 M (528 MB) 94.0 / 94.3, 25.6 M (1.5 GB) 265 / 260; M = 7 2.2 M (185 MB) 35.4 / 35.4, 4.4 M (370 MB) 65.1 / 64.9, 6.6 M
-// 95.6 / 93.3; bf16 M = 8 4.4 M 65.5 / 62.1.  From eight workers on they take over where the streaming shapes begin: one pass leaves
-// what it writes in the memory-side cache up to there, M = 8 2.0 M 33.6 / 37.2, bf16 2.4 M 34.4 / 38.5, M = 12 1.5 M 35.4 / 39.5, M = 16 1.1 M 35.2 /
-// 37.1.  Up to the next step of the rule M = 6 and 7 differ by type: 268 MB fp32 49.0 / 49.8 and 47.8 / 49.9, bf16 51.8 / 50.9 and 51.6 / 49.8, 537 MB
-// fp32 94.4 / 94.2 and 91.8 / 92.8, bf16 98.1 / 93.7 and 96.8 / 94.4.
+// 95.6 / 93.3; M = 9 1.1 M (119 MB) 23.1 / 24.0; M = 16 1.1 M (211 MB) 38.8 / 37.7; bf16 M = 8 4.4 M 65.5 / 62.1.  Up to the next
+// step of the rule M = 6 and 7 differ by type: 268 MB fp32 49.0 / 49.8 and 47.8 / 49.9, bf16 51.8 / 50.9 and 51.6 / 49.8, 537 MB
+// fp32 94.4 / 94.2 and 91.8 / 92.8, bf16 98.1 / 93.7 and 96.8 / 94.4.  From eight workers on one pass with its lines kept is faster up to 92 MB written
+// as long as nothing else comes between the steps, twelve states in turn it is not: M = 8 1.6 M 25.0 / 28.5 and 33.4 / 30.1, 2.5 M 39.9 / 42.2 and 51.0 / 45.4, M = 16 1.1 M 35.1 /
+// 36.6 and 44.4 / 38.1, bf16 M = 8 2.4 M 32.9 / 35.8 and 41.8 / 39.0.
 // Without momentum where the streaming shapes begin, bytes of gradients: fp32 M = 2 8.4 M (67 MB) 22.7 / 27.2, 33.5 M (268 MB) 83.2 /
 // 86.8 before the line and 92.3 / 88.4 behind it, 67 M 183 / 166, M = 4 4.2 M 17.6 / 21.8, 16.8 M 66.6 / 67.0, 33.6 M 122.4 / 125.1,
 // 134 M 503 / 493, M = 8 4.2 M 29.6 / 32.3, 8.4 M 57.7 / 58.1 and 61.7 / 57.0, 16.8 M 116 / 106, M = 16 4.2 M 53.2 / 54.2, 7.8 M
@@ -156,8 +162,7 @@ inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
 inline bool split_pays(int M, size_t d, bool has_m, size_t worker_bytes) {
     if (M < 2 || d < ((size_t)1 << 20)) return false;
     if (!has_m) return streams(M, d, false, worker_bytes);
-    if (M >= 8) return streams(M, d, true, worker_bytes);
-    return M >= 3 && d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 6 ? 28 : 30));
+    return M >= 3 && d * (size_t)M * worker_bytes >= ((size_t)1 << (M >= 8 ? 27 : M >= 6 ? 28 : 30));
 }
 
 // A launch may have at most 2^32 - 1 threads, which a shape with one row of quads a lane reaches at 2^34

@@ -75,7 +75,26 @@ def check_small_steps_leave_their_lines_to_the_l2(rules):
                 assert kernel == "step_kernel" and s["NEAR"] and s["STORE"] == s["STORE_X"] == STREAM, (M, bf16, d, s)
 
 
-CHECKS = {f.__name__: f for f in (check_ternary_steps_have_one_store_policy, check_small_steps_leave_their_lines_to_the_l2)}
+def check_lines_of_steps_with_momentum(rules):
+    # bytes of gradients and momentum, which counts twice: the streaming shapes, and with packed_out the second launch
+    for bf16 in (0, 1):
+        for M in (2, 3, 4, 5, 7, 8, 9, 12, 16, 17, 33, 64):
+            size = M * (10 if bf16 else 12)
+            line = -(-(5 << 25) // size)
+            (_, before), = rules.step_shapes(line - 1, M, bf16, True)
+            (_, behind), = rules.step_shapes(line, M, bf16, True)
+            assert before["NEAR"] and before["HOLD"] == 0 and not behind["NEAR"] and behind["HOLD"] and behind["STORE"] == THROUGH, (M, bf16)
+            before, behind = rules.ternary_shapes(line - 1, M, bf16, True), rules.ternary_shapes(line, M, bf16, True)
+            assert before[0][1]["NEAR"] and not behind[0][1]["NEAR"] and behind[0][1]["STORE"] == THROUGH, (M, bf16)
+            if M == 2:
+                continue
+            line = max(-(-(1 << (27 if M >= 8 else 28 if M >= 6 else 30)) // size), 1 << 20)     # nor below 2^20 coordinates
+            for d, kernels in ((line - 1, ["step_kernel"]), (line, ["pack_kernel", "vote_apply_kernel"])):
+                assert [k for k, _ in rules.step_shapes(d, M, bf16, True, packed=True)] == kernels, (M, bf16, d)
+
+
+CHECKS = {f.__name__: f for f in (check_ternary_steps_have_one_store_policy, check_small_steps_leave_their_lines_to_the_l2,
+                                  check_lines_of_steps_with_momentum)}
 
 
 @pytest.mark.parametrize("name", sorted(CHECKS))
