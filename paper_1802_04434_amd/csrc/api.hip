@@ -114,12 +114,12 @@ inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = s
 // something does.  us, kept / streaming, one state, three in turn, twelve and more, and one state behind a 600 MB copy (copy and step): M = 4 4.4 M 36.3 / 39.0, 36.9 / 39.2,
 // 44.6 / 39.4, 155.0 / 152.9; M = 7 2.2 M 29.9 / 33.4, 31.4 / 34.4, 38.6 / 34.7, 149.7 / 147.4; M = 16 1.1 M 34.8 / 37.6, 35.4 / 37.5, 44.0 / 37.6, 155.3 / 150.1; M = 33 650,000
 // 41.1 / 42.7, 43.1 / 42.9, 54.1 / 42.9, 164.6 / 154.6.
-// With momentum, what a step of the latency shape writes is left in the memory-side cache (kKeep), where the next step finds it unless much else has come between.
-// Below some 16 MB (one worker or bf16 gradients 24 MB, both 48 MB, more than eight workers 32 MB) keeping costs 1-6 %: M = 7 400,001 (13) 7.8 / 7.3, 272,474
-// (9) 5.7 / 6.0, M = 16 400,001 (27) 15.3 / 15.8, 550,003 (37) 20.9 / 19.5, bf16 M = 8 400,001 (14) 7.6 / 8.0, 700,001 (25) 11.9 / 11.7, M = 4 900,001
-// (18) 8.7 / 8.9, 1.7 M (34) 15.3 / 14.9, M = 1 2.2 M (18) 8.35 / 8.5, 5.0 M (40) 17.2 / 16.3, bf16 4.4 M (35)
-// 13.9 / 14.7, 8.8 M (70) 26.2 / 26.1, 11 M (88) 32.1 / 30.2.
-// Beyond, the streaming shapes still keep the first kKeepX bytes of x, the buffer that the program reads next.  us, nothing kept / 64 MB / 84 MB / all of x, one state
+// Below the line the latency shape leaves its lines to the L2 with nt.  Kept as well, from some 16 MB written on, us, to the L2 / kept: one state M = 7 700,001 10.0 / 10.5,
+// 1.5 M 23.1 / 19.8, M = 4 1.2 M 10.3 / 10.4, M = 16 600,000 19.6 / 18.3, three in turn 12.0 / 11.0, 25.4 / 22.1, 12.5 / 11.4, 22.1 / 22.4, twelve and more 12.7 / 14.9,
+// 26.0 / 27.7, 13.1 / 14.6, 22.7 / 27.5, M = 64 150,000 25.4 / 25.8, 27.3 / 34.0, 32.9 / 44.9, M = 1 4.0 M 12.1 / 10.5, 13.7 / 12.7, 14.8 / 15.8; gradients alone, where x is all
+// that is written, M = 3 5.0 M 14.5 / 13.7, 17.1 / 16.6, 17.7 / 18.9, bf16 M = 8 9.0 M 34.4 / 32.9, 36.4 / 34.7, 37.4 / 40.3; behind a 600 MB copy level in all of them.  A step
+// that finds its lines again is one with nothing before it; bucket after bucket, or layer after layer, of a larger model finds none.
+// The streaming shapes keep the first kKeepX bytes of x, the buffer that the program reads next, and so do smaller steps of one worker without momentum (one_keeps).  us, nothing kept / 64 MB / 84 MB / all of x, one state
 // again and again: M = 1 without momentum 25.6 M 47.1 / 45.3 / 44.5 / 43.9, 138 M 241.4 / 239.6 / 239.2 / 255, with 25.6 M 77.0 / 75.0 / 73.4 / 72.3, M = 2 25.6 M
 // 122.3 / 118.4 / 117.1 / 116.2, bf16 alone M = 8 25.6 M 96.5 / 92.6 / 90.9 / 89.5, 18 M 68.6 / 64.5 / 64.0 / 64.0; three states in turn, which is why it is not more: 47.0 / 45.4 /
 // 44.8 / 47.7, 243.0 / 241.6 / 244.1 / 253, 77.0 / 74.2 / 73.0 / 77.6, 122.3 / 118.0 / 116.8 / 122.3, 98.7 / 93.6 / 92.3 / 100.7, 69.8 / 64.7 / 64.0 / 64.0.  Gradients alone M = 7 25.6 M
@@ -134,10 +134,9 @@ inline uint32_t x_tiles_kept(int M, size_t d, size_t worker_bytes, size_t tile_b
     return d * (M * worker_bytes + 2 * sizeof(float)) < (size_t)1 << 31 ? (uint32_t)(kKeepX / tile_bytes) : 0;
 }
 inline size_t step_written(int M, size_t d, bool has_m) { return d * sizeof(float) * (has_m ? M + 1 : 1); }
-inline bool step_keeps(int M, size_t d, bool has_m, bool bf16) {
-    const size_t written = step_written(M, d, has_m);
-    const size_t least = (size_t)(M > 8 ? 4 : M == 1 && bf16 ? 6 : bf16 || M == 1 ? 3 : 2) << 23;
-    return written >= least && written < kKeepMost;
+// One worker's gradients alone, x being all that is written, in the shape of its smaller steps
+inline bool one_keeps(int M, size_t d, bool has_m, bool bf16) {
+    return M == 1 && !has_m && d * sizeof(float) >= (size_t)(bf16 ? 6 : 3) << 23 && d * sizeof(float) < kKeepMost;
 }
 inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
     return d * (size_t)M * worker_bytes >= (has_m ? (size_t)5 << 25 : (size_t)1 << 28);
@@ -287,13 +286,13 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
     using ss::kKeep;
     using ss::kStream;
     using ss::kThrough;
-    const bool keep = step_keeps(M, d, HAS_M, kBf16);
     if constexpr (MT == 1) {
         // One worker: one-wave blocks; from 2^24 coordinates on, with momentum beyond kKeepMost, written through and with a cap.  us, as below 2^24 /
         // capped / four waves of two rows: with momentum fp32 8.8 M 28.6 / 29.2 / 29.1, 17.6 M 55.8 / 54.7 / 57.2, 25.6 M 79.9 /
         // 77.8 / 82.2, 138 M 433 / 410 / 477, bf16 25.6 M 72.1 / 70.2 / 73.2; without fp32 17.6 M 33.0 / 33.1 / 33.8, 25.6 M
         // 46.8 / 46.8 / 48.3, 60 M 108 / 106 / 116, bf16 138 M 206 / 201 / 226
-        if (keep) return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kKeep, kKeep, 8, HAS_M, G>(a, d, stream);
+        if constexpr (!HAS_M)
+            if (one_keeps(1, d, false, kBf16)) return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kKeep, kKeep, 8, false, G>(a, d, stream);
         if constexpr (HAS_M)
             if (step_written(1, d, true) >= kKeepMost) return launch_step_shape<1, NPTR, 64, 1, 1, 10, false, kThrough, kKeep, 0, true, G>(a, d, stream);
         if (d >= ((size_t)1 << 24)) return launch_step_shape<1, NPTR, 64, 1, 1, HAS_M ? 10 : 6, false, kThrough, kKeep, 0, HAS_M, G>(a, d, stream);
@@ -332,8 +331,6 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
         // 272,474 M = 16 6.0 / 6.0 / 6.5, 8.8 M M = 4 34.3 / 34.2 / 35.6
         constexpr int BW = MT > 0 && MT < 8 ? MT : 8;
         const bool small = d < ((size_t)1 << 20);
-        if (keep && small) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kKeep, kKeep, 6, HAS_M, G>(a, d, stream);
-        if (keep) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kKeep, kKeep, 8, HAS_M, G>(a, d, stream);
         // Written lines that stay in every cache (26 MB in all, up to seven workers, whose loads are one stage) lose: us, the same state again / three
         // in turn / a hundred, to the L2 with nt against without: M = 7 272,474 4.7 / 5.4 / 6.2 against 4.7 / 6.0 / 9.5, M = 5 400,001 4.6 / 5.6 / 6.3 against
         // 4.6 / 6.1 / 8.9, M = 3 700,001 4.9 / 6.0 / 6.7 against 4.9 / 6.4 / 8.0.
@@ -611,7 +608,7 @@ int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     if constexpr (VOTE) {
         // two rows where a row a lane has too many threads
         if (d >= kOneRowMaxD) return launch_ternary_shape<1, 2, 13, false, kThrough, 0, HAS_M, true, G>(a, d, stream);
-        const bool keep = step_keeps(a.M, d, HAS_M, kBf16);
+        const bool keep = one_keeps(a.M, d, HAS_M, kBf16);
         if (a.M == 1 ? !keep && (d >= ((size_t)1 << 24) || step_written(1, d, HAS_M) >= kKeepMost) : streams(a.M, d, HAS_M, kBytes)) {
             // us, KB held back: with momentum fp32 11 / 13 / 16: 25.6 M M = 1 80.8 / 84.7 / 92.4, M = 2 125.7 / 133.3 / 146.4, M = 4 217.9 /
             // 219.9 / 235.7, M = 7 367.9 / 360.6 / 375.2, M = 16 868 / 840 / 831, bf16 11 / 12 / 14: M = 3 151.3 / 157.5 / 172.8, M = 8
@@ -632,8 +629,8 @@ int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
             }
         }
         const bool small = d < ((size_t)1 << 20);
-        if (keep && small) return launch_ternary_shape<8, 1, 0, true, kKeep, 6, HAS_M, true, G>(a, d, stream);
-        if (keep) return launch_ternary_shape<8, 1, 0, true, kKeep, 8, HAS_M, true, G>(a, d, stream);
+        if constexpr (!HAS_M)
+            if (keep) return launch_ternary_shape<8, 1, 0, true, kKeep, 8, false, true, G>(a, d, stream);
         if (small) return launch_ternary_shape<8, 1, 0, true, kStream, 6, HAS_M, true, G>(a, d, stream);
         return launch_ternary_shape<8, 1, 0, true, kStream, 8, HAS_M, true, G>(a, d, stream);
     } else if constexpr (HAS_M) {

@@ -93,8 +93,19 @@ def check_lines_of_steps_with_momentum(rules):
                 assert [k for k, _ in rules.step_shapes(d, M, bf16, True, packed=True)] == kernels, (M, bf16, d)
 
 
+def check_momentum_is_not_kept_in_the_cache(rules):
+    # of what a step writes only x is ever left in the memory-side cache
+    for M in (1, 2, 3, 4, 5, 7, 8, 9, 16, 17, 33, 64):
+        for bf16 in (0, 1):
+            for momentum in (True, False):
+                for written in (10e6, 20e6, 30e6, 50e6, 70e6, 91e6, 95e6, 300e6):
+                    d = int(written) // (4 * (M + 1 if momentum else 1))
+                    for kernel, s in rules.step_shapes(d, M, bf16, momentum) + rules.ternary_shapes(d, M, bf16, momentum):
+                        assert s["STORE"] != KEEP or M == 1 and not momentum, (M, bf16, momentum, d, s)
+
+
 CHECKS = {f.__name__: f for f in (check_ternary_steps_have_one_store_policy, check_small_steps_leave_their_lines_to_the_l2,
-                                  check_lines_of_steps_with_momentum)}
+                                  check_lines_of_steps_with_momentum, check_momentum_is_not_kept_in_the_cache)}
 
 
 @pytest.mark.parametrize("name", sorted(CHECKS))
