@@ -119,15 +119,20 @@ inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = s
 // 26.0 / 27.7, 13.1 / 14.6, 22.7 / 27.5, M = 64 150,000 25.4 / 25.8, 27.3 / 34.0, 32.9 / 44.9, M = 1 4.0 M 12.1 / 10.5, 13.7 / 12.7, 14.8 / 15.8; gradients alone, where x is all
 // that is written, M = 3 5.0 M 14.5 / 13.7, 17.1 / 16.6, 17.7 / 18.9, bf16 M = 8 9.0 M 34.4 / 32.9, 36.4 / 34.7, 37.4 / 40.3; behind a 600 MB copy level in all of them.  A step
 // that finds its lines again is one with nothing before it; bucket after bucket, or layer after layer, of a larger model finds none.
-// The streaming shapes keep the first kKeepX bytes of x, the buffer that the program reads next, and so do smaller steps of one worker without momentum (one_keeps).  us, nothing kept / 64 MB / 84 MB / all of x, one state
-// again and again: M = 1 without momentum 25.6 M 47.1 / 45.3 / 44.5 / 43.9, 138 M 241.4 / 239.6 / 239.2 / 255, with 25.6 M 77.0 / 75.0 / 73.4 / 72.3, M = 2 25.6 M
-// 122.3 / 118.4 / 117.1 / 116.2, bf16 alone M = 8 25.6 M 96.5 / 92.6 / 90.9 / 89.5, 18 M 68.6 / 64.5 / 64.0 / 64.0; three states in turn, which is why it is not more: 47.0 / 45.4 /
-// 44.8 / 47.7, 243.0 / 241.6 / 244.1 / 253, 77.0 / 74.2 / 73.0 / 77.6, 122.3 / 118.0 / 116.8 / 122.3, 98.7 / 93.6 / 92.3 / 100.7, 69.8 / 64.7 / 64.0 / 64.0.  Gradients alone M = 7 25.6 M
-// 135.9 / 131.5 / 132.2 / 140.2, with abstentions M = 3 173.6 / 169.2 / 169.2 / 174.0.  The more other traffic, the less: M = 4 17.6 M with momentum 150.5 / - / 143.3, M = 7
-// 246 / - / 245.6, bf16 alone M = 16 25.6 M 166.1 / 162.6 / 162.6 / 169.9, M = 24 9 M level; vote and update gain nothing (M = 8 bf16 6.6 M with the bits 90.9 / - / 90.1,
-// M = 12 8.8 M 203 / - / 203).
+// The streaming shapes of the binary step keep the first kKeepX bytes of x, the buffer that the program reads next, without momentum up to eight workers (kKeepXWorkers); so do
+// smaller steps of one worker without momentum (one_keeps).  us, nothing kept / 64 MB / 84 MB / all of x, one state again and again: M = 1 without momentum 25.6 M 47.1 / 45.3 /
+// 44.5 / 43.9, 138 M 241.4 / 239.6 / 239.2 / 255, with 25.6 M 77.0 / 75.0 / 73.4 / 72.3, M = 2 25.6 M 122.3 / 118.4 / 117.1 / 116.2, bf16 alone M = 8 25.6 M 96.5 / 92.6 / 90.9 /
+// 89.5, 18 M 68.6 / 64.5 / 64.0 / 64.0; three states in turn, which is why it is not more: 47.0 / 45.4 / 44.8 / 47.7, 243.0 / 241.6 / 244.1 / 253, 77.0 / 74.2 / 73.0 / 77.6,
+// 122.3 / 118.0 / 116.8 / 122.3, 98.7 / 93.6 / 92.3 / 100.7, 69.8 / 64.7 / 64.0 / 64.0.
+// That holds for steps that follow one another closely.  Twelve states in turn, and step, a read of x and a 600 MB copy (all three), not / kept: with momentum M = 1 25.6 M 77.9 / 79.1
+// and 226.1 / 226.3, M = 2 122.0 / 123.5 and 271.5 / 271.5, M = 4 5.0 M 45.0 / 43.5 and 166.8 / 166.2, M = 7 8.0 M 114.8 / 115.0 and 243.3 / 240.6, bf16 M = 5 25 M 223.2 / 224.9 and
+// 372.9 / 371.5; alone M = 1 25.6 M 47.3 / 48.8 and 195.8 / 195.9, M = 3 76.7 / 78.5 and 225.2 / 225.5, M = 7 135.5 / 141.3 and 288.9 / 292.2, bf16 M = 6 25 M 80.0 / 81.9 and 228.4 / 227.7,
+// M = 8 25.6 M 98.3 / 101.7 and 246.1 / 248.8.  Above eight workers alone it costs more than it gives: three states, twelve, step and read and copy, M = 9 12 M 84.5 / 81.3, 83.7 / 88.2,
+// 219.0 / 219.0, 30 M 197.5 / 194.0, 196.0 / 205.5, 361.4 / 365.4, bf16 M = 16 10 M 67.0 / 66.6, 68.9 / 73.1, 199.5 / 199.1, M = 24 9 M 85.1 / 83.0, 89.5 / 94.8, 218.0 / 218.1.
+// Vote and update gain nothing (M = 8 bf16 6.6 M with the bits 90.9 / - / 90.1, M = 12 8.8 M 203 / - / 203), the ternary step loses (launch_ternary).
 // Without momentum, where x alone is written, the streaming shapes pay from 2^28 bytes of gradients on.
 constexpr size_t kKeepMost = (size_t)11 << 23, kKeepX = (size_t)9 << 23;
+constexpr int kKeepXWorkers = 8;
 // Tiles of x that are kept: none in a step that moves 2^31 bytes or more, where what is kept no longer waits for the next step but costs its way out, us without /
 // with 75 MB: M = 1 300 M 876 / 885, bf16 alone M = 2 380 M 672 / 682; below M = 1 alone 138 M 241.6 / 240.5, M = 2 60 M 282.5 / 279.1.
 inline uint32_t x_tiles_kept(int M, size_t d, size_t worker_bytes, size_t tile_bytes) {
@@ -262,8 +267,9 @@ int launch_octets(ss::StepArgs<NPTR> &a, size_t d, hipStream_t stream) {
     a.x_kept = x_tiles_kept(a.M, d, sizeof(uint16_t), 2 * BLOCK * sizeof(ss::f32x4));
     a.words_total = t.words_total;
     // two policies in one kernel cost the sums 4 % (M = 9 100 M 440 us against 459 with no tile kept)
-    if (a.x_kept == 0 || a.sums || a.sum_update) return launch(ss::step_bf16_kernel<MT, NPTR, BLOCK, BW, HOLD_KB, STORE, STORE>, grid, 0, stream, a, BLOCK);
-    return launch(ss::step_bf16_kernel<MT, NPTR, BLOCK, BW, HOLD_KB, STORE, ss::kKeep>, grid, 0, stream, a, BLOCK);
+    if constexpr (MT > 0 && MT <= kKeepXWorkers)
+        if (a.x_kept && !a.sums && !a.sum_update) return launch(ss::step_bf16_kernel<MT, NPTR, BLOCK, BW, HOLD_KB, STORE, ss::kKeep>, grid, 0, stream, a, BLOCK);
+    return launch(ss::step_bf16_kernel<MT, NPTR, BLOCK, BW, HOLD_KB, STORE, STORE>, grid, 0, stream, a, BLOCK);
 }
 
 // what distinguishes the variants of the step (see ss_step_flags)
@@ -321,7 +327,7 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
                 // fp32: four workers a stage make up for the missing momentum stream.  us, against two four-wave blocks a unit before:
                 // 25.6 M M = 3 76.4 / 83.1, 4 91.8 / 94.6, 7 135.4 / 145.5, 8 153.8 / 160.1, 9 169.0 / 178.3, 16 279.8 / 288.5, 138 M
                 // M = 2 319 / 345, M = 7 734 / 806
-                return launch_step_shape<MT, NPTR, 64, 4, 1, MT == 2 ? 11 : 13, false, kThrough, kKeep, 0, false, G>(a, d, stream);
+                return launch_step_shape<MT, NPTR, 64, 4, 1, MT == 2 ? 11 : 13, false, kThrough, (MT > 0 && MT <= kKeepXWorkers ? kKeep : kThrough), 0, false, G>(a, d, stream);
             }
         }
         // Latency shape: the loads of up to eight workers go out together, nothing is held back, buffers are addressed

@@ -104,8 +104,23 @@ def check_momentum_is_not_kept_in_the_cache(rules):
                         assert s["STORE"] != KEEP or M == 1 and not momentum, (M, bf16, momentum, d, s)
 
 
+def check_which_steps_keep_x(rules):
+    # the streaming shapes of steps that move less than 2^31 bytes, of up to eight workers where there is no momentum
+    for M in (2, 3, 4, 5, 6, 7, 8, 9, 12, 16, 17, 33, 64):
+        for bf16 in (0, 1):
+            for momentum in (True, False):
+                size = (2 if bf16 else 4) + (8 if momentum else 0)
+                line, most = -(-(5 << 25 if momentum else 1 << 28) // (M * size)), -(-(1 << 31) // (M * size + 8))
+                for d, kept in ((line, True), (line + 1003, True), (most - 1, True), (most, False), (2 * most, False)):
+                    for flags, sums in ((0, False), (2, False), (0, True)):
+                        (_, s), = rules.step_shapes(d, M, bf16, momentum, flags=flags, sums=sums)
+                        keeps = kept and not flags and not sums and (momentum or M <= 8)
+                        assert (s["STORE_X"] == KEEP) == keeps and (keeps or s["STORE_X"] == s["STORE"]), (M, bf16, momentum, d, flags, sums, s)
+
+
 CHECKS = {f.__name__: f for f in (check_ternary_steps_have_one_store_policy, check_small_steps_leave_their_lines_to_the_l2,
-                                  check_lines_of_steps_with_momentum, check_momentum_is_not_kept_in_the_cache)}
+                                  check_lines_of_steps_with_momentum, check_momentum_is_not_kept_in_the_cache,
+                                  check_which_steps_keep_x)}
 
 
 @pytest.mark.parametrize("name", sorted(CHECKS))
