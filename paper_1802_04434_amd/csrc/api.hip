@@ -931,22 +931,29 @@ int ss_welford_update(const void *g, ss_dtype gdt, float *mean, float *m2, uint6
     if (grid > kMaxGrid) return SS_ERR_ARG;
     const ss::WelfordArgs a{g, mean, m2, (float)n, (uint32_t)t.n_tiles, d};
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    // m2 is left in the memory-side cache (kKeep) for the next update and for sigma, the mean as long as both are not too much for it.
-    // In order, with 14 waves a unit; between 2^21 and 2^24 coordinates runs of half a megabyte a die.  us, update, sigma and two densities,
-    // everything written through / m2 and sigma kept / the mean too, in order: 1.1 M 18.3 / 17.1 / 16.5 (runs 17.7), 8.8 M 61.6 / 57.4 / 56.5
+    // From 2^21 coordinates on m2 is left in the memory-side cache (kKeep) for the next update and for sigma, the mean as long as both are not
+    // too much for it: runs of half a megabyte a die below 2^24, in order with 14 waves a unit beyond.  us, update, sigma and two densities,
+    // everything written through / m2 and sigma kept / the mean too, in order: 8.8 M 61.6 / 57.4 / 56.5
     // (runs 55.7), 17.6 M 105.8 / 99.3 / 98.2 (runs 100.5), 30 M 169.2 / 158.1 / 156.9, 40 M 220.0 / 205.1 / 205.5, 48 M 261.6 / 243.8 / 251.0, 60 M 323 / 302 / 317, 138 M
     // 742 / 736 / 742; m2 alone kept 60 M 303.6, 80 M 405.5 (428, with sigma 419.7), 138 M 715, 390 M 2,024 (2,059).
-    const bool runs = d >= ((size_t)1 << 21) && d < ((size_t)1 << 24), both = d < ((size_t)5 << 23);
+    // An update that nothing reads soon gains nothing: twelve states and more in turn, and one behind a 600 MB copy (copy and update), to the L2 or through / so: 4.4 M 15.4 / 16.3 and 127.4 /
+    // 128.0, 8.8 M 28.5 / 29.5 and 142.0 / 142.3, 25.6 M 78.0 / 78.1 and 189.0 / 193.2, 40 M 118.9 / 119.6 and 229.9 / 237.9, 138 M 409.1 / 408.9 and 529.7 / 527.5.  Below 2^21 it
+    // loses and the four calls together gain little: kept in order against runs to the L2, twelve and more in turn, update alone 272,474 2.76 / 2.53, 700,001 4.44 / 3.56, 1.1 M 6.27 / 5.04,
+    // 1.8 M 8.32 / 7.43, all four 12.25 / 12.58, 15.83 / 15.88, 17.3 / 18.0, 21.2 / 22.4.
     using ss::kKeep;
+    using ss::kStream;
     using ss::kThrough;
+    const bool small = d < ((size_t)1 << 21), runs = d < ((size_t)1 << 24), both = d < ((size_t)5 << 23);
     if (gdt == SS_F32) {
-        if (runs) return launch(ss::welford_update_kernel<0, kKeep, 9, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
-        if (both) return launch(ss::welford_update_kernel<11, kKeep, 0, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
-        return launch(ss::welford_update_kernel<11, kThrough, 0, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
+        if (small) return launch(ss::welford_update_kernel<0, kStream, kStream, 9, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
+        if (runs) return launch(ss::welford_update_kernel<0, kKeep, kKeep, 9, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
+        if (both) return launch(ss::welford_update_kernel<11, kKeep, kKeep, 0, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
+        return launch(ss::welford_update_kernel<11, kThrough, kKeep, 0, ss::F32Grad>, grid, 0, stream, a, ss::kWave);
     }
-    if (runs) return launch(ss::welford_update_kernel<0, kKeep, 9, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
-    if (both) return launch(ss::welford_update_kernel<11, kKeep, 0, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
-    return launch(ss::welford_update_kernel<11, kThrough, 0, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
+    if (small) return launch(ss::welford_update_kernel<0, kStream, kStream, 9, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
+    if (runs) return launch(ss::welford_update_kernel<0, kKeep, kKeep, 9, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
+    if (both) return launch(ss::welford_update_kernel<11, kKeep, kKeep, 0, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
+    return launch(ss::welford_update_kernel<11, kThrough, kKeep, 0, ss::Bf16Grad>, grid, 0, stream, a, ss::kWave);
 }
 
 int ss_welford_sigma(const float *m2, uint64_t n, float *sigma, size_t d, void *hip_stream) {

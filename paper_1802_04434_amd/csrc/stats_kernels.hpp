@@ -36,7 +36,7 @@ __device__ __forceinline__ void welford1(float g, float n, float &mean, float &m
 
 // One-wave blocks of one row.  Five streams; the shapes and what is left in the memory-side cache for the next update, for sigma and
 // for the densities are the host's (ss_welford_update).
-template <int HOLD_KB, int STORE_MEAN, uint32_t CHUNK, typename G>
+template <int HOLD_KB, int STORE_MEAN, int STORE_M2, uint32_t CHUNK, typename G>
 __global__ __launch_bounds__(kWave) void welford_update_kernel(const WelfordArgs a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, reinterpret_cast<uint32_t *>(a.mean));
     constexpr uint32_t kGrad = kWaveCoords * sizeof(typename G::elem), kFloat = kWaveCoords * sizeof(float);
@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kWave) void welford_update_kernel(const WelfordArgs
             m2[c] = m2_c;
         }
         st_quad<STORE_MEAN>(mean_w, lane * 16, mean);
-        st_quad<kKeep>(m2_w, lane * 16, m2);
+        st_quad<STORE_M2>(m2_w, lane * 16, m2);
         return;
     }
     const size_t i = a.n_tiles * (size_t)kWaveCoords + (size_t)(blockIdx.x - a.n_tiles) * kWave + lane;

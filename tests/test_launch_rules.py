@@ -14,7 +14,8 @@ STREAM, KEEP, THROUGH = 2, 16, 18       # store policies: the L2 writes back, le
 
 PARAMETERS = {"step_kernel": "MT NPTR BLOCK BW R HOLD NEAR STORE STORE_X CHUNK HAS_M",
               "step_bf16_kernel": "MT NPTR BLOCK BW HOLD STORE STORE_X",
-              "ternary_step_kernel": "BW R HOLD NEAR STORE CHUNK HAS_M VOTE"}
+              "ternary_step_kernel": "BW R HOLD NEAR STORE CHUNK HAS_M VOTE",
+              "welford_update_kernel": "HOLD STORE_MEAN STORE_M2 CHUNK"}
 
 
 class DlInfo(ctypes.Structure):
@@ -118,9 +119,22 @@ def check_which_steps_keep_x(rules):
                         assert (s["STORE_X"] == KEEP) == keeps and (keeps or s["STORE_X"] == s["STORE"]), (M, bf16, momentum, d, flags, sums, s)
 
 
+def check_what_an_update_of_the_statistics_keeps(rules):
+    # nothing below 2^21 coordinates, both below 5 x 2^23, then m2
+    vp, size = ctypes.c_void_p, ctypes.c_size_t
+    for bf16 in (0, 1):
+        for d, mean, m2 in ((1000, STREAM, STREAM), ((1 << 21) - 1, STREAM, STREAM), (1 << 21, KEEP, KEEP), ((1 << 24) - 1, KEEP, KEEP), (1 << 24, KEEP, KEEP),
+                            ((5 << 23) - 1, KEEP, KEEP), (5 << 23, THROUGH, KEEP), (400_000_001, THROUGH, KEEP)):
+            rules.shim.record_anew(-1)
+            assert rules.lib.ss_welford_update(vp(rules.buffer(4 * d)), bf16, vp(rules.buffer(4 * d)), vp(rules.buffer(4 * d)), size(3), size(d), None) == 0
+            (kernel, s), = [shape(t) for t in rules.kernels()]
+            assert kernel == "welford_update_kernel" and (s["STORE_MEAN"], s["STORE_M2"]) == (mean, m2), (bf16, d, s)
+            assert (s["CHUNK"] == 9) == (d < 1 << 24)
+
+
 CHECKS = {f.__name__: f for f in (check_ternary_steps_have_one_store_policy, check_small_steps_leave_their_lines_to_the_l2,
                                   check_lines_of_steps_with_momentum, check_momentum_is_not_kept_in_the_cache,
-                                  check_which_steps_keep_x)}
+                                  check_which_steps_keep_x, check_what_an_update_of_the_statistics_keeps)}
 
 
 @pytest.mark.parametrize("name", sorted(CHECKS))
