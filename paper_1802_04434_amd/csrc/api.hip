@@ -131,18 +131,19 @@ inline Tiling make_tiling(size_t d, int rows, bool covers_padding, int block = s
 // 219.0 / 219.0, 30 M 197.5 / 194.0, 196.0 / 205.5, 361.4 / 365.4, bf16 M = 16 10 M 67.0 / 66.6, 68.9 / 73.1, 199.5 / 199.1, M = 24 9 M 85.1 / 83.0, 89.5 / 94.8, 218.0 / 218.1.
 // Vote and update gain nothing (M = 8 bf16 6.6 M with the bits 90.9 / - / 90.1, M = 12 8.8 M 203 / - / 203), the ternary step loses (launch_ternary).
 // Without momentum, where x alone is written, the streaming shapes pay from 2^28 bytes of gradients on.
-constexpr size_t kKeepMost = (size_t)11 << 23, kKeepX = (size_t)9 << 23;
+constexpr size_t kKeepX = (size_t)9 << 23;
 constexpr int kKeepXWorkers = 8;
 // Tiles of x that are kept: none in a step that moves 2^31 bytes or more, where what is kept no longer waits for the next step but costs its way out, us without /
 // with 75 MB: M = 1 300 M 876 / 885, bf16 alone M = 2 380 M 672 / 682; below M = 1 alone 138 M 241.6 / 240.5, M = 2 60 M 282.5 / 279.1.
 inline uint32_t x_tiles_kept(int M, size_t d, size_t worker_bytes, size_t tile_bytes) {
     return d * (M * worker_bytes + 2 * sizeof(float)) < (size_t)1 << 31 ? (uint32_t)(kKeepX / tile_bytes) : 0;
 }
-inline size_t step_written(int M, size_t d, bool has_m) { return d * sizeof(float) * (has_m ? M + 1 : 1); }
-// One worker's gradients alone, x being all that is written, in the shape of its smaller steps
-inline bool one_keeps(int M, size_t d, bool has_m, bool bf16) {
-    return M == 1 && !has_m && d * sizeof(float) >= (size_t)(bf16 ? 6 : 3) << 23 && d * sizeof(float) < kKeepMost;
-}
+// One worker streams from 11 x 2^23 bytes of momentum and x written on (x alone where there is no momentum); there it keeps its x also below, in the
+// shape of its smaller steps.  us, written lines to the L2 / kept / streaming, three states: alone 8.0 M 15.8 / 15.6 / -, 20 M - / 35.0 / 37.7, bf16 20 M - / 29.8 / 32.6, twelve
+// and more 16.8 / 17.4 / -, - / 38.9 / 37.8, - / 32.7 / 32.6; with momentum 13 M to the L2 / streaming 42.7 / 38.3 and 43.0 / 42.6.  Kept from 24 MB of x on, bf16 48: 4.4 M bf16 13.9 / 14.7.
+constexpr size_t kOneWorkerStreams = (size_t)11 << 23;
+inline bool one_streams(size_t d, bool has_m) { return d * sizeof(float) * (has_m ? 2 : 1) >= kOneWorkerStreams; }
+inline bool one_keeps(size_t d, bool bf16) { return d * sizeof(float) >= (size_t)(bf16 ? 6 : 3) << 23; }
 inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
     return d * (size_t)M * worker_bytes >= (has_m ? (size_t)5 << 25 : (size_t)1 << 28);
 }
@@ -293,15 +294,13 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
     using ss::kStream;
     using ss::kThrough;
     if constexpr (MT == 1) {
-        // One worker: one-wave blocks; from 2^24 coordinates on, with momentum beyond kKeepMost, written through and with a cap.  us, as below 2^24 /
+        // One worker: one-wave blocks; written through and with a cap from one_streams on.  us, as below it /
         // capped / four waves of two rows: with momentum fp32 8.8 M 28.6 / 29.2 / 29.1, 17.6 M 55.8 / 54.7 / 57.2, 25.6 M 79.9 /
         // 77.8 / 82.2, 138 M 433 / 410 / 477, bf16 25.6 M 72.1 / 70.2 / 73.2; without fp32 17.6 M 33.0 / 33.1 / 33.8, 25.6 M
         // 46.8 / 46.8 / 48.3, 60 M 108 / 106 / 116, bf16 138 M 206 / 201 / 226
+        if (one_streams(d, HAS_M)) return launch_step_shape<1, NPTR, 64, 1, 1, HAS_M ? 10 : 6, false, kThrough, kKeep, 0, HAS_M, G>(a, d, stream);
         if constexpr (!HAS_M)
-            if (one_keeps(1, d, false, kBf16)) return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kKeep, kKeep, 8, false, G>(a, d, stream);
-        if constexpr (HAS_M)
-            if (step_written(1, d, true) >= kKeepMost) return launch_step_shape<1, NPTR, 64, 1, 1, 10, false, kThrough, kKeep, 0, true, G>(a, d, stream);
-        if (d >= ((size_t)1 << 24)) return launch_step_shape<1, NPTR, 64, 1, 1, HAS_M ? 10 : 6, false, kThrough, kKeep, 0, HAS_M, G>(a, d, stream);
+            if (one_keeps(d, kBf16)) return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kKeep, kKeep, 8, false, G>(a, d, stream);
         return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kStream, kStream, 8, HAS_M, G>(a, d, stream);
     } else {
         if (streams(M, d, HAS_M, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0))) {
@@ -614,8 +613,7 @@ int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
     if constexpr (VOTE) {
         // two rows where a row a lane has too many threads
         if (d >= kOneRowMaxD) return launch_ternary_shape<1, 2, 13, false, kThrough, 0, HAS_M, true, G>(a, d, stream);
-        const bool keep = one_keeps(a.M, d, HAS_M, kBf16);
-        if (a.M == 1 ? !keep && (d >= ((size_t)1 << 24) || step_written(1, d, HAS_M) >= kKeepMost) : streams(a.M, d, HAS_M, kBytes)) {
+        if (a.M == 1 ? one_streams(d, HAS_M) : streams(a.M, d, HAS_M, kBytes)) {
             // us, KB held back: with momentum fp32 11 / 13 / 16: 25.6 M M = 1 80.8 / 84.7 / 92.4, M = 2 125.7 / 133.3 / 146.4, M = 4 217.9 /
             // 219.9 / 235.7, M = 7 367.9 / 360.6 / 375.2, M = 16 868 / 840 / 831, bf16 11 / 12 / 14: M = 3 151.3 / 157.5 / 172.8, M = 8
             // 60 M 840 / 832 / 887; gradients alone 10 / 13: fp32 M = 3 80.2 / 83.1, M = 7 143.2 / 137.6, bf16 M = 7 90.3 / 115.4.
@@ -636,7 +634,7 @@ int launch_ternary(ss::TernaryStepArgs &a, size_t d, hipStream_t stream) {
         }
         const bool small = d < ((size_t)1 << 20);
         if constexpr (!HAS_M)
-            if (keep) return launch_ternary_shape<8, 1, 0, true, kKeep, 8, false, true, G>(a, d, stream);
+            if (a.M == 1 && one_keeps(d, kBf16)) return launch_ternary_shape<8, 1, 0, true, kKeep, 8, false, true, G>(a, d, stream);
         if (small) return launch_ternary_shape<8, 1, 0, true, kStream, 6, HAS_M, true, G>(a, d, stream);
         return launch_ternary_shape<8, 1, 0, true, kStream, 8, HAS_M, true, G>(a, d, stream);
     } else if constexpr (HAS_M) {

@@ -132,9 +132,23 @@ def check_what_an_update_of_the_statistics_keeps(rules):
             assert (s["CHUNK"] == 9) == (d < 1 << 24)
 
 
+def check_lines_of_one_worker(rules):
+    # 11 x 2^23 bytes of momentum and x, where the streaming shape begins; without momentum x is kept from 24 MB (bf16 48 MB) on
+    for bf16 in (0, 1):
+        for momentum in (True, False):
+            line, kept = -(-(11 << 23) // (8 if momentum else 4)), (6 if bf16 else 3) << 21
+            for d in (1000, kept - 1, kept, (1 << 24) - 1, 1 << 24, line - 1, line, 4 * line):
+                (_, s), = rules.step_shapes(d, 1, bf16, momentum)
+                (_, t), = rules.ternary_shapes(d, 1, bf16, momentum)
+                store = THROUGH if d >= line else KEEP if d >= kept and not momentum else STREAM
+                assert s["STORE"] == t["STORE"] == store and s["NEAR"] == t["NEAR"] == (d < line), (bf16, momentum, d, s, t)
+                assert s["STORE_X"] == (KEEP if d >= line else store), (bf16, momentum, d, s)
+
+
 CHECKS = {f.__name__: f for f in (check_ternary_steps_have_one_store_policy, check_small_steps_leave_their_lines_to_the_l2,
                                   check_lines_of_steps_with_momentum, check_momentum_is_not_kept_in_the_cache,
-                                  check_which_steps_keep_x, check_what_an_update_of_the_statistics_keeps)}
+                                  check_which_steps_keep_x, check_what_an_update_of_the_statistics_keeps,
+                                  check_lines_of_one_worker)}
 
 
 @pytest.mark.parametrize("name", sorted(CHECKS))
