@@ -144,8 +144,9 @@ inline uint32_t x_tiles_kept(int M, size_t d, size_t worker_bytes, size_t tile_b
 constexpr size_t kOneWorkerStreams = (size_t)11 << 23;
 inline bool one_streams(size_t d, bool has_m) { return d * sizeof(float) * (has_m ? 2 : 1) >= kOneWorkerStreams; }
 inline bool one_keeps(size_t d, bool bf16) { return d * sizeof(float) >= (size_t)(bf16 ? 6 : 3) << 23; }
+constexpr size_t kStreams = (size_t)5 << 25;    // with momentum
 inline bool streams(int M, size_t d, bool has_m, size_t worker_bytes) {
-    return d * (size_t)M * worker_bytes >= (has_m ? (size_t)5 << 25 : (size_t)1 << 28);
+    return d * (size_t)M * worker_bytes >= (has_m ? kStreams : (size_t)1 << 28);
 }
 
 // Given packed_out buffers, the step runs as two launches - pack_kernel over all workers, then vote
@@ -303,7 +304,8 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
             if (one_keeps(d, kBf16)) return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kKeep, kKeep, 8, false, G>(a, d, stream);
         return launch_step_shape<1, NPTR, 64, 1, 1, 0, true, kStream, kStream, 8, HAS_M, G>(a, d, stream);
     } else {
-        if (streams(M, d, HAS_M, (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0))) {
+        constexpr size_t kWorkerBytes = (kBf16 ? 2 : 4) + (HAS_M ? 8 : 0);
+        if (streams(M, d, HAS_M, kWorkerBytes)) {
             // Streaming shapes: one-wave blocks of one row, written through, tiles in order.
             if constexpr (HAS_M) {
                 // One worker a stage and 10 to 14 waves a unit, the fewer the more workers.  KB held back and us, against the
@@ -335,12 +337,14 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
         // 13.3, 1.1 M M = 7 (runs of 256) 18.4 / 18.6 / 19.6, M = 16 38.8 / 38.8 / 43.7, 4.4 M M = 4 - / 42.1 / 44.3, gradients alone
         // 272,474 M = 16 6.0 / 6.0 / 6.5, 8.8 M M = 4 34.3 / 34.2 / 35.6
         constexpr int BW = MT > 0 && MT < 8 ? MT : 8;
-        const bool small = d < ((size_t)1 << 20);
         // Written lines that stay in every cache (26 MB in all, up to seven workers, whose loads are one stage) lose: us, the same state again / three
         // in turn / a hundred, to the L2 with nt against without: M = 7 272,474 4.7 / 5.4 / 6.2 against 4.7 / 6.0 / 9.5, M = 5 400,001 4.6 / 5.6 / 6.3 against
         // 4.6 / 6.1 / 8.9, M = 3 700,001 4.9 / 6.0 / 6.7 against 4.9 / 6.4 / 8.0.
-        if (small) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, kStream, 6, HAS_M, G>(a, d, stream);
-        return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, kStream, 8, HAS_M, G>(a, d, stream);
+        // at 2^20 coordinates these stream already
+        constexpr bool kAlwaysBelow = MT > 0 && HAS_M && MT * kWorkerBytes << 20 >= kStreams;
+        if constexpr (!kAlwaysBelow)
+            if (d >= ((size_t)1 << 20)) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, kStream, 8, HAS_M, G>(a, d, stream);
+        return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, kStream, 6, HAS_M, G>(a, d, stream);
     }
 }
 
@@ -578,8 +582,8 @@ int launch_quorum_vote(const ss::QuorumVoteArgs &a, hipStream_t stream) {
         if (few) return launch(ss::quorum_vote_kernel<P, ss::kBlock, 0, 0, 8>, grid, 0, stream, a);
         return launch(ss::quorum_vote_kernel<P, ss::kWave, 16, 0, 8>, grid, 0, stream, a, ss::kWave);
     } else {
-        if (a.M == 4 && a.d >= kVoteRuns) return launch(ss::quorum_vote_kernel<P, ss::kWave, 16, 0, 8>, grid, 0, stream, a, ss::kWave);
         if constexpr (P == 3) {
+            if (a.M == 4 && a.d >= kVoteRuns) return launch(ss::quorum_vote_kernel<P, ss::kWave, 16, 0, 8>, grid, 0, stream, a, ss::kWave);
             if (a.d >= ((size_t)5 << 22) && a.d < kVoteHalves) return launch(ss::quorum_vote_kernel<P, ss::kWave, 0, kVoteChunk, 4>, grid, 0, stream, a, ss::kWave);
         } else {
             if (a.d >= kVoteHalves && a.d < kVoteInOrder) return launch(ss::quorum_vote_kernel<P, ss::kWave, 26, kVoteLongChunk, 8>, grid, 0, stream, a, ss::kWave);

@@ -145,10 +145,62 @@ def check_lines_of_one_worker(rules):
                 assert s["STORE_X"] == (KEEP if d >= line else store), (bf16, momentum, d, s)
 
 
+def check_every_kernel_is_reached(rules):
+    # the launch shapes that the library holds are those that some call takes
+    seen = set()
+    f, vp, size = ctypes.c_float, ctypes.c_void_p, ctypes.c_size_t
+    L = rules.lib
+
+    def call(fn, *args):
+        rules.shim.record_anew(-1)
+        if fn(*args) == 0:
+            seen.update(rules.kernels())
+
+    for M in range(1, 65):
+        for bf16 in (0, 1):
+            for momentum in (True, False):
+                worker = (2 if bf16 else 4) + (8 if momentum else 0)
+                lines = [-(-b // (M * worker)) for b in (5 << 25, 1 << 27, 1 << 28, 1 << 30, 1 << 31)] + [-(-(1 << 31) // (M * worker + 8))]
+                lines += [1 << 20, 1 << 24, 3 << 21, 6 << 21, -(-(11 << 23) // 4), -(-(11 << 23) // 8), 1 << 28, 1 << 33]
+                for d in sorted({e for line in lines for e in (line - 1, line, 2 * line)} | {1000}):
+                    for how in ({}, {"sums": True}, {"packed": True}, {"packed": True, "sums": True}):
+                        if rules.step(d, M, bf16, momentum, **how)[0] == 0:
+                            seen.update(rules.kernels())
+                    rules.ternary_shapes(d, M, bf16, momentum)
+                    seen.update(rules.kernels())
+                    g, x, v, z = [rules.buffer(4 * d) for _ in range(4)]
+                    m = rules.table([rules.buffer(4 * d) for _ in range(M)]) if momentum else None
+                    call(L.ss_signum_vote_step_ternary_scratch, rules.table([g] * M), bf16, m, M, f(0.9), f(0.1), 2, f(0.1), vp(x), vp(v), vp(z),
+                         vp(rules.buffer(1 << 40)), size(1 << 40), size(d), None)
+        for d in sorted({e for p in range(20, 36) for q in (1 << p, 3 << p, 5 << p) for e in (q - 1, q)} | {1000}):
+            words = (d + 127) // 128 * 16
+            neg, zero = rules.table([rules.buffer(words) for _ in range(M)]), rules.table([rules.buffer(words) for _ in range(M)])
+            call(L.ss_majority_vote, neg, M, vp(rules.buffer(words)), size(d), None)
+            call(L.ss_vote_sum, neg, M, vp(rules.buffer(d)), size(d), None)
+            call(L.ss_quorum_vote, neg, zero, M, 2, vp(rules.buffer(words)), vp(rules.buffer(words)), size(d), None)
+            if M > 1:
+                continue
+            a, b, c, n = vp(rules.buffer(4 * d)), vp(rules.buffer(4 * d)), vp(rules.buffer(4 * d)), size(d)
+            call(L.ss_sign_apply, a, b, f(0.1), n, None)
+            call(L.ss_sum_apply, a, b, f(0.1), n, None)
+            call(L.ss_ternary_apply, a, b, c, f(0.1), n, None)
+            call(L.ss_welford_sigma, a, size(3), b, n, None)
+            call(L.ss_density, a, n, b, c, None)
+            call(L.ss_stream_copy, a, b, size(4 * d), None)
+            for bf16 in (0, 1):
+                call(L.ss_welford_update, a, bf16, b, c, size(3), n, None)
+                for m in (None, c):
+                    call(L.ss_signum_pack, a, bf16, m, f(0.9), b, n, None)
+                    call(L.ss_signum_pack_ternary, a, bf16, m, f(0.9), f(0.1), b, vp(rules.buffer(d // 8 + 16)), n, None)
+    held = subprocess.run(["nm", "-D", "--defined-only", L._name], capture_output=True, text=True, check=True).stdout
+    held = {t.split()[-1] for t in held.splitlines() if t.split()[1] in "VD" and t.split()[-1].startswith("_ZN2ss")}
+    assert seen <= held and held == seen, sorted(held - seen)
+
+
 CHECKS = {f.__name__: f for f in (check_ternary_steps_have_one_store_policy, check_small_steps_leave_their_lines_to_the_l2,
                                   check_lines_of_steps_with_momentum, check_momentum_is_not_kept_in_the_cache,
                                   check_which_steps_keep_x, check_what_an_update_of_the_statistics_keeps,
-                                  check_lines_of_one_worker)}
+                                  check_lines_of_one_worker, check_every_kernel_is_reached)}
 
 
 @pytest.mark.parametrize("name", sorted(CHECKS))
