@@ -83,7 +83,7 @@ def test_small_step_with_workers_left_over(ss, oracle, d, M, momentum):
     ((1 << 28) // 84 - 5, 7, "f32", True), ((1 << 28) // 80 + 77, 8, "bf16", True),
 ])
 def test_step_on_both_sides_of_a_launch_shape(ss, oracle, d, M, dtype, momentum):
-    # one worker beyond 2^24 coordinates; several workers at 2^28 bytes of gradients and momentum, where scratch is lent to
+    # one worker in the streaming shape; several workers at 2^28 bytes of gradients and momentum, where scratch is lent to
     # eight and more
     rng = np.random.default_rng(d)
     g = [make_grad(rng, d, dtype, scale=0.5) for _ in range(M)]

@@ -108,7 +108,7 @@ def test_vote_and_update_around_a_tile(ss, oracle, M, dtype, flags, extra):
 
 
 # One pass.  Runs of 64 tiles of 256 coordinates a die below 2^20 coordinates, of 256 above; the streaming shapes begin at
-# 11 x 2^23 bytes of momentum and x written (2^28 bytes of gradients without momentum), one worker's at 2^24 coordinates.
+# 5 x 2^25 bytes of gradients and momentum, which counts twice (2^28 without momentum), one worker's at 11 x 2^23 bytes of momentum and x.
 STEPS = [((1 << 17) - 1, 7, "f32", True), ((1 << 17) + 77, 16, "bf16", True), ((1 << 17) + 255, 1, "f32", True),
          ((1 << 18) + 256, 9, "f32", True), ((1 << 20) - 1, 3, "bf16", False), ((1 << 20) + 300, 6, "f32", False),
          ((5 << 25) // 84 - 1, 7, "f32", True), ((5 << 25) // 84 + 1, 7, "f32", True), ((5 << 25) // 24 + 255, 2, "f32", True),
@@ -132,9 +132,9 @@ def test_one_pass_around_runs_and_rules(ss, oracle, d, M, dtype, momentum):
     assert_same_floats(x_dev, x, "x")
 
 
-# Where what a step writes is left in the memory-side cache: both ends of that range (16 to 48 MB, by workers and type, to 11 x 2^23
-# bytes of momentum and x), the small steps of up to seven workers whose lines stay in every cache (25 x 2^20 bytes in all), and the two
-# launches that packed_out takes beyond it.  Two steps in a row, binary and with abstentions: the second reads what the first left.
+# Two steps in a row, binary, with the workers' bits (the smaller ones) and with abstentions: the second reads what the first left, x in part from the
+# memory-side cache.  Sizes around 16 to 92 MB written, with one worker both ends of the range in which x is kept (24 or 48 MB of x, 11 x 2^23 bytes),
+# with several both sides of the line from which it is (5 x 2^25 bytes of gradients and momentum, 2^28 without).
 MOST = 11 << 23
 KEPT = [((1 << 24) // 32 - 1, 7, "f32", True), ((1 << 24) // 32 + 1, 7, "f32", True), (MOST // 32 - 1, 7, "f32", True), (MOST // 32, 7, "f32", True),
         ((3 << 23) // 36 + 1, 8, "bf16", True), (MOST // 36 - 255, 8, "bf16", True), (MOST // 36 + 1, 8, "f32", True),
@@ -145,11 +145,12 @@ KEPT = [((1 << 24) // 32 - 1, 7, "f32", True), ((1 << 24) // 32 + 1, 7, "f32", T
         (MOST // 4 + 1, 4, "bf16", False)]
 
 
-# Beyond, the first 9 x 2^23 bytes of x are kept and the rest is not: the line between tiles of 256 (bf16 gradients alone 512) coordinates
-# and the ragged end behind it.
+# The first 9 x 2^23 bytes of x are kept and the rest is not (without momentum up to eight workers): the line between tiles of 256 (bf16 gradients alone
+# 512) coordinates and the ragged end behind it.
 X = (9 << 23) // 4
 KEPT += [(MOST // 4 + 255, 1, "f32", False), (X + 3 * 256 + 77, 1, "bf16", True), (X - 1, 2, "f32", True), (X + 257, 4, "f32", False), (X + 511, 9, "bf16", False),
-         (X + 512 + 33, 8, "bf16", False), ((1 << 28) // 12 + 513, 6, "bf16", False)]
+         (X + 512 + 33, 8, "bf16", False), ((1 << 28) // 12 + 513, 6, "bf16", False),
+         ((3 << 21) - 1, 1, "f32", False), ((3 << 21) + 513, 1, "f32", False), ((6 << 21) - 257, 1, "bf16", False), ((6 << 21) + 1, 1, "bf16", False)]
 
 
 @pytest.mark.parametrize("d,M,dtype,momentum", KEPT)
@@ -178,7 +179,7 @@ def test_steps_that_leave_their_lines_in_the_caches(ss, oracle, d, M, dtype, mom
 
 
 # with packed_out, on both sides of the line from which two launches pay: 2^30 bytes for three to five workers, 2^28 for six and
-# seven, for eight and more where the streaming shapes begin; 2^28 without momentum
+# seven, 2^27 for eight and more; 2^28 without momentum
 @pytest.mark.parametrize("d,M,dtype,momentum", [((1 << 30) // 36 - 3, 3, "f32", True), ((1 << 30) // 36 + 3, 3, "f32", True),
                                                 ((1 << 27) // 80 - 1, 8, "bf16", True), ((1 << 27) // 80 + 1, 8, "bf16", True),
                                                 ((1 << 25) // 2 - 1, 2, "bf16", False), ((1 << 25) // 2 + 1, 2, "bf16", False),
@@ -187,6 +188,7 @@ def test_steps_that_leave_their_lines_in_the_caches(ss, oracle, d, M, dtype, mom
                                                 ((1 << 28) // 72 - 1, 6, "f32", True), ((1 << 28) // 72 + 4095, 6, "f32", True),
                                                 ((1 << 28) // 70 + 255, 7, "bf16", True), ((1 << 27) // 90 + 129, 9, "bf16", True),
                                                 ((1 << 27) // 144 + (1 << 17), 12, "f32", True),
+                                                ((1 << 27) // 96 - 255, 8, "f32", True), ((1 << 27) // 96 + 1, 8, "f32", True),
                                                 ((1 << 28) // 4 - 1, 2, "bf16", False), ((1 << 28) // 4 + 129, 2, "bf16", False),
                                                 ((1 << 28) // 28, 7, "f32", False), ((1 << 28) // 28 + 1, 7, "f32", False),
                                                 ((1 << 28) // 32 - 255, 16, "bf16", False), ((1 << 20) + 4097, 33, "f32", False),
@@ -275,8 +277,8 @@ def test_updates_and_statistics_around_rules(ss, oracle, d):
     assert torch.equal(to[:d // 4 * 4].view(torch.int32), x0[:d // 4 * 4].view(torch.int32)) and bool((to[d // 4 * 4:] == 9).all())
 
 
-# Update after update, sigma and the densities, each reading what the one before left in the caches: runs between 2^21 and 2^24 coordinates,
-# the mean kept up to 5 x 2^23, sigma up to 2^26; densities in tiles of three rows below 3 x 2^18 coordinates, eight below 2^25, six beyond, a
+# Update after update, sigma and the densities, each reading what the one before left in the caches: an update in runs below 2^24 coordinates, m2 kept
+# from 2^21 on, the mean up to 5 x 2^23, sigma up to 2^26; densities in tiles of three rows below 3 x 2^18 coordinates, eight below 2^25, six beyond, a
 # row being 2,048 coordinates: one tile less than a row, one and two tiles, a round of the most blocks.
 # A sum's error is at most its longest chain of additions (below 800) x 2^-53 = 9e-14.
 @pytest.mark.parametrize("d", [6 * 2048 - 1, 6 * 2048 + 3, (3 << 18) - 1, (3 << 18), (1 << 21) - 1, (1 << 21) + 2047, 256 * 8 * 2048 + 5, (1 << 24) + 1,

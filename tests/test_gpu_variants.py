@@ -87,7 +87,7 @@ def test_step_variants_small_and_ragged(ss, oracle, M, dtype, momentum, flags):
 
 @pytest.mark.parametrize("flags", [1, 2, 3])
 def test_step_variants_streaming_shape(ss, oracle, flags):
-    # large enough to hand the signs over through packed_out, with a ragged tail
+    # one pass in the streaming shape, and large enough to hand the signs over through packed_out; a ragged tail
     run_variant(ss, oracle, 7, 2_200_000 + 37, "f32", True, flags, seed=flags, steps=2)
     run_variant(ss, oracle, 9, 1_500_000 + 5, "bf16", True, flags, seed=10 + flags, steps=1)
 

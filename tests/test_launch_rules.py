@@ -197,10 +197,43 @@ def check_every_kernel_is_reached(rules):
     assert seen <= held and held == seen, sorted(held - seen)
 
 
+def check_gpu_tests_reach_both_sides(rules):
+    # the lists of sizes in test_gpu_stream_shapes straddle the rules that they name
+    sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    import test_gpu_stream_shapes as gpu
+
+    def parameters(test):
+        return [mark.args[1] for mark in test.pytestmark if mark.name == "parametrize"][0]
+
+    def groups(M, momentum):
+        return 1 if M == 1 else 2 if not momentum or M == 2 else 3 if M < 6 else 6 if M < 8 else 8 if M < 17 else 17
+
+    launches, steps, ternary, kept = {}, {}, {}, {}
+    for d, M, dtype, momentum in parameters(gpu.test_packed_out_on_both_sides_of_two_launches):
+        n = len(rules.step_shapes(d, M, int(dtype == "bf16"), momentum, packed=True))
+        launches.setdefault((momentum, groups(M, momentum)), set()).add(n)
+    assert all(launches[g] == {1, 2} for g in ((True, 3), (True, 6), (True, 8), (False, 2))) and launches[True, 2] == {1}, launches
+    for d, M, dtype, momentum in gpu.STEPS + gpu.KEPT:
+        (_, s), = rules.step_shapes(d, M, int(dtype == "bf16"), momentum)
+        steps.setdefault((M > 1, momentum), set()).add((s.get("NEAR", 0), s["STORE"], s["STORE_X"]))
+        if d % 256 and 4 * d > 9 << 23 and s["STORE_X"] == KEEP != s["STORE"]:
+            kept.setdefault(M > 1, set()).add(d)
+    near, streaming = (1, STREAM, STREAM), (0, THROUGH, KEEP)
+    for group, shapes in steps.items():
+        assert {near, streaming} <= shapes, (group, shapes)
+    assert (1, KEEP, KEEP) in steps[False, False] and (0, THROUGH, THROUGH) in steps[True, False] and len(kept[False]) > 1 and len(kept[True]) > 1
+    for d, M, dtype, momentum in parameters(gpu.test_one_pass_ternary_around_rules):
+        (_, s), = rules.ternary_shapes(d, M, int(dtype == "bf16"), momentum)
+        ternary.setdefault(momentum, set()).add((s["NEAR"], s["STORE"], s["HOLD"]))
+    assert ternary[True] == {(1, STREAM, 0), (0, THROUGH, 11), (0, THROUGH, 12), (0, THROUGH, 13)}, ternary
+    assert ternary[False] == {(0, THROUGH, 7), (0, THROUGH, 10)}, ternary
+
+
 CHECKS = {f.__name__: f for f in (check_ternary_steps_have_one_store_policy, check_small_steps_leave_their_lines_to_the_l2,
                                   check_lines_of_steps_with_momentum, check_momentum_is_not_kept_in_the_cache,
                                   check_which_steps_keep_x, check_what_an_update_of_the_statistics_keeps,
-                                  check_lines_of_one_worker, check_every_kernel_is_reached)}
+                                  check_lines_of_one_worker, check_every_kernel_is_reached,
+                                  check_gpu_tests_reach_both_sides)}
 
 
 @pytest.mark.parametrize("name", sorted(CHECKS))
