@@ -552,6 +552,7 @@ int launch_vote_any(const uint32_t *const *packed, int M, uint32_t *voted, size_
 // 7.7 / 8.1, 60 M 20.5 / 21.5, M = 16 17.6 M 9.5 / 9.0; eight / four a batch: M = 5 25.6 M 6.7 / 7.3, M = 12 13 M 6.1 / 6.5, 25.6 M 12.0 / 10.9, M = 16
 // 25.6 M 14.8 / 12.4, M = 24 13 M 9.8 / 10.0, 17.6 M 13.9 / 13.4, 25.6 M 19.4 / 18.3, 60 M 41.8 / 41.9; beyond, in order / in runs: M = 7 138 M 43.3 / 43.6, M = 9
 // 80 M 32.6 / 32.1, M = 12 80 M 35.8 / 34.6, 138 M 57.9 / 56.8, M = 13 138 M 61.1 / 59.5, M = 33 138 M 121.5 / 118, 250 M 211 / 210, M = 24 1,000 M 646 / 652.
+// Three sets of buffers in turn, as above; over some fifty, to the L2 / through: M = 3 5.0 M 3.7 / 3.7, 14 M 4.5 / 4.8, 25.6 M 6.2 / 6.7, M = 7 9.0 M 4.9 / 4.8, 14 M 5.6 / 6.2.
 template <int P>
 int launch_vote_sum(const ss::VoteSumArgs &a, size_t grid, hipStream_t stream) {
     using ss::kStream;
@@ -972,7 +973,8 @@ int ss_welford_sigma(const float *m2, uint64_t n, float *sigma, size_t d, void *
     const ss::SigmaArgs a{m2, sigma, (float)n, (uint32_t)t.n_tiles, d};
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (two_rows) return launch(ss::welford_sigma_kernel<2, ss::kThrough>, grid, 0, stream, a, ss::kWave);
-    // kept for the density that reads it next while the cache can hold all of it: 60 M 301.8 us of statistics against 303.6, 80 M 419.7 / 405.5
+    // kept for the density that reads it next while the cache can hold all of it: 60 M 301.8 us of statistics against 303.6, 80 M 419.7 / 405.5.
+    // By itself over sixty vectors in turn, to the L2 or through / kept: 272,474 2.34 / 2.49, 1.1 M 3.24 / 3.6, 4.4 M 7.6 / 7.8, 25.6 M 31.9 / 32.1.
     if (d >= ((size_t)1 << 26)) return launch(ss::welford_sigma_kernel<1, ss::kThrough>, grid, 0, stream, a, ss::kWave);
     return launch(ss::welford_sigma_kernel<1, ss::kKeep>, grid, 0, stream, a, ss::kWave);
 }

@@ -260,8 +260,8 @@ __device__ __forceinline__ void octet_rest(const StepArgs<NPTR> &a, int w0, int 
     }
 }
 
-// BW, HOLD_KB as for step_kernel; a tile is one row of BLOCK octets.  The first x_kept tiles leave x in the memory-side cache: us at 25.6 M
-// coordinates, M = 8, none of x / 64 MB of it, the same state 96.5 / 92.6, three in turn 98.7 / 93.6
+// BW, HOLD_KB as for step_kernel; a tile is one row of BLOCK octets.  Up to eight workers the first x_kept tiles leave x in the memory-side
+// cache: us at 25.6 M coordinates, M = 8, none of x / 75 MB of it, the same state 96.8 / 93.3, three in turn 97.2 / 92.9, twelve 98.2 / 101.1 (see kKeepX)
 template <int MT, int NPTR, int BLOCK, int BW, int HOLD_KB, int STORE, int STORE_X>
 __global__ __launch_bounds__(BLOCK) void step_bf16_kernel(const StepArgs<NPTR> a) {
     reserve_lds<HOLD_KB>(a.d == ~(size_t)0, a.p.packed[0]);
