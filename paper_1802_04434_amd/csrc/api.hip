@@ -138,9 +138,10 @@ constexpr int kKeepXWorkers = 8;
 inline uint32_t x_tiles_kept(int M, size_t d, size_t worker_bytes, size_t tile_bytes) {
     return d * (M * worker_bytes + 2 * sizeof(float)) < (size_t)1 << 31 ? (uint32_t)(kKeepX / tile_bytes) : 0;
 }
-// One worker streams from 11 x 2^23 bytes of momentum and x written on (x alone where there is no momentum); there it keeps its x also below, in the
-// shape of its smaller steps.  us, written lines to the L2 / kept / streaming, three states: alone 8.0 M 15.8 / 15.6 / -, 20 M - / 35.0 / 37.7, bf16 20 M - / 29.8 / 32.6, twelve
-// and more 16.8 / 17.4 / -, - / 38.9 / 37.8, - / 32.7 / 32.6; with momentum 13 M to the L2 / streaming 42.7 / 38.3 and 43.0 / 42.6.  Kept from 24 MB of x on, bf16 48: 4.4 M bf16 13.9 / 14.7.
+// One worker streams from 11 x 2^23 bytes of momentum and x written on (x alone where there is no momentum): us, to the L2 / streaming with x kept, three states in turn, with
+// momentum 13 M 42.7 / 38.3, twelve 43.0 / 42.6.  Without momentum x is kept below as well, in the shape of the smaller steps, from 24 MB of it on (bf16 48): to the L2 / kept, one
+// state, three, a dozen and more, and step, a read of x and a 600 MB copy: 6.4 M 11.3 / 10.4, 12.7 / 12.7, 14.0 / 14.6, 137.5 / 137.1; 12 M 21.2 / 19.5, 23.1 / 21.9, 23.9 / 24.5,
+// 154.9 / 153.2; bf16 12.8 M 19.6 / 17.4, 21.2 / 19.4, 21.7 / 22.1, 153.5 / 152.8; against streaming 20 M 37.9 / 34.6, 38.0 / 35.0, 38.0 / 38.9, 179.8 / 178.2.
 constexpr size_t kOneWorkerStreams = (size_t)11 << 23;
 inline bool one_streams(size_t d, bool has_m) { return d * sizeof(float) * (has_m ? 2 : 1) >= kOneWorkerStreams; }
 inline bool one_keeps(size_t d, bool bf16) { return d * sizeof(float) >= (size_t)(bf16 ? 6 : 3) << 23; }
@@ -340,7 +341,7 @@ int launch_step_m(int M, const void *const *g, float *const *m, uint32_t *const 
         // Written lines that stay in every cache (26 MB in all, up to seven workers, whose loads are one stage) lose: us, the same state again / three
         // in turn / a hundred, to the L2 with nt against without: M = 7 272,474 4.7 / 5.4 / 6.2 against 4.7 / 6.0 / 9.5, M = 5 400,001 4.6 / 5.6 / 6.3 against
         // 4.6 / 6.1 / 8.9, M = 3 700,001 4.9 / 6.0 / 6.7 against 4.9 / 6.4 / 8.0.
-        // at 2^20 coordinates these stream already
+        // Sixteen workers with momentum stream before they come to 2^20 coordinates.
         constexpr bool kAlwaysBelow = MT > 0 && HAS_M && MT * kWorkerBytes << 20 >= kStreams;
         if constexpr (!kAlwaysBelow)
             if (d >= ((size_t)1 << 20)) return launch_step_shape<MT, NPTR, 64, BW, 1, 0, true, kStream, kStream, 8, HAS_M, G>(a, d, stream);
